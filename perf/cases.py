@@ -215,6 +215,64 @@ def run(s):
     return s["out"]
 
 
+def _f32(v):
+    """A hyper-parameter as the C structures carry it."""
+    return torch.tensor(v, dtype=torch.float32).item()
+
+
+def _orthogonalise(mom, steps, hp):
+    """`steps` Newton-Schulz iterations on a batch of matrices in 64 bits."""
+    a, b, c = _f32(hp.ns_a), _f32(hp.ns_b), _f32(hp.ns_c)
+    x = mom / mom.flatten(1).norm(dim=1)[:, None, None]
+    tall = x.shape[1] > x.shape[2]
+    if tall:
+        x = x.transpose(1, 2).contiguous()
+    for _ in range(steps):
+        s = torch.matmul(x, x.transpose(1, 2).contiguous())
+        x = a * x + torch.matmul(b * s + c * torch.matmul(s, s), x)
+    return x.transpose(1, 2).contiguous() if tall else x
+
+
+def exact(case, seed):
+    """What the first pass on these inputs gives, in 64 bits (all state arrays start from zero)."""
+    gen = torch.Generator(device="cuda").manual_seed(wl.BASE_SEED + int(seed))
+    specs = _specs(case)
+    params = [_bank(spec, wl.WEIGHT_STD, _DTYPE[case["w"]], gen)[0] for spec in specs]
+    grads = _gradients(specs, _DTYPE[case["g"]], gen, sets=1)[0]
+    out, state, slots, at = [], [], [], 0
+    for spec, whole in zip(specs, params):
+        count, shape = spec[0], spec[1:]
+        g = torch.stack([t.double() for t in grads[at:at + count]])
+        at += count
+        w = whole.double().reshape((count,) + shape)
+        if case["path"] == "adamw":
+            lr, b1, b2, eps, wd = (_f32(v) for v in (1e-3, 0.9, 0.95, 1e-8, 0.1))
+            # first step: the bias corrections make the corrected moments g and g^2
+            out.append(w * (1.0 - lr * wd) - lr * g / (g.abs() + eps))
+            state += [(1.0 - b1) * g, (1.0 - b2) * g * g]
+            continue
+        hp = wl.HParams(ns_steps=case["steps"])
+        lr, beta = _f32(hp.lr), _f32(hp.beta_a)
+        a = (1.0 - beta) * g
+        m = g + _f32(hp.alpha) * a
+        keep, scale = 1.0 - lr * _f32(hp.weight_decay), lr * _f32(hp.gamma_coeff) * math.sqrt(max(shape))
+        each = max(1, 2 ** 26 // math.prod(shape))
+        for i in range(0, count, each):
+            w[i:i + each].mul_(keep).sub_(_orthogonalise(m[i:i + each], case["steps"], hp), alpha=scale)
+        out.append(w)
+        if case["accel"] == "one":
+            state += [beta * a - (1.0 - beta) * g, m]
+        elif case["accel"] == "slot":
+            state += [a, m]
+            room = torch.zeros((count, (math.prod(shape) + 7) // 8 * 8), dtype=torch.float64, device="cuda")
+            room[:, :math.prod(shape)] = g.flatten(1)
+            slots.append(room)
+        else:
+            state += [g, a, m]
+    # one output for each output of run(): whole tensors, then the state arrays
+    return out + state + slots
+
+
 def work(case):
     size = {"f32": 4, "bf16": 2}
     specs = _specs(case)
