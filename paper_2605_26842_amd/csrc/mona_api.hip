@@ -76,6 +76,14 @@ struct Group {
   int64_t x_stride = 0, s_stride = 0;  // elements per matrix
 };
 
+// Groups whose products are launched together: one group, or up to kMaxMerged groups that run small tiles only and
+// share a launch per position in their chains of products.
+struct Unit {
+  std::vector<int> groups;
+  bool merged = false;
+  int lane = 0;              // stream: 0 is the caller's
+};
+
 struct Layout {
   int count = 0;
   int ssize = 4;             // bytes per element of the stored G_{k-1}, A (or C)
@@ -93,7 +101,7 @@ struct Layout {
   std::vector<int> first_block, num_blocks;
   // The block table is ordered: early groups (fp32-gradient matrices, then bf16), then the late group (same).
   int range_end[4] = {0, 0, 0, 0};     // ends of those four ranges of blocks
-  std::vector<int> lane_of_group;      // group index -> lane (stream) its products run on
+  std::vector<Unit> units;             // what the products of the groups are launched as, in launch order per lane
   int lanes = 1;
   int late_group = -1;                 // group whose elementwise pass runs beside the products of the others
   std::vector<int32_t> order;          // matrix indices: early matrices, then those of the late group
@@ -157,11 +165,10 @@ constexpr long long kChipTiles = 256;      // one tile per CU
 constexpr int kOverlapCuShare = 4;
 constexpr double kSlowPassBytesPerSec = 2.8e12, kProductFlopPerSec = 1.0e15, kProductSlowdown = 1.13;
 
-struct TileShape { int bm, bn; };
-
-// block tile used by one product of a group
-TileShape pick_tile(const Group& g, int kind, int count) {
-  if (g.f32 || g.gran < 256) return {128, 128};
+// whether one product of a group runs on the 256 x 256 kernel
+bool large_tiles(const Group& g, int kind, int count) {
+  if (g.f32 || g.gran < 256) return false;
+  if (g.large_with_company) return true;
   long long tiles;
   if (kind == OP_APPLY) {
     tiles = (long long)(g.rows_pad / 256) * (g.cols_pad / 256) * count;
@@ -170,23 +177,28 @@ TileShape pick_tile(const Group& g, int kind, int count) {
     tiles = t * (t + 1) / 2 * count;
   }
   // too few large tiles to fill 256 CUs, unless groups running beside this one make up for it
-  if (tiles < 192 && !g.large_with_company) return {128, 128};
-  return {256, 256};
+  return tiles >= 192;
+}
+bool small_tiles_only(const Group& g) {
+  const int count = (int)g.members.size();
+  return !large_tiles(g, OP_GRAM, count) && !large_tiles(g, OP_APPLY, count);
 }
 
 // tiles one product launch of a group computes
-long long launch_tiles(const Group& g, int kind, TileShape tile, int count) {
-  if (kind == OP_APPLY) return (long long)(g.rows_pad / tile.bm) * (g.cols_pad / tile.bn) * count;
-  const long long t = g.p_pad / tile.bm;
+long long launch_tiles(const Group& g, int kind, int tile, int count) {
+  if (kind == OP_APPLY) return (long long)(g.rows_pad / tile) * (g.cols_pad / tile) * count;
+  const long long t = g.p_pad / tile;
   return t * (t + 1) / 2 * count;
 }
-
 
 // Streams and order of the step.
 //
 // Lanes.  A group whose every launch covers the chip many times over gains nothing from company (two
 // persistent kernels sharing the CUs only disturb each other's L2 reuse: measured slower), so such groups
-// stay in a row on the caller's stream; the others, sorted by work, each go to the least loaded lane.
+// stay in a row on the caller's stream; the others, sorted by work, each go to the least loaded lane, except that
+// the groups that run small tiles only are merged first: their products are bound by the latency of a launch, and a
+// launch takes as long for eight groups as for one (measured on nine ragged matrices: 982 us a step with a chain of
+// launches for each group on four lanes).
 //
 // Late group (on request: mona_options.overlap).  The elementwise pass is bound by HBM and leaves the matrix
 // units idle; the products are bound by the matrix units (and by power) and leave HBM half idle.  When the
@@ -198,65 +210,90 @@ long long launch_tiles(const Group& g, int kind, TileShape tile, int count) {
 // (13 % from the CUs they give up, the rest from sharing HBM), which leaves 3.6 % of the step; not the default.
 void plan_lanes(Layout& L, const mona_options& opt) {
   const int want = opt.max_streams == 0 ? kDefaultLanes : opt.max_streams;
-  L.lanes = std::max(1, std::min<int>(want, (int)L.groups.size()));
-  std::vector<std::pair<double, int>> order;
-  std::vector<double> load(L.lanes, 0.0);
-  L.lane_of_group.assign(L.groups.size(), 0);
   L.late_group = -1;
-  std::vector<long long> fewest_of(L.groups.size(), 0);
-  std::vector<int> row;
+  L.units.clear();
+  const int ngroups = (int)L.groups.size();
+  std::vector<long long> fewest_of(ngroups, 0);
+  std::vector<double> work_of(ngroups, 0.0);
+  std::vector<int> row, beside;
   bool any_big = false;
-  for (size_t gi = 0; gi < L.groups.size(); ++gi) {
+  for (int gi = 0; gi < ngroups; ++gi) {
     const Group& g = L.groups[gi];
     long long fewest = -1;
     for (int kind = OP_GRAM; kind <= OP_APPLY; ++kind) {
-      const long long t = launch_tiles(g, kind, pick_tile(g, kind, (int)g.members.size()), (int)g.members.size());
+      const int tile = large_tiles(g, kind, (int)g.members.size()) ? 256 : 128;
+      const long long t = launch_tiles(g, kind, tile, (int)g.members.size());
       if (fewest < 0 || t < fewest) fewest = t;
     }
     fewest_of[gi] = fewest;
     any_big = any_big || fewest >= kBigLaunchTiles;
-  }
-  std::vector<double> work_of(L.groups.size(), 0.0);
-  for (size_t gi = 0; gi < L.groups.size(); ++gi) {
-    const Group& g = L.groups[gi];
     const double p = std::min(g.rows_pad, g.cols_pad), q = std::max(g.rows_pad, g.cols_pad);
-    // flop of five iterations on the symmetric count: literal 5 (3 p^2 q + p^3), chunks (3, 2), chunks (2, 2, 1)
+    // flop of five iterations on the symmetric count: literal 5 (3 p^2 q + p^3), chunks (3, 2), chunks (2, 2, 1);
+    // an fp32 product takes 16 times the time of a bf16 one
     const double per = g.fused == 2 ? 6.0 * p * p * q + 14.0 * p * p * p
                        : g.fused == 1 ? 9.0 * p * p * q + 11.0 * p * p * p : 5.0 * (3.0 * p * p * q + p * p * p);
-    const double work = per * (double)g.members.size();
-    work_of[gi] = work;
+    work_of[gi] = per * (double)g.members.size() * (g.f32 ? 16.0 : 1.0);
+  }
+  for (int gi = 0; gi < ngroups; ++gi) {
     // Beside a group that keeps the caller's stream, only groups too small to fill the chip by
     // themselves go to the side streams (their launch latency hides behind the large group); a
     // mid-sized group there gained 0.3 % at most (4 squares of 4096 beside 384 experts), and in a row
     // the per-launch times of a profile add up to the phase time.
     const bool in_row = fewest_of[gi] >= kBigLaunchTiles || (any_big && fewest_of[gi] >= kChipTiles);
-    if (in_row) { load[0] += work; row.push_back((int)gi); }
-    else order.emplace_back(-work, (int)gi);
+    (in_row ? row : beside).push_back(gi);
   }
-  std::sort(order.begin(), order.end());
-  for (auto& pr : order) {
-    const int lane = (int)(std::min_element(load.begin(), load.end()) - load.begin());
-    L.lane_of_group[pr.second] = lane;
-    load[lane] += -pr.first;
-  }
+  std::stable_sort(beside.begin(), beside.end(), [&](int x, int y) { return work_of[x] > work_of[y]; });
   // The groups on the lanes run side by side.  When their launches, taken together, put a large tile
   // on at least half of the CUs, each of them uses the large-tile kernel even where its own launch
   // alone would be too small for it (measured on one dense block of hidden size 2048: 2.43 against
   // 2.80 ms per step).
-  if (L.lanes > 1) {
+  if (std::min(want, ngroups) > 1) {
     long long together = 0;
-    for (auto& pr : order) {
-      Group& g = L.groups[pr.second];
+    for (int gi : beside) {
+      const Group& g = L.groups[gi];
       if (g.f32 || g.gran < 256) continue;
       long long fewest = -1;
       for (int kind = OP_GRAM; kind <= OP_APPLY; ++kind) {
-        const long long t = launch_tiles(g, kind, TileShape{256, 256}, (int)g.members.size());
+        const long long t = launch_tiles(g, kind, 256, (int)g.members.size());
         if (fewest < 0 || t < fewest) fewest = t;
       }
       together += fewest;
     }
     if (together >= 128)
-      for (auto& pr : order) L.groups[pr.second].large_with_company = true;
+      for (int gi : beside) L.groups[gi].large_with_company = true;
+  }
+  // Units: every group that uses the large-tile kernel by itself; the others merged, bf16 and fp32 apart (one kernel
+  // per launch).
+  auto add_unit = [&](bool merged) -> Unit& {
+    L.units.emplace_back();
+    L.units.back().merged = merged;
+    return L.units.back();
+  };
+  for (int gi : row) add_unit(false).groups.push_back(gi);
+  const size_t first_beside = L.units.size();
+  int open[2] = {-1, -1};    // unit that still takes groups, by precision
+  for (int gi : beside) {
+    const Group& g = L.groups[gi];
+    if (!small_tiles_only(g)) { add_unit(false).groups.push_back(gi); continue; }
+    int& u = open[g.f32 ? 1 : 0];
+    if (u < 0 || (int)L.units[u].groups.size() == kMaxMerged) { add_unit(true); u = (int)L.units.size() - 1; }
+    L.units[u].groups.push_back(gi);
+  }
+  const int parallel = (int)(L.units.size() - first_beside) + (row.empty() ? 0 : 1);
+  L.lanes = std::max(1, std::min(want, parallel));
+  std::vector<double> load(L.lanes, 0.0);
+  for (int gi : row) load[0] += work_of[gi];
+  std::vector<std::pair<double, size_t>> order;
+  for (size_t u = first_beside; u < L.units.size(); ++u) {
+    double work = 0.0;
+    for (int gi : L.units[u].groups) work += work_of[gi];
+    order.emplace_back(-work, u);
+  }
+  std::sort(order.begin(), order.end());
+  for (auto& pr : order) {
+    const int lane = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+    L.units[pr.second].lane = lane;
+    load[lane] -= pr.first;
   }
   if (opt.overlap == MONA_OVERLAP_LATE_GROUP && row.size() >= 2 && !L.external_state) {
     int late = -1;
@@ -268,6 +305,9 @@ void plan_lanes(Layout& L, const mona_options& opt) {
       if (gi != late) others += work_of[gi];
     const double slow_pass = 30.0 * most / kSlowPassBytesPerSec;
     if (kProductSlowdown * others / kProductFlopPerSec >= 0.95 * slow_pass && slow_pass >= 1.0e-3) L.late_group = late;
+    // the late group comes last: its elementwise pass must have finished, and from then on the chip is free
+    if (L.late_group >= 0)
+      std::stable_partition(L.units.begin(), L.units.end(), [&](const Unit& u) { return u.groups[0] != L.late_group; });
   }
 }
 
@@ -444,14 +484,44 @@ double gemm_flops(const GemmArgs& a) {
   return 2.0 * a.tile_m * a.tile_n * (double)a.K * a.tiles_per_mat * a.count;
 }
 
-// One product launch of the plan.
+// One product of the plan.
 struct Op {
   GemmArgs a;
   int kind = 0;       // OpKind
   int iter = 0;       // Newton-Schulz iteration it belongs to
-  TileShape tile{128, 128};
-  bool tp = false, tq = false;
+  bool large = false; // 256 x 256 kernel; otherwise the tile is chosen when the launch is put together
+  int m = 0, n = 0;   // rows and columns of the result without padding
 };
+
+void set_tile(Op& op, int tile) {
+  GemmArgs& a = op.a;
+  a.tile_m = a.tile_n = tile;
+  // tiles that hold nothing but padding are left out where the padding is wider than a tile
+  a.tiles_m = (op.m + tile - 1) / tile;
+  a.tiles_n = (op.n + tile - 1) / tile;
+  a.tiles_per_mat = a.symmetric ? a.tiles_n * (a.tiles_n + 1) / 2 : a.tiles_m * a.tiles_n;
+}
+
+// Tile of a launch of small tiles: 64 x 64 (four times the workgroups, each with a quarter of the work) until there
+// are enough 128 x 128 tiles.  Measured, us per step with the limit at 64 / 128 / 256 tiles: 2 x 768 x 3072 both ways
+// 464 / 409 / 409, one 2048 x 2048 404 / 404 / 457, a block of hidden size 1000 537 / 537 / 564.  An fp32 tile takes 16
+// times as long, so there an even share for every CU matters more: 128 x 128 only from four such tiles per CU on
+// (limit 64 / 512 / none: 16 x 768 x 1536 2981 / 2563 / 2505, a block of hidden size 1024 3051 / 2520 / 2365,
+// 64 x 1024 x 2048 20562 / 20541 / 21622).
+constexpr long long kMinTiles128 = 128, kMinTiles128F32 = 1024;
+void choose_small_tile(Op* const* ops, int n, bool f32) {
+  long long tiles = 0;
+  for (int i = 0; i < n; ++i) {
+    set_tile(*ops[i], 128);
+    tiles += (long long)ops[i]->a.tiles_per_mat * ops[i]->a.count;
+  }
+  for (int i = 0; i < n; ++i) {
+    const long long t128 = ops[i]->a.tiles_per_mat;
+    set_tile(*ops[i], 64);
+    // (a 64 x 64 tile costs about 0.3 of a 128 x 128 one: where 128 pads the sides that much, 64 is less work)
+    if (tiles >= (f32 ? kMinTiles128F32 : kMinTiles128) && ops[i]->a.tiles_per_mat * 3 >= t128 * 10) set_tile(*ops[i], 128);
+  }
+}
 
 // Newton-Schulz iterations per chunk.  Literal schedule: one.  Fused schedules: three and then twos, or twos
 // only (measured on bf16-rounded products: fusing the late iterations, or more than three of them, loses
@@ -489,7 +559,7 @@ struct OpBuilder {
 
   OpBuilder(const mona_state* st_, const Group& g_, const mona_hparams& hp_, std::vector<Op>& out_);
   GemmArgs base() const;
-  void push(GemmArgs& a, int kind, int iter, bool tp, bool tq, TileShape tile);
+  void push(GemmArgs& a, int kind, int iter, bool tp, bool tq, bool large);
   void gram(int src, void* S, bool first, int iter);
   void poly(void* S, void* dst, float diag, int iter);
   void symprod(void* P, void* Q, void* dst, int iter);
@@ -518,21 +588,14 @@ GemmArgs OpBuilder::base() const {
   return a;
 }
 
-void OpBuilder::push(GemmArgs& a, int kind, int iter, bool tp, bool tq, TileShape tile) {
-  a.tile_m = tile.bm;
-  a.tile_n = tile.bn;
-  a.sym_ratio = tile.bm / tile.bn;
-  a.tiles_m = a.M / tile.bm;
-  a.tiles_n = a.N / tile.bn;
-  if (a.symmetric) {
-    // row block ti keeps the column blocks from its diagonal on
-    a.tiles_per_mat = 0;
-    for (int ti = 0; ti < a.tiles_m; ++ti) a.tiles_per_mat += a.tiles_n - a.sym_ratio * ti;
-  } else {
-    a.tiles_per_mat = a.tiles_m * a.tiles_n;
-  }
+void OpBuilder::push(GemmArgs& a, int kind, int iter, bool tp, bool tq, bool large) {
+  a.trans_p = tp ? 1 : 0;
+  a.trans_q = tq ? 1 : 0;
   Op op;
-  op.a = a; op.kind = kind; op.iter = iter; op.tile = tile; op.tp = tp; op.tq = tq;
+  op.a = a; op.kind = kind; op.iter = iter; op.large = large;
+  op.m = a.symmetric ? std::min(g.m, g.n) : g.m;
+  op.n = a.symmetric ? std::min(g.m, g.n) : g.n;
+  if (large) set_tile(op, 256);
   out.push_back(op);
 }
 
@@ -552,12 +615,11 @@ void OpBuilder::gram(int src, void* S, bool first, int iter) {
   a.symmetric = 1;
   a.alpha = 1.0f; a.beta = 0.0f;
   if (first) a.post = POST_INV2;
-  push(a, OP_GRAM, iter, g.tall, g.tall, pick_tile(g, OP_GRAM, cnt));
+  push(a, OP_GRAM, iter, g.tall, g.tall, large_tiles(g, OP_GRAM, cnt));
 }
 
 void OpBuilder::poly(void* S, void* dst, float diag, int iter) {
-  const TileShape tile = pick_tile(g, OP_POLY, cnt);
-  const bool symk = tile.bm == 256;
+  const bool symk = large_tiles(g, OP_POLY, cnt);
   GemmArgs a = base();
   a.P = S; a.Q = S; a.E = S; a.C = dst;
   a.strideP = a.strideQ = a.strideE = a.strideC = g.s_stride;
@@ -566,12 +628,11 @@ void OpBuilder::poly(void* S, void* dst, float diag, int iter) {
   a.symmetric = 1;
   a.alpha = hp.ns_c; a.beta = hp.ns_b;
   a.diag = diag;
-  push(a, OP_POLY, iter, symk, symk, tile);
+  push(a, OP_POLY, iter, symk, symk, symk);
 }
 
 void OpBuilder::symprod(void* P, void* Q, void* dst, int iter) {
-  const TileShape tile = pick_tile(g, OP_SYMPROD, cnt);
-  const bool symk = tile.bm == 256;
+  const bool symk = large_tiles(g, OP_SYMPROD, cnt);
   GemmArgs a = base();
   a.P = P; a.Q = Q; a.E = nullptr; a.C = dst;
   a.strideP = a.strideQ = a.strideC = g.s_stride;
@@ -579,12 +640,11 @@ void OpBuilder::symprod(void* P, void* Q, void* dst, int iter) {
   a.M = a.N = a.K = g.p_pad;
   a.symmetric = 1;
   a.alpha = 1.0f; a.beta = 0.0f;
-  push(a, OP_SYMPROD, iter, symk, symk, tile);
+  push(a, OP_SYMPROD, iter, symk, symk, symk);
 }
 
 void OpBuilder::apply(int src, void* Bm, bool with_e, float beta, bool first, bool last, int iter) {
-  const TileShape tile = pick_tile(g, OP_APPLY, cnt);
-  const bool symk = tile.bm == 256;
+  const bool symk = large_tiles(g, OP_APPLY, cnt);
   GemmArgs a = base();
   a.E = with_e ? X[src] : nullptr; a.C = X[src ^ 1];
   a.strideE = a.strideC = g.x_stride;
@@ -611,7 +671,7 @@ void OpBuilder::apply(int src, void* Bm, bool with_e, float beta, bool first, bo
     a.w_keep = 1.0f - hp.lr * hp.weight_decay;
     a.o_scale = hp.lr * hp.gamma_coeff * sqrtf((float)std::max(g.m, g.n));
   }
-  push(a, OP_APPLY, iter, tp, tq, tile);
+  push(a, OP_APPLY, iter, tp, tq, symk);
 }
 
 int OpBuilder::build() {
@@ -970,35 +1030,74 @@ int enqueue_step(mona_state* st, const mona_hparams* hp, hipStream_t s) {
     forked = true;
     for (hipStream_t q : st->side) STEP_TRY(hipStreamWaitEvent(q, st->fork_ev, 0));
   }
-  std::vector<Op> ops;
+  const bool each = st->profiling > 1;
   const int ngroups = (int)L.groups.size();
-  for (int pos = 0; pos < ngroups; ++pos) {
-    // the late group comes last: its elementwise pass must have finished, and from then on the chip is free
-    int gi = pos;
-    if (L.late_group >= 0) gi = pos == ngroups - 1 ? L.late_group : (pos < L.late_group ? pos : pos + 1);
-    Group& g = L.groups[gi];
-    const int lane = fork ? L.lane_of_group[gi] : 0;
-    hipStream_t gs = lane == 0 ? s : st->side[lane - 1];
-    int cu_cap = 0;
-    if (overlap && gi == L.late_group) {
-      STEP_TRY(hipStreamWaitEvent(s, st->late_done, 0));
-      late_forked = false;
-    } else if (overlap) {
-      cu_cap = device_cu_count() - st->late_cus;
+  std::vector<std::vector<Op>> ops(ngroups);
+  for (int gi = 0; gi < ngroups; ++gi) L.groups[gi].o_buf = OpBuilder(st, L.groups[gi], *hp, ops[gi]).build();
+  // one launch: a product of one group, or the products of a merged unit at one position of their chains
+  struct Launch {
+    int n = 0;
+    int group[kMaxMerged];
+    Op* op[kMaxMerged];
+  };
+  std::vector<std::vector<Launch>> queue(L.lanes);
+  for (const Unit& u : L.units) {
+    auto& q = queue[fork ? u.lane : 0];
+    if (u.merged && !each) {
+      for (size_t pos = 0;; ++pos) {
+        Launch l;
+        for (int gi : u.groups)
+          if (pos < ops[gi].size()) { l.group[l.n] = gi; l.op[l.n++] = &ops[gi][pos]; }
+        if (l.n == 0) break;
+        q.push_back(l);
+      }
+    } else {
+      for (int gi : u.groups)
+        for (Op& op : ops[gi]) {
+          Launch l;
+          l.n = 1; l.group[0] = gi; l.op[0] = &op;
+          q.push_back(l);
+        }
     }
-    ops.clear();
-    g.o_buf = OpBuilder(st, g, *hp, ops).build();
-    for (const Op& op : ops) {
+  }
+  // the lanes are fed in turn, so that no lane waits for the host to have enqueued all of another
+  std::vector<size_t> at(L.lanes, 0);
+  for (bool more = true; more;) {
+    more = false;
+    for (int lane = 0; lane < L.lanes; ++lane) {
+      if (at[lane] == queue[lane].size()) continue;
+      more = true;
+      Launch& l = queue[lane][at[lane]++];
+      const int gi = l.group[0];
+      const bool f32 = L.groups[gi].f32;
+      hipStream_t gs = lane == 0 ? s : st->side[lane - 1];
+      int cu_cap = 0;
+      if (overlap && gi == L.late_group) {
+        if (late_forked) STEP_TRY(hipStreamWaitEvent(s, st->late_done, 0));
+        late_forked = false;
+      } else if (overlap) {
+        cu_cap = device_cu_count() - st->late_cus;
+      }
       LaunchRecord rec;
-      const bool each = st->profiling > 1;
       if (each) {
         if (!get_event_pair(st, &rec.e0, &rec.e1)) return bail(hipErrorOutOfMemory, "hipEventCreate");
         STEP_TRY(hipEventRecord(rec.e0, gs));
       }
-      STEP_TRY(launch_ns_gemm(op.a, op.tile.bm, op.tp, op.tq, g.f32, cu_cap, gs));
+      if (l.op[0]->large) {
+        STEP_TRY(launch_ns_gemm(l.op[0]->a, cu_cap, gs));
+      } else {
+        choose_small_tile(l.op, l.n, f32);
+        // the longest chains of K first: their tiles are the last to finish
+        std::stable_sort(l.op, l.op + l.n, [](const Op* x, const Op* y) { return x->a.K > y->a.K; });
+        GemmBatch batch;
+        batch.n = l.n;
+        for (int i = 0; i < l.n; ++i) batch.a[i] = l.op[i]->a;
+        STEP_TRY(launch_ns_small(batch, f32, gs));
+      }
       if (each) {
+        const Op& op = *l.op[0];
         STEP_TRY(hipEventRecord(rec.e1, gs));
-        rec.kind = op.kind; rec.group = gi; rec.iter = op.iter; rec.tile = op.tile.bm * 1000 + op.tile.bn;
+        rec.kind = op.kind; rec.group = gi; rec.iter = op.iter; rec.tile = op.a.tile_m * 1000 + op.a.tile_n;
         rec.flops = gemm_flops(op.a);
         st->records.push_back(rec);
       }
@@ -1353,7 +1452,11 @@ int mona_plan_info(mona_state* st, int32_t ns_steps, int64_t* launches_out, doub
   for (const Group& g : L.groups) {
     ops.clear();
     OpBuilder(st, g, hp, ops).build();
-    for (const Op& op : ops) flops += gemm_flops(op.a);
+    for (Op& op : ops) {
+      Op* one = &op;
+      if (!op.large) choose_small_tile(&one, 1, g.f32);
+      flops += gemm_flops(op.a);
+    }
     launches += (int64_t)ops.size();
   }
   double bytes = 0.0;

@@ -65,7 +65,7 @@ struct GemmArgs {
   int32_t ldp, ldq, lde, ldc;
   int32_t M, N, K;          // padded problem size, multiples of the tile
   int32_t tile_m, tile_n;   // BM, BN of the kernel that will run
-  int32_t sym_ratio;        // BM / BN (symmetric products walk the block triangle with it)
+  int32_t trans_p, trans_q; // 1: the operand is stored K-major
   int32_t tiles_m, tiles_n; // M / BM, N / BN
   int32_t tiles_per_mat;    // tiles_m * tiles_n, or the triangle count when symmetric
   int32_t count;            // matrices in the group
@@ -81,6 +81,15 @@ struct GemmArgs {
   const MatDynamic* dyn;    // per matrix (EPI_UPDATE: w pointer)
   float w_keep;             // 1 - eta * lambda
   float o_scale;            // eta * gamma
+};
+
+// One launch of the small-tile kernels: the products that several shape groups run at the same position of their
+// chains (passed by value: nothing is copied from the host).
+constexpr int kMaxMerged = 8;
+struct GemmBatch {
+  int32_t n;                        // products in the batch
+  int32_t slot_end[kMaxMerged];     // workgroups per die up to and including product g (filled at launch)
+  GemmArgs a[kMaxMerged];
 };
 
 // records the text mona_last_error() returns (thread-local) and hands `code` back
@@ -102,8 +111,8 @@ hipError_t launch_plain_update(const MatStatic* stat, const MatDynamic* dyn, con
                                const BlockWork* work, int num_blocks, void* const* o_ptrs, float lr, float wd,
                                float gamma_coeff, int store_o, hipStream_t s);
 // cu_cap > 0: the persistent large-tile kernel uses at most that many CUs (the rest are busy elsewhere)
-hipError_t launch_ns_gemm(const GemmArgs& a, int tile, bool transP, bool transQ, bool f32, int cu_cap,
-                          hipStream_t s);
+hipError_t launch_ns_gemm(const GemmArgs& a, int cu_cap, hipStream_t s);   // 256 x 256 tiles, bf16
+hipError_t launch_ns_small(GemmBatch& b, bool f32, hipStream_t s);         // 64 x 64 or 128 x 128 tiles
 int device_cu_count();
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 

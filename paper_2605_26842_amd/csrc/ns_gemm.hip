@@ -14,190 +14,16 @@
 // are padded by the host to multiples of the tile and the padding is kept zero, so the main loops
 // have no bounds checks.  Symmetric products compute the block-upper-triangular tiles and mirror them.
 //
-// Three kernels:
-//   ns_gemm_bf16_dma_kernel  the workhorse: persistent, 256 x 256 tile, 8 wavefronts of 128 x 64,
-//                            v_mfma_f32_32x32x16_bf16 with fp32 accumulation, operands sent straight from
-//                            global memory into a ring of four LDS stages of K = 32 (K-major tiles
-//                            are read from LDS with the transposing read), epilogue BlockEpilogue;
-//   ns_gemm_bf16_kernel      128 x 128 tile, 4 wavefronts, register-staged LDS double buffer of K = 64
-//                            (a K-major operand is transposed in registers on its way into LDS), for
-//                            launches too small to fill the chip with large tiles;
-//   ns_gemm_f32_kernel       v_mfma_f32_32x32x2_f32, 128 x 128 tile, K step 16, for fp32 products.
-#include "mona_internal.h"
-
-#include <type_traits>
+// Here: ns_gemm_bf16_dma_kernel, for launches that fill the chip with large tiles: persistent, 256 x 256 tile,
+// 8 wavefronts of 128 x 64, v_mfma_f32_32x32x16_bf16 with fp32 accumulation, operands sent straight from global
+// memory into a ring of four LDS stages of K = 32 (K-major tiles are read from LDS with the transposing read),
+// epilogue BlockEpilogue.  Smaller launches and fp32 products: ns_small.hip.
+#include "ns_tile.h"
 
 namespace mona {
 
 namespace {
 
-typedef bf16_t bf16x8 __attribute__((ext_vector_type(8)));
-typedef bf16_t bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
-constexpr int kThreads = 256;
-constexpr int kXcds = 8;   // MI355X: 8 accelerator dies, workgroups are dealt to them round-robin
-
-// compile-time loop: f(integral_constant<int, 0>), ..., f(integral_constant<int, N - 1>)
-template <int I> struct IC { static constexpr int value = I; constexpr operator int() const { return I; } };
-template <int N, int I = 0, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(IC<I>{});
-    static_for<N, I + 1>(f);
-  }
-}
-
-// ---- tile decode ---------------------------------------------------------------------
-constexpr int kBandRows = 6;
-
-struct TileId {
-  int mat, ti, tj;
-  bool valid;
-};
-
-// Workgroup L runs on die L % 8.  Give every die one contiguous range of the logical tile
-// order (matrix-major), so that tiles that share operands share that die's L2.
-__device__ __forceinline__ TileId decode_logical(const GemmArgs& a, int logical, bool in_range) {
-  TileId t;
-  const int total = a.tiles_per_mat * a.count;
-  t.valid = in_range && logical < total;
-  t.mat = logical / a.tiles_per_mat;
-  int r = logical - t.mat * a.tiles_per_mat;
-  if (a.symmetric) {
-    // row block ti holds the column blocks from its diagonal onwards: tj >= ratio * ti,
-    // ratio = tile rows / tile columns
-    int ti = 0, row = a.tiles_n;
-    while (r >= row && row > 0) { r -= row; row -= a.sym_ratio; ++ti; }
-    t.ti = ti;
-    t.tj = ti * a.sym_ratio + r;
-  } else {
-    // Bands of up to kBandRows tile rows, walked column by column: the 32 workgroups of a die then hold
-    // a block of about 6 x 5 tiles at any time, which shares 11 operand panels in the die's L2 instead of
-    // the 18 of two full tile rows.
-    const int full = a.tiles_m / kBandRows;                 // complete bands
-    const int in_full = full * kBandRows * a.tiles_n;
-    int rows = kBandRows, first = 0;
-    if (r >= in_full) { r -= in_full; rows = a.tiles_m - full * kBandRows; first = full * kBandRows; }
-    else { const int b = r / (kBandRows * a.tiles_n); r -= b * kBandRows * a.tiles_n; first = b * kBandRows; }
-    t.tj = r / rows;
-    t.ti = first + (r - t.tj * rows);
-  }
-  return t;
-}
-
-// One tile per workgroup: workgroup L runs on die L % 8.
-__device__ __forceinline__ TileId decode_tile(const GemmArgs& a) {
-  const int per_xcd = gridDim.x / kXcds;
-  return decode_logical(a, (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds, true);
-}
-
-// ---- LDS layout ------------------------------------------------------------------------
-// An operand tile is R rows of 64 bf16 (128 bytes = 8 chunks of 16 bytes).  The chunk index is
-// XOR-swizzled with the row so that 16 consecutive rows at one logical chunk fall on 16
-// different 16-byte bank groups (the fragment read), as do 2 rows x 8 chunks (the tile store).
-__device__ __forceinline__ int lds_slot(int row, int chunk) {
-  return row * 8 + (chunk ^ ((row & 7) ^ ((row >> 3) & 1)));
-}
-
-__device__ __forceinline__ uint32_t pack_lo(uint32_t x, uint32_t y) {  // (x.lo16, y.lo16)
-  return __builtin_amdgcn_perm(y, x, 0x05040100u);
-}
-__device__ __forceinline__ uint32_t pack_hi(uint32_t x, uint32_t y) {  // (x.hi16, y.hi16)
-  return __builtin_amdgcn_perm(y, x, 0x07060302u);
-}
-
-// ---- operand loaders (global -> registers -> LDS) ---------------------------------------
-// R: rows of the tile (BM or BN).  Each thread moves R/32 chunks of 16 bytes per K step.
-template <int R, bool TRANS>
-struct Loader {
-  static constexpr int kRegs = R / 32;
-  u32x4 v[kRegs];
-
-  // src: first element of this matrix; r0: first tile row; k0: first k; ld: leading dimension
-  __device__ __forceinline__ void load(const bf16_t* __restrict__ src, int ld, int r0, int k0) {
-    const int tid = threadIdx.x;
-    if constexpr (!TRANS) {
-      const int chunk = tid & 7, row = tid >> 3;
-      static_for<kRegs>([&](auto i) {
-        v[i] = *reinterpret_cast<const u32x4*>(src + (size_t)(r0 + row + 32 * i) * ld + k0 + chunk * 8);
-      });
-    } else {
-      // K-major storage: element (k, r) at src[k * ld + r].  Each thread takes kRegs consecutive
-      // k-rows of 8 consecutive r.
-      constexpr int kKB = 64 / kRegs;           // k-blocks per K step
-      const int kb = tid % kKB, rb = tid / kKB;
-      static_for<kRegs>([&](auto i) {
-        v[i] = *reinterpret_cast<const u32x4*>(src + (size_t)(k0 + kb * kRegs + i) * ld + r0 + rb * 8);
-      });
-    }
-  }
-
-  __device__ __forceinline__ void store(u32x4* __restrict__ lds) const {
-    const int tid = threadIdx.x;
-    if constexpr (!TRANS) {
-      const int chunk = tid & 7, row = tid >> 3;
-      static_for<kRegs>([&](auto i) { lds[lds_slot(row + 32 * i, chunk)] = v[i]; });
-    } else {
-      constexpr int kKB = 64 / kRegs;
-      const int kb = tid % kKB, rb = tid / kKB;
-      // transpose the kRegs x 8 block held in v[] to 8 rows of kRegs k-values
-      // word(i, cw): 32-bit word cw of k-row i, i.e. columns 2 cw and 2 cw + 1
-      auto word = [&](int i, int cw) -> uint32_t {
-        return cw == 0 ? v[i].x : cw == 1 ? v[i].y : cw == 2 ? v[i].z : v[i].w;
-      };
-      if constexpr (kRegs == 8) {
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-          u32x4 o;
-          const int cw = c >> 1;
-          if ((c & 1) == 0) {
-            o.x = pack_lo(word(0, cw), word(1, cw));
-            o.y = pack_lo(word(2, cw), word(3, cw));
-            o.z = pack_lo(word(4, cw), word(5, cw));
-            o.w = pack_lo(word(6, cw), word(7, cw));
-          } else {
-            o.x = pack_hi(word(0, cw), word(1, cw));
-            o.y = pack_hi(word(2, cw), word(3, cw));
-            o.z = pack_hi(word(4, cw), word(5, cw));
-            o.w = pack_hi(word(6, cw), word(7, cw));
-          }
-          lds[lds_slot(rb * 8 + c, kb)] = o;
-        }
-      } else {
-        static_assert(kRegs == 4 || kRegs == 8, "tile rows must be 128 or 256");
-        // 4 k-values per row: half a chunk
-        u32x2* lds2 = reinterpret_cast<u32x2*>(lds);
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-          u32x2 o;
-          const int cw = c >> 1;
-          if ((c & 1) == 0) {
-            o.x = pack_lo(word(0, cw), word(1, cw));
-            o.y = pack_lo(word(2, cw), word(3, cw));
-          } else {
-            o.x = pack_hi(word(0, cw), word(1, cw));
-            o.y = pack_hi(word(2, cw), word(3, cw));
-          }
-          lds2[lds_slot(rb * 8 + c, kb >> 1) * 2 + (kb & 1)] = o;
-        }
-      }
-    }
-  }
-};
-
-__device__ __forceinline__ float to_f32(bf16_t v) { return (float)v; }
-__device__ __forceinline__ float to_f32(float v) { return v; }
-
-// ---- epilogue -----------------------------------------------------------------------------
-// The accumulators of a wavefront (MI x NI blocks of 32 x 32; acc[v] of a block sits at
-// row = (v / 4) * 8 + (lane / 32) * 4 + (v % 4), col = lane % 32) are staged through LDS one
-// 32-row band at a time, so that every global access of the epilogue is a 16-byte vector that
-// runs along a row:  out = post * (beta * E + alpha * acc), then either a plain store (plus the
-// mirrored store of a symmetric product) or the parameter update of Eq. muon_update.
 // Orders the LDS traffic of one wavefront for the compiler (lanes exchange data through a region
 // only this wavefront touches; the LDS unit itself executes a wavefront's accesses in order).
 __device__ __forceinline__ void wave_sync() {
@@ -206,191 +32,6 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <typename T> struct Chunk;           // 16 bytes of T
-template <> struct Chunk<bf16_t> { static constexpr int N = 8; typedef bf16x8 vec; };
-template <> struct Chunk<float> { static constexpr int N = 4; typedef f32x4 vec; };
-
-template <typename T, int WN, int MI, int NI>
-struct Epilogue {
-  static constexpr int CH = Chunk<T>::N;
-  typedef typename Chunk<T>::vec vec_t;
-  static constexpr int LDW = WN + 4;             // floats per staged row (+4: the two half-waves
-                                                 // write rows 4 apart, keep them on different banks)
-  static constexpr int CPR = WN / CH;            // chunks per row
-  static constexpr int PASSES = 32 * CPR / 64;   // chunks per lane per band
-
-  const GemmArgs& a;
-  int lane, row_w0, col_w0;
-  bool mirror, update, skip_w, w_vec_ok, w_pref;
-  float post;
-  const T* __restrict__ E;
-  T* __restrict__ C;
-  int wm_real, wn_real, w_is_bf16;
-  void* wptr;
-  vec_t ev[2][PASSES];       // E operands of the current and the next band
-  bf16x8 wv[2][PASSES];      // bf16 parameters of the current and the next band (update only)
-
-  __device__ __forceinline__ Epilogue(const GemmArgs& args, int tmat, int row0, int col0, bool mir)
-      : a(args), lane(threadIdx.x & 63), row_w0(row0), col_w0(col0), mirror(mir) {
-    const int mi = a.members ? a.members[tmat] : tmat;
-    post = 1.0f;
-    if (a.post == POST_INV) post = a.scales[mi].inv;
-    else if (a.post == POST_INV2) post = a.scales[mi].inv2;
-    E = a.E ? static_cast<const T*>(a.E) + (size_t)tmat * a.strideE : nullptr;
-    C = static_cast<T*>(a.C) + (size_t)tmat * a.strideC;
-    update = a.epilogue == EPI_UPDATE;
-    wm_real = wn_real = w_is_bf16 = 0;
-    skip_w = true;
-    wptr = nullptr;
-    if (update) {
-      const MatStatic& ms = a.stat[mi];
-      wm_real = ms.m; wn_real = ms.n; w_is_bf16 = ms.w_dtype;
-      wptr = a.dyn[mi].w;
-      skip_w = (a.scales[mi].status & 2u) != 0;
-    }
-    w_vec_ok = (wn_real % CH) == 0;
-    // bf16 parameters whose rows are whole 16-byte chunks are fetched a band ahead
-    w_pref = update && !skip_w && w_is_bf16 && CH == 8 && w_vec_ok;
-  }
-
-  // Issue the global loads band `band` needs (E chunks, and the parameter chunks of an update)
-  // into slot band & 1.  Called a band ahead so the latency overlaps other work.
-  template <int BAND>
-  __device__ __forceinline__ void prefetch() {
-    constexpr int slot = BAND & 1;
-#pragma unroll
-    for (int pss = 0; pss < PASSES; ++pss) {
-      const int idx = pss * 64 + lane;
-      const int grow = row_w0 + BAND * 32 + idx / CPR, gcol = col_w0 + (idx % CPR) * CH;
-      if (E != nullptr) ev[slot][pss] = *reinterpret_cast<const vec_t*>(E + (size_t)grow * a.lde + gcol);
-      if constexpr (CH == 8) {
-        if (w_pref && grow < wm_real && gcol + CH <= wn_real)
-          wv[slot][pss] = *reinterpret_cast<const bf16x8*>(static_cast<const bf16_t*>(wptr) +
-                                                          (size_t)grow * wn_real + gcol);
-      }
-    }
-  }
-
-  // prefetch<0>() must have been called.  lds_f: LDS scratch of (#wavefronts x 32 x LDW) floats.
-  __device__ __forceinline__ void run(f32x16 (&acc)[MI][NI], float* __restrict__ lds_f) {
-    const int wave = threadIdx.x >> 6;
-    float* __restrict__ stage = lds_f + wave * (32 * LDW);   // private to this wavefront
-    // Every wavefront has finished reading operand tiles before any staging overwrites them.  From
-    // here on a wavefront only touches its own staging rows, so no workgroup barrier (and above all
-    // no fence, which would wait for the global stores in flight) is needed between bands.
-    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this wavefront's LDS reads have returned
-    __builtin_amdgcn_s_barrier();
-    static_for<MI>([&](auto i) {
-      constexpr int slot = i & 1;
-      if constexpr (i + 1 < MI) prefetch<i + 1>();
-      wave_sync();         // previous band fully consumed
-      static_for<NI>([&](auto j) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int r = (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
-          stage[r * LDW + j * 32 + (lane & 31)] = acc[i][j][v];
-        }
-      });
-      wave_sync();
-#pragma unroll
-      for (int pss = 0; pss < PASSES; ++pss) {
-        const int idx = pss * 64 + lane;
-        const int r = idx / CPR, ch = idx % CPR;
-        const int grow = row_w0 + i * 32 + r, gcol = col_w0 + ch * CH;
-        float val[CH];
-        {
-          const f32x4* src = reinterpret_cast<const f32x4*>(stage + r * LDW + ch * CH);
-#pragma unroll
-          for (int q = 0; q < CH / 4; ++q) {
-            const f32x4 t4 = src[q];
-            val[q * 4 + 0] = t4.x; val[q * 4 + 1] = t4.y; val[q * 4 + 2] = t4.z; val[q * 4 + 3] = t4.w;
-          }
-        }
-        if (E != nullptr) {
-#pragma unroll
-          for (int e = 0; e < CH; ++e) val[e] = post * (a.alpha * val[e] + a.beta * to_f32(ev[slot][pss][e]));
-        } else {
-#pragma unroll
-          for (int e = 0; e < CH; ++e) val[e] = post * (a.alpha * val[e]);
-        }
-        if (a.diag != 0.0f) {
-#pragma unroll
-          for (int e = 0; e < CH; ++e) val[e] += (grow == gcol + e) ? a.diag : 0.0f;
-        }
-        vec_t ov;
-#pragma unroll
-        for (int e = 0; e < CH; ++e) ov[e] = (T)val[e];
-        if (!update || a.store_out) *reinterpret_cast<vec_t*>(C + (size_t)grow * a.ldc + gcol) = ov;
-        if (mirror) {
-          // keep the rounded result for the transposed store below
-          f32x4* dst = reinterpret_cast<f32x4*>(stage + r * LDW + ch * CH);
-#pragma unroll
-          for (int q = 0; q < CH / 4; ++q) {
-            f32x4 t4 = {to_f32(ov[q * 4 + 0]), to_f32(ov[q * 4 + 1]), to_f32(ov[q * 4 + 2]), to_f32(ov[q * 4 + 3])};
-            dst[q] = t4;
-          }
-        }
-        if (update && !skip_w && grow < wm_real) {
-          // W <- (1 - eta lambda) W - eta gamma O, O as stored in the working precision
-          const size_t wi = (size_t)grow * wn_real + gcol;
-          if (w_vec_ok && gcol + CH <= wn_real) {
-            if (w_is_bf16) {
-              typedef bf16_t wv_t __attribute__((ext_vector_type(CH)));
-              wv_t* wp = reinterpret_cast<wv_t*>(static_cast<bf16_t*>(wptr) + wi);
-              wv_t w_in;
-              if constexpr (CH == 8) w_in = wv[slot][pss];
-              else w_in = *wp;
-#pragma unroll
-              for (int e = 0; e < CH; ++e) w_in[e] = (bf16_t)(a.w_keep * (float)w_in[e] - a.o_scale * to_f32(ov[e]));
-              *wp = w_in;
-            } else {
-              f32x4* wp = reinterpret_cast<f32x4*>(static_cast<float*>(wptr) + wi);
-#pragma unroll
-              for (int q = 0; q < CH / 4; ++q) {
-                f32x4 w4 = wp[q];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) w4[e] = a.w_keep * w4[e] - a.o_scale * to_f32(ov[q * 4 + e]);
-                wp[q] = w4;
-              }
-            }
-          } else {
-#pragma unroll
-            for (int e = 0; e < CH; ++e) {
-              if (gcol + e < wn_real) {
-                if (w_is_bf16) {
-                  bf16_t* w = static_cast<bf16_t*>(wptr) + wi + e;
-                  *w = (bf16_t)(a.w_keep * (float)*w - a.o_scale * to_f32(ov[e]));
-                } else {
-                  float* w = static_cast<float*>(wptr) + wi + e;
-                  *w = a.w_keep * *w - a.o_scale * to_f32(ov[e]);
-                }
-              }
-            }
-          }
-        }
-      }
-      if (mirror) {
-        // transposed copy of this band: C[col][row], 16-byte pieces along the band's 32 rows
-        wave_sync();
-        constexpr int RCH = 32 / CH;               // row-chunks per band
-        constexpr int MPASSES = WN * RCH / 64;
-        constexpr int RPI = 64 / RCH;              // rows of the mirrored tile one store touches: all RCH pieces
-                                                   // of a row go out together (stores that touch fewer rows
-                                                   // are cheaper)
-#pragma unroll
-        for (int pss = 0; pss < MPASSES; ++pss) {
-          const int c = pss * RPI + lane % RPI, rc = lane / RPI;
-          vec_t ov;
-#pragma unroll
-          for (int e = 0; e < CH; ++e) ov[e] = (T)stage[(rc * CH + e) * LDW + c];
-          *reinterpret_cast<vec_t*>(C + (size_t)(col_w0 + c) * a.ldc + row_w0 + i * 32 + rc * CH) = ov;
-        }
-      }
-    });
-  }
-};
-
-#define MONA_AS3_EPI __attribute__((address_space(3)))
 // Eight transposed LDS reads (4 rows x 16 columns of bf16 per group of 16 lanes and read): four column slabs
 // of 16 (32 bytes apart) for rows r0 .. r0 + 3, and the same for rows r0 + 4 .. r0 + 7 (1024 bytes = 4 staged
 // rows further on), then one wait.  A free function: an asm statement cannot name variables captured by a
@@ -560,7 +201,7 @@ struct BlockEpilogue {
     }
     const int srow = lane & 31, shalf = lane >> 5;       // staging writes: row and 4-column half
     const int prow = lane >> 3, q = lane & 7;            // passes: row inside the pass and 8-column chunk
-    const uint32_t stage_addr = (uint32_t)(uintptr_t)(MONA_AS3_EPI const char*)stage;
+    const uint32_t stage_addr = (uint32_t)(uintptr_t)(MONA_AS3 const char*)stage;
     static_for<MI>([&](auto i) {
       wave_sync();         // previous block row fully consumed
       static_for<NI>([&](auto j) {
@@ -668,94 +309,6 @@ struct BlockEpilogue {
   }
 };
 
-// ---- bf16 kernel -----------------------------------------------------------------------------
-template <int BM, int BN, bool TP, bool TQ>
-__global__ __launch_bounds__(kThreads) void ns_gemm_bf16_kernel(const GemmArgs a) {
-  constexpr int BK = 64;
-  constexpr int WM = BM / 2, WN = BN / 2;   // per-wavefront tile
-  constexpr int MI = WM / 32, NI = WN / 32; // MFMA blocks per wavefront
-  __shared__ __attribute__((aligned(16))) u32x4 lds[2][(BM + BN) * 8];
-
-  const TileId t = decode_tile(a);
-  if (!t.valid) return;
-
-  const bf16_t* __restrict__ P = static_cast<const bf16_t*>(a.P) + (size_t)t.mat * a.strideP;
-  const bf16_t* __restrict__ Q = static_cast<const bf16_t*>(a.Q) + (size_t)t.mat * a.strideQ;
-  const int m0 = t.ti * BM, n0 = t.tj * BN;
-
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-
-  f32x16 acc[MI][NI];
-#pragma unroll
-  for (int i = 0; i < MI; ++i)
-#pragma unroll
-    for (int j = 0; j < NI; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-
-  Loader<BM, TP> lp;
-  Loader<BN, TQ> lq;
-  const int KT = a.K / BK;
-
-  // Software pipeline: tile kt+1 travels global -> registers while tile kt is multiplied, and is
-  // written to the other LDS buffer during the last quarter of the step; MFMA fragments are
-  // double-buffered so the reads of quarter kk+1 are in flight while quarter kk is multiplied.
-  const int frow = lane & 31, fchunk = lane >> 5;
-  bf16x8 fa[2][MI], fb[2][NI];
-  auto load_frags = [&](auto slot, int buf, int kk) {
-    const u32x4* __restrict__ ps = lds[buf];
-    const u32x4* __restrict__ qs = lds[buf] + BM * 8;
-    static_for<MI>([&](auto i) {
-      fa[slot][i] = __builtin_bit_cast(bf16x8, ps[lds_slot(wm * WM + i * 32 + frow, kk * 2 + fchunk)]);
-    });
-    static_for<NI>([&](auto j) {
-      fb[slot][j] = __builtin_bit_cast(bf16x8, qs[lds_slot(wn * WN + j * 32 + frow, kk * 2 + fchunk)]);
-    });
-  };
-  auto multiply = [&](auto slot) {
-    static_for<MI>([&](auto i) {
-      static_for<NI>([&](auto j) {
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[slot][i], fb[slot][j], acc[i][j], 0, 0, 0);
-      });
-    });
-  };
-  auto kstep = [&](auto has_next, int kt) {
-    const int buf = kt & 1;
-    if constexpr (has_next) {
-      lp.load(P, a.ldp, m0, (kt + 1) * BK);
-      lq.load(Q, a.ldq, n0, (kt + 1) * BK);
-    }
-    // keep the phases of the step in program order: the loads above must be issued a full step
-    // before their data is needed, not sunk next to the LDS writes that consume them
-    __builtin_amdgcn_sched_barrier(0);
-    static_for<BK / 16>([&](auto kk) {
-      if constexpr (kk + 1 < BK / 16) load_frags(IC<(kk + 1) & 1>{}, buf, kk + 1);
-      if constexpr (has_next && kk == BK / 16 - 1) {
-        lp.store(lds[buf ^ 1]);
-        lq.store(lds[buf ^ 1] + BM * 8);
-      }
-      multiply(IC<kk & 1>{});
-      __builtin_amdgcn_sched_barrier(0);
-    });
-    __syncthreads();
-    if constexpr (has_next) load_frags(IC<0>{}, buf ^ 1, 0);
-  };
-
-  lp.load(P, a.ldp, m0, 0);
-  lq.load(Q, a.ldq, n0, 0);
-  lp.store(lds[0]);
-  lq.store(lds[0] + BM * 8);
-  __syncthreads();
-  load_frags(IC<0>{}, 0, 0);
-  for (int kt = 0; kt + 1 < KT; ++kt) kstep(IC<1>{}, kt);
-  kstep(IC<0>{}, KT - 1);
-
-  Epilogue<bf16_t, WN, MI, NI> epi(a, t.mat, m0 + wm * WM, n0 + wn * WN, a.symmetric && (t.ti != t.tj));
-  epi.template prefetch<0>();
-  epi.run(acc, reinterpret_cast<float*>(&lds[0][0]));
-}
-
 // ---- bf16 kernel, direct-to-LDS pipeline ------------------------------------------------------
 // Block tile BM x BN, WGM x WGN wavefronts of 128 x 64 each, K step 32, a ring of STAGES LDS
 // stages filled straight from global memory (global_load_lds, 16 bytes per lane, no staging
@@ -770,9 +323,6 @@ __global__ __launch_bounds__(kThreads) void ns_gemm_bf16_kernel(const GemmArgs a
 //     fetch a 4 (k) x 16 (r) block and each receives the 4 k-values of one r.
 // A direct load writes lane l's 16 bytes at (wave-uniform base) + 16 l, so the swizzle is applied
 // by choosing which global chunk each lane fetches.
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-#define MONA_AS1 __attribute__((address_space(1)))
-#define MONA_AS3 __attribute__((address_space(3)))
 
 // A fragment as the LDS read instructions deliver it.  The registers are written when the data
 // returns, not when the read is issued, so until the matching wait they must stay exactly where
@@ -824,8 +374,6 @@ __device__ __forceinline__ void lds_read_t(FragT& f, uint32_t addr) {
   asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.lo) : "v"(addr), "n"(OFF));
   asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.hi) : "v"(addr), "n"(OFF + PITCH4));
 }
-// s_waitcnt vmcnt(n), leaving the other counters alone (gfx9 encoding)
-#define MONA_WAIT_VM(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
 
 template <int BM, int BN, int WGM, int WGN, int STAGES, int MIN_BLOCKS, bool TP, bool TQ, bool UPD, bool HAS_E, bool DIAG>
 __global__ __launch_bounds__(64 * WGM * WGN, MIN_BLOCKS) void ns_gemm_bf16_dma_kernel(const GemmArgs a) {
@@ -1084,117 +632,6 @@ __global__ __launch_bounds__(64 * WGM * WGN, MIN_BLOCKS) void ns_gemm_bf16_dma_k
     t = next;
   }
 }
-#undef MONA_WAIT_VM
-
-// ---- fp32 kernel ------------------------------------------------------------------------------
-// 128 x 128 tile, K step 16.  LDS holds each operand k-major ([k][row], padded) so a fragment
-// read (32 consecutive rows at one k) is conflict-free.
-template <bool TP, bool TQ>
-__global__ __launch_bounds__(kThreads) void ns_gemm_f32_kernel(const GemmArgs a) {
-  constexpr int BM = 128, BN = 128, BK = 16;
-  constexpr int LDR = 128 + 4;   // padded row count per k
-  constexpr int kStageFloats = 4 * 32 * (64 + 4);          // epilogue staging, 4 wavefronts
-  constexpr int kTileFloats = 2 * 2 * BK * LDR;
-  __shared__ __attribute__((aligned(16))) float lds_raw[kTileFloats > kStageFloats ? kTileFloats : kStageFloats];
-  float (*lds)[2][BK * LDR] = reinterpret_cast<float (*)[2][BK * LDR]>(lds_raw);
-
-  const TileId t = decode_tile(a);
-  if (!t.valid) return;
-  const float* __restrict__ P = static_cast<const float*>(a.P) + (size_t)t.mat * a.strideP;
-  const float* __restrict__ Q = static_cast<const float*>(a.Q) + (size_t)t.mat * a.strideQ;
-  const int m0 = t.ti * BM, n0 = t.tj * BN;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int tid = threadIdx.x;
-
-  f32x16 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-
-  // each thread moves 2 x float4 per operand per K step
-  f32x4 rp[2], rq[2];
-  auto gload = [&](const float* __restrict__ src, int ld, int r0, int k0, bool trans, f32x4* r) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int id = tid + i * kThreads;               // 0..511 float4 slots of a 128 x 16 tile
-      if (!trans) {
-        const int row = id >> 2, kq = id & 3;          // 4 float4 per row (16 k)
-        r[i] = *reinterpret_cast<const f32x4*>(src + (size_t)(r0 + row) * ld + k0 + kq * 4);
-      } else {
-        const int k = id >> 5, rq4 = id & 31;          // 32 float4 per k-row (128 rows)
-        r[i] = *reinterpret_cast<const f32x4*>(src + (size_t)(k0 + k) * ld + r0 + rq4 * 4);
-      }
-    }
-  };
-  auto lstore = [&](float* __restrict__ dst, bool trans, const f32x4* r) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int id = tid + i * kThreads;
-      if (!trans) {
-        const int row = id >> 2, kq = id & 3;
-        dst[(kq * 4 + 0) * LDR + row] = r[i].x;
-        dst[(kq * 4 + 1) * LDR + row] = r[i].y;
-        dst[(kq * 4 + 2) * LDR + row] = r[i].z;
-        dst[(kq * 4 + 3) * LDR + row] = r[i].w;
-      } else {
-        const int k = id >> 5, rq4 = id & 31;
-        *reinterpret_cast<f32x4*>(dst + k * LDR + rq4 * 4) = r[i];
-      }
-    }
-  };
-
-  const int KT = a.K / BK;
-  gload(P, a.ldp, m0, 0, TP, rp);
-  gload(Q, a.ldq, n0, 0, TQ, rq);
-  lstore(lds[0][0], TP, rp);
-  lstore(lds[0][1], TQ, rq);
-  __syncthreads();
-  const int frow = lane & 31, fk = lane >> 5;
-  for (int kt = 0; kt < KT; ++kt) {
-    const int buf = kt & 1;
-    if (kt + 1 < KT) {
-      gload(P, a.ldp, m0, (kt + 1) * BK, TP, rp);
-      gload(Q, a.ldq, n0, (kt + 1) * BK, TQ, rq);
-    }
-    const float* __restrict__ sp = lds[buf][0];
-    const float* __restrict__ sq = lds[buf][1];
-#pragma unroll
-    for (int kk = 0; kk < BK / 2; ++kk) {
-      float fa[2], fb[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) fa[i] = sp[(kk * 2 + fk) * LDR + wm * 64 + i * 32 + frow];
-#pragma unroll
-      for (int j = 0; j < 2; ++j) fb[j] = sq[(kk * 2 + fk) * LDR + wn * 64 + j * 32 + frow];
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i], fb[j], acc[i][j], 0, 0, 0);
-    }
-    if (kt + 1 < KT) {
-      lstore(lds[buf ^ 1][0], TP, rp);
-      lstore(lds[buf ^ 1][1], TQ, rq);
-    }
-    __syncthreads();
-  }
-
-  Epilogue<float, 64, 2, 2> epi(a, t.mat, m0 + wm * 64, n0 + wn * 64, a.symmetric && (t.ti != t.tj));
-  epi.template prefetch<0>();
-  epi.run(acc, lds_raw);
-}
-
-template <int BM, int BN>
-hipError_t launch_bf16(const GemmArgs& a, bool tp, bool tq, int grid, hipStream_t s) {
-  if (!tp && !tq) hipLaunchKernelGGL((ns_gemm_bf16_kernel<BM, BN, false, false>), dim3(grid), dim3(kThreads), 0, s, a);
-  else if (!tp && tq) hipLaunchKernelGGL((ns_gemm_bf16_kernel<BM, BN, false, true>), dim3(grid), dim3(kThreads), 0, s, a);
-  else if (tp && tq) hipLaunchKernelGGL((ns_gemm_bf16_kernel<BM, BN, true, true>), dim3(grid), dim3(kThreads), 0, s, a);
-  else return hipErrorInvalidValue;   // (transposed P, plain Q) never occurs in the plan
-  return hipGetLastError();
-}
 
 }  // namespace
 
@@ -1208,52 +645,41 @@ int device_cu_count() {
   return num_cus;
 }
 
-hipError_t launch_ns_gemm(const GemmArgs& a, int tile, bool transP, bool transQ, bool f32, int cu_cap, hipStream_t s) {
+hipError_t launch_ns_gemm(const GemmArgs& a, int cu_cap, hipStream_t s) {
   const long long total = (long long)a.tiles_per_mat * a.count;
   if (total <= 0) return hipSuccess;
-  if (total > 0x7fffff00LL) return hipErrorInvalidValue;
+  if (total > 0x7fffff00LL || a.tile_m != 256 || a.tile_n != 256) return hipErrorInvalidValue;
   const int grid = (int)((total + kXcds - 1) / kXcds) * kXcds;
-  if (f32) {
-    if (tile != 128) return hipErrorInvalidValue;
-    if (!transP && !transQ) hipLaunchKernelGGL((ns_gemm_f32_kernel<false, false>), dim3(grid), dim3(kThreads), 0, s, a);
-    else if (!transP && transQ) hipLaunchKernelGGL((ns_gemm_f32_kernel<false, true>), dim3(grid), dim3(kThreads), 0, s, a);
-    else if (transP && transQ) hipLaunchKernelGGL((ns_gemm_f32_kernel<true, true>), dim3(grid), dim3(kThreads), 0, s, a);
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
-  }
-  if (tile == 256 && a.tile_n == 256) {
-    // persistent: one workgroup per CU walks its share of the tiles
-    static const int num_cus = device_cu_count();
-    // (cu_cap: the caller keeps some CUs for a kernel that runs beside this one; every workgroup of a
-    // persistent launch must be resident at once or the tile walk falls into two rounds)
-    const int cap = (cu_cap >= kXcds && cu_cap < num_cus) ? cu_cap / kXcds * kXcds : num_cus;
-    const int pgrid = grid < cap ? grid : cap;
+  const bool transP = a.trans_p != 0, transQ = a.trans_q != 0;
+  // persistent: one workgroup per CU walks its share of the tiles
+  static const int num_cus = device_cu_count();
+  // (cu_cap: the caller keeps some CUs for a kernel that runs beside this one; every workgroup of a
+  // persistent launch must be resident at once or the tile walk falls into two rounds)
+  const int cap = (cu_cap >= kXcds && cu_cap < num_cus) ? cu_cap / kXcds * kXcds : num_cus;
+  const int pgrid = grid < cap ? grid : cap;
 #define MONA_LAUNCH_DMA(TP_, TQ_, UPD_, E_)                                                                        \
   hipLaunchKernelGGL((ns_gemm_bf16_dma_kernel<256, 256, 2, 4, 4, 1, TP_, TQ_, UPD_, E_, false>), dim3(pgrid), dim3(512), 0, s, a)
-    const bool upd = a.epilogue == EPI_UPDATE, has_e = a.E != nullptr;
-    // the plan uses: Gram and the products of two commuting symmetric matrices (no E; both operands row-major,
-    // or both K-major); poly and the apply of a wide matrix (E, both operands K-major); the apply of a tall
-    // matrix (P row-major, Q K-major; with E in the literal schedule, without in the fused one); and the
-    // apply that carries the update (P row-major: a K-major P leaves it no registers; with or without E)
-    if (a.diag != 0.0f) {
-      // only the poly launches of the fused schedule (symmetric, E, both operands K-major) add a diagonal term
-      if (!(transP && transQ && !upd && has_e && a.symmetric)) return hipErrorInvalidValue;
-      hipLaunchKernelGGL((ns_gemm_bf16_dma_kernel<256, 256, 2, 4, 4, 1, true, true, false, true, true>), dim3(pgrid),
-                         dim3(512), 0, s, a);
-    }
-    else if (!transP && !transQ && !upd && !has_e) MONA_LAUNCH_DMA(false, false, false, false);
-    else if (transP && transQ && !upd && !has_e) MONA_LAUNCH_DMA(true, true, false, false);
-    else if (transP && transQ && !upd && has_e) MONA_LAUNCH_DMA(true, true, false, true);
-    else if (!transP && transQ && !upd && has_e) MONA_LAUNCH_DMA(false, true, false, true);
-    else if (!transP && transQ && !upd && !has_e) MONA_LAUNCH_DMA(false, true, false, false);
-    else if (!transP && transQ && upd && has_e) MONA_LAUNCH_DMA(false, true, true, true);
-    else if (!transP && transQ && upd && !has_e) MONA_LAUNCH_DMA(false, true, true, false);
-    else return hipErrorInvalidValue;
-#undef MONA_LAUNCH_DMA
-    return hipGetLastError();
+  const bool upd = a.epilogue == EPI_UPDATE, has_e = a.E != nullptr;
+  // the plan uses: Gram and the products of two commuting symmetric matrices (no E; both operands row-major,
+  // or both K-major); poly and the apply of a wide matrix (E, both operands K-major); the apply of a tall
+  // matrix (P row-major, Q K-major; with E in the literal schedule, without in the fused one); and the
+  // apply that carries the update (P row-major: a K-major P leaves it no registers; with or without E)
+  if (a.diag != 0.0f) {
+    // only the poly launches of the fused schedule (symmetric, E, both operands K-major) add a diagonal term
+    if (!(transP && transQ && !upd && has_e && a.symmetric)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((ns_gemm_bf16_dma_kernel<256, 256, 2, 4, 4, 1, true, true, false, true, true>), dim3(pgrid),
+                       dim3(512), 0, s, a);
   }
-  if (tile == 128) return launch_bf16<128, 128>(a, transP, transQ, grid, s);
-  return hipErrorInvalidValue;
+  else if (!transP && !transQ && !upd && !has_e) MONA_LAUNCH_DMA(false, false, false, false);
+  else if (transP && transQ && !upd && !has_e) MONA_LAUNCH_DMA(true, true, false, false);
+  else if (transP && transQ && !upd && has_e) MONA_LAUNCH_DMA(true, true, false, true);
+  else if (!transP && transQ && !upd && has_e) MONA_LAUNCH_DMA(false, true, false, true);
+  else if (!transP && transQ && !upd && !has_e) MONA_LAUNCH_DMA(false, true, false, false);
+  else if (!transP && transQ && upd && has_e) MONA_LAUNCH_DMA(false, true, true, true);
+  else if (!transP && transQ && upd && !has_e) MONA_LAUNCH_DMA(false, true, true, false);
+  else return hipErrorInvalidValue;
+#undef MONA_LAUNCH_DMA
+  return hipGetLastError();
 }
 
 }  // namespace mona

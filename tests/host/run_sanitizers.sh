@@ -9,7 +9,7 @@ mkdir -p "$out"
 src="$root/paper_2605_26842_amd/csrc"
 san="-Xarch_host -fsanitize=address -Xarch_host -fsanitize=undefined -Xarch_host -fno-omit-frame-pointer"
 objs=""
-for f in mona_api state_update ns_gemm adamw; do
+for f in mona_api state_update ns_gemm ns_small adamw; do
   /opt/rocm/bin/hipcc --offload-arch=gfx950 -O1 -g -std=c++17 -fPIC -fno-gpu-rdc \
     -Xclang -target-feature -Xclang -packed-fp32-ops -Wno-unused-command-line-argument $san \
     -c "$src/$f.hip" -o "$out/$f.o" 2>&1 | grep -v "not a recognized feature" || true
