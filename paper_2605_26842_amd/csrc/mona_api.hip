@@ -99,6 +99,7 @@ struct Layout {
   std::vector<int> group_of, rank_in_group;
   std::vector<BlockWork> blocks;       // ordered: fp32-gradient matrices first, then bf16
   std::vector<int> first_block, num_blocks;
+  int max_blocks = 0;                  // most blocks of any matrix
   // The block table is ordered: early groups (fp32-gradient matrices, then bf16), then the late group (same).
   int range_end[4] = {0, 0, 0, 0};     // ends of those four ranges of blocks
   std::vector<Unit> units;             // what the products of the groups are launched as, in launch order per lane
@@ -408,6 +409,7 @@ void build_layout(const mona_matrix* mats, int count, const mona_options& opt, b
       const int nb = (int)((ne + kEwChunk - 1) / kEwChunk);
       L.first_block[i] = (int)L.blocks.size();
       L.num_blocks[i] = nb;
+      L.max_blocks = std::max(L.max_blocks, nb);
       for (int c = 0; c < nb; ++c) L.blocks.push_back(BlockWork{i, c});
     }
     L.range_end[pass] = (int)L.blocks.size();
@@ -1007,8 +1009,8 @@ int enqueue_step(mona_state* st, const mona_hparams* hp, hipStream_t s) {
     STEP_TRY(hipStreamWaitEvent(st->late_stream, st->late_fork, 0));
     STEP_TRY(pass(L.range_end[1], L.range_end[2], 0, st->late_stream));
     STEP_TRY(pass(L.range_end[2], L.range_end[3], 1, st->late_stream));
-    STEP_TRY(launch_norm_finalize(stat, partials, scales, order + L.num_early, count - L.num_early, hp->ns_eps,
-                                  st->late_stream));
+    STEP_TRY(launch_norm_finalize(stat, partials, scales, order + L.num_early, count - L.num_early,
+                                  L.max_blocks, hp->ns_eps, st->late_stream));
     STEP_TRY(hipEventRecord(st->late_done, st->late_stream));
   }
   STEP_TRY(pass(0, L.range_end[0], 0, s));
@@ -1018,7 +1020,8 @@ int enqueue_step(mona_state* st, const mona_hparams* hp, hipStream_t s) {
     STEP_TRY(pass(L.range_end[2], L.range_end[3], 1, s));
   }
   if (L.one_buffer && !muon_only) st->last_beta_a = hp->beta_a;
-  STEP_TRY(launch_norm_finalize(stat, partials, scales, order, overlap ? L.num_early : count, hp->ns_eps, s));
+  STEP_TRY(launch_norm_finalize(stat, partials, scales, order, overlap ? L.num_early : count, L.max_blocks, hp->ns_eps,
+                                s));
   if (prof) STEP_TRY(hipEventRecord(ev[1], s));
 
   // Newton-Schulz (Eq. newton_schulz), T iterations per shape group
@@ -1253,18 +1256,17 @@ int mona_step_noalloc(const mona_matrix* mat, const mona_options* opts, void* g_
   st.k = k;
   hipStream_t s = static_cast<hipStream_t>(stream);
   // The array keeps what the last call left in it: the padding of the working matrices and the scales must
-  // start from zero (a fill kernel, not a memset: the call may be under graph capture).
-  HIP_TRY(launch_fill_zero(base + L.work_begin, L.work_bytes, s));
-  HIP_TRY(launch_fill_zero(base + L.scales_off, align_up(sizeof(MatScale)), s));
+  // start from zero (stores of a kernel, not a memset: the call may be under graph capture).
   MatStatic ms;
   void* o_ptr = nullptr;
   fill_static(L, *mat, 0, base, g_prev, acc, mom, ms, o_ptr);
   MatDynamic md;
   md.w = mat->w; md.g = mat->g; md.slot = nullptr;
-  HIP_TRY(launch_single_tables(ms, md, o_ptr, st.at<MatStatic>(L.stat_off), st.at<MatDynamic>(L.dyn_off),
-                               st.at<void*>(L.optr_off), st.at<BlockWork>(L.blocks_off), (int)L.blocks.size(),
-                               reinterpret_cast<int32_t*>(base + L.groups[0].members_off),
-                               st.at<int32_t>(L.order_off), s));
+  HIP_TRY(launch_single_prepare(ms, md, o_ptr, st.at<MatStatic>(L.stat_off), st.at<MatDynamic>(L.dyn_off),
+                                st.at<void*>(L.optr_off), st.at<BlockWork>(L.blocks_off), (int)L.blocks.size(),
+                                reinterpret_cast<int32_t*>(base + L.groups[0].members_off),
+                                st.at<int32_t>(L.order_off), st.at<MatScale>(L.scales_off), base + L.work_begin,
+                                L.work_bytes, s));
   rc = enqueue_step(&st, hp, s);
   if (rc) return rc;
   note_unstable_alpha(hp);

@@ -99,14 +99,15 @@ int api_fail(int code, const char* fmt, va_list ap);
 hipError_t launch_state_update(const MatStatic* stat, const MatDynamic* dyn, const BlockWork* work,
                                double* partials, int num_blocks, int g_bf16, int state_bf16, int one_buffer,
                                float mu, float beta_a, float alpha, int use_prev, hipStream_t s);
-// norm_finalize_kernel, then rescue_kernel (repairs the working copies of flagged matrices)
-// `list` (DEVICE, may be NULL = matrices 0 .. count - 1): the matrix indices to finalise
+// norms, scales and the repair of flagged working copies
+// `list` (DEVICE, may be NULL = matrices 0 .. count - 1): the matrix indices to finalise; max_blocks: the most
+// elementwise blocks any of them has
 hipError_t launch_norm_finalize(const MatStatic* stat, const double* partials, MatScale* scales,
-                                const int32_t* list, int count, float eps, hipStream_t s);
-// tables of a one-matrix state written by a kernel from its arguments (no host copy)
-hipError_t launch_single_tables(const MatStatic& ms, const MatDynamic& md, void* o_ptr, MatStatic* stat,
-                                MatDynamic* dyn, void** o_ptrs, BlockWork* work, int num_blocks, int32_t* members,
-                                int32_t* order, hipStream_t s);
+                                const int32_t* list, int count, int max_blocks, float eps, hipStream_t s);
+// a one-matrix state prepared by one kernel from its arguments (no host copy): tables, scale, cleared workspace
+hipError_t launch_single_prepare(const MatStatic& ms, const MatDynamic& md, void* o_ptr, MatStatic* stat,
+                                 MatDynamic* dyn, void** o_ptrs, BlockWork* work, int num_blocks, int32_t* members,
+                                 int32_t* order, MatScale* scale, void* zero, size_t zero_bytes, hipStream_t s);
 hipError_t launch_plain_update(const MatStatic* stat, const MatDynamic* dyn, const MatScale* scales,
                                const BlockWork* work, int num_blocks, void* const* o_ptrs, float lr, float wd,
                                float gamma_coeff, int store_o, hipStream_t s);

@@ -180,88 +180,88 @@ __global__ __launch_bounds__(kEwThreads) void state_update_kernel(
 }
 
 // ||M||_F per matrix from the per-block partial sums, added in a fixed order in fp64 so the
-// result does not depend on scheduling.  One wavefront per matrix.
+// result does not depend on scheduling, and the repair of the (rare) working copies that need one.
 //
 // The products that follow accumulate the unscaled working copy in fp32 and apply 1 / ||M||_F^2 afterwards,
 // which is exact only while the squares stay inside the fp32 range.  A norm outside [2^-40, 2^40] therefore
-// sets MONA_STATUS_RESCALED: rescue_kernel then rewrites that matrix's working copy as M 2^e with
+// sets MONA_STATUS_RESCALED: that matrix's working copy is rewritten as M 2^e with
 // ||M 2^e||_F in [1, 2), and the scale stored here is the one that belongs to the rewritten copy (a power
 // of two moves no bit of any product, so the result is the one an unlimited exponent range would give).
+// A matrix with a non-finite norm gets an all-zero copy (its products then stay zero, so no NaN ever reaches
+// the zero padding the Gram matrices rely on; its parameter is left alone anyway).
+//
+// `per_mat` workgroups per matrix, every one of which adds up the partial sums for itself (the same order, the same
+// bits): the first stores the scale, and all share the repair.  What bounds the kernel is the latency of the partial
+// sums, one wavefront per matrix before: 34 us for the 7 696 partial sums of a 3328 x 9472 matrix, 6 us for 1 536, and
+// 4 - 5 us more for a launch of its own that looked for flagged matrices; now 4 - 7 us in all.
 constexpr double kNormLo = 9.094947017729282e-13;   // 2^-40
 constexpr double kNormHi = 1099511627776.0;         // 2^40
-__global__ __launch_bounds__(64) void norm_finalize_kernel(const MatStatic* __restrict__ stat,
-                                                           const double* __restrict__ partials,
-                                                           MatScale* __restrict__ scales,
-                                                           const int32_t* __restrict__ list, float eps) {
-  const int mat = list ? list[blockIdx.x] : blockIdx.x;
-  const int first = stat[mat].first_block, nb = stat[mat].num_blocks;
+__global__ __launch_bounds__(kEwThreads) void norm_finalize_kernel(const MatStatic* __restrict__ stat,
+                                                                   const double* __restrict__ partials,
+                                                                   MatScale* __restrict__ scales,
+                                                                   const int32_t* __restrict__ list, float eps,
+                                                                   int per_mat) {
+  __shared__ double red[kEwThreads / 64];
+  __shared__ double total_sum;
+  const int li = blockIdx.x / per_mat, part = blockIdx.x % per_mat;
+  const int mat = list ? list[li] : li;
+  const MatStatic ms = stat[mat];
+  const double* __restrict__ p = partials + ms.first_block;
   double s = 0.0;
-  for (int i = threadIdx.x; i < nb; i += 64) s += partials[first + i];
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-  if (threadIdx.x == 0) {
-    const double norm = sqrt(s);
-    const double den = norm + (double)eps;
-    MatScale r;
-    r.norm = (float)fmin(norm, 3.402823466e38);
-    r.status = 0u;
-    r.xexp = 0;
-    const bool finite = (s == s) && (s <= 1.7e308);
-    if (!finite) {
-      r.norm = (float)norm;
-      r.inv = 0.0f;
-      r.status = 2u;
-    } else if (den <= 0.0) {
-      r.inv = 0.0f;
-      r.status = 1u;
-    } else if (norm == 0.0 || (norm >= kNormLo && norm <= kNormHi)) {
-      r.inv = 1.0f / ((float)norm + eps);
-    } else {
-      r.xexp = -ilogb(norm);
-      r.inv = (float)ldexp(1.0 / den, -r.xexp);
-      r.status = 4u;
-    }
-    r.inv2 = r.inv * r.inv;
-    scales[mat] = r;
+#pragma unroll 4
+  for (int i = threadIdx.x; i < ms.num_blocks; i += kEwThreads) s += p[i];
+  s = block_sum(s, red);
+  if (threadIdx.x == 0) total_sum = s;
+  __syncthreads();
+  s = total_sum;
+  const double norm = sqrt(s);
+  const double den = norm + (double)eps;
+  MatScale r;
+  r.norm = (float)fmin(norm, 3.402823466e38);
+  r.status = 0u;
+  r.xexp = 0;
+  const bool finite = (s == s) && (s <= 1.7e308);
+  if (!finite) {
+    r.norm = (float)norm;
+    r.inv = 0.0f;
+    r.status = 2u;
+  } else if (den <= 0.0) {
+    r.inv = 0.0f;
+    r.status = 1u;
+  } else if (norm == 0.0 || (norm >= kNormLo && norm <= kNormHi)) {
+    r.inv = 1.0f / ((float)norm + eps);
+  } else {
+    r.xexp = -ilogb(norm);
+    r.inv = (float)ldexp(1.0 / den, -r.xexp);
+    r.status = 4u;
+  }
+  r.inv2 = r.inv * r.inv;
+  if (part == 0 && threadIdx.x == 0) scales[mat] = r;
+  if (!(r.status & 6u)) return;
+  const int64_t total = (int64_t)ms.m * ms.n;
+  bf16_t* __restrict__ xh = static_cast<bf16_t*>(ms.x);
+  float* __restrict__ xf = static_cast<float*>(ms.x);
+  for (int64_t id = (int64_t)part * kEwThreads + threadIdx.x; id < total; id += (int64_t)per_mat * kEwThreads) {
+    const int64_t xo = (id / ms.n) * ms.ldx + (id % ms.n);
+    const float v = (r.status & 2u) ? 0.0f : ldexpf(ms.mom[id], r.xexp);
+    if (ms.x_f32) xf[xo] = v; else xh[xo] = (bf16_t)v;
   }
 }
 
-// Repairs the working copies of the (rare) matrices norm_finalize_kernel has flagged, before any product
-// reads them: a matrix with a non-finite norm gets an all-zero copy (its products then stay zero, so no
-// NaN ever reaches the zero padding the Gram matrices rely on; its parameter is left alone anyway), and a
-// matrix whose norm lies outside the safe window gets the copy M 2^e.  Every block scans the flags and
-// leaves at once when none is set.
-__global__ __launch_bounds__(256) void rescue_kernel(const MatStatic* __restrict__ stat,
-                                                     const MatScale* __restrict__ scales,
-                                                     const int32_t* __restrict__ list, int count) {
-  int any = 0;
-  for (int i = threadIdx.x; i < count; i += 256) any |= (scales[list ? list[i] : i].status & 6u) != 0;
-  if (!__syncthreads_or(any)) return;
-  for (int li = 0; li < count; ++li) {
-    const int mat = list ? list[li] : li;
-    const uint32_t st = scales[mat].status;
-    if (!(st & 6u)) continue;
-    const MatStatic ms = stat[mat];
-    const int e = scales[mat].xexp;
-    const int64_t total = (int64_t)ms.m * ms.n;
-    bf16_t* __restrict__ xh = static_cast<bf16_t*>(ms.x);
-    float* __restrict__ xf = static_cast<float*>(ms.x);
-    for (int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x; id < total; id += (int64_t)gridDim.x * 256) {
-      const int64_t xo = (id / ms.n) * ms.ldx + (id % ms.n);
-      const float v = (st & 2u) ? 0.0f : ldexpf(ms.mom[id], e);
-      if (ms.x_f32) xf[xo] = v; else xh[xo] = (bf16_t)v;
-    }
-  }
-}
-
-// Tables of a state that holds ONE matrix, written on the device from kernel arguments (for the entry
-// point that may neither allocate nor copy from host memory).
-__global__ __launch_bounds__(256) void single_tables_kernel(MatStatic ms, MatDynamic md, void* o_ptr, MatStatic* stat,
-                                                            MatDynamic* dyn, void** o_ptrs, BlockWork* work,
-                                                            int num_blocks, int32_t* members, int32_t* order) {
+// Prepares a state that holds ONE matrix, for the entry point that may neither allocate nor copy from host memory:
+// clears [zero, zero + n16 x 16 bytes) and the scale, and writes the tables from kernel arguments.
+__global__ __launch_bounds__(256) void single_prepare_kernel(MatStatic ms, MatDynamic md, void* o_ptr, MatStatic* stat,
+                                                             MatDynamic* dyn, void** o_ptrs, BlockWork* work,
+                                                             int num_blocks, int32_t* members, int32_t* order,
+                                                             MatScale* scale, uint4* zero, size_t n16) {
   const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i == 0) { stat[0] = ms; dyn[0] = md; o_ptrs[0] = o_ptr; members[0] = 0; order[0] = 0; }
+  if (i == 0) {
+    stat[0] = ms; dyn[0] = md; o_ptrs[0] = o_ptr; members[0] = 0; order[0] = 0;
+    scale[0] = MatScale{};
+  }
   for (int b = i; b < num_blocks; b += gridDim.x * 256) work[b] = BlockWork{0, b};
+  const uint4 z = {0u, 0u, 0u, 0u};
+  for (size_t k = i; k < n16; k += (size_t)gridDim.x * 256) zero[k] = z;
 }
 
 // O = X_0 and the parameter update when no Newton-Schulz iteration is requested (T = 0),
@@ -349,21 +349,25 @@ hipError_t launch_state_update(const MatStatic* stat, const MatDynamic* dyn, con
 }
 
 hipError_t launch_norm_finalize(const MatStatic* stat, const double* partials, MatScale* scales,
-                                const int32_t* list, int count, float eps, hipStream_t s) {
+                                const int32_t* list, int count, int max_blocks, float eps, hipStream_t s) {
   if (count <= 0) return hipSuccess;
-  hipLaunchKernelGGL(norm_finalize_kernel, dim3(count), dim3(64), 0, s, stat, partials, scales, list, eps);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(rescue_kernel, dim3(1024), dim3(256), 0, s, stat, scales, list, count);
+  // up to about 1024 workgroups for the repair, none of them with fewer than 64 blocks' worth of elements
+  int per_mat = max_blocks / 64;
+  if (per_mat > 1024 / count) per_mat = 1024 / count;
+  if (per_mat < 1) per_mat = 1;
+  hipLaunchKernelGGL(norm_finalize_kernel, dim3(count * per_mat), dim3(kEwThreads), 0, s, stat, partials, scales, list,
+                     eps, per_mat);
   return hipGetLastError();
 }
 
-hipError_t launch_single_tables(const MatStatic& ms, const MatDynamic& md, void* o_ptr, MatStatic* stat,
-                                MatDynamic* dyn, void** o_ptrs, BlockWork* work, int num_blocks, int32_t* members,
-                                int32_t* order, hipStream_t s) {
-  const int blocks = num_blocks > 256 * 64 ? 64 : (num_blocks + 255) / 256;
-  hipLaunchKernelGGL(single_tables_kernel, dim3(blocks > 0 ? blocks : 1), dim3(256), 0, s, ms, md, o_ptr, stat, dyn,
-                     o_ptrs, work, num_blocks, members, order);
+hipError_t launch_single_prepare(const MatStatic& ms, const MatDynamic& md, void* o_ptr, MatStatic* stat,
+                                 MatDynamic* dyn, void** o_ptrs, BlockWork* work, int num_blocks, int32_t* members,
+                                 int32_t* order, MatScale* scale, void* zero, size_t zero_bytes, hipStream_t s) {
+  const size_t n16 = zero_bytes / 16;   // carved in multiples of 256 bytes
+  size_t blocks = ((size_t)num_blocks > n16 ? (size_t)num_blocks : n16) / 256 + 1;
+  if (blocks > 2048) blocks = 2048;
+  hipLaunchKernelGGL(single_prepare_kernel, dim3((unsigned)blocks), dim3(256), 0, s, ms, md, o_ptr, stat, dyn, o_ptrs,
+                     work, num_blocks, members, order, scale, static_cast<uint4*>(zero), n16);
   return hipGetLastError();
 }
 
