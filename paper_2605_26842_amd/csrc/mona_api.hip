@@ -604,8 +604,10 @@ void OpBuilder::push(GemmArgs& a, int kind, int iter, bool tp, bool tq, bool lar
 // The p x p matrices are symmetric bit for bit outside their diagonal tiles (mirrored tiles are copies), and
 // inside a diagonal tile either triangle is the product to rounding, so as operands they may be read K-major
 // as well as row-major.  The large-tile kernel fetches a K-major operand as 32 contiguous 512-byte rows
-// instead of 64-byte pieces of 256 rows and runs 7-13 % faster per K step on it (measured), so it reads them
-// that way; the small-tile kernels gain nothing from it.
+// instead of 64-byte pieces of 256 rows and runs 7-13 % faster per K step on it (measured).  The small-tile kernel
+// gains the same way in bf16 (128- or 256-byte rows; us per step, row-major -> K-major: 1 x 2048 x 8192 716 -> 683,
+// 3328 x 3328 1079 -> 1018, 3072 x 12288 1926 -> 1781, 512 x 256 unchanged) and nothing in fp32, where a product is
+// bound by its multiplications (a block of hidden size 1024: 2353 row-major, 2373 K-major).
 
 void OpBuilder::gram(int src, void* S, bool first, int iter) {
   GemmArgs a = base();
@@ -621,7 +623,7 @@ void OpBuilder::gram(int src, void* S, bool first, int iter) {
 }
 
 void OpBuilder::poly(void* S, void* dst, float diag, int iter) {
-  const bool symk = large_tiles(g, OP_POLY, cnt);
+  const bool large = large_tiles(g, OP_POLY, cnt), symk = !g.f32;
   GemmArgs a = base();
   a.P = S; a.Q = S; a.E = S; a.C = dst;
   a.strideP = a.strideQ = a.strideE = a.strideC = g.s_stride;
@@ -630,11 +632,11 @@ void OpBuilder::poly(void* S, void* dst, float diag, int iter) {
   a.symmetric = 1;
   a.alpha = hp.ns_c; a.beta = hp.ns_b;
   a.diag = diag;
-  push(a, OP_POLY, iter, symk, symk, symk);
+  push(a, OP_POLY, iter, symk, symk, large);
 }
 
 void OpBuilder::symprod(void* P, void* Q, void* dst, int iter) {
-  const bool symk = large_tiles(g, OP_SYMPROD, cnt);
+  const bool large = large_tiles(g, OP_SYMPROD, cnt), symk = !g.f32;
   GemmArgs a = base();
   a.P = P; a.Q = Q; a.E = nullptr; a.C = dst;
   a.strideP = a.strideQ = a.strideC = g.s_stride;
@@ -642,11 +644,11 @@ void OpBuilder::symprod(void* P, void* Q, void* dst, int iter) {
   a.M = a.N = a.K = g.p_pad;
   a.symmetric = 1;
   a.alpha = 1.0f; a.beta = 0.0f;
-  push(a, OP_SYMPROD, iter, symk, symk, symk);
+  push(a, OP_SYMPROD, iter, symk, symk, large);
 }
 
 void OpBuilder::apply(int src, void* Bm, bool with_e, float beta, bool first, bool last, int iter) {
-  const bool symk = large_tiles(g, OP_APPLY, cnt);
+  const bool large = large_tiles(g, OP_APPLY, cnt), symk = !g.f32;
   GemmArgs a = base();
   a.E = with_e ? X[src] : nullptr; a.C = X[src ^ 1];
   a.strideE = a.strideC = g.x_stride;
@@ -661,7 +663,7 @@ void OpBuilder::apply(int src, void* Bm, bool with_e, float beta, bool first, bo
   } else {               // X' = beta X + B X
     a.P = Bm; a.strideP = g.s_stride; a.ldp = g.p_pad;
     a.Q = X[src]; a.strideQ = g.x_stride; a.ldq = g.cols_pad;
-    tp = symk && !last;   // the launch that carries the update has no register to spare for a K-major P
+    tp = symk && !(large && last);   // the large-tile launch with the update has no register for a K-major P
     tq = true;
   }
   a.symmetric = 0;
@@ -673,7 +675,7 @@ void OpBuilder::apply(int src, void* Bm, bool with_e, float beta, bool first, bo
     a.w_keep = 1.0f - hp.lr * hp.weight_decay;
     a.o_scale = hp.lr * hp.gamma_coeff * sqrtf((float)std::max(g.m, g.n));
   }
-  push(a, OP_APPLY, iter, tp, tq, symk);
+  push(a, OP_APPLY, iter, tp, tq, large);
 }
 
 int OpBuilder::build() {
