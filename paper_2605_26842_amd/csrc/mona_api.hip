@@ -161,6 +161,12 @@ constexpr int kDefaultLanes = 4;   // streams the shape groups of one step are s
 // 3072 the two expert groups of a 128-expert layer run side by side and lose 5 % to each other's L2 traffic.
 constexpr long long kBigLaunchTiles = 1536;
 constexpr long long kChipTiles = 256;      // one tile per CU
+// 128 x 128 tiles up to which small groups share their launches.  Measured, us per step, all merged -> the groups with
+// more tiles apart: a block of hidden size 1000 (144 tiles, 72, 36) 510 -> 487, one of 1024 (144, 36, 36) 536 -> 490,
+// 16 x 512 x 768 both ways (160, 160) 429 -> 386; the other way round, a block of hidden size 512 (40, 20, 10) 180
+// merged and 213 or 270 apart.
+constexpr long long kMergedTiles = 128;
+constexpr long long kMinTiles256 = 112;    // large tiles from which a product uses them
 // CUs the late group's elementwise pass keeps to itself (a quarter of the chip): the HBM-bound pass still
 // moves 2.8 TB/s there, and the power-limited products lose 13 % on the other three quarters (measured).
 constexpr int kOverlapCuShare = 4;
@@ -177,8 +183,11 @@ bool large_tiles(const Group& g, int kind, int count) {
     const long long t = g.p_pad / 256;
     tiles = t * (t + 1) / 2 * count;
   }
-  // too few large tiles to fill 256 CUs, unless groups running beside this one make up for it
-  return tiles >= 192;
+  // Too few large tiles to fill 256 CUs, unless groups running beside this one make up for it.  Measured, us per step
+  // with the line at 192 / 128 / 96 tiles: 4 x 2048 x 2048 (144 tiles a p x p product) 1039 / 872 / 869, 4096 x 4096
+  // (136) 1817 / 1470 / 1460, 10 x 1024 x 1024 (100) 525 / 473 / 488, 12 x 1024 x 2048 (120) 781 / 760 / 779,
+  // 20 x 768 x 768 (120) 490 / 451 / 448; at 64 one 2048 x 2048 goes from 398 to 490.
+  return tiles >= kMinTiles256;
 }
 bool small_tiles_only(const Group& g) {
   const int count = (int)g.members.size();
@@ -199,7 +208,9 @@ long long launch_tiles(const Group& g, int kind, int tile, int count) {
 // stay in a row on the caller's stream; the others, sorted by work, each go to the least loaded lane, except that
 // the groups that run small tiles only are merged first: their products are bound by the latency of a launch, and a
 // launch takes as long for eight groups as for one (measured on nine ragged matrices: 982 us a step with a chain of
-// launches for each group on four lanes).
+// launches for each group on four lanes).  They are merged only until their launches put a tile on half of the CUs:
+// from there on a merged launch lasts longer with every group, and chains on lanes of their own fill each other's
+// gaps (kMergedTiles has the figures).
 //
 // Late group (on request: mona_options.overlap).  The elementwise pass is bound by HBM and leaves the matrix
 // units idle; the products are bound by the matrix units (and by power) and leave HBM half idle.  When the
@@ -272,13 +283,20 @@ void plan_lanes(Layout& L, const mona_options& opt) {
   };
   for (int gi : row) add_unit(false).groups.push_back(gi);
   const size_t first_beside = L.units.size();
-  int open[2] = {-1, -1};    // unit that still takes groups, by precision
+  std::vector<long long> tiles_in(L.groups.size() + 1, 0);   // 128 x 128 tiles of each unit's smallest launches
   for (int gi : beside) {
     const Group& g = L.groups[gi];
     if (!small_tiles_only(g)) { add_unit(false).groups.push_back(gi); continue; }
-    int& u = open[g.f32 ? 1 : 0];
-    if (u < 0 || (int)L.units[u].groups.size() == kMaxMerged) { add_unit(true); u = (int)L.units.size() - 1; }
+    size_t u = first_beside;
+    for (; u < L.units.size(); ++u) {
+      const Unit& q = L.units[u];
+      if (q.merged && L.groups[q.groups[0]].f32 == g.f32 && (int)q.groups.size() < kMaxMerged &&
+          (want == 1 || tiles_in[u] + fewest_of[gi] <= kMergedTiles))
+        break;
+    }
+    if (u == L.units.size()) add_unit(true);
     L.units[u].groups.push_back(gi);
+    tiles_in[u] += fewest_of[gi];
   }
   const int parallel = (int)(L.units.size() - first_beside) + (row.empty() ? 0 : 1);
   L.lanes = std::max(1, std::min(want, parallel));

@@ -17,6 +17,12 @@ CASES = {
     "eleven groups": ([(70 + 13 * i, 90 + 40 * ((7 * i) % 11)) for i in range(11)], 0, range(11)),
     # enough 128 x 128 tiles, at most one a CU (13 x 10) and more (13 x 20), last tile partly padding
     "tiles of 128": ([(500, 610)] * 13 + [(610, 500)] * 2, 0, (0, 12, 13, 14)),
+    # the most products of one tile each that stay on small tiles, and one more: 256 x 256 tiles
+    "111 large tiles": ([(256, 512)] * 111, 0, (0, 110)),
+    "112 large tiles": ([(256, 512)] * 112, 0, (0, 111)),
+    # groups that fill half the chip run apart, the smaller ones share their launches, in either precision
+    "apart and merged": ([(520, 640)] * 9 + [(640, 700)] * 3 + [(300, 260)] * 4 + [(70, 5)], 0, (0, 9, 12, 16)),
+    "apart and merged, fp32": ([(520, 640)] * 9 + [(640, 700)] * 3 + [(300, 260)] * 4 + [(70, 5)], 1, (0, 9, 12, 16)),
     # fp32 products: 64 x 64 tiles with and without company on the CU, 128 x 128 tiles for the last product
     "fp32 edges": ([(3, 5), (64, 64), (65, 200), (200, 65), (130, 1030)], 1, range(5)),
     "fp32 tiles of 128": ([(700, 1100)] * 10 + [(1100, 700)], 1, (0, 9, 10)),
