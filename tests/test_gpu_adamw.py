@@ -149,3 +149,11 @@ def test_adamw_mixed_dtypes_in_one_list_and_checkpoint():
     assert lib.mona_adamw_state_import(h_b, blob.data_ptr(), n.value - 256, 2, 0) == B.MONA_ESHAPE
     for h in (h_full, h_a, h_b):
         assert lib.mona_adamw_free_state(h) == B.MONA_OK
+
+
+@pytest.mark.parametrize("count", [127, 128, 129, 300])
+def test_adamw_pointer_table_in_the_arguments_and_in_the_arena(count):
+    # 128 tensors are the most whose pointers travel with the launch; every step brings new gradient buffers
+    say("[case] adamw tensors", count)
+    shapes = [(1 + 37 * (i % 5),) for i in range(count - 1)] + [(4097,)]
+    run_case(shapes, torch.float32, torch.float32, B.mona_adamw_hparams(1e-2, 0.9, 0.95, 1e-8, 0.1), steps=2, seed=5)
