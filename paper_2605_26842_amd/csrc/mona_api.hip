@@ -1185,20 +1185,27 @@ int step_impl(mona_state* st, const mona_matrix* mats, void* const* slots, int32
       if (st->last_dyn[i].w != mats[i].w || st->last_dyn[i].g != mats[i].g ||
           st->last_dyn[i].slot != (slots ? slots[i] : nullptr)) { changed = true; break; }
   if (changed) {
-    const int slot = st->ring_next;
-    if (st->ring_used[slot]) HIP_TRY(hipEventSynchronize(st->ring_ev[slot]));
     st->last_dyn.resize(count);
     for (int i = 0; i < count; ++i) {
       st->last_dyn[i].w = mats[i].w;
       st->last_dyn[i].g = mats[i].g;
       st->last_dyn[i].slot = slots ? slots[i] : nullptr;
-      st->ring[slot][i] = st->last_dyn[i];
     }
-    HIP_TRY(hipMemcpyAsync(st->arena + L.dyn_off, st->ring[slot], sizeof(MatDynamic) * count, hipMemcpyHostToDevice,
-                           s));
-    HIP_TRY(hipEventRecord(st->ring_ev[slot], s));
-    st->ring_used[slot] = true;
-    st->ring_next = (slot + 1) % kRing;
+    if (count <= kInlineMats) {
+      DynTable t;
+      memset(&t, 0, sizeof t);
+      std::copy(st->last_dyn.begin(), st->last_dyn.end(), t.v);
+      HIP_TRY(launch_write_dyn(t, count, st->at<MatDynamic>(L.dyn_off), s));
+    } else {
+      const int slot = st->ring_next;
+      if (st->ring_used[slot]) HIP_TRY(hipEventSynchronize(st->ring_ev[slot]));
+      std::copy(st->last_dyn.begin(), st->last_dyn.end(), st->ring[slot]);
+      HIP_TRY(hipMemcpyAsync(st->arena + L.dyn_off, st->ring[slot], sizeof(MatDynamic) * count, hipMemcpyHostToDevice,
+                             s));
+      HIP_TRY(hipEventRecord(st->ring_ev[slot], s));
+      st->ring_used[slot] = true;
+      st->ring_next = (slot + 1) % kRing;
+    }
     st->dyn_valid = true;
   }
   rc = enqueue_step(st, hp, s);

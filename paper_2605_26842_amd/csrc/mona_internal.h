@@ -95,7 +95,15 @@ struct GemmBatch {
 // records the text mona_last_error() returns (thread-local) and hands `code` back
 int api_fail(int code, const char* fmt, va_list ap);
 
+// The pointers of a short list, passed by value: 96 entries are 2.3 KB of the 4 KB an argument block may hold.
+constexpr int kInlineMats = 96;
+struct DynTable {
+  MatDynamic v[kInlineMats];
+};
+
 // kernels (defined in the .hip files)
+// dyn[0 .. n) = t.v[0 .. n), n <= kInlineMats
+hipError_t launch_write_dyn(const DynTable& t, int n, MatDynamic* dyn, hipStream_t s);
 hipError_t launch_state_update(const MatStatic* stat, const MatDynamic* dyn, const BlockWork* work,
                                double* partials, int num_blocks, int g_bf16, int state_bf16, int one_buffer,
                                float mu, float beta_a, float alpha, int use_prev, hipStream_t s);

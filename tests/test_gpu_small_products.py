@@ -23,6 +23,9 @@ CASES = {
     # groups that fill half the chip run apart, the smaller ones share their launches, in either precision
     "apart and merged": ([(520, 640)] * 9 + [(640, 700)] * 3 + [(300, 260)] * 4 + [(70, 5)], 0, (0, 9, 12, 16)),
     "apart and merged, fp32": ([(520, 640)] * 9 + [(640, 700)] * 3 + [(300, 260)] * 4 + [(70, 5)], 1, (0, 9, 12, 16)),
+    # the most matrices whose pointers travel with a launch, and one more
+    "96 matrices": ([(40, 72)] * 96, 0, (0, 95)),
+    "97 matrices": ([(40, 72)] * 97, 0, (0, 96)),
     # fp32 products: 64 x 64 tiles with and without company on the CU, 128 x 128 tiles for the last product
     "fp32 edges": ([(3, 5), (64, 64), (65, 200), (200, 65), (130, 1030)], 1, range(5)),
     "fp32 tiles of 128": ([(700, 1100)] * 10 + [(1100, 700)], 1, (0, 9, 10)),
