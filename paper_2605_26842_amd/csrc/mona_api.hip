@@ -475,7 +475,7 @@ struct mona_state {
   hipStream_t late_stream = nullptr;
   hipEvent_t late_fork = nullptr, late_done = nullptr;
   int late_cus = 0;                    // CUs that stream may use (0: no such stream)
-  // pinned ring for the per-step pointer table
+  // pinned ring for the per-step pointer table of lists longer than kInlineMats
   MatDynamic* ring[kRing] = {nullptr, nullptr, nullptr, nullptr};
   hipEvent_t ring_ev[kRing];
   bool ring_used[kRing] = {false, false, false, false};
