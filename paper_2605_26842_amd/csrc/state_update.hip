@@ -193,14 +193,63 @@ __global__ __launch_bounds__(kEwThreads) void state_update_kernel(
 // `per_mat` workgroups per matrix, every one of which adds up the partial sums for itself (the same order, the same
 // bits): the first stores the scale, and all share the repair.  What bounds the kernel is the latency of the partial
 // sums, one wavefront per matrix before: 34 us for the 7 696 partial sums of a 3328 x 9472 matrix, 6 us for 1 536, and
-// 4 - 5 us more for a launch of its own that looked for flagged matrices; now 4 - 7 us in all.
+// 4 - 5 us more for a launch of its own that looked for flagged matrices; now 4 - 7 us in all where no matrix is flagged.
+//
+// The repair has to stay wide whatever the length of the list: one expert without gradients in a long list would
+// otherwise hold up every product behind it.  Where the list is too long for one workgroup to every kRepairBlocks
+// blocks' worth of elements of every matrix, repair is 0 here and rescue_kernel does it (4 us of a step of 2 ms and more).
 constexpr double kNormLo = 9.094947017729282e-13;   // 2^-40
 constexpr double kNormHi = 1099511627776.0;         // 2^40
+constexpr int kRepairBlocks = 16, kRepairGroups = 2048;
+
+// The share of workgroup `part` of `parts` in the rewriting of one flagged working copy.  Bound by HBM once wide enough:
+// 16-byte loads of M, four in flight per lane, one 32-bit division for four elements.
+__device__ __forceinline__ void repair_copy(const MatStatic& ms, const MatScale& r, int part, int parts) {
+  const bool clear = (r.status & 2u) != 0;
+  // m * n is below 2^31, and the walk passes its end by at most 4 x 2048 x 256 units: 32 bits hold every index
+  const uint32_t n = (uint32_t)ms.n, total = (uint32_t)ms.m * n;
+  const uint32_t units = (total + 3) / 4, step = (uint32_t)parts * kEwThreads;
+  bf16_t* __restrict__ xh = static_cast<bf16_t*>(ms.x);
+  float* __restrict__ xf = static_cast<float*>(ms.x);
+  const float* __restrict__ mom = ms.mom;
+  for (uint32_t u0 = (uint32_t)part * kEwThreads + threadIdx.x; u0 < units; u0 += 4 * step) {
+    f32x4 v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t id = 4 * (u0 + j * step);
+      v[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      if (clear || id >= total) continue;
+      if (total - id >= 4) v[j] = *reinterpret_cast<const f32x4*>(mom + id);
+      else
+        for (uint32_t e = 0; e < total - id; ++e) v[j][e] = mom[id + e];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t id = 4 * (u0 + j * step);
+      if (id >= total) continue;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[j][e] = ldexpf(v[j][e], r.xexp);
+      uint32_t row = id / n, col = id - row * n;
+      if (n % 4 == 0) {                              // the four elements are in one row, 16-byte aligned there
+        const int64_t xo = (int64_t)row * ms.ldx + col;
+        if (ms.x_f32) *reinterpret_cast<f32x4*>(xf + xo) = v[j];
+        else *reinterpret_cast<bf16x4*>(xh + xo) = bf16x4{(bf16_t)v[j].x, (bf16_t)v[j].y, (bf16_t)v[j].z, (bf16_t)v[j].w};
+        continue;
+      }
+      for (uint32_t e = 0; e < 4 && e < total - id; ++e) {
+        const int64_t xo = (int64_t)row * ms.ldx + col;
+        if (ms.x_f32) xf[xo] = v[j][e]; else xh[xo] = (bf16_t)v[j][e];
+        if (++col == n) { col = 0; ++row; }
+      }
+    }
+  }
+}
+
 __global__ __launch_bounds__(kEwThreads) void norm_finalize_kernel(const MatStatic* __restrict__ stat,
                                                                    const double* __restrict__ partials,
                                                                    MatScale* __restrict__ scales,
                                                                    const int32_t* __restrict__ list, float eps,
-                                                                   int per_mat) {
+                                                                   int per_mat, int repair) {
   __shared__ double red[kEwThreads / 64];
   __shared__ double total_sum;
   const int li = blockIdx.x / per_mat, part = blockIdx.x % per_mat;
@@ -237,14 +286,21 @@ __global__ __launch_bounds__(kEwThreads) void norm_finalize_kernel(const MatStat
   }
   r.inv2 = r.inv * r.inv;
   if (part == 0 && threadIdx.x == 0) scales[mat] = r;
-  if (!(r.status & 6u)) return;
-  const int64_t total = (int64_t)ms.m * ms.n;
-  bf16_t* __restrict__ xh = static_cast<bf16_t*>(ms.x);
-  float* __restrict__ xf = static_cast<float*>(ms.x);
-  for (int64_t id = (int64_t)part * kEwThreads + threadIdx.x; id < total; id += (int64_t)per_mat * kEwThreads) {
-    const int64_t xo = (id / ms.n) * ms.ldx + (id % ms.n);
-    const float v = (r.status & 2u) ? 0.0f : ldexpf(ms.mom[id], r.xexp);
-    if (ms.x_f32) xf[xo] = v; else xh[xo] = (bf16_t)v;
+  if (repair && (r.status & 6u)) repair_copy(ms, r, part, per_mat);
+}
+
+// The repair of a long list: every workgroup scans the flags, leaves at once when none is set, and takes its share of
+// every flagged matrix.  Bound by the scan (4 us for 388 matrices) or, where it repairs, by HBM.
+__global__ __launch_bounds__(kEwThreads) void rescue_kernel(const MatStatic* __restrict__ stat,
+                                                            const MatScale* __restrict__ scales,
+                                                            const int32_t* __restrict__ list, int count) {
+  int any = 0;
+  for (int i = threadIdx.x; i < count; i += kEwThreads) any |= (scales[list ? list[i] : i].status & 6u) != 0;
+  if (!__syncthreads_or(any)) return;
+  for (int li = 0; li < count; ++li) {
+    const int mat = list ? list[li] : li;
+    const MatScale r = scales[mat];
+    if (r.status & 6u) repair_copy(stat[mat], r, blockIdx.x, gridDim.x);
   }
 }
 
@@ -365,12 +421,21 @@ hipError_t launch_write_dyn(const DynTable& t, int n, MatDynamic* dyn, hipStream
 hipError_t launch_norm_finalize(const MatStatic* stat, const double* partials, MatScale* scales,
                                 const int32_t* list, int count, int max_blocks, float eps, hipStream_t s) {
   if (count <= 0) return hipSuccess;
-  // up to about 1024 workgroups for the repair, none of them with fewer than 64 blocks' worth of elements
-  int per_mat = max_blocks / 64;
-  if (per_mat > 1024 / count) per_mat = 1024 / count;
-  if (per_mat < 1) per_mat = 1;
+  // Workgroups of kRepairBlocks blocks' worth of elements each, as long as all of them are resident at once (eight to a
+  // CU); otherwise one a matrix, and the repair in a launch of its own.  Measured, us per step without and with one
+  // matrix out of range: 256 x 512 alone 102, 127 (one workgroup for 64 blocks: 349); 768 x 256 among 256 979, 995 (1349);
+  // 2048 x 4096 behind 600 of 16 x 24 745, 835 (one workgroup a matrix and no launch of its own: 17409);
+  // 4096 x 1536 among 388 13.78 ms, 13.80 (two workgroups: 21.36).
+  int per_mat = (max_blocks + kRepairBlocks - 1) / kRepairBlocks;
+  const bool apart = per_mat > 1 && (long long)count * per_mat > kRepairGroups;
+  if (apart) per_mat = 1;
   hipLaunchKernelGGL(norm_finalize_kernel, dim3(count * per_mat), dim3(kEwThreads), 0, s, stat, partials, scales, list,
-                     eps, per_mat);
+                     eps, per_mat, apart ? 0 : 1);
+  if (apart) {
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(rescue_kernel, dim3(1024), dim3(kEwThreads), 0, s, stat, scales, list, count);
+  }
   return hipGetLastError();
 }
 

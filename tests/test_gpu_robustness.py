@@ -169,3 +169,77 @@ def test_alpha_outside_the_theorems_range_is_noted_not_refused():
     opt.step(g, wl.HParams(beta_a=0.9, alpha=-10.0, flags=B.MONA_FLAG_MUON_ONLY))   # alpha is ignored there
     assert lib.mona_last_error() == b""
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("rest, shape", [(0, (257, 1001)), (600, (257, 1001)), (600, (1024, 700)), (64, (300, 1000)),
+                                         (2100, (130, 70))])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_repair_of_one_flagged_matrix_in_a_list(rest, shape, precision):
+    """The working copy of a matrix whose norm is out of range is rewritten in the launch that forms the norms, or in a
+    launch of its own where the list is too long for that: either way O is the oracle's, a non-finite matrix
+    leaves everything else alone, and the zero padding survives."""
+    say(f"[case] {rest} small matrices and one {shape}, precision {precision}")
+    dev = "cuda:0"
+    shapes = [(12 + i % 5, 20 + i % 7) for i in range(rest)] + [shape]
+    weights = [wl.draw_weight(s, 5600 + i, torch.float32) for i, s in enumerate(shapes)]
+    grads = [wl.GradientStream(s, 5700 + i).next() for i, s in enumerate(shapes)]
+    watch = [len(shapes) - 1] + ([0] if rest else [])
+    tol = H.TOL_NS_F32 if precision else H.TOL_NS_BF16
+    hp = dataclasses.replace(wl.HParams(), flags=B.MONA_FLAG_KEEP_O)
+    dev_w = [w.to(dev) for w in weights]
+    opt = B.MonaOptimizer(dev_w, ns_precision=precision)
+    start = opt.export_state().clone()
+
+    def step(last):
+        gs = grads[:-1] + [last]
+        opt.step([g.to(dev) for g in gs], hp)
+        torch.cuda.synchronize()
+        return gs
+
+    for scale in (1e-25, 1e18):
+        gs = step(grads[-1] * scale)
+        assert opt.status() == [0] * rest + [B.MONA_STATUS_RESCALED]
+        ref = H.run_oracle_for(weights, [gs], hp, watch)
+        for i in watch:
+            assert H.rel_fro(H.f64(opt.last_o(i)), ref[i][0]["O"]) <= tol, (scale, i)
+        opt.import_state(start, 0)
+    before = dev_w[-1].clone()
+    bad = grads[-1].clone()
+    bad[-1, -1] = float("nan")
+    step(bad)
+    assert opt.status() == [0] * rest + [B.MONA_STATUS_NONFINITE]
+    assert torch.equal(before, dev_w[-1]) and not H.f64(opt.last_o(len(shapes) - 1)).any()
+    # (no import here: it would clear the padding, which the repair must have left zero by itself)
+    for view in (opt.g_prev, opt.accel, opt.momentum):
+        view(len(shapes) - 1).zero_()
+    step(grads[-1])
+    ref = H.run_oracle_for(weights, [grads], hp, watch[:1])
+    assert H.rel_fro(H.f64(opt.last_o(watch[0])), ref[watch[0]][0]["O"]) <= tol
+
+
+@pytest.mark.parametrize("rest, shape", [(0, (4096, 1536)), (64, (4096, 1536)), (600, (4096, 1536))])
+def test_repair_does_not_hold_up_the_step(rest, shape):
+    """A flagged matrix costs one more pass over it, by the whole chip, whatever the length of the list: 25 MB read and
+    13 written, 10 us at 4 TB/s.  Half a millisecond leaves room for one launch and for a quiet chip; a repair
+    whose width shrinks with the list took 12 ms."""
+    say(f"[case] repair time, {rest} small matrices and one {shape}")
+    dev = "cuda:0"
+    shapes = [(16, 24)] * rest + [shape]
+    weights = [torch.zeros(s, device=dev) for s in shapes]
+    best = []
+    for scale in (1.0, 1e-20):
+        grads = [wl.GradientStream(s, 5800 + i, dev).next() for i, s in enumerate(shapes)]
+        grads[-1].mul_(scale)
+        opt = B.MonaOptimizer(weights)
+        times = []
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            opt.step(grads, wl.HParams())
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        assert opt.status() == [0] * rest + [0 if scale == 1.0 else B.MONA_STATUS_RESCALED]
+        best.append(min(times[1:]))
+    say(f"[repair] step {best[0]:.3f} ms, with one flagged matrix {best[1]:.3f} ms")
+    assert best[1] - best[0] < 0.5
