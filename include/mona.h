@@ -174,10 +174,11 @@ int mona_init_state(const mona_matrix* mats, int32_t count, const mona_options* 
  * order, as at init (else MONA_ESHAPE); w and g pointers may differ from step to step.
  * Successive steps on one state must be issued on the same stream or be ordered by the
  * caller.
- * Graph capture: with profiling off and the same w / g pointers as in the previous call
- * (so that no pointer table is uploaded) the call enqueues only kernel launches and the
- * event record / wait pairs that fork and join its side streams -- no memset, no copy --
- * and may be recorded into a HIP graph on a capturing stream.
+ * Graph capture: with profiling off the call enqueues only kernel launches and the event record / wait
+ * pairs that fork and join its side streams -- no memset, no copy -- and may be recorded into a HIP graph
+ * on a capturing stream.  The recorded step holds this call's w / g (and slot) pointers: a replay uses them
+ * whatever eager steps, with whatever pointers, came before it.  A state that has been captured once writes its
+ * pointers in front of every later step as well (one small launch for every 96 matrices).
  * The hyper-parameters are baked into the recorded launches, and the host-side step
  * counter counts calls, not replays (it only matters for MONA_FLAG_FIRST_DIFF_ZERO at
  * the first step).

@@ -34,10 +34,14 @@ int fail(int code, const char* fmt, ...) {
   va_end(ap);
   return rc;
 }
-#define HIP_TRY(expr)                                                                       \
-  do {                                                                                      \
-    hipError_t e__ = (expr);                                                                \
-    if (e__ != hipSuccess) return fail(MONA_EHIP, "%s: %s", #expr, hipGetErrorString(e__)); \
+// (the error is taken off the runtime's record, where the check behind the next call's first launch would find it again)
+#define HIP_TRY(expr)                                                     \
+  do {                                                                    \
+    hipError_t e__ = (expr);                                              \
+    if (e__ != hipSuccess) {                                              \
+      (void)hipGetLastError();                                            \
+      return fail(MONA_EHIP, "%s: %s", #expr, hipGetErrorString(e__));    \
+    }                                                                     \
   } while (0)
 
 struct VecStatic {
@@ -260,6 +264,7 @@ int mona_adamw_init_state(const mona_vector* vecs, int32_t count, void* arena, s
     hipError_t e__ = (expr);                                                            \
     if (e__ != hipSuccess) {                                                            \
       destroy(st);                                                                      \
+      (void)hipGetLastError();                                                          \
       return fail(MONA_EHIP, "%s: %s", #expr, hipGetErrorString(e__));                  \
     }                                                                                   \
   } while (0)
@@ -323,6 +328,7 @@ int mona_adamw_step(mona_adamw_state* st, const mona_vector* vecs, int32_t count
     for (int i = 0; i < count; ++i)
       if (st->last_dyn[i].w != vecs[i].w || st->last_dyn[i].g != vecs[i].g) { changed = true; break; }
   if (changed) {
+    st->dyn_valid = false;           // until the new table is on its way: a failure below must not leave a stale match
     const int slot = st->ring_next;
     if (st->ring_used[slot]) HIP_TRY(hipEventSynchronize(st->ring_ev[slot]));
     st->last_dyn.resize(count);

@@ -41,10 +41,14 @@ int fail(int code, const char* fmt, ...) {
   return rc;
 }
 
-#define HIP_TRY(expr)                                                                       \
-  do {                                                                                      \
-    hipError_t e__ = (expr);                                                                \
-    if (e__ != hipSuccess) return fail(MONA_EHIP, "%s: %s", #expr, hipGetErrorString(e__)); \
+// (the error is taken off the runtime's record, where the check behind the next call's first launch would find it again)
+#define HIP_TRY(expr)                                                     \
+  do {                                                                    \
+    hipError_t e__ = (expr);                                              \
+    if (e__ != hipSuccess) {                                              \
+      (void)hipGetLastError();                                            \
+      return fail(MONA_EHIP, "%s: %s", #expr, hipGetErrorString(e__));    \
+    }                                                                     \
   } while (0)
 
 constexpr size_t kAlign = 256;
@@ -480,8 +484,9 @@ struct mona_state {
   hipEvent_t ring_ev[kRing];
   bool ring_used[kRing] = {false, false, false, false};
   int ring_next = 0;
-  std::vector<MatDynamic> last_dyn;
-  bool dyn_valid = false;
+  std::vector<MatDynamic> last_dyn;  // the pointer table enqueued last
+  bool dyn_valid = false;            // last_dyn is what the device's table holds at this point of the stream
+  bool captured = false;             // a step of this state was recorded into a graph (see step_impl)
   int device = 0;
   // profiling
   int profiling = 0;
@@ -850,6 +855,7 @@ int mona_init_state(const mona_matrix* mats, int32_t count, const mona_options* 
     if (st->late_fork) (void)hipEventDestroy(st->late_fork);
     if (st->late_done) (void)hipEventDestroy(st->late_done);
     delete st;
+    (void)hipGetLastError();
     return code;
   };
 #define INIT_TRY(expr)                                                                                   \
@@ -985,6 +991,7 @@ int enqueue_step(mona_state* st, const mona_hparams* hp, hipStream_t s) {
         (void)hipStreamWaitEvent(s, st->side_done[i], 0);
       }
     st->failed = true;
+    (void)hipGetLastError();
     return fail(MONA_EHIP, "%s: %s (the step was abandoned half way: the state arrays are unusable until a checkpoint "
                 "is imported with mona_state_import)", what, hipGetErrorString(e));
   };
@@ -1178,24 +1185,36 @@ int step_impl(mona_state* st, const mona_matrix* mats, void* const* slots, int32
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
 
-  // per-step pointer table
-  bool changed = !st->dyn_valid;
+  // Per-step pointer table.  It is written again only when a pointer has changed since the last table that was enqueued;
+  // from the first capture on it is written by every step, captured or not: a recorded write takes effect when the graph
+  // is replayed, which this side does not see.  A recorded table travels in kernel arguments, whatever its length, because
+  // a copy node would read the pinned ring at the time of the replay.
+  if (s != nullptr) {                // (the null stream cannot be captured)
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(s, &cap));
+    if (cap != hipStreamCaptureStatusNone) st->captured = true;
+  }
+  bool changed = !st->dyn_valid || st->captured;
   if (!changed)
     for (int i = 0; i < count; ++i)
       if (st->last_dyn[i].w != mats[i].w || st->last_dyn[i].g != mats[i].g ||
           st->last_dyn[i].slot != (slots ? slots[i] : nullptr)) { changed = true; break; }
   if (changed) {
+    st->dyn_valid = false;           // until the new table is on its way: a failure below must not leave a stale match
     st->last_dyn.resize(count);
     for (int i = 0; i < count; ++i) {
       st->last_dyn[i].w = mats[i].w;
       st->last_dyn[i].g = mats[i].g;
       st->last_dyn[i].slot = slots ? slots[i] : nullptr;
     }
-    if (count <= kInlineMats) {
-      DynTable t;
-      memset(&t, 0, sizeof t);
-      std::copy(st->last_dyn.begin(), st->last_dyn.end(), t.v);
-      HIP_TRY(launch_write_dyn(t, count, st->at<MatDynamic>(L.dyn_off), s));
+    if (count <= kInlineMats || st->captured) {
+      for (int first = 0; first < count; first += kInlineMats) {
+        const int n = std::min(kInlineMats, count - first);
+        DynTable t;
+        memset(&t, 0, sizeof t);
+        std::copy_n(st->last_dyn.begin() + first, n, t.v);
+        HIP_TRY(launch_write_dyn(t, n, st->at<MatDynamic>(L.dyn_off) + first, s));
+      }
     } else {
       const int slot = st->ring_next;
       if (st->ring_used[slot]) HIP_TRY(hipEventSynchronize(st->ring_ev[slot]));

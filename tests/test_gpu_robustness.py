@@ -243,3 +243,37 @@ def test_repair_does_not_hold_up_the_step(rest, shape):
         best.append(min(times[1:]))
     say(f"[repair] step {best[0]:.3f} ms, with one flagged matrix {best[1]:.3f} ms")
     assert best[1] - best[0] < 0.5
+
+
+@pytest.mark.parametrize("shapes", [[(256, 512), (100, 300)], [(40, 72)] * 97])
+def test_eager_steps_with_other_buffers_between_graph_replays(shapes):
+    """A graph holds the pointers of the step that was recorded, and eager steps before, between and after its replays
+    their own, with a table of at most and of more than 96 matrices."""
+    say(f"[case] {len(shapes)} matrices, replays and eager steps with other buffers in turn")
+    dev = "cuda:0"
+    hp = wl.HParams()
+    ends = []
+    for use_graph in (False, True):
+        weights = [wl.draw_weight(s, 5900 + i, torch.float32, dev) for i, s in enumerate(shapes)]
+        buffers = [[wl.GradientStream(s, 6000 + 100 * k + i, dev).next() for i, s in enumerate(shapes)] for k in range(2)]
+        opt = B.MonaOptimizer(weights)
+        graph = None
+        opt.step(buffers[0], hp)
+        torch.cuda.synchronize()
+        if use_graph:
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph):
+                opt.step(buffers[0], hp)
+            torch.cuda.synchronize()
+        for k in range(3):
+            opt.step(buffers[1], hp)
+            opt.step(buffers[1], hp)
+            if use_graph:
+                graph.replay()
+            else:
+                opt.step(buffers[0], hp)
+        opt.step(buffers[1], hp)
+        torch.cuda.synchronize()
+        ends.append(weights + [opt.momentum(i).clone() for i in range(len(shapes))])
+    for i, (x, y) in enumerate(zip(*ends)):
+        assert torch.equal(x, y), i
