@@ -280,13 +280,16 @@ int mona_last_step_times(mona_state* st, float* ms_out);
  * last 32 of them if there were more); *steps_out says over how many.  Waits for those steps. */
 int mona_mean_step_times(mona_state* st, float* ms_out, int32_t* steps_out);
 
-/* With mona_set_profiling(st, 2) every Newton-Schulz product launch of a step is bracketed
- * by its own pair of events.  mona_last_step_launches waits for the step and fills up to
- * max_records entries (out may be NULL to query the count).
+/* With mona_set_profiling(st, 2) every Newton-Schulz product of a step is launched by itself, in a row on
+ * the caller's stream, and bracketed by its own pair of events.  Products of several small shape groups that
+ * an ordinary step puts into one launch keep the tiles and the split of K they have there, so the results are
+ * those of an ordinary step bit for bit; their times add up to more than the common launch takes.
+ * mona_last_step_launches waits for the step and fills up to max_records entries, one per product (out may
+ * be NULL to query the count).
  *   kind: 0 = Gram (X X^T), 1 = poly (b S + c S S [+ a I]), 2 = apply (a X + B X, or R X),
  *         3 = product of two commuting symmetric p x p matrices (fused schedule)
  *   tile:  block tile of the kernel, rows * 1000 + columns (e.g. 256128)
- *   flops: MFMA flop the launch issues (tiles x 2 x rows x columns x K), padding included */
+ *   flops: MFMA flop the product issues (tiles x 2 x rows x columns x K), padding included */
 typedef struct mona_launch_time {
   int32_t kind, group, iter, tile;
   int32_t m, n, count;   /* shape of the group's matrices and how many there are */
@@ -296,8 +299,9 @@ typedef struct mona_launch_time {
 int mona_last_step_launches(mona_state* st, mona_launch_time* out, int32_t max_records,
                             int32_t* n_out);
 
-/* Number of kernel launches and executed MFMA flop of the Newton-Schulz part of one
- * step under the current plan (host-only bookkeeping, for roofline reporting). */
+/* Number of kernel launches and executed MFMA flop of the Newton-Schulz part of one ordinary
+ * step (products of several small shape groups that share a launch count as one launch; host-only
+ * bookkeeping, for roofline reporting). */
 int mona_plan_info(mona_state* st, int32_t ns_steps, int64_t* launches_out,
                    double* ns_flops_executed_out, double* elementwise_bytes_out);
 

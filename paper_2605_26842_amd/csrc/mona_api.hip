@@ -513,6 +513,7 @@ double gemm_flops(const GemmArgs& a) {
 struct Op {
   GemmArgs a;
   int kind = 0;       // OpKind
+  int group = 0;
   int iter = 0;       // Newton-Schulz iteration it belongs to
   bool large = false; // 256 x 256 kernel; otherwise the tile is chosen when the launch is put together
   int m = 0, n = 0;   // rows and columns of the result without padding
@@ -734,6 +735,62 @@ int OpBuilder::build() {
     iter += n;
   }
   return T == 0 ? 1 : src;
+}
+
+// One launch of the step: a product of one group, or the products of a merged unit at one position of their chains.
+struct Launch {
+  int n = 0;
+  Op* op[kMaxMerged];
+  bool wide = false;   // small tiles: eight wavefronts a tile (see launch_ns_small)
+};
+
+// The products of one step as they are launched, lane by lane: what enqueue_step issues and mona_plan_info counts.
+struct Plan {
+  std::vector<std::vector<Op>> ops;         // by group
+  std::vector<int> o_buf;                   // by group: the ping-pong buffer that holds O_k afterwards
+  std::vector<std::vector<Launch>> lanes;
+};
+
+void build_plan(const mona_state* st, const mona_hparams& hp, Plan& plan) {
+  const Layout& L = st->L;
+  const size_t ngroups = L.groups.size();
+  plan.ops.resize(ngroups);
+  plan.lanes.resize(L.lanes);
+  for (size_t gi = 0; gi < ngroups; ++gi) {
+    plan.o_buf.push_back(OpBuilder(st, L.groups[gi], hp, plan.ops[gi]).build());
+    for (Op& op : plan.ops[gi]) op.group = (int)gi;
+  }
+  auto add = [&](std::vector<Launch>& lane, Launch l) {
+    if (!l.op[0]->large) {
+      choose_small_tile(l.op, l.n, L.groups[l.op[0]->group].f32);
+      // the longest chains of K first: their tiles are the last to finish
+      std::stable_sort(l.op, l.op + l.n, [](const Op* x, const Op* y) { return x->a.K > y->a.K; });
+      long long slots = 0;
+      for (int i = 0; i < l.n; ++i) slots += slots_per_die(l.op[i]->a);
+      // at most one workgroup per CU: eight wavefronts each, two per SIMD, so that one multiplies while the other reads
+      l.wide = slots * kXcds <= device_cu_count();
+    }
+    lane.push_back(l);
+  };
+  for (const Unit& u : L.units) {
+    std::vector<Launch>& lane = plan.lanes[u.lane];
+    if (u.merged) {
+      for (size_t pos = 0;; ++pos) {
+        Launch l;
+        for (int gi : u.groups)
+          if (pos < plan.ops[gi].size()) l.op[l.n++] = &plan.ops[gi][pos];
+        if (l.n == 0) break;
+        add(lane, l);
+      }
+    } else {
+      for (int gi : u.groups)
+        for (Op& op : plan.ops[gi]) {
+          Launch l;
+          l.n = 1; l.op[0] = &op;
+          add(lane, l);
+        }
+    }
+  }
 }
 
 // Static description of matrix i: where its state arrays and its working copy live.
@@ -1001,6 +1058,10 @@ int enqueue_step(mona_state* st, const mona_hparams* hp, hipStream_t s) {
     if (e__ != hipSuccess) return bail(e__, #expr);      \
   } while (0)
 
+  Plan plan;
+  build_plan(st, *hp, plan);
+  for (size_t gi = 0; gi < L.groups.size(); ++gi) L.groups[gi].o_buf = plan.o_buf[gi];
+
   const bool prof = st->profiling > 0;
   hipEvent_t* const ev = st->ev[st->prof_steps % kProfSets];
   st->times_ready = false;
@@ -1061,73 +1122,49 @@ int enqueue_step(mona_state* st, const mona_hparams* hp, hipStream_t s) {
     for (hipStream_t q : st->side) STEP_TRY(hipStreamWaitEvent(q, st->fork_ev, 0));
   }
   const bool each = st->profiling > 1;
-  const int ngroups = (int)L.groups.size();
-  std::vector<std::vector<Op>> ops(ngroups);
-  for (int gi = 0; gi < ngroups; ++gi) L.groups[gi].o_buf = OpBuilder(st, L.groups[gi], *hp, ops[gi]).build();
-  // one launch: a product of one group, or the products of a merged unit at one position of their chains
-  struct Launch {
-    int n = 0;
-    int group[kMaxMerged];
-    Op* op[kMaxMerged];
+  // one product, or several as one launch
+  auto launch = [&](Op* const* op, int n, bool wide, int cu_cap, hipStream_t q) {
+    if (op[0]->large) return launch_ns_gemm(op[0]->a, cu_cap, q);
+    GemmBatch batch;
+    batch.n = n;
+    for (int i = 0; i < n; ++i) batch.a[i] = op[i]->a;
+    return launch_ns_small(batch, L.groups[op[0]->group].f32, wide, q);
   };
-  std::vector<std::vector<Launch>> queue(L.lanes);
-  for (const Unit& u : L.units) {
-    auto& q = queue[fork ? u.lane : 0];
-    if (u.merged && !each) {
-      for (size_t pos = 0;; ++pos) {
-        Launch l;
-        for (int gi : u.groups)
-          if (pos < ops[gi].size()) { l.group[l.n] = gi; l.op[l.n++] = &ops[gi][pos]; }
-        if (l.n == 0) break;
-        q.push_back(l);
-      }
-    } else {
-      for (int gi : u.groups)
-        for (Op& op : ops[gi]) {
-          Launch l;
-          l.n = 1; l.group[0] = gi; l.op[0] = &op;
-          q.push_back(l);
-        }
+  if (!fork)                     // one lane after the other on the caller's stream
+    for (int lane = 1; lane < L.lanes; ++lane) {
+      plan.lanes[0].insert(plan.lanes[0].end(), plan.lanes[lane].begin(), plan.lanes[lane].end());
+      plan.lanes[lane].clear();
     }
-  }
   // the lanes are fed in turn, so that no lane waits for the host to have enqueued all of another
   std::vector<size_t> at(L.lanes, 0);
   for (bool more = true; more;) {
     more = false;
     for (int lane = 0; lane < L.lanes; ++lane) {
-      if (at[lane] == queue[lane].size()) continue;
+      const std::vector<Launch>& queue = plan.lanes[lane];
+      if (at[lane] == queue.size()) continue;
       more = true;
-      Launch& l = queue[lane][at[lane]++];
-      const int gi = l.group[0];
-      const bool f32 = L.groups[gi].f32;
+      const Launch& l = queue[at[lane]++];
       hipStream_t gs = lane == 0 ? s : st->side[lane - 1];
       int cu_cap = 0;
-      if (overlap && gi == L.late_group) {
+      if (overlap && l.op[0]->group == L.late_group) {
         if (late_forked) STEP_TRY(hipStreamWaitEvent(s, st->late_done, 0));
         late_forked = false;
       } else if (overlap) {
         cu_cap = device_cu_count() - st->late_cus;
       }
-      LaunchRecord rec;
-      if (each) {
+      if (!each) {
+        STEP_TRY(launch(l.op, l.n, l.wide, cu_cap, gs));
+        continue;
+      }
+      // each product timed by itself, on the tiles and with the split of K that it has in the common launch
+      for (int i = 0; i < l.n; ++i) {
+        const Op& op = *l.op[i];
+        LaunchRecord rec;
         if (!get_event_pair(st, &rec.e0, &rec.e1)) return bail(hipErrorOutOfMemory, "hipEventCreate");
         STEP_TRY(hipEventRecord(rec.e0, gs));
-      }
-      if (l.op[0]->large) {
-        STEP_TRY(launch_ns_gemm(l.op[0]->a, cu_cap, gs));
-      } else {
-        choose_small_tile(l.op, l.n, f32);
-        // the longest chains of K first: their tiles are the last to finish
-        std::stable_sort(l.op, l.op + l.n, [](const Op* x, const Op* y) { return x->a.K > y->a.K; });
-        GemmBatch batch;
-        batch.n = l.n;
-        for (int i = 0; i < l.n; ++i) batch.a[i] = l.op[i]->a;
-        STEP_TRY(launch_ns_small(batch, f32, gs));
-      }
-      if (each) {
-        const Op& op = *l.op[0];
+        STEP_TRY(launch(l.op + i, 1, l.wide, cu_cap, gs));
         STEP_TRY(hipEventRecord(rec.e1, gs));
-        rec.kind = op.kind; rec.group = gi; rec.iter = op.iter; rec.tile = op.a.tile_m * 1000 + op.a.tile_n;
+        rec.kind = op.kind; rec.group = op.group; rec.iter = op.iter; rec.tile = op.a.tile_m * 1000 + op.a.tile_n;
         rec.flops = gemm_flops(op.a);
         st->records.push_back(rec);
       }
@@ -1494,19 +1531,13 @@ int mona_plan_info(mona_state* st, int32_t ns_steps, int64_t* launches_out, doub
   mona_hparams hp;
   memset(&hp, 0, sizeof hp);
   hp.ns_steps = ns_steps;
+  Plan plan;
+  build_plan(st, hp, plan);
   double flops = 0.0;
   int64_t launches = 0;
-  std::vector<Op> ops;
-  for (const Group& g : L.groups) {
-    ops.clear();
-    OpBuilder(st, g, hp, ops).build();
-    for (Op& op : ops) {
-      Op* one = &op;
-      if (!op.large) choose_small_tile(&one, 1, g.f32);
-      flops += gemm_flops(op.a);
-    }
-    launches += (int64_t)ops.size();
-  }
+  for (const auto& lane : plan.lanes) launches += (int64_t)lane.size();
+  for (const auto& ops : plan.ops)
+    for (const Op& op : ops) flops += gemm_flops(op.a);
   double bytes = 0.0;
   for (int i = 0; i < L.count; ++i) {
     const double ne = (double)st->mats[i].m * st->mats[i].n;

@@ -92,6 +92,10 @@ struct GemmBatch {
   GemmArgs a[kMaxMerged];
 };
 
+constexpr int kXcds = 8;   // MI355X: 8 accelerator dies, workgroups are dealt to them round-robin
+// workgroups per die of a launch of small tiles
+inline long long slots_per_die(const GemmArgs& a) { return ((long long)a.tiles_per_mat * a.count + kXcds - 1) / kXcds; }
+
 // records the text mona_last_error() returns (thread-local) and hands `code` back
 int api_fail(int code, const char* fmt, va_list ap);
 
@@ -121,7 +125,8 @@ hipError_t launch_plain_update(const MatStatic* stat, const MatDynamic* dyn, con
                                float gamma_coeff, int store_o, hipStream_t s);
 // cu_cap > 0: the persistent large-tile kernel uses at most that many CUs (the rest are busy elsewhere)
 hipError_t launch_ns_gemm(const GemmArgs& a, int cu_cap, hipStream_t s);   // 256 x 256 tiles, bf16
-hipError_t launch_ns_small(GemmBatch& b, bool f32, hipStream_t s);         // 64 x 64 or 128 x 128 tiles
+// 64 x 64 or 128 x 128 tiles; wide: eight wavefronts a tile and one workgroup per CU instead of four and two
+hipError_t launch_ns_small(GemmBatch& b, bool f32, bool wide, hipStream_t s);
 int device_cu_count();
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 

@@ -494,20 +494,18 @@ __global__ __launch_bounds__(WIDE ? 512 : 256) void ns_small_kernel(const GemmBa
 
 }  // namespace
 
-hipError_t launch_ns_small(GemmBatch& b, bool f32, hipStream_t s) {
+hipError_t launch_ns_small(GemmBatch& b, bool f32, bool wide, hipStream_t s) {
   if (b.n < 1 || b.n > kMaxMerged) return hipErrorInvalidValue;
   long long slots = 0;
   for (int g = 0; g < b.n; ++g) {
     const GemmArgs& a = b.a[g];
     if ((a.tile_m != 64 && a.tile_m != 128) || a.tile_n != a.tile_m || (a.trans_p && !a.trans_q)) return hipErrorInvalidValue;
-    slots += ((long long)a.tiles_per_mat * a.count + kXcds - 1) / kXcds;
+    slots += slots_per_die(a);
     if (slots * kXcds > 0x7fffff00LL) return hipErrorInvalidValue;
     b.slot_end[g] = (int32_t)slots;
   }
   const dim3 grid((unsigned)(slots * kXcds));
   if (grid.x == 0) return hipSuccess;
-  // At most one workgroup per CU: eight wavefronts each, two per SIMD, so that one multiplies while the other reads.
-  const bool wide = (long long)grid.x <= device_cu_count();
   if (f32 && wide) hipLaunchKernelGGL((ns_small_kernel<float, true>), grid, dim3(512), 0, s, b);
   else if (f32) hipLaunchKernelGGL((ns_small_kernel<float, false>), grid, dim3(256), 0, s, b);
   else if (wide) hipLaunchKernelGGL((ns_small_kernel<bf16_t, true>), grid, dim3(512), 0, s, b);

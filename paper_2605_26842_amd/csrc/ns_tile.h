@@ -14,8 +14,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kXcds = 8;   // MI355X: 8 accelerator dies, workgroups are dealt to them round-robin
-
 // compile-time loop: f(integral_constant<int, 0>), ..., f(integral_constant<int, N - 1>)
 template <int I> struct IC { static constexpr int value = I; constexpr operator int() const { return I; } };
 template <int N, int I = 0, typename F>

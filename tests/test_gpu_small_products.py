@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+from paper_2605_26842_amd import binding as B
 from paper_2605_26842_amd import workloads as wl
 from tests import gpu_harness as H
 
@@ -56,3 +57,21 @@ def test_small_products_against_the_oracle(name, param):
         want = H.expected_update(s.W_before, s.O, hp, False)
         terms = np.abs(s.W_before) + np.abs(want - s.W_before)
         assert (np.abs(s.W - want) <= np.abs(want) * 2.0 ** -8 + terms * 2.0 ** -22).all(), (name, i)
+
+
+@pytest.mark.parametrize("name", ["edges of 64", "apart and merged", "apart and merged, fp32"])
+def test_launches_timed_one_by_one_give_the_same_bits(name):
+    shapes, precision, _ = CASES[name]
+    shapes = shapes + [(500, 610), (640, 500), (512, 700)]
+    print(f"[case] {name}", flush=True)
+    ends = []
+    for level in (0, 2):
+        weights = [wl.draw_weight(s, 300 + i, torch.float32, "cuda:0") for i, s in enumerate(shapes)]
+        opt = B.MonaOptimizer(weights, ns_precision=precision)
+        opt.set_profiling(level)
+        for k in range(2):
+            opt.step([wl.GradientStream(s, 400 + 50 * k + i, "cuda:0").next() for i, s in enumerate(shapes)], wl.HParams())
+        torch.cuda.synchronize()
+        ends.append(weights)
+    for i, (x, y) in enumerate(zip(*ends)):
+        assert torch.equal(x, y), (name, i)
