@@ -1,6 +1,6 @@
 // Host side of libmona: argument checking, arena layout, shape grouping and the launch plan
-// of one MONA step (Alg. 1).  All arithmetic happens in the kernels of state_update.hip and
-// ns_gemm.hip; this file only decides what is launched on which buffers.
+// of one MONA step (Alg. 1).  All arithmetic happens in the kernels of state_update.hip,
+// ns_gemm.hip and ns_small.hip; this file only decides what is launched on which buffers.
 #include "../../include/mona.h"
 #include "mona_internal.h"
 
@@ -638,7 +638,6 @@ void OpBuilder::gram(int src, void* S, bool first, int iter) {
   a.P = X[src]; a.Q = X[src]; a.E = nullptr; a.C = S;
   a.strideP = a.strideQ = g.x_stride; a.strideC = g.s_stride;
   a.ldp = a.ldq = g.cols_pad; a.ldc = g.p_pad;
-  a.M = a.N = g.p_pad;
   a.K = g.tall ? g.rows_pad : g.cols_pad;
   a.symmetric = 1;
   a.alpha = 1.0f; a.beta = 0.0f;
@@ -652,7 +651,7 @@ void OpBuilder::poly(void* S, void* dst, float diag, int iter) {
   a.P = S; a.Q = S; a.E = S; a.C = dst;
   a.strideP = a.strideQ = a.strideE = a.strideC = g.s_stride;
   a.ldp = a.ldq = a.lde = a.ldc = g.p_pad;
-  a.M = a.N = a.K = g.p_pad;
+  a.K = g.p_pad;
   a.symmetric = 1;
   a.alpha = hp.ns_c; a.beta = hp.ns_b;
   a.diag = diag;
@@ -665,7 +664,7 @@ void OpBuilder::symprod(void* P, void* Q, void* dst, int iter) {
   a.P = P; a.Q = Q; a.E = nullptr; a.C = dst;
   a.strideP = a.strideQ = a.strideC = g.s_stride;
   a.ldp = a.ldq = a.ldc = g.p_pad;
-  a.M = a.N = a.K = g.p_pad;
+  a.K = g.p_pad;
   a.symmetric = 1;
   a.alpha = 1.0f; a.beta = 0.0f;
   push(a, OP_SYMPROD, iter, symk, symk, large);
@@ -678,7 +677,6 @@ void OpBuilder::apply(int src, void* Bm, bool with_e, float beta, bool first, bo
   a.strideE = a.strideC = g.x_stride;
   a.lde = a.ldc = g.cols_pad;
   a.K = g.p_pad;
-  a.M = g.rows_pad; a.N = g.cols_pad;
   bool tp, tq;
   if (g.tall) {          // X' = beta X + X B
     a.P = X[src]; a.strideP = g.x_stride; a.ldp = g.cols_pad;
@@ -922,7 +920,7 @@ int mona_init_state(const mona_matrix* mats, int32_t count, const mona_options* 
   } while (0)
 
   INIT_TRY(hipGetDevice(&st->device));
-  for (int i = 0; i < kRing; ++i) {
+  for (int i = 0; i < kRing && count > kInlineMats; ++i) {   // shorter lists need no staging
     void* p = nullptr;
     INIT_TRY(hipHostMalloc(&p, sizeof(MatDynamic) * (size_t)count, hipHostMallocDefault));
     st->ring[i] = static_cast<MatDynamic*>(p);

@@ -63,10 +63,10 @@ struct GemmArgs {
   const void* P; const void* Q; const void* E; void* C;
   int64_t strideP, strideQ, strideE, strideC;  // elements between consecutive matrices of the group
   int32_t ldp, ldq, lde, ldc;
-  int32_t M, N, K;          // padded problem size, multiples of the tile
+  int32_t K;                // padded, a multiple of 128
   int32_t tile_m, tile_n;   // BM, BN of the kernel that will run
   int32_t trans_p, trans_q; // 1: the operand is stored K-major
-  int32_t tiles_m, tiles_n; // M / BM, N / BN
+  int32_t tiles_m, tiles_n; // tiles that hold rows or columns of the result; tiles of padding alone are left out
   int32_t tiles_per_mat;    // tiles_m * tiles_n, or the triangle count when symmetric
   int32_t count;            // matrices in the group
   int32_t symmetric;        // 1: only tiles with tj >= ti are computed, the result is mirrored
