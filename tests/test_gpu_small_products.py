@@ -1,5 +1,7 @@
 """The small-tile product kernels (64 x 64 and 128 x 128, one launch for several shape groups) at the sizes where they can
 go wrong, against the float64 oracle."""
+import itertools
+
 import numpy as np
 import pytest
 import torch
@@ -24,7 +26,7 @@ CASES = {
     # groups that fill half the chip run apart, the smaller ones share their launches, in either precision
     "apart and merged": ([(520, 640)] * 9 + [(640, 700)] * 3 + [(300, 260)] * 4 + [(70, 5)], 0, (0, 9, 12, 16)),
     "apart and merged, fp32": ([(520, 640)] * 9 + [(640, 700)] * 3 + [(300, 260)] * 4 + [(70, 5)], 1, (0, 9, 12, 16)),
-    # the most matrices whose pointers travel with a launch, and one more
+    # the most matrices whose pointers travel with a launch, and one more: three steps, each with new gradient buffers
     "96 matrices": ([(40, 72)] * 96, 0, (0, 95)),
     "97 matrices": ([(40, 72)] * 97, 0, (0, 96)),
     # fp32 products: 64 x 64 tiles with and without company on the CU, 128 x 128 tiles for the last product
@@ -39,7 +41,8 @@ def test_small_products_against_the_oracle(name, param):
     shapes, precision, watch = CASES[name]
     print(f"[case] {name}", flush=True)
     weights = [wl.draw_weight(s, 300 + i, param) for i, s in enumerate(shapes)]
-    grads = [[wl.GradientStream(s, 400 + i).next() for i, s in enumerate(shapes)]]
+    streams = [wl.GradientStream(s, 400 + i) for i, s in enumerate(shapes)]
+    grads = [[g.next() for g in streams] for _ in range(3 if name.endswith("matrices") else 1)]
     hp = wl.HParams()
     opt, dev_w, hist = H.run_gpu(weights, grads, hp, precision, watch=watch)
     # the suite's bounds: bf16 products round every stored intermediate to 8 bits (measured 1.1e-2 to 1.4e-2 on short
@@ -51,12 +54,12 @@ def test_small_products_against_the_oracle(name, param):
     # bf16 parameters: O against the oracle, and the stored parameter against the update formed from that O in float64:
     # half an ulp for the store, and three fp32 roundings of the terms (which cancel where the result is tiny)
     ref = H.run_oracle_for(weights, grads, hp, watch)
-    for i in watch:
-        s = hist[0][i]
-        assert H.rel_fro(s.O, ref[i][0]["O"]) <= tol, (name, i)
+    for k, i in itertools.product(range(len(grads)), watch):
+        s = hist[k][i]
+        assert H.rel_fro(s.O, ref[i][k]["O"]) <= tol, (name, k, i)
         want = H.expected_update(s.W_before, s.O, hp, False)
         terms = np.abs(s.W_before) + np.abs(want - s.W_before)
-        assert (np.abs(s.W - want) <= np.abs(want) * 2.0 ** -8 + terms * 2.0 ** -22).all(), (name, i)
+        assert (np.abs(s.W - want) <= np.abs(want) * 2.0 ** -8 + terms * 2.0 ** -22).all(), (name, k, i)
 
 
 @pytest.mark.parametrize("name", ["edges of 64", "apart and merged", "apart and merged, fp32"])
