@@ -522,7 +522,8 @@ struct Op {
 void set_tile(Op& op, int tile) {
   GemmArgs& a = op.a;
   a.tile_m = a.tile_n = tile;
-  // tiles that hold nothing but padding are left out where the padding is wider than a tile
+  // tiles that hold nothing but padding are left out where the padding is wider than a tile: all of it is zero, in every
+  // buffer of a group that runs small tiles (the large tiles of a group cover its padding in every product)
   a.tiles_m = (op.m + tile - 1) / tile;
   a.tiles_n = (op.n + tile - 1) / tile;
   a.tiles_per_mat = a.symmetric ? a.tiles_n * (a.tiles_n + 1) / 2 : a.tiles_m * a.tiles_n;
@@ -655,6 +656,7 @@ void OpBuilder::poly(void* S, void* dst, float diag, int iter) {
   a.symmetric = 1;
   a.alpha = hp.ns_c; a.beta = hp.ns_b;
   a.diag = diag;
+  a.diag_n = std::min(g.m, g.n);
   push(a, OP_POLY, iter, symk, symk, large);
 }
 

@@ -72,6 +72,7 @@ struct GemmArgs {
   int32_t symmetric;        // 1: only tiles with tj >= ti are computed, the result is mirrored
   float alpha, beta;
   float diag;               // added to the main diagonal of the result (symmetric products only)
+  int32_t diag_n;           // rows of the result without padding: small tiles add diag to these only
   int32_t post;             // PostScale, indexed through `members`
   int32_t epilogue;         // GemmEpilogue
   int32_t store_out;        // EPI_UPDATE: also store O

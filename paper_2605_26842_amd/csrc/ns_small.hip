@@ -403,7 +403,9 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, c
 #pragma unroll
       for (int e = 0; e < CH; ++e) val[e] = post * (a.alpha * val[e]);
     }
-    if (a.diag != 0.0f) {
+    if (a.diag != 0.0f && grow < a.diag_n) {
+      // not to the padding: that must be zero in every buffer, because a product whose tiles are 64 wide in this step may
+      // leave out padding that a 128-wide tile wrote in another
 #pragma unroll
       for (int e = 0; e < CH; ++e) val[e] += (grow == gcol + e) ? a.diag : 0.0f;
     }

@@ -1,5 +1,6 @@
 """The small-tile product kernels (64 x 64 and 128 x 128, one launch for several shape groups) at the sizes where they can
 go wrong, against the float64 oracle."""
+import dataclasses
 import itertools
 
 import numpy as np
@@ -78,3 +79,31 @@ def test_launches_timed_one_by_one_give_the_same_bits(name):
         ends.append(weights)
     for i, (x, y) in enumerate(zip(*ends)):
         assert torch.equal(x, y), (name, i)
+
+
+def test_padding_stays_zero_when_the_iterations_change_from_step_to_step():
+    """The tile of a product depends on what shares its launch, and that on the number of iterations: 1080 x 6000 (17 tiles of
+    64 a side, or 9 of 128 with 64 columns of padding) has another tile at some positions of a chain of 3, 5 and 9 iterations,
+    so a buffer's padding may be written by one step and read, unwritten, by the next.  Powers of a in it would leave the bf16
+    range within 75 steps and turn the parameter into NaN; O must be that of the same gradients in a fresh state, bit for bit."""
+    print("[case] iterations 9, then 5 and 3 in turn", flush=True)
+    shapes = [(1080, 6000), (1024, 1536), (1000, 1000)]
+    dev = "cuda:0"
+    hp = dataclasses.replace(wl.HParams(), flags=B.MONA_FLAG_KEEP_O)
+    grads = [wl.GradientStream(s, 700 + i, dev).next() for i, s in enumerate(shapes)]
+    weights = [wl.draw_weight(s, 600 + i, torch.float32, dev) for i, s in enumerate(shapes)]
+    opt = B.MonaOptimizer(weights)
+    for k, steps in enumerate([9] + [5, 3] * 40):
+        opt.step(grads, dataclasses.replace(hp, ns_steps=steps))
+        if k % 20 == 0:
+            torch.cuda.synchronize()
+            print(f"[step] {k}", flush=True)
+    saved = opt.export_state()
+    opt.step(grads, hp)
+    got = [opt.last_o(i).clone() for i in range(len(shapes))]
+    fresh = B.MonaOptimizer(weights)
+    fresh.import_state(saved, 1)
+    fresh.step(grads, hp)
+    for i in range(len(shapes)):
+        assert torch.isfinite(weights[i]).all(), i
+        assert torch.equal(got[i], fresh.last_o(i)), i
