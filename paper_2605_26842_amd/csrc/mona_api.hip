@@ -165,12 +165,15 @@ constexpr int kDefaultLanes = 4;   // streams the shape groups of one step are s
 // 3072 the two expert groups of a 128-expert layer run side by side and lose 5 % to each other's L2 traffic.
 constexpr long long kBigLaunchTiles = 1536;
 constexpr long long kChipTiles = 256;      // one tile per CU
-// 128 x 128 tiles up to which small groups share their launches.  Measured, us per step, all merged -> the groups with
-// more tiles apart: a block of hidden size 1000 (144 tiles, 72, 36) 510 -> 487, one of 1024 (144, 36, 36) 536 -> 490,
-// 16 x 512 x 768 both ways (160, 160) 429 -> 386; the other way round, a block of hidden size 512 (40, 20, 10) 180
-// merged and 213 or 270 apart.
+// 128 x 128 tiles up to which small groups share their launches.  Measured, us per step (three runs, within 0.3 %) with the
+// line at 64 / 96 / 128 / 176: hidden size 512 (40, 20, 10 tiles) 187 / 173 / 173 / 173, hidden size 700 (84, 21)
+// 223 / 223 / 232 / 232, 12 x 384 x 1000 and 4 x 500 x 500 (72, 40) 227 / 227 / 221 / 222, 5 x 520 x 640 and 3 x 640 x 520 (75, 45)
+// 190 / 191 / 186 / 186, hidden size 640 (75, 30, 15) 265 / 274 / 268 / 268, hidden size 768 (84, 42, 21) 312 / 312 / 308 / 346,
+// hidden size 1000 (144, 72, 36) 515 / 515 / 476 / 476, 16 x 512 x 768 both ways (160, 160) 365 on every line: 128 is best or within
+// 1 % of it but for one.
 constexpr long long kMergedTiles = 128;
-constexpr long long kMinTiles256 = 112;    // large tiles from which a product uses them
+// large tiles from which a product uses them; matrices from which it does where p is a single tile
+constexpr long long kMinTiles256 = 128, kMinSingles256 = 112;
 // CUs the late group's elementwise pass keeps to itself (a quarter of the chip): the HBM-bound pass still
 // moves 2.8 TB/s there, and the power-limited products lose 13 % on the other three quarters (measured).
 constexpr int kOverlapCuShare = 4;
@@ -188,10 +191,12 @@ bool large_tiles(const Group& g, int kind, int count) {
     tiles = t * (t + 1) / 2 * count;
   }
   // Too few large tiles to fill 256 CUs, unless groups running beside this one make up for it.  Measured, us per step
-  // with the line at 192 / 128 / 96 tiles: 4 x 2048 x 2048 (144 tiles a p x p product) 1039 / 872 / 869, 4096 x 4096
-  // (136) 1817 / 1470 / 1460, 10 x 1024 x 1024 (100) 525 / 473 / 488, 12 x 1024 x 2048 (120) 781 / 760 / 779,
-  // 20 x 768 x 768 (120) 490 / 451 / 448; at 64 one 2048 x 2048 goes from 398 to 490.
-  return tiles >= kMinTiles256;
+  // (three runs, within 0.3 %) with the line at 192 / 128 / 112 tiles: from 128 tiles on large tiles are faster, 4 x 2048 x 2048
+  // (144 tiles a p x p product) 1043 / 847 / 847, 4096 x 4096 (136) 1816 / 1454 / 1452; below, they lose, 12 x 1024 x 2048 (120)
+  // 748 / 748 / 768, 4 x 1792 x 1792 (112) 694 / 694 / 714, 8 x 1280 x 1280 (120) 568 / 568 / 580, 20 x 768 x 768 (120 and 180)
+  // 461 / 431 / 429, except where every symmetric product is a single tile, 115 x 256 x 512 349 / 349 / 325, 120 x 256 x 256
+  // 267 / 267 / 248 (but not where the apply alone has them, 60 x 256 x 500 - / 246 / 265, 8 x 256 x 3840 - / 227 / 236).
+  return tiles >= kMinTiles256 || (g.p_pad == 256 && count >= kMinSingles256);
 }
 bool small_tiles_only(const Group& g) {
   const int count = (int)g.members.size();

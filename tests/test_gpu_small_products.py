@@ -21,9 +21,11 @@ CASES = {
     "eleven groups": ([(70 + 13 * i, 90 + 40 * ((7 * i) % 11)) for i in range(11)], 0, range(11)),
     # enough 128 x 128 tiles, at most one a CU (13 x 10) and more (13 x 20), last tile partly padding
     "tiles of 128": ([(500, 610)] * 13 + [(610, 500)] * 2, 0, (0, 12, 13, 14)),
-    # the most products of one tile each that stay on small tiles, and one more: 256 x 256 tiles
+    # the most products of one tile, and of three, that stay on small tiles, and one matrix more: 256 x 256 tiles
     "111 large tiles": ([(256, 512)] * 111, 0, (0, 110)),
     "112 large tiles": ([(256, 512)] * 112, 0, (0, 111)),
+    "126 large tiles": ([(500, 510)] * 42, 0, (0, 41)),
+    "129 large tiles": ([(500, 510)] * 43, 0, (0, 42)),
     # groups that fill half the chip run apart, the smaller ones share their launches, in either precision
     "apart and merged": ([(520, 640)] * 9 + [(640, 700)] * 3 + [(300, 260)] * 4 + [(70, 5)], 0, (0, 9, 12, 16)),
     "apart and merged, fp32": ([(520, 640)] * 9 + [(640, 700)] * 3 + [(300, 260)] * 4 + [(70, 5)], 1, (0, 9, 12, 16)),
