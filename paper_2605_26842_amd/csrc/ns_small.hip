@@ -10,8 +10,10 @@
 //   * a launch of few tiles uses 64 x 64 tiles whose wavefronts split K between them (each its own slabs of LDS, no
 //     workgroup barrier before the sum), a launch of more tiles 128 x 128 (the host decides, product by product).
 // Measured, us per step, one chain of launches per group on a register-staged 128 x 128 kernel -> here: one 256 x 512
-// matrix 170 -> 106, 512 x 1408 269 -> 142, nine ragged matrices 983 -> 200, a block of hidden size 1000 665 -> 570,
-// one of hidden size 1024 with fp32 products 4590 -> 2376 (70 TFLOP/s; from 512 tiles on 100 - 110 of 154).
+// matrix 170 -> 99, 512 x 1408 269 -> 137, nine ragged matrices 980 -> 180 to 194, a block of hidden size 1000 664 -> 509,
+// one of hidden size 1024 with fp32 products 4583 -> 2283 (73 TFLOP/s; launches that fill the chip many times over 130 of 154).
+// A launch costs 5 us (64 x 64) to 9 - 11 us (128 x 128) beside its K loop, and 1024 of K 4.7 and 9.4 us for a tile on a CU of
+// its own, 8.6 and 19.4 us for two.
 //
 // One workgroup per tile, every wavefront 64 x 64 (2 x 2 blocks of 32 x 32, 64 accumulators); four wavefronts and 64 KB
 // of ring, two workgroups per CU, or (launches of at most one workgroup per CU) eight and 128 KB:
