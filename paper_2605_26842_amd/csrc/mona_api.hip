@@ -58,8 +58,6 @@ constexpr int kPairsMinShortSide = 1024;   // padded short side from which it fu
 size_t align_up(size_t v, size_t a = kAlign) { return (v + a - 1) / a * a; }
 int round_up(int v, int a) { return (v + a - 1) / a * a; }
 
-enum OpKind { OP_GRAM = 0, OP_POLY = 1, OP_APPLY = 2, OP_SYMPROD = 3 };
-
 struct Group {
   int m = 0, n = 0;          // native shape
   bool tall = false;         // m > n: Gram matrix on the column side
@@ -97,7 +95,7 @@ struct Layout {
   std::vector<size_t> gprev_off, acc_off, mom_off;
   size_t state_begin = 0, state_bytes = 0;     // persistent {G_prev, A, M}
   size_t work_begin = 0, work_bytes = 0;       // X, S, B of every group (zeroed once)
-  size_t stat_off = 0, dyn_off = 0, scales_off = 0, partials_off = 0, blocks_off = 0, optr_off = 0;
+  size_t stat_off = 0, dyn_off = 0, scales_off = 0, partials_off = 0, blocks_off = 0, optr_off = 0, chain_off = 0;
   size_t total = 0;
   std::vector<Group> groups;
   std::vector<int> group_of, rank_in_group;
@@ -456,6 +454,9 @@ void build_layout(const mona_matrix* mats, int count, const mona_options& opt, b
   L.partials_off = off; off = align_up(off + sizeof(double) * L.blocks.size());
   L.blocks_off = off;   off = align_up(off + sizeof(BlockWork) * L.blocks.size());
   for (Group& g : L.groups) { g.members_off = off; off = align_up(off + sizeof(int32_t) * g.members.size()); }
+  // (the static workspace has its own place for it, so that the matrices that fit are those they always were)
+  if (external_state) L.chain_off = MONA_NOALLOC_SCRATCH_BYTES;
+  else { L.chain_off = off; off = align_up(off + kChainBytes); }
   L.total = off;
 }
 
@@ -516,22 +517,39 @@ double gemm_flops(const GemmArgs& a) {
 
 // One product of the plan.
 struct Op {
-  GemmArgs a;
+  GemmArgs a;         // what `code` stands for (expand_op)
+  uint32_t code = 0;  // op code (OpField)
   int kind = 0;       // OpKind
   int group = 0;
   int iter = 0;       // Newton-Schulz iteration it belongs to
   bool large = false; // 256 x 256 kernel; otherwise the tile is chosen when the launch is put together
-  int m = 0, n = 0;   // rows and columns of the result without padding
 };
 
-void set_tile(Op& op, int tile) {
-  GemmArgs& a = op.a;
-  a.tile_m = a.tile_n = tile;
-  // tiles that hold nothing but padding are left out where the padding is wider than a tile: all of it is zero, in every
-  // buffer of a group that runs small tiles (the large tiles of a group cover its padding in every product)
-  a.tiles_m = (op.m + tile - 1) / tile;
-  a.tiles_n = (op.n + tile - 1) / tile;
-  a.tiles_per_mat = a.symmetric ? a.tiles_n * (a.tiles_n + 1) / 2 : a.tiles_m * a.tiles_n;
+// One launch of the step: a product of one group, the products of a merged unit at one position of their chains, or
+// (chain >= 0) whole chains.
+struct Launch {
+  int n = 0;
+  Op* op[kMaxMerged];
+  bool wide = false;   // small tiles: eight wavefronts a tile (see launch_ns_small)
+  int chain = -1;      // index in Plan::chains
+  int wgs = 0;         // workgroups of a chain launch
+};
+
+// The products of one step as they are launched, lane by lane: what enqueue_step issues and mona_plan_info counts.
+struct Plan {
+  StepDesc step;
+  std::vector<GroupDesc> desc;              // by group
+  std::vector<std::vector<Op>> ops;         // by group
+  std::vector<int> o_buf;                   // by group: the ping-pong buffer that holds O_k afterwards
+  std::vector<std::vector<Launch>> lanes;
+  std::vector<ChainArgs> chains;
+  size_t chain_bytes = 0;                   // of rolls and flags, to be cleared before the products
+  int chain_tasks = 0;
+};
+
+void set_tile(const Plan& plan, Op& op, int tile) {
+  op.code = (op.code & ~(3u << OPF_TILE)) | (tile == 32 ? 0u : tile == 64 ? 1u : tile == 128 ? 2u : 3u) << OPF_TILE;
+  expand_op(plan.step, plan.desc[op.group], op.code, op.a);
 }
 
 // Tile of a launch of small tiles: 64 x 64 (four times the workgroups, each with a quarter of the work) until there
@@ -541,17 +559,19 @@ void set_tile(Op& op, int tile) {
 // (limit 64 / 512 / none: 16 x 768 x 1536 2981 / 2563 / 2505, a block of hidden size 1024 3051 / 2520 / 2365,
 // 64 x 1024 x 2048 20562 / 20541 / 21622).
 constexpr long long kMinTiles128 = 128, kMinTiles128F32 = 1024;
-void choose_small_tile(Op* const* ops, int n, bool f32) {
+void choose_small_tile(const Plan& plan, Op* const* ops, int n) {
   long long tiles = 0;
   for (int i = 0; i < n; ++i) {
-    set_tile(*ops[i], 128);
+    set_tile(plan, *ops[i], 128);
     tiles += (long long)ops[i]->a.tiles_per_mat * ops[i]->a.count;
   }
   for (int i = 0; i < n; ++i) {
+    const bool f32 = plan.desc[ops[i]->group].f32 != 0;
     const long long t128 = ops[i]->a.tiles_per_mat;
-    set_tile(*ops[i], 64);
+    set_tile(plan, *ops[i], 64);
     // (a 64 x 64 tile costs about 0.3 of a 128 x 128 one: where 128 pads the sides that much, 64 is less work)
-    if (tiles >= (f32 ? kMinTiles128F32 : kMinTiles128) && ops[i]->a.tiles_per_mat * 3 >= t128 * 10) set_tile(*ops[i], 128);
+    if (tiles >= (f32 ? kMinTiles128F32 : kMinTiles128) && ops[i]->a.tiles_per_mat * 3 >= t128 * 10)
+      set_tile(plan, *ops[i], 128);
   }
 }
 
@@ -581,53 +601,29 @@ std::vector<int> chunk_sizes(int T, int fused) {
 // on the symmetric count, i.e. fewer whenever q > p.  Every p x p result is computed on the upper block
 // triangle and mirrored.  A chunk of one iteration is the literal iteration.
 struct OpBuilder {
-  const mona_state* st;
   const Group& g;
+  int gi;
   const mona_hparams& hp;
+  Plan& plan;
   std::vector<Op>& out;
   int cnt;
-  void* X[2];
-  void* PP[6];
 
-  OpBuilder(const mona_state* st_, const Group& g_, const mona_hparams& hp_, std::vector<Op>& out_);
-  GemmArgs base() const;
-  void push(GemmArgs& a, int kind, int iter, bool tp, bool tq, bool large);
-  void gram(int src, void* S, bool first, int iter);
-  void poly(void* S, void* dst, float diag, int iter);
-  void symprod(void* P, void* Q, void* dst, int iter);
-  void apply(int src, void* Bm, bool with_e, float beta, bool first, bool last, int iter);
+  OpBuilder(const Group& g_, int gi_, const mona_hparams& hp_, Plan& plan_)
+      : g(g_), gi(gi_), hp(hp_), plan(plan_), out(plan_.ops[gi_]), cnt((int)g_.members.size()) {}
+  void push(uint32_t code, int kind, int iter, bool tp, bool tq);
+  void gram(int src, uint32_t S, bool first, int iter);
+  void poly(uint32_t S, uint32_t dst, bool diag, int iter);
+  void symprod(uint32_t P, uint32_t Q, uint32_t dst, int iter);
+  void apply(int src, uint32_t Bm, bool with_e, bool first, bool last, int iter);
   int build();   // returns the ping-pong buffer that holds O_k afterwards
 };
 
-OpBuilder::OpBuilder(const mona_state* st_, const Group& g_, const mona_hparams& hp_, std::vector<Op>& out_)
-    : st(st_), g(g_), hp(hp_), out(out_), cnt((int)g_.members.size()) {
-  char* base = st->arena;
-  for (int b = 0; b < 2; ++b) X[b] = base + g.x_off[b];
-  for (int b = 0; b < 6; ++b) PP[b] = b < g.npp ? base + g.pp_off[b] : nullptr;
-}
-
-GemmArgs OpBuilder::base() const {
-  const Layout& L = st->L;
-  GemmArgs a;
-  memset(&a, 0, sizeof a);
-  a.count = cnt;
-  a.members = reinterpret_cast<const int32_t*>(st->arena + g.members_off);
-  a.scales = st->at<MatScale>(L.scales_off);
-  a.stat = st->at<MatStatic>(L.stat_off);
-  a.dyn = st->at<MatDynamic>(L.dyn_off);
-  a.epilogue = EPI_STORE;
-  a.post = POST_NONE;
-  return a;
-}
-
-void OpBuilder::push(GemmArgs& a, int kind, int iter, bool tp, bool tq, bool large) {
-  a.trans_p = tp ? 1 : 0;
-  a.trans_q = tq ? 1 : 0;
+void OpBuilder::push(uint32_t code, int kind, int iter, bool tp, bool tq) {
   Op op;
-  op.a = a; op.kind = kind; op.iter = iter; op.large = large;
-  op.m = a.symmetric ? std::min(g.m, g.n) : g.m;
-  op.n = a.symmetric ? std::min(g.m, g.n) : g.n;
-  if (large) set_tile(op, 256);
+  op.code = code | (uint32_t)kind << OPF_KIND | (uint32_t)tp << OPF_TP | (uint32_t)tq << OPF_TQ;
+  op.kind = kind; op.group = gi; op.iter = iter;
+  op.large = large_tiles(g, kind, cnt);
+  set_tile(plan, op, op.large ? 256 : 64);
   out.push_back(op);
 }
 
@@ -639,72 +635,27 @@ void OpBuilder::push(GemmArgs& a, int kind, int iter, bool tp, bool tq, bool lar
 // 3328 x 3328 1079 -> 1018, 3072 x 12288 1926 -> 1781, 512 x 256 unchanged) and nothing in fp32, where a product is
 // bound by its multiplications (a block of hidden size 1024: 2353 row-major, 2373 K-major).
 
-void OpBuilder::gram(int src, void* S, bool first, int iter) {
-  GemmArgs a = base();
-  a.P = X[src]; a.Q = X[src]; a.E = nullptr; a.C = S;
-  a.strideP = a.strideQ = g.x_stride; a.strideC = g.s_stride;
-  a.ldp = a.ldq = g.cols_pad; a.ldc = g.p_pad;
-  a.K = g.tall ? g.rows_pad : g.cols_pad;
-  a.symmetric = 1;
-  a.alpha = 1.0f; a.beta = 0.0f;
-  if (first) a.post = POST_INV2;
-  push(a, OP_GRAM, iter, g.tall, g.tall, large_tiles(g, OP_GRAM, cnt));
+void OpBuilder::gram(int src, uint32_t S, bool first, int iter) {
+  push(S << OPF_C | (uint32_t)src << OPF_SRC | (uint32_t)first << OPF_FIRST, OP_GRAM, iter, g.tall, g.tall);
 }
 
-void OpBuilder::poly(void* S, void* dst, float diag, int iter) {
-  const bool large = large_tiles(g, OP_POLY, cnt), symk = !g.f32;
-  GemmArgs a = base();
-  a.P = S; a.Q = S; a.E = S; a.C = dst;
-  a.strideP = a.strideQ = a.strideE = a.strideC = g.s_stride;
-  a.ldp = a.ldq = a.lde = a.ldc = g.p_pad;
-  a.K = g.p_pad;
-  a.symmetric = 1;
-  a.alpha = hp.ns_c; a.beta = hp.ns_b;
-  a.diag = diag;
-  a.diag_n = std::min(g.m, g.n);
-  push(a, OP_POLY, iter, symk, symk, large);
+void OpBuilder::poly(uint32_t S, uint32_t dst, bool diag, int iter) {
+  push(S << OPF_P | S << OPF_Q | dst << OPF_C | (uint32_t)diag << OPF_DIAG, OP_POLY, iter, !g.f32, !g.f32);
 }
 
-void OpBuilder::symprod(void* P, void* Q, void* dst, int iter) {
-  const bool large = large_tiles(g, OP_SYMPROD, cnt), symk = !g.f32;
-  GemmArgs a = base();
-  a.P = P; a.Q = Q; a.E = nullptr; a.C = dst;
-  a.strideP = a.strideQ = a.strideC = g.s_stride;
-  a.ldp = a.ldq = a.ldc = g.p_pad;
-  a.K = g.p_pad;
-  a.symmetric = 1;
-  a.alpha = 1.0f; a.beta = 0.0f;
-  push(a, OP_SYMPROD, iter, symk, symk, large);
+void OpBuilder::symprod(uint32_t P, uint32_t Q, uint32_t dst, int iter) {
+  push(P << OPF_P | Q << OPF_Q | dst << OPF_C, OP_SYMPROD, iter, !g.f32, !g.f32);
 }
 
-void OpBuilder::apply(int src, void* Bm, bool with_e, float beta, bool first, bool last, int iter) {
-  const bool large = large_tiles(g, OP_APPLY, cnt), symk = !g.f32;
-  GemmArgs a = base();
-  a.E = with_e ? X[src] : nullptr; a.C = X[src ^ 1];
-  a.strideE = a.strideC = g.x_stride;
-  a.lde = a.ldc = g.cols_pad;
-  a.K = g.p_pad;
-  bool tp, tq;
-  if (g.tall) {          // X' = beta X + X B
-    a.P = X[src]; a.strideP = g.x_stride; a.ldp = g.cols_pad;
-    a.Q = Bm; a.strideQ = g.s_stride; a.ldq = g.p_pad;
-    tp = false; tq = symk;
-  } else {               // X' = beta X + B X
-    a.P = Bm; a.strideP = g.s_stride; a.ldp = g.p_pad;
-    a.Q = X[src]; a.strideQ = g.x_stride; a.ldq = g.cols_pad;
-    tp = symk && !(large && last);   // the large-tile launch with the update has no register for a K-major P
-    tq = true;
-  }
-  a.symmetric = 0;
-  a.alpha = 1.0f; a.beta = with_e ? beta : 0.0f;
-  if (first) a.post = POST_INV;
-  if (last) {
-    a.epilogue = EPI_UPDATE;
-    a.store_out = (hp.flags & MONA_FLAG_KEEP_O) ? 1 : 0;
-    a.w_keep = 1.0f - hp.lr * hp.weight_decay;
-    a.o_scale = hp.lr * hp.gamma_coeff * sqrtf((float)std::max(g.m, g.n));
-  }
-  push(a, OP_APPLY, iter, tp, tq, large);
+void OpBuilder::apply(int src, uint32_t Bm, bool with_e, bool first, bool last, int iter) {
+  const bool symk = !g.f32;
+  uint32_t code = Bm << OPF_P | Bm << OPF_Q | (uint32_t)src << OPF_SRC | (uint32_t)with_e << OPF_E |
+                  (uint32_t)first << OPF_FIRST | (uint32_t)last << OPF_LAST;
+  if (hp.flags & MONA_FLAG_KEEP_O) code |= 1u << OPF_STORE;
+  // tall: X' = a X + X B, the Q operand is B; wide: X' = a X + B X, P is B and Q is X
+  // (the large-tile launch with the update has no register for a K-major P)
+  if (g.tall) push(code, OP_APPLY, iter, false, symk);
+  else push(code, OP_APPLY, iter, symk && !(last && large_tiles(g, OP_APPLY, cnt)), true);
 }
 
 int OpBuilder::build() {
@@ -715,15 +666,15 @@ int OpBuilder::build() {
     const int n = chunks[ci];
     const bool first = ci == 0, last = ci + 1 == chunks.size();
     if (n == 1) {
-      gram(src, PP[0], first, iter);
-      poly(PP[0], PP[1], 0.0f, iter);
-      apply(src, PP[1], true, hp.ns_a, first, last, iter);
+      gram(src, 0, first, iter);
+      poly(0, 1, false, iter);
+      apply(src, 1, true, first, last, iter);
     } else {
-      void* S = PP[0]; void* S2 = PP[1]; void* U = PP[2]; void* Q = PP[3]; void* R = PP[4]; void* R2 = PP[5];
+      uint32_t S = 0, S2 = 1, U = 2, Q = 3, R = 4, R2 = 5;
       gram(src, S, first, iter);
       for (int i = 0; i < n; ++i) {
-        void* Qi = i == 0 ? R : Q;                 // Q_0 is R_0
-        poly(S, Qi, hp.ns_a, iter + i);
+        const uint32_t Qi = i == 0 ? R : Q;        // Q_0 is R_0
+        poly(S, Qi, true, iter + i);
         if (i + 1 < n) {
           symprod(S, Qi, U, iter + i);
           symprod(U, Qi, S2, iter + i);
@@ -734,7 +685,7 @@ int OpBuilder::build() {
           std::swap(R, R2);
         }
       }
-      apply(src, R, false, 0.0f, first, last, iter + n - 1);
+      apply(src, R, false, first, last, iter + n - 1);
     }
     src ^= 1;
     iter += n;
@@ -742,32 +693,134 @@ int OpBuilder::build() {
   return T == 0 ? 1 : src;
 }
 
-// One launch of the step: a product of one group, or the products of a merged unit at one position of their chains.
-struct Launch {
-  int n = 0;
-  Op* op[kMaxMerged];
-  bool wide = false;   // small tiles: eight wavefronts a tile (see launch_ns_small)
-};
+// Tiles of the products of `groups` at position `pos` when all of them are `tile` wide.
+long long tiles_at(Plan& plan, const std::vector<int>& groups, size_t pos, int tile) {
+  long long tiles = 0;
+  for (int gi : groups) {
+    if (pos >= plan.ops[gi].size()) continue;
+    Op& op = plan.ops[gi][pos];
+    set_tile(plan, op, tile);
+    tiles += (long long)op.a.tiles_per_mat * op.a.count;
+  }
+  return tiles;
+}
 
-// The products of one step as they are launched, lane by lane: what enqueue_step issues and mona_plan_info counts.
-struct Plan {
-  std::vector<std::vector<Op>> ops;         // by group
-  std::vector<int> o_buf;                   // by group: the ping-pong buffer that holds O_k afterwards
-  std::vector<std::vector<Launch>> lanes;
-};
+// Whether the products of these groups may go out as one launch (ns_chain_kernel) instead of one launch per position.
+//
+// Where the line lies.  A chain saves 2 to 4 us of every product, but its workgroups are one to a CU and its tiles 64 x 64
+// at most, dealt without regard to the die they are on.  Measured, us per step with launches / as a chain, with the work of the
+// widest position (64 x 64 tiles times K, in thousands): 256 x 256 (4) 94 / 66, 512 x 512 (33) 111 / 98, 512 x 2048 (131) 147 / 130,
+// 4 x 300 x 900 (115) 131 / 111, 200 x 64 x 128 (51, fp32) 147 / 134, 768 x 768 (110) 133 / 131, 4 x 512 x 512 (131) 120 / 118;
+// beyond it 1024 x 1024 (262) 152 / 158, 6 x 384 x 1000 (221) 150 / 156, 30 x 256 x 512 (245) 155 / 180, 250 x 70 x 100
+// (192, 1000 tiles) 166 / 223, 700 x 2000 (270) 168 / 165.
+constexpr long long kChainTiles = 448, kChainWork = 140000;
+// The tile a chain takes at one position: 32 x 32 as long as every one has a CU of its own.
+int chain_tile(Plan& plan, const std::vector<int>& groups, size_t pos) {
+  return tiles_at(plan, groups, pos, 32) <= device_cu_count() ? 32 : 64;
+}
+// Tasks of the chain, 0 if there is none.
+int chainable(const Layout& L, Plan& plan, const std::vector<int>& groups) {
+  if (!device_runs_chains() || groups.size() > (size_t)kMaxMerged) return 0;
+  size_t ops = 0, positions = 0;
+  for (int gi : groups) {
+    const Group& g = L.groups[gi];
+    ops += plan.ops[gi].size();
+    positions = std::max(positions, plan.ops[gi].size());
+    // a matrix is addressed with 32-bit byte offsets
+    if (std::max(g.x_stride, g.s_stride) * g.esize >= (int64_t)1 << 31) return 0;
+  }
+  if (ops == 0 || ops > (size_t)kMaxChainOps) return 0;
+  long long tasks = 0;
+  for (size_t pos = 0; pos < positions; ++pos) {
+    if (tiles_at(plan, groups, pos, 64) > kChainTiles) return 0;
+    long long work = 0;
+    for (int gi : groups)
+      if (pos < plan.ops[gi].size()) {
+        const GemmArgs& a = plan.ops[gi][pos].a;
+        work += (long long)a.tiles_per_mat * a.count * a.K;
+      }
+    if (work > kChainWork) return 0;
+    tasks += tiles_at(plan, groups, pos, chain_tile(plan, groups, pos));
+  }
+  return tasks <= kMaxChainTasks ? (int)tasks : 0;
+}
 
-void build_plan(const mona_state* st, const mona_hparams& hp, Plan& plan) {
+// Puts the chain of `groups` together: the tiles of every product, then the tasks in order.  `launches` receives the
+// products position by position, as they are launched when each is timed by itself; returns the chain's own launch.
+Launch build_chain(const mona_state* st, Plan& plan, const std::vector<int>& groups, std::vector<Launch>& launches) {
+  const Layout& L = st->L;
+  const int cus = device_cu_count();
+  char* const area = st->arena + L.chain_off;
+  ChainArgs c;
+  memset(&c, 0, sizeof c);
+  c.step = plan.step;
+  c.roll = reinterpret_cast<ChainRoll*>(area) + plan.chains.size();
+  c.flags = reinterpret_cast<uint32_t*>(area + kMaxChains * sizeof(ChainRoll)) + plan.chain_tasks;
+  struct Before { int32_t first = 0, per_mat = 0; };
+  std::vector<Before> before(groups.size());
+  long long tasks = 0, most = 0;
+  for (size_t j = 0; j < groups.size(); ++j) c.group[j] = plan.desc[groups[j]];
+  for (size_t pos = 0;; ++pos) {
+    Launch l;
+    const long long here = tiles_at(plan, groups, pos, chain_tile(plan, groups, pos));
+    for (int gi : groups)
+      if (pos < plan.ops[gi].size()) l.op[l.n++] = &plan.ops[gi][pos];
+    if (l.n == 0) break;
+    // the longest K first: its tiles are the last to finish
+    std::stable_sort(l.op, l.op + l.n, [](const Op* x, const Op* y) { return x->a.K > y->a.K; });
+    for (int i = 0; i < l.n; ++i) {
+      const Op& op = *l.op[i];
+      const size_t j = std::find(groups.begin(), groups.end(), op.group) - groups.begin();
+      const int32_t first = (int32_t)tasks;
+      tasks += (long long)op.a.tiles_per_mat * op.a.count;
+      c.op[c.ops++] = ChainOp{(int32_t)tasks, before[j].first, before[j].per_mat, op.code | (uint32_t)j << OPF_GROUP};
+      before[j].first = first;
+      before[j].per_mat = op.a.tiles_per_mat;
+    }
+    most = std::max(most, here);
+    l.wide = true;
+    launches.push_back(l);
+  }
+  c.tasks = (int32_t)tasks;
+  Launch chain;
+  chain.wgs = (int)std::min<long long>(most, cus);
+  chain.chain = (int)plan.chains.size();
+  plan.chains.push_back(c);
+  plan.chain_tasks += round_up((int)tasks, 4);
+  plan.chain_bytes = kMaxChains * sizeof(ChainRoll) + plan.chain_tasks * sizeof(uint32_t);
+  return chain;
+}
+
+// `one_by_one`: every product as a launch of its own, on the tiles and with the split of K it has in the ordinary step.
+void build_plan(const mona_state* st, const mona_hparams& hp, Plan& plan, bool one_by_one) {
   const Layout& L = st->L;
   const size_t ngroups = L.groups.size();
+  memset(&plan.step, 0, sizeof plan.step);
+  plan.step.scales = st->at<MatScale>(L.scales_off);
+  plan.step.stat = st->at<MatStatic>(L.stat_off);
+  plan.step.dyn = st->at<MatDynamic>(L.dyn_off);
+  plan.step.ns_a = hp.ns_a; plan.step.ns_b = hp.ns_b; plan.step.ns_c = hp.ns_c;
+  plan.step.w_keep = 1.0f - hp.lr * hp.weight_decay;
   plan.ops.resize(ngroups);
   plan.lanes.resize(L.lanes);
-  for (size_t gi = 0; gi < ngroups; ++gi) {
-    plan.o_buf.push_back(OpBuilder(st, L.groups[gi], hp, plan.ops[gi]).build());
-    for (Op& op : plan.ops[gi]) op.group = (int)gi;
+  for (const Group& g : L.groups) {
+    GroupDesc d;
+    memset(&d, 0, sizeof d);
+    d.x = st->arena + g.x_off[0];
+    d.x_step = (int64_t)(g.x_off[1] - g.x_off[0]);
+    d.pp = st->arena + g.pp_off[0];
+    d.pp_step = (int64_t)(g.pp_off[1] - g.pp_off[0]);
+    d.members = reinterpret_cast<const int32_t*>(st->arena + g.members_off);
+    d.count = (int32_t)g.members.size();
+    d.m = g.m; d.n = g.n; d.rows_pad = g.rows_pad; d.cols_pad = g.cols_pad;
+    d.tall = g.tall; d.f32 = g.f32;
+    d.o_scale = hp.lr * hp.gamma_coeff * sqrtf((float)std::max(g.m, g.n));
+    plan.desc.push_back(d);
   }
+  for (size_t gi = 0; gi < ngroups; ++gi) plan.o_buf.push_back(OpBuilder(L.groups[gi], (int)gi, hp, plan).build());
   auto add = [&](std::vector<Launch>& lane, Launch l) {
     if (!l.op[0]->large) {
-      choose_small_tile(l.op, l.n, L.groups[l.op[0]->group].f32);
+      choose_small_tile(plan, l.op, l.n);
       // the longest chains of K first: their tiles are the last to finish
       std::stable_sort(l.op, l.op + l.n, [](const Op* x, const Op* y) { return x->a.K > y->a.K; });
       long long slots = 0;
@@ -777,6 +830,34 @@ void build_plan(const mona_state* st, const mona_hparams& hp, Plan& plan) {
     }
     lane.push_back(l);
   };
+  // Chains, where all of the step fits into them: a chain's workgroups wait on their CUs, so beside launches that fill the
+  // chip it takes more than it gives (128 x 768 x 256 and 4 x 128 x 512: 628 us a step with launches, 687 with a chain).
+  std::vector<std::vector<int>> chains;
+  bool all = std::all_of(L.units.begin(), L.units.end(), [](const Unit& u) { return u.merged; });
+  for (size_t u = 0; all && u < L.units.size(); ++u) {
+    auto joined = [&](std::vector<int> chain) {
+      chain.insert(chain.end(), L.units[u].groups.begin(), L.units[u].groups.end());
+      return chain;
+    };
+    auto it = std::find_if(chains.begin(), chains.end(),
+                           [&](const std::vector<int>& chain) { return chainable(L, plan, joined(chain)) > 0; });
+    if (it != chains.end()) *it = joined(*it);
+    else chains.push_back(joined({}));
+    all = chains.size() <= (size_t)kMaxChains && chainable(L, plan, chains.back()) > 0;
+  }
+  int tasks = 0;
+  for (const auto& groups : chains) tasks += all ? round_up(chainable(L, plan, groups), 4) : 0;
+  all = all && tasks <= kMaxChainTasks;
+  if (all) {
+    for (size_t i = 0; i < chains.size(); ++i) {
+      std::vector<Launch> singles;
+      const Launch chain = build_chain(st, plan, chains[i], singles);
+      std::vector<Launch>& lane = plan.lanes[i % plan.lanes.size()];
+      if (one_by_one) lane.insert(lane.end(), singles.begin(), singles.end());
+      else lane.push_back(chain);
+    }
+    return;
+  }
   for (const Unit& u : L.units) {
     std::vector<Launch>& lane = plan.lanes[u.lane];
     if (u.merged) {
@@ -1064,7 +1145,7 @@ int enqueue_step(mona_state* st, const mona_hparams* hp, hipStream_t s) {
   } while (0)
 
   Plan plan;
-  build_plan(st, *hp, plan);
+  build_plan(st, *hp, plan, st->profiling > 1);
   for (size_t gi = 0; gi < L.groups.size(); ++gi) L.groups[gi].o_buf = plan.o_buf[gi];
 
   const bool prof = st->profiling > 0;
@@ -1103,7 +1184,7 @@ int enqueue_step(mona_state* st, const mona_hparams* hp, hipStream_t s) {
     STEP_TRY(pass(L.range_end[1], L.range_end[2], 0, st->late_stream));
     STEP_TRY(pass(L.range_end[2], L.range_end[3], 1, st->late_stream));
     STEP_TRY(launch_norm_finalize(stat, partials, scales, order + L.num_early, count - L.num_early,
-                                  L.max_blocks, hp->ns_eps, st->late_stream));
+                                  L.max_blocks, hp->ns_eps, nullptr, 0, st->late_stream));
     STEP_TRY(hipEventRecord(st->late_done, st->late_stream));
   }
   STEP_TRY(pass(0, L.range_end[0], 0, s));
@@ -1114,13 +1195,15 @@ int enqueue_step(mona_state* st, const mona_hparams* hp, hipStream_t s) {
   }
   if (L.one_buffer && !muon_only) st->last_beta_a = hp->beta_a;
   STEP_TRY(launch_norm_finalize(stat, partials, scales, order, overlap ? L.num_early : count, L.max_blocks, hp->ns_eps,
-                                s));
+                                st->arena + L.chain_off, plan.chain_bytes, s));
   if (prof) STEP_TRY(hipEventRecord(ev[1], s));
 
   // Newton-Schulz (Eq. newton_schulz), T iterations per shape group
   st->fused_update = T > 0;
   // per-launch timing serialises the launches on the caller's stream so that each interval is one kernel
-  const bool fork = !st->side.empty() && st->profiling < 2 && T > 0;
+  bool fork = false;
+  for (int lane = 1; lane < L.lanes; ++lane) fork = fork || !plan.lanes[lane].empty();
+  fork = fork && st->profiling < 2;
   if (fork) {
     STEP_TRY(hipEventRecord(st->fork_ev, s));
     forked = true;
@@ -1150,6 +1233,10 @@ int enqueue_step(mona_state* st, const mona_hparams* hp, hipStream_t s) {
       more = true;
       const Launch& l = queue[at[lane]++];
       hipStream_t gs = lane == 0 ? s : st->side[lane - 1];
+      if (l.chain >= 0) {
+        STEP_TRY(launch_ns_chain(plan.chains[l.chain], l.wgs, gs));
+        continue;
+      }
       int cu_cap = 0;
       if (overlap && l.op[0]->group == L.late_group) {
         if (late_forked) STEP_TRY(hipStreamWaitEvent(s, st->late_done, 0));
@@ -1285,7 +1372,7 @@ namespace {
 // static device array.  Every GPU the library runs on holds its own copy, at its own address, until the
 // process ends.
 constexpr size_t kScratchBytes = MONA_NOALLOC_SCRATCH_BYTES;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kChainBytes];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -1537,7 +1624,7 @@ int mona_plan_info(mona_state* st, int32_t ns_steps, int64_t* launches_out, doub
   memset(&hp, 0, sizeof hp);
   hp.ns_steps = ns_steps;
   Plan plan;
-  build_plan(st, hp, plan);
+  build_plan(st, hp, plan, false);
   double flops = 0.0;
   int64_t launches = 0;
   for (const auto& lane : plan.lanes) launches += (int64_t)lane.size();

@@ -84,6 +84,88 @@ struct GemmArgs {
   float o_scale;            // eta * gamma
 };
 
+// ---- products, compactly ------------------------------------------------------------------
+// What all products of a shape group share, and what those of a step share; with an op code they say all that GemmArgs
+// says (expand_op, on the host for a launch, on the device for the kernel that runs a whole chain of products).
+struct GroupDesc {
+  char* x;                  // ping-pong buffer 0 of X; buffer 1 is x_step bytes on
+  char* pp;                 // p x p matrix 0; the others every pp_step bytes
+  int64_t x_step, pp_step;
+  const int32_t* members;   // group member -> matrix index
+  int32_t count, m, n;      // matrices, their shape
+  int32_t rows_pad, cols_pad;
+  int32_t tall, f32;
+  float o_scale;            // eta * gamma
+};
+struct StepDesc {
+  const MatScale* scales;
+  const MatStatic* stat;
+  const MatDynamic* dyn;
+  float ns_a, ns_b, ns_c;
+  float w_keep;             // 1 - eta * lambda
+};
+
+enum OpKind : uint32_t { OP_GRAM = 0, OP_POLY = 1, OP_APPLY = 2, OP_SYMPROD = 3 };
+// Fields of an op code (bit offsets).  P, Q, C: numbers of p x p matrices; SRC: the ping-pong buffer an X operand is in.
+enum OpField : uint32_t {
+  OPF_KIND = 0, OPF_P = 2, OPF_Q = 5, OPF_C = 8, OPF_SRC = 11,
+  OPF_E = 12,       // apply: adds a X
+  OPF_DIAG = 13,    // poly: adds a I
+  OPF_FIRST = 14,   // the first product that reads the unscaled working copy: carries the scale
+  OPF_LAST = 15,    // apply: carries the parameter update
+  OPF_STORE = 16,   // (with LAST) also stores O
+  OPF_TP = 17, OPF_TQ = 18,   // the operand is read K-major
+  OPF_TILE = 19,    // 0: 32 x 32, 1: 64 x 64, 2: 128 x 128, 3: 256 x 256
+};
+__host__ __device__ inline uint32_t op_field(uint32_t code, uint32_t at, uint32_t mask = 1u) { return (code >> at) & mask; }
+
+__host__ __device__ inline void expand_op(const StepDesc& st, const GroupDesc& g, uint32_t code, GemmArgs& a) {
+  const uint32_t kind = op_field(code, OPF_KIND, 3u), src = op_field(code, OPF_SRC);
+  const int32_t p_pad = g.tall ? g.cols_pad : g.rows_pad, p_real = g.m < g.n ? g.m : g.n;
+  const int64_t x_stride = (int64_t)g.rows_pad * g.cols_pad, s_stride = (int64_t)p_pad * p_pad;
+  char* const xs = g.x + (src ? g.x_step : 0);
+  auto pp = [&](uint32_t at) { return g.pp + (int64_t)op_field(code, at, 7u) * g.pp_step; };
+  const bool apply = kind == OP_APPLY, last = op_field(code, OPF_LAST), first = op_field(code, OPF_FIRST);
+  a.count = g.count;
+  a.members = g.members; a.scales = st.scales; a.stat = st.stat; a.dyn = st.dyn;
+  a.symmetric = apply ? 0 : 1;
+  a.trans_p = (int32_t)op_field(code, OPF_TP); a.trans_q = (int32_t)op_field(code, OPF_TQ);
+  a.alpha = 1.0f; a.beta = 0.0f; a.diag = 0.0f; a.diag_n = p_real;
+  a.post = POST_NONE; a.epilogue = EPI_STORE; a.store_out = 0;
+  a.w_keep = st.w_keep; a.o_scale = g.o_scale;
+  // operands: the p x p matrices numbered by the code, an X operand in place of one or both
+  a.P = pp(OPF_P); a.Q = pp(OPF_Q); a.C = pp(OPF_C); a.E = nullptr;
+  a.strideP = a.strideQ = a.strideE = a.strideC = s_stride;
+  a.ldp = a.ldq = a.lde = a.ldc = p_pad;
+  a.K = p_pad;
+  if (kind == OP_GRAM) {                        // S = X X^T (tall: X^T X)
+    a.P = a.Q = xs; a.strideP = a.strideQ = x_stride; a.ldp = a.ldq = g.cols_pad;
+    a.K = g.tall ? g.rows_pad : g.cols_pad;
+    if (first) a.post = POST_INV2;
+  } else if (kind == OP_POLY) {                 // b S + c S S (+ a I)
+    a.E = a.P;
+    a.alpha = st.ns_c; a.beta = st.ns_b;
+    if (op_field(code, OPF_DIAG)) a.diag = st.ns_a;
+  } else if (apply) {                           // a X + B X (tall: a X + X B), or B X alone
+    if (g.tall) { a.P = xs; a.strideP = x_stride; a.ldp = g.cols_pad; }
+    else        { a.Q = xs; a.strideQ = x_stride; a.ldq = g.cols_pad; }
+    a.C = g.x + (src ? 0 : g.x_step);
+    a.strideE = a.strideC = x_stride;
+    a.lde = a.ldc = g.cols_pad;
+    if (op_field(code, OPF_E)) { a.E = xs; a.beta = st.ns_a; }
+    if (first) a.post = POST_INV;
+    if (last) { a.epilogue = EPI_UPDATE; a.store_out = (int32_t)op_field(code, OPF_STORE); }
+  }
+  // Tiles that hold nothing but padding are left out where the padding is wider than a tile: all of it is zero, in every
+  // buffer of a group that runs small tiles (the large tiles of a group cover its padding in every product).
+  const int32_t shift = 5 + (int32_t)op_field(code, OPF_TILE, 3u), tile = 1 << shift;
+  const int32_t rm = apply ? g.m : p_real, rn = apply ? g.n : p_real;
+  a.tile_m = a.tile_n = tile;
+  a.tiles_m = (rm + tile - 1) >> shift;
+  a.tiles_n = (rn + tile - 1) >> shift;
+  a.tiles_per_mat = a.symmetric ? a.tiles_n * (a.tiles_n + 1) / 2 : a.tiles_m * a.tiles_n;
+}
+
 // One launch of the small-tile kernels: the products that several shape groups run at the same position of their
 // chains (passed by value: nothing is copied from the host).
 constexpr int kMaxMerged = 8;
@@ -92,6 +174,35 @@ struct GemmBatch {
   int32_t slot_end[kMaxMerged];     // workgroups per die up to and including product g (filled at launch)
   GemmArgs a[kMaxMerged];
 };
+
+// All products of a step of up to kMaxMerged shape groups as one launch (ns_chain_kernel), passed by value.
+constexpr int kMaxChainOps = 180, kMaxChainTasks = 11264;   // (tasks: of all chains of a step)
+struct ChainOp {
+  int32_t end;             // tasks (tiles) up to and including this product
+  int32_t before;          // first task of the same group's product before
+  int32_t before_per_mat;  // tiles a matrix has there (0: none)
+  uint32_t code;           // op code; the group in the bits from OPF_GROUP on
+};
+constexpr uint32_t OPF_GROUP = 24;
+// Shared by the workgroups of a chain launch; zero when it starts.
+struct ChainRoll {
+  uint32_t reported;       // workgroups that have reported, and whether the roll is closed
+  uint32_t pad[31];
+  uint32_t workgroups;     // those that take part, once it is closed
+  uint32_t pad2[31];
+};
+struct ChainArgs {
+  StepDesc step;
+  ChainRoll* roll;
+  uint32_t* flags;         // one for each task; zero when the launch starts
+  int32_t ops, tasks;
+  GroupDesc group[kMaxMerged];
+  ChainOp op[kMaxChainOps];
+};
+static_assert(sizeof(ChainArgs) <= 4000, "an argument block holds 4 KB");
+// What every step clears before its products: the rolls and the flags of its chain launches, one after the other.
+constexpr int kMaxChains = 4;
+constexpr size_t kChainBytes = kMaxChains * sizeof(ChainRoll) + kMaxChainTasks * sizeof(uint32_t);
 
 constexpr int kXcds = 8;   // MI355X: 8 accelerator dies, workgroups are dealt to them round-robin
 // workgroups per die of a launch of small tiles
@@ -114,9 +225,10 @@ hipError_t launch_state_update(const MatStatic* stat, const MatDynamic* dyn, con
                                float mu, float beta_a, float alpha, int use_prev, hipStream_t s);
 // norms, scales and the repair of flagged working copies
 // `list` (DEVICE, may be NULL = matrices 0 .. count - 1): the matrix indices to finalise; max_blocks: the most
-// elementwise blocks any of them has
+// elementwise blocks any of them has; zero: memory to clear on the way (a multiple of 16 bytes)
 hipError_t launch_norm_finalize(const MatStatic* stat, const double* partials, MatScale* scales,
-                                const int32_t* list, int count, int max_blocks, float eps, hipStream_t s);
+                                const int32_t* list, int count, int max_blocks, float eps, void* zero, size_t zero_bytes,
+                                hipStream_t s);
 // a one-matrix state prepared by one kernel from its arguments (no host copy): tables, scale, cleared workspace
 hipError_t launch_single_prepare(const MatStatic& ms, const MatDynamic& md, void* o_ptr, MatStatic* stat,
                                  MatDynamic* dyn, void** o_ptrs, BlockWork* work, int num_blocks, int32_t* members,
@@ -128,7 +240,10 @@ hipError_t launch_plain_update(const MatStatic* stat, const MatDynamic* dyn, con
 hipError_t launch_ns_gemm(const GemmArgs& a, int cu_cap, hipStream_t s);   // 256 x 256 tiles, bf16
 // 64 x 64 or 128 x 128 tiles; wide: eight wavefronts a tile and one workgroup per CU instead of four and two
 hipError_t launch_ns_small(GemmBatch& b, bool f32, bool wide, hipStream_t s);
+// a whole chain of products on the same tiles; `wgs` workgroups
+hipError_t launch_ns_chain(const ChainArgs& c, int wgs, hipStream_t s);
 int device_cu_count();
+bool device_runs_chains();
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 
 }  // namespace mona

@@ -102,6 +102,35 @@ __device__ __forceinline__ void rest_tt(u32x2 (&al)[2][2], u32x2 (&ah)[2][2], u3
                :
                : "memory");
 }
+// the same for a tile of a single block (T = 32: K-major rows of 64 bytes)
+__device__ __forceinline__ void read1_rr(u32x4 (&a)[2], u32x4 (&b)[2], uint32_t ra0, uint32_t ra1, uint32_t rb0, uint32_t rb1) {
+  asm volatile(
+      "ds_read_b128 %0, %4\n\tds_read_b128 %2, %6\n\tds_read_b128 %1, %5\n\tds_read_b128 %3, %7\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(a[0]), "=&v"(a[1]), "=&v"(b[0]), "=&v"(b[1])
+      : "v"(ra0), "v"(ra1), "v"(rb0), "v"(rb1)
+      : "memory");
+}
+__device__ __forceinline__ void read1_rt(u32x4 (&a)[2], u32x2 (&bl)[2], u32x2 (&bh)[2], uint32_t ra0, uint32_t ra1, uint32_t tb) {
+  asm volatile(
+      "ds_read_b128 %0, %6\n\tds_read_b64_tr_b16 %2, %8\n\tds_read_b64_tr_b16 %4, %8 offset:256\n\t"
+      "ds_read_b128 %1, %7\n\tds_read_b64_tr_b16 %3, %8 offset:1024\n\tds_read_b64_tr_b16 %5, %8 offset:1280\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(a[0]), "=&v"(a[1]), "=&v"(bl[0]), "=&v"(bl[1]), "=&v"(bh[0]), "=&v"(bh[1])
+      : "v"(ra0), "v"(ra1), "v"(tb)
+      : "memory");
+}
+__device__ __forceinline__ void read1_tt(u32x2 (&al)[2], u32x2 (&ah)[2], u32x2 (&bl)[2], u32x2 (&bh)[2], uint32_t ta, uint32_t tb) {
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %8\n\tds_read_b64_tr_b16 %2, %8 offset:256\n\t"
+      "ds_read_b64_tr_b16 %4, %9\n\tds_read_b64_tr_b16 %6, %9 offset:256\n\t"
+      "ds_read_b64_tr_b16 %1, %8 offset:1024\n\tds_read_b64_tr_b16 %3, %8 offset:1280\n\t"
+      "ds_read_b64_tr_b16 %5, %9 offset:1024\n\tds_read_b64_tr_b16 %7, %9 offset:1280\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(al[0]), "=&v"(al[1]), "=&v"(ah[0]), "=&v"(ah[1]), "=&v"(bl[0]), "=&v"(bl[1]), "=&v"(bh[0]), "=&v"(bh[1])
+      : "v"(ta), "v"(tb)
+      : "memory");
+}
 // fp32, one half of a stage (8 values of k): lane half h holds k = 4 h + e, e = 0..3, of both operands.
 __device__ __forceinline__ void read32_rr(f32x4 (&a)[2], f32x4 (&b)[2], uint32_t ra, uint32_t rb) {
   asm volatile(
@@ -148,6 +177,31 @@ __device__ __forceinline__ void read32_tt(float (&a)[2][4], float (&b)[2][4], ui
       : "memory");
 }
 
+__device__ __forceinline__ void read32_1_rr(f32x4& a, f32x4& b, uint32_t ra, uint32_t rb) {
+  asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %3\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(a), "=&v"(b) : "v"(ra), "v"(rb) : "memory");
+}
+template <int KK>
+__device__ __forceinline__ void read32_1_rt(f32x4& a, float (&b)[4], uint32_t ra, uint32_t tb) {
+  asm volatile(
+      "ds_read_b128 %0, %5\n\tds_read_b32 %1, %6 offset:%7\n\tds_read_b32 %2, %6 offset:%8\n\t"
+      "ds_read_b32 %3, %6 offset:%9\n\tds_read_b32 %4, %6 offset:%10\n\ts_waitcnt lgkmcnt(0)"
+      : "=&v"(a), "=&v"(b[0]), "=&v"(b[1]), "=&v"(b[2]), "=&v"(b[3])
+      : "v"(ra), "v"(tb), "n"(KK * 1024), "n"(KK * 1024 + 128), "n"(KK * 1024 + 256), "n"(KK * 1024 + 384)
+      : "memory");
+}
+template <int KK>
+__device__ __forceinline__ void read32_1_tt(float (&a)[4], float (&b)[4], uint32_t ta, uint32_t tb) {
+  asm volatile(
+      "ds_read_b32 %0, %8 offset:%10\n\tds_read_b32 %1, %8 offset:%11\n\t"
+      "ds_read_b32 %2, %8 offset:%12\n\tds_read_b32 %3, %8 offset:%13\n\t"
+      "ds_read_b32 %4, %9 offset:%10\n\tds_read_b32 %5, %9 offset:%11\n\t"
+      "ds_read_b32 %6, %9 offset:%12\n\tds_read_b32 %7, %9 offset:%13\n\ts_waitcnt lgkmcnt(0)"
+      : "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[3]), "=&v"(b[0]), "=&v"(b[1]), "=&v"(b[2]), "=&v"(b[3])
+      : "v"(ta), "v"(tb), "n"(KK * 1024), "n"(KK * 1024 + 128), "n"(KK * 1024 + 256), "n"(KK * 1024 + 384)
+      : "memory");
+}
+
 __device__ __forceinline__ bf16x8 frag(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 __device__ __forceinline__ bf16x8 frag(u32x2 lo, u32x2 hi) {
   const u32x4 v = {lo.x, lo.y, hi.x, hi.y};
@@ -161,7 +215,8 @@ template <typename E, int T, bool WIDE>
 struct Geo {
   static constexpr int ES = sizeof(E);
   static constexpr int KB = 64 / ES;                // k values of a slab
-  static constexpr int WC = T / 64;                 // wavefronts along a side of the tile
+  static constexpr int WC = T == 128 ? 2 : 1;       // wavefronts along a side of the tile
+  static constexpr int NB = T == 32 ? 1 : 2;        // 32 x 32 blocks along a side of a wavefront's part of it
   static constexpr int WAVES = WIDE ? 8 : 4, THREADS = 64 * WAVES;
   static constexpr int KS = WAVES / (WC * WC);      // wavefronts along K
   static constexpr int BK = KB * KS;                // k values of a stage
@@ -173,36 +228,84 @@ struct Geo {
   static constexpr int LDW = T + 4;                 // floats per staged row of the epilogue (+4: rows on different banks)
   static constexpr int RING = STAGES * STAGE, STAGING = KS * T * LDW * 4;
   static constexpr int LDS = RING > STAGING ? RING : STAGING;
-  static_assert(T == 64 || T == 128, "64 or 128");
+  static_assert(T == 32 || T == 64 || T == 128, "32, 64 or 128");
 };
 
-// C tile (ti, tj) of matrix t.mat.  lds: Geo<E, T, WIDE>::LDS bytes, 256-byte aligned.
-template <typename E, int T, bool WIDE, bool TP, bool TQ>
-__device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, char* lds) {
+// 16 bytes of an array that other workgroups of the same launch write or read (SHARED: coherent across the dies at device
+// scope, without any cache being written back or invalidated), or that only earlier and later launches do.  `bytes` from
+// the start of the array, which is wavefront-uniform and smaller than 4 GB where it is shared.
+constexpr int kDeviceScope = 16;   // sc1
+template <bool SHARED>
+struct Array {
+  char* p;
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ Array(void* base, int64_t size) : p(static_cast<char*>(base)) {
+    if constexpr (SHARED) r = __builtin_amdgcn_make_buffer_rsrc(base, 0, (int)(uint32_t)size, 0x00020000);
+  }
+  template <typename V> __device__ __forceinline__ V load(size_t bytes) const {
+    if constexpr (SHARED) return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, (int)(uint32_t)bytes, 0, kDeviceScope));
+    else return *reinterpret_cast<const V*>(p + bytes);
+  }
+  template <typename V> __device__ __forceinline__ void store(size_t bytes, V v) const {
+    if constexpr (SHARED) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, (int)(uint32_t)bytes, 0, kDeviceScope);
+    else *reinterpret_cast<V*>(p + bytes) = v;
+  }
+};
+
+// What the epilogue of a tile needs to know of its matrix: two or three loads that depend on each other, made before the
+// first operand is waited for.
+struct TileMatrix {
+  float post;
+  bool skip_w;
+  int m, n, w_dtype;
+  void* w;
+};
+__device__ __forceinline__ TileMatrix look_up(const GemmArgs& a, const TileId& t) {
+  TileMatrix v = {1.0f, true, 0, 0, 0, nullptr};
+  if (a.post == POST_NONE && a.epilogue != EPI_UPDATE) return v;
+  const int mi = a.members[t.mat];
+  if (a.post == POST_INV) v.post = a.scales[mi].inv;
+  else if (a.post == POST_INV2) v.post = a.scales[mi].inv2;
+  if (a.epilogue == EPI_UPDATE) {
+    const MatStatic& ms = a.stat[mi];
+    v.m = ms.m; v.n = ms.n; v.w_dtype = ms.w_dtype;
+    v.w = a.dyn[mi].w;
+    v.skip_w = (a.scales[mi].status & 2u) != 0;
+  }
+  return v;
+}
+
+// C tile (ti, tj) of matrix t.mat.  lds: Geo<E, T, WIDE>::LDS bytes, 256-byte aligned.  SHARED: other workgroups of this
+// launch write the operands and read the result.
+template <typename E, int T, bool WIDE, bool TP, bool TQ, bool SHARED>
+__device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, const TileMatrix& v, int tid, char* lds) {
+  // every contraction is written out below: a product comes out the same, bit for bit, in whichever kernel it runs
+#pragma clang fp contract(off)
   typedef Geo<E, T, WIDE> G;
   constexpr int ES = G::ES, CH = Chunk<E>::N;
   typedef typename Chunk<E>::vec vec_t;
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kg = G::kPrivate ? wave : wave >> 2, w4 = wave & 3;
   const int wm = G::kPrivate ? 0 : w4 >> 1, wn = G::kPrivate ? 0 : w4 & 1;
   const int m0 = t.ti * T, n0 = t.tj * T;
 
   // E operand of the epilogue: requested first, so that it has arrived long before it is used
-  constexpr int CPR = T / CH;                       // chunks per tile row
-  constexpr int U = T * T / CH / G::THREADS;          // chunks per lane
-  const E* __restrict__ Eb = a.E ? static_cast<const E*>(a.E) + (size_t)t.mat * a.strideE : nullptr;
+  constexpr int CPR = T / CH, CHUNKS = T * T / CH;  // chunks per tile row, chunks of the tile
+  constexpr int U = (CHUNKS + G::THREADS - 1) / G::THREADS;   // chunks per lane (T = 32: of the first lanes only)
+  constexpr bool kAll = CHUNKS % G::THREADS == 0;
   vec_t ev[U];
-  if (Eb) {
+  if (a.E) {
+    const Array<SHARED> Eb(static_cast<E*>(const_cast<void*>(a.E)) + (size_t)t.mat * a.strideE, a.strideE * ES);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int idx = u * G::THREADS + tid;
-      ev[u] = *reinterpret_cast<const vec_t*>(Eb + (size_t)(m0 + idx / CPR) * a.lde + n0 + (idx % CPR) * CH);
+      if (kAll || idx < CHUNKS) ev[u] = Eb.template load<vec_t>(((size_t)(m0 + idx / CPR) * a.lde + n0 + (idx % CPR) * CH) * ES);
     }
   }
 
   // ---- direct loads: lane l of load q fetches unit S (16 bytes) of the slab ----
-  constexpr int NL = G::kPrivate ? 4 : 2;           // loads per operand, wavefront and stage
+  constexpr int NL = G::kPrivate ? T / 16 : 2;      // loads per operand, wavefront and stage
   static_assert(NL * 64 * (G::kPrivate ? 1 : 4) == T * 4, "a slab is 4 T units");
   const E* gp[NL];
   const E* gq[NL];
@@ -216,7 +319,7 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, c
       }
       constexpr int CPK = T / CH;                   // chunks per k-row
       const int k = S / CPK;
-      const int x = ES == 4 ? ((k >> 2) & 1) << 3 : (T == 128 ? (k & 3) << 2 : ((k >> 1) & 1) << 2);
+      const int x = T == 32 ? 0 : ES == 4 ? ((k >> 2) & 1) << 3 : (T == 128 ? (k & 3) << 2 : ((k >> 1) & 1) << 2);
       return src + (size_t)(kg * G::KB + k) * ld + r0 + ((S % CPK) ^ x) * CH;
     };
     gp[q] = addr(a.P, a.strideP, a.ldp, m0, TP);
@@ -227,11 +330,12 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, c
   auto issue = [&](int stage, int kt) {
     char* const sp = lds + stage * G::STAGE + kg * 2 * G::SLAB + (G::kPrivate ? 0 : w4 * NL * 1024);
     static_for<NL>([&](auto q) {
-      __builtin_amdgcn_global_load_lds((const MONA_AS1 void*)(gp[q] + kt * incp), (MONA_AS3 void*)(sp + q * 1024), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((const MONA_AS1 void*)(gp[q] + kt * incp), (MONA_AS3 void*)(sp + q * 1024), 16, 0,
+                                       SHARED ? kDeviceScope : 0);
     });
     static_for<NL>([&](auto q) {
       __builtin_amdgcn_global_load_lds((const MONA_AS1 void*)(gq[q] + kt * incq),
-                                       (MONA_AS3 void*)(sp + G::SLAB + q * 1024), 16, 0, 0);
+                                       (MONA_AS3 void*)(sp + G::SLAB + q * 1024), 16, 0, SHARED ? kDeviceScope : 0);
     });
   };
 
@@ -244,11 +348,11 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, c
     if (!trans) return b + (w * 64 + frow) * 64 + (((2 * which + half) ^ ((frow >> 2) & 3)) << 4);
     if constexpr (ES == 4) {
       const int c = w * 16 + which * 8 + (frow >> 2);
-      return b + 4 * half * (T * 4) + ((c ^ (half << 3)) << 4) + (frow & 3) * 4;
+      return b + 4 * half * (T * 4) + ((T == 32 ? c : c ^ (half << 3)) << 4) + (frow & 3) * 4;
     } else {
       const int tx = (lane & 15) >> 2, nl = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
       const int c = w * 8 + which * 4 + (nl >> 3);
-      const int x = T == 128 ? tx << 2 : (tx >> 1) << 2;
+      const int x = T == 32 ? 0 : T == 128 ? tx << 2 : (tx >> 1) << 2;
       return b + (8 * half + tx) * (T * 2) + ((c ^ x) << 4) + (nl & 7) * 2;
     }
   };
@@ -258,11 +362,12 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, c
     fb[i] = frag_addr(TQ, wn, 1, i);
   });
 
-  f32x16 acc[2][2];
+  constexpr int NB = G::NB;
+  f32x16 acc[NB][NB];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < NB; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
@@ -270,7 +375,35 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, c
   // a lane holds one output row and, per group of four registers, four consecutive columns)
   auto read_then = [&](int stage, auto&& after_reads) {
     const uint32_t so = stage * G::STAGE;
-    if constexpr (ES == 2) {
+    if constexpr (T == 32 && ES == 2) {
+      u32x4 ar[2], br[2];
+      u32x2 al[2], ah[2], bl[2], bh[2];
+      if constexpr (!TP && !TQ) read1_rr(ar, br, fa[0] + so, fa[1] + so, fb[0] + so, fb[1] + so);
+      else if constexpr (!TP) read1_rt(ar, bl, bh, fa[0] + so, fa[1] + so, fb[0] + so);
+      else read1_tt(al, ah, bl, bh, fa[0] + so, fb[0] + so);
+      after_reads();
+      static_for<2>([&](auto kk) {
+        bf16x8 pa, qb;
+        if constexpr (TP) pa = frag(al[kk], ah[kk]); else pa = frag(ar[kk]);
+        if constexpr (TQ) qb = frag(bl[kk], bh[kk]); else qb = frag(br[kk]);
+        acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qb, pa, acc[0][0], 0, 0, 0);
+      });
+    } else if constexpr (T == 32) {
+      static_for<2>([&](auto kk) {
+        f32x4 ar, br;
+        float at[4], bt[4];
+        if constexpr (!TP && !TQ) read32_1_rr(ar, br, fa[kk] + so, fb[kk] + so);
+        else if constexpr (!TP) read32_1_rt<kk>(ar, bt, fa[kk] + so, fb[0] + so);
+        else read32_1_tt<kk>(at, bt, fa[0] + so, fb[0] + so);
+        if constexpr (kk == 1) after_reads();
+        static_for<4>([&](auto e) {
+          float pa, qb;
+          pa = TP ? at[e] : elem(ar, e);
+          qb = TQ ? bt[e] : elem(br, e);
+          acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(qb, pa, acc[0][0], 0, 0, 0);
+        });
+      });
+    } else if constexpr (ES == 2) {
       u32x4 ar[2][2], br[2][2];
       u32x2 al[2][2], ah[2][2], bl[2][2], bh[2][2];
       if constexpr (!TP && !TQ) read_rr(ar, br, fa[0] + so, fa[1] + so, fb[0] + so, fb[1] + so);
@@ -353,39 +486,30 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, c
   }
 
   // ---- epilogue: the K shares of the tile meet in LDS, every global access is a 16-byte piece of a row ----
-  const int mi = a.members ? a.members[t.mat] : t.mat;
-  float post = 1.0f;
-  if (a.post == POST_INV) post = a.scales[mi].inv;
-  else if (a.post == POST_INV2) post = a.scales[mi].inv2;
-  const bool mirror = a.symmetric && t.ti != t.tj, update = a.epilogue == EPI_UPDATE;
-  bool skip_w = true;
-  int wm_real = 0, wn_real = 0, w_is_bf16 = 0;
-  void* wptr = nullptr;
-  if (update) {
-    const MatStatic& ms = a.stat[mi];
-    wm_real = ms.m; wn_real = ms.n; w_is_bf16 = ms.w_dtype;
-    wptr = a.dyn[mi].w;
-    skip_w = (a.scales[mi].status & 2u) != 0;
-  }
+  const bool mirror = a.symmetric && t.ti != t.tj, update = a.epilogue == EPI_UPDATE, skip_w = v.skip_w;
+  const int wm_real = v.m, wn_real = v.n, w_is_bf16 = v.w_dtype;
+  void* const wptr = v.w;
+  const float post = v.post;
   const bool w_vec = wn_real % CH == 0;             // rows of W are whole chunks, 16-byte (fp32: 32-byte) aligned
   __syncthreads();                                  // every wavefront has finished reading operands
   float* const sum = reinterpret_cast<float*>(lds);
   {
     float* const mine = sum + kg * T * G::LDW + (wm * 64 + frow) * G::LDW + wn * 64 + 4 * half;
-    static_for<2>([&](auto i) {
-      static_for<2>([&](auto j) {
+    static_for<NB>([&](auto i) {
+      static_for<NB>([&](auto j) {
         static_for<4>([&](auto vg) {
-          const f32x4 v = {acc[i][j][vg * 4 + 0], acc[i][j][vg * 4 + 1], acc[i][j][vg * 4 + 2], acc[i][j][vg * 4 + 3]};
-          *reinterpret_cast<f32x4*>(mine + i * 32 * G::LDW + j * 32 + 8 * vg) = v;
+          const f32x4 q = {acc[i][j][vg * 4 + 0], acc[i][j][vg * 4 + 1], acc[i][j][vg * 4 + 2], acc[i][j][vg * 4 + 3]};
+          *reinterpret_cast<f32x4*>(mine + i * 32 * G::LDW + j * 32 + 8 * vg) = q;
         });
       });
     });
   }
   __syncthreads();
-  E* __restrict__ C = static_cast<E*>(a.C) + (size_t)t.mat * a.strideC;
+  const Array<SHARED> C(static_cast<E*>(a.C) + (size_t)t.mat * a.strideC, a.strideC * ES);
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int idx = u * G::THREADS + tid;
+    if (!kAll && idx >= CHUNKS) break;
     const int r = idx / CPR, ch = idx % CPR;
     const int grow = m0 + r, gcol = n0 + ch * CH;
     float val[CH];
@@ -398,9 +522,9 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, c
         for (int e = 0; e < 4; ++e) val[q * 4 + e] = s == 0 ? p[e] : val[q * 4 + e] + p[e];
       });
     });
-    if (Eb) {
+    if (a.E) {
 #pragma unroll
-      for (int e = 0; e < CH; ++e) val[e] = post * (a.alpha * val[e] + a.beta * (float)ev[u][e]);
+      for (int e = 0; e < CH; ++e) val[e] = post * fmaf(a.alpha, val[e], a.beta * (float)ev[u][e]);
     } else {
 #pragma unroll
       for (int e = 0; e < CH; ++e) val[e] = post * (a.alpha * val[e]);
@@ -414,7 +538,7 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, c
     vec_t ov;
 #pragma unroll
     for (int e = 0; e < CH; ++e) ov[e] = (E)val[e];
-    if (!update || a.store_out) *reinterpret_cast<vec_t*>(C + (size_t)grow * a.ldc + gcol) = ov;
+    if (!update || a.store_out) C.store(((size_t)grow * a.ldc + gcol) * ES, ov);
     if (mirror) {
       // the rounded result, for the transposed pass below, in place of the share this lane alone has read
       static_for<CH / 4>([&](auto q) {
@@ -431,14 +555,14 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, c
           wv_t* wp = reinterpret_cast<wv_t*>(static_cast<bf16_t*>(wptr) + wi);
           wv_t w = *wp;
 #pragma unroll
-          for (int e = 0; e < CH; ++e) w[e] = (bf16_t)(a.w_keep * (float)w[e] - a.o_scale * (float)ov[e]);
+          for (int e = 0; e < CH; ++e) w[e] = (bf16_t)fmaf(a.w_keep, (float)w[e], -(a.o_scale * (float)ov[e]));
           *wp = w;
         } else {
           f32x4* wp = reinterpret_cast<f32x4*>(static_cast<float*>(wptr) + wi);
           static_for<CH / 4>([&](auto q) {
             f32x4 w = wp[q];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) w[e] = a.w_keep * w[e] - a.o_scale * (float)ov[q * 4 + e];
+            for (int e = 0; e < 4; ++e) w[e] = fmaf(a.w_keep, w[e], -(a.o_scale * (float)ov[q * 4 + e]));
             wp[q] = w;
           });
         }
@@ -448,10 +572,10 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, c
           if (gcol + e < wn_real) {
             if (w_is_bf16) {
               bf16_t* w = static_cast<bf16_t*>(wptr) + wi + e;
-              *w = (bf16_t)(a.w_keep * (float)*w - a.o_scale * (float)ov[e]);
+              *w = (bf16_t)fmaf(a.w_keep, (float)*w, -(a.o_scale * (float)ov[e]));
             } else {
               float* w = static_cast<float*>(wptr) + wi + e;
-              *w = a.w_keep * *w - a.o_scale * (float)ov[e];
+              *w = fmaf(a.w_keep, *w, -(a.o_scale * (float)ov[e]));
             }
           }
         }
@@ -463,12 +587,15 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, c
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int grp = u * G::WAVES + wave;
-      const int c = (grp % (T / 8)) * 8 + (lane >> 3), rc = (grp / (T / 8)) * 8 + (lane & 7);
+      // (T = 32 in bf16: there are four pieces to a column, sixteen columns to a wavefront)
+      const int grp = u * G::WAVES + wave, idx = u * G::THREADS + tid;
+      if (!kAll && idx >= CHUNKS) break;
+      const int c = CPR < 8 ? idx / CPR : (grp % (T / 8)) * 8 + (lane >> 3);
+      const int rc = CPR < 8 ? idx % CPR : (grp / (T / 8)) * 8 + (lane & 7);
       vec_t ov;
 #pragma unroll
       for (int e = 0; e < CH; ++e) ov[e] = (E)sum[(rc * CH + e) * G::LDW + c];
-      *reinterpret_cast<vec_t*>(C + (size_t)(n0 + c) * a.ldc + m0 + rc * CH) = ov;
+      C.store(((size_t)(n0 + c) * a.ldc + m0 + rc * CH) * ES, ov);
     }
   }
 }
@@ -488,12 +615,117 @@ __global__ __launch_bounds__(WIDE ? 512 : 256) void ns_small_kernel(const GemmBa
   const int per_die = b.slot_end[g] - first, local = slot - first;
   const TileId t = decode_logical(a, die * per_die + local, local < per_die);
   if (!t.valid) return;
+  const TileMatrix v = look_up(a, t);
   auto run = [&](auto tile) {
-    if (!a.trans_p && !a.trans_q) small_tile<E, tile, WIDE, false, false>(a, t, lds);
-    else if (!a.trans_p) small_tile<E, tile, WIDE, false, true>(a, t, lds);
-    else small_tile<E, tile, WIDE, true, true>(a, t, lds);
+    if (!a.trans_p && !a.trans_q) small_tile<E, tile, WIDE, false, false, false>(a, t, v, threadIdx.x, lds);
+    else if (!a.trans_p) small_tile<E, tile, WIDE, false, true, false>(a, t, v, threadIdx.x, lds);
+    else small_tile<E, tile, WIDE, true, true, false>(a, t, v, threadIdx.x, lds);
   };
+  if constexpr (WIDE)
+    if (a.tile_m == 32) { run(IC<32>{}); return; }
   if (a.tile_m == 64) run(IC<64>{}); else run(IC<128>{});
+}
+
+// All products of a step of several small groups in one launch.
+//
+// A chain of small products is bound by what every launch of its own costs: 5 to 7 us with 16 to 100 tiles, of which the
+// products themselves are two to four.  Here the tiles of all products are tasks, numbered product by product in the
+// order of the chains; workgroup w of W takes the tasks w, w + W, w + 2 W, ..., waits for the tiles of its matrix in the
+// product before (ChainArgs::flags, one word a task), computes the tile and raises the task's flag.
+//   * No workgroup waits for one that does not run.  W is not the size of the grid but the number of workgroups that have
+//     reported when the first of them closes the roll (all of the grid, unless the chip is busy with something else for
+//     kRollPolls polls); whoever comes later leaves at once.  Tasks wait for lower numbers only, and a workgroup takes its
+//     own in order, so the lowest unfinished task always has all it needs.  (Numbers go by the order of reporting: a
+//     workgroup begins its first task before the roll is closed.  Waiting for that, so as to give every die
+//     neighbouring tiles by the workgroup's index, costs 6 to 7 us a step and gains at most 4 where the tiles are many.)
+//   * The dies have an L2 each.  What one workgroup writes and another reads goes through device-scope (sc1) accesses, which
+//     are coherent by themselves; a flag follows when the stores have completed (vmcnt 0 in every wavefront, then the
+//     barrier).  Measured from the last store of a product to the first operands of the next: about 2 us, against 4 to 6 us
+//     with the caches written back and invalidated (release and acquire fences); plain loads in their place would save
+//     another 2 us a step.
+//   * 32 x 32 tiles, K split between the eight wavefronts, where every one has a CU of its own: a tile of 64 x 64 takes 2.8 us
+//     with K = 256 and 4.4 with 512, one of 32 x 32 2.1 and 2.5 (the CU's own 64 bytes a cycle from L2, and latency).
+// Measured, us per step, launches -> chain: one 256 x 512 matrix 99 -> 72, 512 x 1408 without allocation 137 -> 118, nine ragged
+// matrices in both precisions 189 -> 83 (which had waited for the host).  Tickets instead of fixed numbers, drawn by an atomic
+// operation for every task, and a counter of finished tiles instead of flags: 96, 189 and 133.
+constexpr uint32_t kRollClosed = 0x80000000u;
+constexpr int kRollPolls = 64;      // about 50 us
+// A wait lasts microseconds.  Two steps on one workspace at the same time (which the entry points forbid) could clear each
+// other's flags: a workgroup that has polled for about a second goes on without, so that every launch ends.
+constexpr int kPatience = 1 << 20;
+
+__device__ __forceinline__ uint32_t device_load(const uint32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void device_store(uint32_t* p, uint32_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__global__ __launch_bounds__(512) void ns_chain_kernel(const ChainArgs c) {
+  constexpr int LB = Geo<bf16_t, 64, true>::LDS, LF = Geo<float, 64, true>::LDS;
+  __shared__ __attribute__((aligned(256))) char lds[LB > LF ? LB : LF];
+  __shared__ uint32_t shared;
+  ChainRoll* const roll = c.roll;
+  if (threadIdx.x == 0) {
+    const uint32_t n = __hip_atomic_fetch_add(&roll->reported, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (n == 0) {
+      // the first to report closes the roll
+      uint32_t seen = 1;
+      for (int i = 0; i < kRollPolls && (seen = device_load(&roll->reported)) < gridDim.x; ++i) __builtin_amdgcn_s_sleep(8);
+      if (seen < gridDim.x)
+        seen = __hip_atomic_fetch_or(&roll->reported, kRollClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      device_store(&roll->workgroups, seen);
+    }
+    shared = n;
+  }
+  __syncthreads();
+  const uint32_t number = __builtin_amdgcn_readfirstlane(shared);
+  if (number & kRollClosed) return;
+  __syncthreads();
+  int step = 0, patience = kPatience;
+  for (int i = 0, first = 0, task = (int)number; task < c.tasks; task += step) {
+    while (task >= c.op[i].end) first = c.op[i++].end;
+    const uint32_t code = c.op[i].code;
+    const GroupDesc& g = c.group[code >> OPF_GROUP];
+    GemmArgs a;
+    expand_op(c.step, g, code, a);
+    const TileId t = decode_logical(a, task - first, true);
+    const TileMatrix v = look_up(a, t);
+    // the tiles of this matrix in the product before, 64 flags at a time
+    const int per_mat = c.op[i].before_per_mat;
+    const uint32_t* const before = c.flags + c.op[i].before + t.mat * per_mat;
+    if (threadIdx.x < 64) {
+      for (int at = 0; at < per_mat; at += 64) {
+        const int k = at + (int)threadIdx.x;
+        while (patience > 0 && !__all(k >= per_mat || device_load(before + k) != 0u)) { --patience; __builtin_amdgcn_s_sleep(1); }
+      }
+    }
+    __syncthreads();
+    // opaque: what the bodies below derive from the thread's number is not to be hoisted out of the loop, where twelve of
+    // them would share the registers
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    auto run = [&](auto element, auto tile) {
+      typedef decltype(element) E;
+      if (!a.trans_p && !a.trans_q) small_tile<E, tile, true, false, false, true>(a, t, v, tid, lds);
+      else if (!a.trans_p) small_tile<E, tile, true, false, true, true>(a, t, v, tid, lds);
+      else small_tile<E, tile, true, true, true, true>(a, t, v, tid, lds);
+    };
+    if (g.f32) { if (a.tile_m == 32) run(0.0f, IC<32>{}); else run(0.0f, IC<64>{}); }
+    else { if (a.tile_m == 32) run(bf16_t{}, IC<32>{}); else run(bf16_t{}, IC<64>{}); }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // this wavefront's stores are where every die sees them
+    __syncthreads();
+    if (threadIdx.x == 0) device_store(c.flags + task, 1u);
+    if (step == 0) {
+      if (threadIdx.x == 0) {
+        uint32_t n = 0;
+        while (patience > 0 && (n = device_load(&roll->workgroups)) == 0u) { --patience; __builtin_amdgcn_s_sleep(1); }
+        shared = n != 0u ? n : gridDim.x;
+      }
+      __syncthreads();
+      step = (int)__builtin_amdgcn_readfirstlane(shared);
+    }
+  }
 }
 
 }  // namespace
@@ -503,7 +735,7 @@ hipError_t launch_ns_small(GemmBatch& b, bool f32, bool wide, hipStream_t s) {
   long long slots = 0;
   for (int g = 0; g < b.n; ++g) {
     const GemmArgs& a = b.a[g];
-    if ((a.tile_m != 64 && a.tile_m != 128) || a.tile_n != a.tile_m || (a.trans_p && !a.trans_q)) return hipErrorInvalidValue;
+    if ((a.tile_m != 64 && a.tile_m != 128 && !(a.tile_m == 32 && wide)) || a.tile_n != a.tile_m || (a.trans_p && !a.trans_q)) return hipErrorInvalidValue;
     slots += slots_per_die(a);
     if (slots * kXcds > 0x7fffff00LL) return hipErrorInvalidValue;
     b.slot_end[g] = (int32_t)slots;
@@ -514,6 +746,23 @@ hipError_t launch_ns_small(GemmBatch& b, bool f32, bool wide, hipStream_t s) {
   else if (f32) hipLaunchKernelGGL((ns_small_kernel<float, false>), grid, dim3(256), 0, s, b);
   else if (wide) hipLaunchKernelGGL((ns_small_kernel<bf16_t, true>), grid, dim3(512), 0, s, b);
   else hipLaunchKernelGGL((ns_small_kernel<bf16_t, false>), grid, dim3(256), 0, s, b);
+  return hipGetLastError();
+}
+
+// The chain kernel stands on device-scope accesses that are coherent between the dies by themselves, as gfx950 has them.
+bool device_runs_chains() {
+  static const bool yes = []() {
+    int dev = 0, major = 0, minor = 0;
+    return hipGetDevice(&dev) == hipSuccess &&
+           hipDeviceGetAttribute(&major, hipDeviceAttributeComputeCapabilityMajor, dev) == hipSuccess &&
+           hipDeviceGetAttribute(&minor, hipDeviceAttributeComputeCapabilityMinor, dev) == hipSuccess && major == 9 && minor == 5;
+  }();
+  return yes;
+}
+
+hipError_t launch_ns_chain(const ChainArgs& c, int wgs, hipStream_t s) {
+  if (c.ops < 1 || c.ops > kMaxChainOps || c.tasks < 1 || wgs < 1) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(ns_chain_kernel, dim3(wgs), dim3(512), 0, s, c);
   return hipGetLastError();
 }
 

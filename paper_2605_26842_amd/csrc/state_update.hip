@@ -195,6 +195,8 @@ __global__ __launch_bounds__(kEwThreads) void state_update_kernel(
 // sums, one wavefront per matrix before: 34 us for the 7 696 partial sums of a 3328 x 9472 matrix, 6 us for 1 536, and
 // 4 - 5 us more for a launch of its own that looked for flagged matrices; now 4 - 7 us in all where no matrix is flagged.
 //
+// The flags of the products that follow are cleared on the way (ns_chain_kernel).
+//
 // The repair has to stay wide whatever the length of the list: one expert without gradients in a long list would
 // otherwise hold up every product behind it.  Where the list is too long for one workgroup to every kRepairBlocks
 // blocks' worth of elements of every matrix, repair is 0 here and rescue_kernel does it (4 us of a step of 2 ms and more).
@@ -249,7 +251,8 @@ __global__ __launch_bounds__(kEwThreads) void norm_finalize_kernel(const MatStat
                                                                    const double* __restrict__ partials,
                                                                    MatScale* __restrict__ scales,
                                                                    const int32_t* __restrict__ list, float eps,
-                                                                   int per_mat, int repair) {
+                                                                   int per_mat, int repair, uint4* __restrict__ zero,
+                                                                   int n16) {
   __shared__ double red[kEwThreads / 64];
   __shared__ double total_sum;
   const int li = blockIdx.x / per_mat, part = blockIdx.x % per_mat;
@@ -286,6 +289,7 @@ __global__ __launch_bounds__(kEwThreads) void norm_finalize_kernel(const MatStat
   }
   r.inv2 = r.inv * r.inv;
   if (part == 0 && threadIdx.x == 0) scales[mat] = r;
+  for (int i = blockIdx.x * kEwThreads + threadIdx.x; i < n16; i += gridDim.x * kEwThreads) zero[i] = uint4{0u, 0u, 0u, 0u};
   if (repair && (r.status & 6u)) repair_copy(ms, r, part, per_mat);
 }
 
@@ -419,7 +423,8 @@ hipError_t launch_write_dyn(const DynTable& t, int n, MatDynamic* dyn, hipStream
 }
 
 hipError_t launch_norm_finalize(const MatStatic* stat, const double* partials, MatScale* scales,
-                                const int32_t* list, int count, int max_blocks, float eps, hipStream_t s) {
+                                const int32_t* list, int count, int max_blocks, float eps, void* zero, size_t zero_bytes,
+                                hipStream_t s) {
   if (count <= 0) return hipSuccess;
   // Workgroups of kRepairBlocks blocks' worth of elements each, as long as all of them are resident at once (eight to a
   // CU); otherwise one a matrix, and the repair in a launch of its own.  Measured, us per step without and with one
@@ -430,7 +435,7 @@ hipError_t launch_norm_finalize(const MatStatic* stat, const double* partials, M
   const bool apart = per_mat > 1 && (long long)count * per_mat > kRepairGroups;
   if (apart) per_mat = 1;
   hipLaunchKernelGGL(norm_finalize_kernel, dim3(count * per_mat), dim3(kEwThreads), 0, s, stat, partials, scales, list,
-                     eps, per_mat, apart ? 0 : 1);
+                     eps, per_mat, apart ? 0 : 1, static_cast<uint4*>(zero), (int)(zero_bytes / 16));
   if (apart) {
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

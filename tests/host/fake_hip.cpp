@@ -10,6 +10,7 @@ namespace fake {
 std::function<void(const Launch&)> on_launch;
 bool capturing = false;
 std::string fail;
+int capability_major = 256, capability_minor = 256;
 namespace {
 std::map<const void*, std::string> names;
 std::vector<std::function<void()>> recorded;
@@ -104,7 +105,11 @@ hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuc
 hipError_t hipHostMalloc(void** p, size_t n, unsigned) { *p = std::malloc(n); return hipSuccess; }
 hipError_t hipHostFree(void* p) { std::free(p); return hipSuccess; }
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
-hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
+  *v = a == hipDeviceAttributeComputeCapabilityMajor ? capability_major
+       : a == hipDeviceAttributeComputeCapabilityMinor ? capability_minor : 256;
+  return hipSuccess;
+}
 hipError_t hipGetSymbolAddress(void** p, const void*) {
   static char* scratch = static_cast<char*>(std::aligned_alloc(256, (size_t)32 << 20));
   *p = scratch;
