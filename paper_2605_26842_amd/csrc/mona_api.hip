@@ -531,6 +531,7 @@ struct Launch {
   int n = 0;
   Op* op[kMaxMerged];
   bool wide = false;   // small tiles: eight wavefronts a tile (see launch_ns_small)
+  bool split = false;  // fp32 products on the bf16 matrix instructions (see launch_ns_split)
   int chain = -1;      // index in Plan::chains
   int wgs = 0;         // workgroups of a chain launch
 };
@@ -554,23 +555,33 @@ void set_tile(const Plan& plan, Op& op, int tile) {
 
 // Tile of a launch of small tiles: 64 x 64 (four times the workgroups, each with a quarter of the work) until there
 // are enough 128 x 128 tiles.  Measured, us per step with the limit at 64 / 128 / 256 tiles: 2 x 768 x 3072 both ways
-// 464 / 409 / 409, one 2048 x 2048 404 / 404 / 457, a block of hidden size 1000 537 / 537 / 564.  An fp32 tile takes 16
-// times as long, so there an even share for every CU matters more: 128 x 128 only from four such tiles per CU on
-// (limit 64 / 512 / none: 16 x 768 x 1536 2981 / 2563 / 2505, a block of hidden size 1024 3051 / 2520 / 2365,
-// 64 x 1024 x 2048 20562 / 20541 / 21622).
+// 464 / 409 / 409, one 2048 x 2048 404 / 404 / 457, a block of hidden size 1000 537 / 537 / 564.
+// An fp32 tile takes 16 times as long, so there an even share for every CU matters more: 128 x 128 only from four such tiles
+// per CU on.
 constexpr long long kMinTiles128 = 128, kMinTiles128F32 = 1024;
-void choose_small_tile(const Plan& plan, Op* const* ops, int n) {
-  long long tiles = 0;
+constexpr int kShortK = 128;
+// fp32 products (ns_small_kernel_split) keep a CU busy for long, so the rounds of the launch count: us a tile, measured, one workgroup
+// a CU.
+constexpr double kSplit128 = 0.042, kSplit64 = 0.0146, kSplitFixed = 4.0;   // per value of K; prologue and epilogue
+void choose_small_tile(const Plan& plan, Op* const* ops, int n, bool split) {
+  long long tiles = 0, tiles64 = 0;
+  int k = 0;
   for (int i = 0; i < n; ++i) {
+    set_tile(plan, *ops[i], 64);
+    tiles64 += (long long)ops[i]->a.tiles_per_mat * ops[i]->a.count;
     set_tile(plan, *ops[i], 128);
     tiles += (long long)ops[i]->a.tiles_per_mat * ops[i]->a.count;
+    k = std::max(k, ops[i]->a.K);
   }
+  const long long cus = device_cu_count();
+  const double t64 = (double)((tiles64 + cus - 1) / cus) * (k * kSplit64 + kSplitFixed);
+  const double t128 = (double)((tiles + cus - 1) / cus) * (k * kSplit128 + kSplitFixed);
   for (int i = 0; i < n; ++i) {
     const bool f32 = plan.desc[ops[i]->group].f32 != 0;
-    const long long t128 = ops[i]->a.tiles_per_mat;
+    const long long t128_per_mat = ops[i]->a.tiles_per_mat;
     set_tile(plan, *ops[i], 64);
     // (a 64 x 64 tile costs about 0.3 of a 128 x 128 one: where 128 pads the sides that much, 64 is less work)
-    if (tiles >= (f32 ? kMinTiles128F32 : kMinTiles128) && ops[i]->a.tiles_per_mat * 3 >= t128 * 10)
+    if ((split ? t128 <= t64 : tiles >= (f32 ? kMinTiles128F32 : kMinTiles128)) && ops[i]->a.tiles_per_mat * 3 >= t128_per_mat * 10)
       set_tile(plan, *ops[i], 128);
   }
 }
@@ -820,7 +831,10 @@ void build_plan(const mona_state* st, const mona_hparams& hp, Plan& plan, bool o
   for (size_t gi = 0; gi < ngroups; ++gi) plan.o_buf.push_back(OpBuilder(L.groups[gi], (int)gi, hp, plan).build());
   auto add = [&](std::vector<Launch>& lane, Launch l) {
     if (!l.op[0]->large) {
-      choose_small_tile(plan, l.op, l.n);
+      // fp32 products of the shortest K gain nothing from the bf16 instructions (200 x 64 x 1000: 537 us a step without, 576
+      // with them throughout)
+      for (int i = 0; i < l.n; ++i) l.split = l.split || (plan.desc[l.op[i]->group].f32 && l.op[i]->a.K > kShortK);
+      choose_small_tile(plan, l.op, l.n, l.split);
       // the longest chains of K first: their tiles are the last to finish
       std::stable_sort(l.op, l.op + l.n, [](const Op* x, const Op* y) { return x->a.K > y->a.K; });
       long long slots = 0;
@@ -1211,12 +1225,13 @@ int enqueue_step(mona_state* st, const mona_hparams* hp, hipStream_t s) {
   }
   const bool each = st->profiling > 1;
   // one product, or several as one launch
-  auto launch = [&](Op* const* op, int n, bool wide, int cu_cap, hipStream_t q) {
+  auto launch = [&](const Launch& l, Op* const* op, int n, int cu_cap, hipStream_t q) {
     if (op[0]->large) return launch_ns_gemm(op[0]->a, cu_cap, q);
     GemmBatch batch;
     batch.n = n;
     for (int i = 0; i < n; ++i) batch.a[i] = op[i]->a;
-    return launch_ns_small(batch, L.groups[op[0]->group].f32, wide, q);
+    if (l.split) return launch_ns_split(batch, q);
+    return launch_ns_small(batch, L.groups[op[0]->group].f32, l.wide, q);
   };
   if (!fork)                     // one lane after the other on the caller's stream
     for (int lane = 1; lane < L.lanes; ++lane) {
@@ -1245,7 +1260,7 @@ int enqueue_step(mona_state* st, const mona_hparams* hp, hipStream_t s) {
         cu_cap = device_cu_count() - st->late_cus;
       }
       if (!each) {
-        STEP_TRY(launch(l.op, l.n, l.wide, cu_cap, gs));
+        STEP_TRY(launch(l, l.op, l.n, cu_cap, gs));
         continue;
       }
       // each product timed by itself, on the tiles and with the split of K that it has in the common launch
@@ -1254,7 +1269,7 @@ int enqueue_step(mona_state* st, const mona_hparams* hp, hipStream_t s) {
         LaunchRecord rec;
         if (!get_event_pair(st, &rec.e0, &rec.e1)) return bail(hipErrorOutOfMemory, "hipEventCreate");
         STEP_TRY(hipEventRecord(rec.e0, gs));
-        STEP_TRY(launch(l.op + i, 1, l.wide, cu_cap, gs));
+        STEP_TRY(launch(l, l.op + i, 1, cu_cap, gs));
         STEP_TRY(hipEventRecord(rec.e1, gs));
         rec.kind = op.kind; rec.group = op.group; rec.iter = op.iter; rec.tile = op.a.tile_m * 1000 + op.a.tile_n;
         rec.flops = gemm_flops(op.a);

@@ -240,7 +240,9 @@ hipError_t launch_plain_update(const MatStatic* stat, const MatDynamic* dyn, con
 hipError_t launch_ns_gemm(const GemmArgs& a, int cu_cap, hipStream_t s);   // 256 x 256 tiles, bf16
 // 64 x 64 or 128 x 128 tiles; wide: eight wavefronts a tile and one workgroup per CU instead of four and two
 hipError_t launch_ns_small(GemmBatch& b, bool f32, bool wide, hipStream_t s);
-// a whole chain of products on the same tiles; `wgs` workgroups
+// fp32 products as bf16 ones, 64 x 64 or 128 x 128 tiles
+hipError_t launch_ns_split(GemmBatch& b, hipStream_t s);
+// a whole chain of products on small tiles; `wgs` workgroups
 hipError_t launch_ns_chain(const ChainArgs& c, int wgs, hipStream_t s);
 int device_cu_count();
 bool device_runs_chains();

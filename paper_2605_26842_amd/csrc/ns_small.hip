@@ -1,4 +1,5 @@
-// Newton-Schulz products for launches that do not fill the chip with 256 x 256 tiles, and all fp32-class products.
+// Newton-Schulz products for launches that do not fill the chip with 256 x 256 tiles, in bf16 and (the shortest K, and
+// chains; otherwise ns_split.hip) in fp32.
 //
 // What bounds these launches is latency: a handful of tiles, each a short chain of "fetch operands, multiply,
 // store", repeated for 15 or 18 dependent launches per step.  Three things are done about it:
@@ -10,8 +11,7 @@
 //   * a launch of few tiles uses 64 x 64 tiles whose wavefronts split K between them (each its own slabs of LDS, no
 //     workgroup barrier before the sum), a launch of more tiles 128 x 128 (the host decides, product by product).
 // Measured, us per step, one chain of launches per group on a register-staged 128 x 128 kernel -> here: one 256 x 512
-// matrix 170 -> 99, 512 x 1408 269 -> 137, nine ragged matrices 980 -> 180 to 194, a block of hidden size 1000 664 -> 509,
-// one of hidden size 1024 with fp32 products 4583 -> 2283 (73 TFLOP/s; launches that fill the chip many times over 130 of 154).
+// matrix 170 -> 99, 512 x 1408 269 -> 137, nine ragged matrices 980 -> 189 (chains: below), a block of hidden size 1000 664 -> 509.
 // A launch costs 5 us (64 x 64) to 9 - 11 us (128 x 128) beside its K loop, and 1024 of K 4.7 and 9.4 us for a tile on a CU of
 // its own, 8.6 and 19.4 us for two.
 //
@@ -24,15 +24,11 @@
 //     one ds_read_b128 per lane, 16 consecutive rows fall on 16 different bank groups;
 //   K-major operand: the slab's k-rows of T values; read with ds_read_b64_tr_b16 (bf16) or ds_read_b32 (fp32),
 //     chunks XORed so that the rows one read touches lie on different banks.
-#include "ns_tile.h"
+#include "ns_small_tile.h"
 
 namespace mona {
 
 namespace {
-
-template <typename E> struct Chunk;           // 16 bytes of E
-template <> struct Chunk<bf16_t> { static constexpr int N = 8; typedef bf16x8 vec; };
-template <> struct Chunk<float> { static constexpr int N = 4; typedef f32x4 vec; };
 
 // ---- fragment reads ------------------------------------------------------------------------
 // bf16, one stage (two k16 halves): a[half][block], b[half][block].  read_..() issues the reads of both halves in order
@@ -202,11 +198,6 @@ __device__ __forceinline__ void read32_1_tt(float (&a)[4], float (&b)[4], uint32
       : "memory");
 }
 
-__device__ __forceinline__ bf16x8 frag(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
-__device__ __forceinline__ bf16x8 frag(u32x2 lo, u32x2 hi) {
-  const u32x4 v = {lo.x, lo.y, hi.x, hi.y};
-  return __builtin_bit_cast(bf16x8, v);
-}
 __device__ __forceinline__ float elem(const f32x4& v, int e) { return v[e]; }
 __device__ __forceinline__ float elem(const float (&v)[4], int e) { return v[e]; }
 
@@ -225,62 +216,16 @@ struct Geo {
   static constexpr int STAGE = KS * 2 * SLAB;
   // wide: one workgroup per CU with 128 KB of ring; else two with 64 KB each
   static constexpr int STAGES = (WIDE ? 131072 : 65536) / STAGE;
-  static constexpr int LDW = T + 4;                 // floats per staged row of the epilogue (+4: rows on different banks)
+  static constexpr int LDW = staged_ld(T);
   static constexpr int RING = STAGES * STAGE, STAGING = KS * T * LDW * 4;
   static constexpr int LDS = RING > STAGING ? RING : STAGING;
   static_assert(T == 32 || T == 64 || T == 128, "32, 64 or 128");
 };
 
-// 16 bytes of an array that other workgroups of the same launch write or read (SHARED: coherent across the dies at device
-// scope, without any cache being written back or invalidated), or that only earlier and later launches do.  `bytes` from
-// the start of the array, which is wavefront-uniform and smaller than 4 GB where it is shared.
-constexpr int kDeviceScope = 16;   // sc1
-template <bool SHARED>
-struct Array {
-  char* p;
-  __amdgpu_buffer_rsrc_t r;
-  __device__ __forceinline__ Array(void* base, int64_t size) : p(static_cast<char*>(base)) {
-    if constexpr (SHARED) r = __builtin_amdgcn_make_buffer_rsrc(base, 0, (int)(uint32_t)size, 0x00020000);
-  }
-  template <typename V> __device__ __forceinline__ V load(size_t bytes) const {
-    if constexpr (SHARED) return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, (int)(uint32_t)bytes, 0, kDeviceScope));
-    else return *reinterpret_cast<const V*>(p + bytes);
-  }
-  template <typename V> __device__ __forceinline__ void store(size_t bytes, V v) const {
-    if constexpr (SHARED) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, (int)(uint32_t)bytes, 0, kDeviceScope);
-    else *reinterpret_cast<V*>(p + bytes) = v;
-  }
-};
-
-// What the epilogue of a tile needs to know of its matrix: two or three loads that depend on each other, made before the
-// first operand is waited for.
-struct TileMatrix {
-  float post;
-  bool skip_w;
-  int m, n, w_dtype;
-  void* w;
-};
-__device__ __forceinline__ TileMatrix look_up(const GemmArgs& a, const TileId& t) {
-  TileMatrix v = {1.0f, true, 0, 0, 0, nullptr};
-  if (a.post == POST_NONE && a.epilogue != EPI_UPDATE) return v;
-  const int mi = a.members[t.mat];
-  if (a.post == POST_INV) v.post = a.scales[mi].inv;
-  else if (a.post == POST_INV2) v.post = a.scales[mi].inv2;
-  if (a.epilogue == EPI_UPDATE) {
-    const MatStatic& ms = a.stat[mi];
-    v.m = ms.m; v.n = ms.n; v.w_dtype = ms.w_dtype;
-    v.w = a.dyn[mi].w;
-    v.skip_w = (a.scales[mi].status & 2u) != 0;
-  }
-  return v;
-}
-
 // C tile (ti, tj) of matrix t.mat.  lds: Geo<E, T, WIDE>::LDS bytes, 256-byte aligned.  SHARED: other workgroups of this
 // launch write the operands and read the result.
 template <typename E, int T, bool WIDE, bool TP, bool TQ, bool SHARED>
 __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, const TileMatrix& v, int tid, char* lds) {
-  // every contraction is written out below: a product comes out the same, bit for bit, in whichever kernel it runs
-#pragma clang fp contract(off)
   typedef Geo<E, T, WIDE> G;
   constexpr int ES = G::ES, CH = Chunk<E>::N;
   typedef typename Chunk<E>::vec vec_t;
@@ -291,18 +236,8 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, c
   const int m0 = t.ti * T, n0 = t.tj * T;
 
   // E operand of the epilogue: requested first, so that it has arrived long before it is used
-  constexpr int CPR = T / CH, CHUNKS = T * T / CH;  // chunks per tile row, chunks of the tile
-  constexpr int U = (CHUNKS + G::THREADS - 1) / G::THREADS;   // chunks per lane (T = 32: of the first lanes only)
-  constexpr bool kAll = CHUNKS % G::THREADS == 0;
-  vec_t ev[U];
-  if (a.E) {
-    const Array<SHARED> Eb(static_cast<E*>(const_cast<void*>(a.E)) + (size_t)t.mat * a.strideE, a.strideE * ES);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int idx = u * G::THREADS + tid;
-      if (kAll || idx < CHUNKS) ev[u] = Eb.template load<vec_t>(((size_t)(m0 + idx / CPR) * a.lde + n0 + (idx % CPR) * CH) * ES);
-    }
-  }
+  vec_t ev[TileChunks<E, T, G::THREADS>::PER_LANE];
+  load_e<E, T, G::THREADS, SHARED>(a, t, tid, ev);
 
   // ---- direct loads: lane l of load q fetches unit S (16 bytes) of the slab ----
   constexpr int NL = G::kPrivate ? T / 16 : 2;      // loads per operand, wavefront and stage
@@ -486,11 +421,6 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, c
   }
 
   // ---- epilogue: the K shares of the tile meet in LDS, every global access is a 16-byte piece of a row ----
-  const bool mirror = a.symmetric && t.ti != t.tj, update = a.epilogue == EPI_UPDATE, skip_w = v.skip_w;
-  const int wm_real = v.m, wn_real = v.n, w_is_bf16 = v.w_dtype;
-  void* const wptr = v.w;
-  const float post = v.post;
-  const bool w_vec = wn_real % CH == 0;             // rows of W are whole chunks, 16-byte (fp32: 32-byte) aligned
   __syncthreads();                                  // every wavefront has finished reading operands
   float* const sum = reinterpret_cast<float*>(lds);
   {
@@ -505,99 +435,7 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, c
     });
   }
   __syncthreads();
-  const Array<SHARED> C(static_cast<E*>(a.C) + (size_t)t.mat * a.strideC, a.strideC * ES);
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int idx = u * G::THREADS + tid;
-    if (!kAll && idx >= CHUNKS) break;
-    const int r = idx / CPR, ch = idx % CPR;
-    const int grow = m0 + r, gcol = n0 + ch * CH;
-    float val[CH];
-#pragma unroll
-    for (int e = 0; e < CH; ++e) val[e] = 0.0f;
-    static_for<G::KS>([&](auto s) {
-      static_for<CH / 4>([&](auto q) {
-        const f32x4 p = *reinterpret_cast<const f32x4*>(sum + (s * T + r) * G::LDW + ch * CH + q * 4);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) val[q * 4 + e] = s == 0 ? p[e] : val[q * 4 + e] + p[e];
-      });
-    });
-    if (a.E) {
-#pragma unroll
-      for (int e = 0; e < CH; ++e) val[e] = post * fmaf(a.alpha, val[e], a.beta * (float)ev[u][e]);
-    } else {
-#pragma unroll
-      for (int e = 0; e < CH; ++e) val[e] = post * (a.alpha * val[e]);
-    }
-    if (a.diag != 0.0f && grow < a.diag_n) {
-      // not to the padding: that must be zero in every buffer, because a product whose tiles are 64 wide in this step may
-      // leave out padding that a 128-wide tile wrote in another
-#pragma unroll
-      for (int e = 0; e < CH; ++e) val[e] += (grow == gcol + e) ? a.diag : 0.0f;
-    }
-    vec_t ov;
-#pragma unroll
-    for (int e = 0; e < CH; ++e) ov[e] = (E)val[e];
-    if (!update || a.store_out) C.store(((size_t)grow * a.ldc + gcol) * ES, ov);
-    if (mirror) {
-      // the rounded result, for the transposed pass below, in place of the share this lane alone has read
-      static_for<CH / 4>([&](auto q) {
-        const f32x4 p = {(float)ov[q * 4 + 0], (float)ov[q * 4 + 1], (float)ov[q * 4 + 2], (float)ov[q * 4 + 3]};
-        *reinterpret_cast<f32x4*>(sum + r * G::LDW + ch * CH + q * 4) = p;
-      });
-    }
-    if (update && !skip_w && grow < wm_real) {
-      // W <- (1 - eta lambda) W - eta gamma O, O as stored in the working precision
-      const size_t wi = (size_t)grow * wn_real + gcol;
-      if (w_vec && gcol + CH <= wn_real) {
-        if (w_is_bf16) {
-          typedef bf16_t wv_t __attribute__((ext_vector_type(CH)));
-          wv_t* wp = reinterpret_cast<wv_t*>(static_cast<bf16_t*>(wptr) + wi);
-          wv_t w = *wp;
-#pragma unroll
-          for (int e = 0; e < CH; ++e) w[e] = (bf16_t)fmaf(a.w_keep, (float)w[e], -(a.o_scale * (float)ov[e]));
-          *wp = w;
-        } else {
-          f32x4* wp = reinterpret_cast<f32x4*>(static_cast<float*>(wptr) + wi);
-          static_for<CH / 4>([&](auto q) {
-            f32x4 w = wp[q];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) w[e] = fmaf(a.w_keep, w[e], -(a.o_scale * (float)ov[q * 4 + e]));
-            wp[q] = w;
-          });
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < CH; ++e) {
-          if (gcol + e < wn_real) {
-            if (w_is_bf16) {
-              bf16_t* w = static_cast<bf16_t*>(wptr) + wi + e;
-              *w = (bf16_t)fmaf(a.w_keep, (float)*w, -(a.o_scale * (float)ov[e]));
-            } else {
-              float* w = static_cast<float*>(wptr) + wi + e;
-              *w = fmaf(a.w_keep, *w, -(a.o_scale * (float)ov[e]));
-            }
-          }
-        }
-      }
-    }
-  }
-  if (mirror) {
-    // transposed copy: a wavefront writes 8 columns of the tile x 8 pieces of 16 bytes along its rows
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      // (T = 32 in bf16: there are four pieces to a column, sixteen columns to a wavefront)
-      const int grp = u * G::WAVES + wave, idx = u * G::THREADS + tid;
-      if (!kAll && idx >= CHUNKS) break;
-      const int c = CPR < 8 ? idx / CPR : (grp % (T / 8)) * 8 + (lane >> 3);
-      const int rc = CPR < 8 ? idx % CPR : (grp / (T / 8)) * 8 + (lane & 7);
-      vec_t ov;
-#pragma unroll
-      for (int e = 0; e < CH; ++e) ov[e] = (E)sum[(rc * CH + e) * G::LDW + c];
-      C.store(((size_t)(n0 + c) * a.ldc + m0 + rc * CH) * ES, ov);
-    }
-  }
+  finish_tile<E, T, G::KS, G::THREADS, SHARED>(a, t, v, tid, ev, sum);
 }
 
 // One workgroup per tile.  Group g of the batch owns the slots [slot_end[g - 1], slot_end[g]) of every die: workgroup
