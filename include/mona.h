@@ -301,8 +301,9 @@ int mona_last_step_launches(mona_state* st, mona_launch_time* out, int32_t max_r
 
 /* Number of kernel launches and executed MFMA flop of the Newton-Schulz part of one ordinary
  * step (products of several small shape groups that share a launch count as one launch, and so do all
- * products of a step whose groups are so small that they run as one chain; host-only bookkeeping, for
- * roofline reporting).  Profiling level 2 launches and times every product by itself all the same. */
+ * products of a step whose groups are so small that they run as one chain, or of groups whose matrices
+ * get a workgroup each; host-only bookkeeping, for roofline reporting).  Profiling level 2 launches and
+ * times every product by itself all the same. */
 int mona_plan_info(mona_state* st, int32_t ns_steps, int64_t* launches_out,
                    double* ns_flops_executed_out, double* elementwise_bytes_out);
 

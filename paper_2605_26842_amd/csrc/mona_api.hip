@@ -83,6 +83,7 @@ struct Group {
 struct Unit {
   std::vector<int> groups;
   bool merged = false;
+  bool matrix = false;       // a workgroup for each matrix (ns_matrix_kernel)
   int lane = 0;              // stream: 0 is the caller's
 };
 
@@ -106,6 +107,7 @@ struct Layout {
   int range_end[4] = {0, 0, 0, 0};     // ends of those four ranges of blocks
   std::vector<Unit> units;             // what the products of the groups are launched as, in launch order per lane
   int lanes = 1;
+  bool small_enough = false;           // all groups together are as little as a chain takes
   int late_group = -1;                 // group whose elementwise pass runs beside the products of the others
   std::vector<int32_t> order;          // matrix indices: early matrices, then those of the late group
   int num_early = 0;
@@ -172,6 +174,8 @@ constexpr long long kChipTiles = 256;      // one tile per CU
 constexpr long long kMergedTiles = 128;
 // large tiles from which a product uses them; matrices from which it does where p is a single tile
 constexpr long long kMinTiles256 = 128, kMinSingles256 = 112;
+// what a chain of small products takes at most at one position: 64 x 64 tiles, and their K added up (chainable() has the figures)
+constexpr long long kChainTiles = 448, kChainWork = 140000;
 // CUs the late group's elementwise pass keeps to itself (a quarter of the chip): the HBM-bound pass still
 // moves 2.8 TB/s there, and the power-limited products lose 13 % on the other three quarters (measured).
 constexpr int kOverlapCuShare = 4;
@@ -206,6 +210,37 @@ long long launch_tiles(const Group& g, int kind, int tile, int count) {
   if (kind == OP_APPLY) return (long long)(g.rows_pad / tile) * (g.cols_pad / tile) * count;
   const long long t = g.p_pad / tile;
   return t * (t + 1) / 2 * count;
+}
+
+// Whether the matrices of a group get a workgroup each (ns_matrix_kernel), by what their iterations take that way and as
+// products, us of a step.  Alone, products take as long as their launches at least; beside other groups, whose launches they share
+// or run beside, only what they add.  Measured, us per step as products (launches, or a chain) / by matrix: 128 x 128 57 / 32,
+// 100 x 400 70 / 64, 24 x 128 x 512 90 / 75, 60 x 128 x 256 105 / 53, 250 x 70 x 100 170 / 52, 200 x 120 x 600 317 / 189,
+// 250 x 128 x 4000 1983 / 1521, but 40 x 128 x 2000 232 / 327; 256 x 256 x 256 426 / 255, 115 x 256 x 512 383 / 309, 128 x 768 x 256 both
+// ways 820 / 633, but 60 x 256 x 512 235 / 260, 79 x 256 x 834 and others 482 / 569; 4 x 171 x 66 beside 697 x 612 and 365 x 161 144 / 169.
+bool by_matrix(const Group& g, bool alone) {
+  if (g.f32 || g.fused || (g.p_pad != 128 && g.p_pad != 256) || !device_is_gfx950()) return false;
+  const double count = (double)g.members.size(), panels = std::max(g.rows_pad, g.cols_pad) / 128;
+  const double units = count * panels, rounds = std::ceil(count / (double)kChipTiles);
+  if (g.p_pad == 128) {    // (four panels stay in LDS)
+    const double latency = alone ? std::min(50.0 + 0.4 * units, 100.0) : 0.0;
+    return rounds * 5.0 * (2.2 + (panels <= 4 ? 2.2 : 2.9) * panels) < std::max(0.2 * units, latency);
+  }
+  const double unit = panels <= 4 ? 0.75 : count >= kMinSingles256 ? 0.45 : 0.55;
+  return rounds * 5.0 * (9.5 + 7.9 * panels) < std::max(unit * units, alone ? 80.0 : 0.0);
+}
+
+// Whether the groups of the step, all together, are as little as a chain takes (of five literal iterations: the exact check
+// stands in chainable()).
+bool all_in_a_chain(const Layout& L) {
+  long long tiles[2] = {0, 0}, work[2] = {0, 0};
+  for (const Group& g : L.groups) {
+    const long long count = (long long)g.members.size(), p = (std::min(g.m, g.n) + 63) / 64;
+    const long long of[2] = {p * (p + 1) / 2 * count, ((g.m + 63LL) / 64) * ((g.n + 63LL) / 64) * count};
+    const long long k[2] = {std::max(g.rows_pad, g.cols_pad), g.p_pad};
+    for (int i = 0; i < 2; ++i) { tiles[i] += of[i]; work[i] += of[i] * k[i]; }
+  }
+  return std::max(tiles[0], tiles[1]) <= kChainTiles && std::max(work[0], work[1]) <= kChainWork;
 }
 
 // Streams and order of the step.
@@ -253,7 +288,12 @@ void plan_lanes(Layout& L, const mona_options& opt) {
                        : g.fused == 1 ? 9.0 * p * p * q + 11.0 * p * p * p : 5.0 * (3.0 * p * p * q + p * p * p);
     work_of[gi] = per * (double)g.members.size() * (g.f32 ? 16.0 : 1.0);
   }
+  // A workgroup for each matrix: not where a chain that some groups need anyway takes all of them (the others cost it little).
+  const bool only = std::all_of(L.groups.begin(), L.groups.end(), [](const Group& g) { return by_matrix(g, true); });
+  L.small_enough = all_in_a_chain(L);
+  std::vector<int> matrices;
   for (int gi = 0; gi < ngroups; ++gi) {
+    if (only || (!L.small_enough && by_matrix(L.groups[gi], false))) { matrices.push_back(gi); continue; }
     // Beside a group that keeps the caller's stream, only groups too small to fill the chip by
     // themselves go to the side streams (their launch latency hides behind the large group); a
     // mid-sized group there gained 0.3 % at most (4 squares of 4096 beside 384 experts), and in a row
@@ -289,6 +329,14 @@ void plan_lanes(Layout& L, const mona_options& opt) {
     return L.units.back();
   };
   for (int gi : row) add_unit(false).groups.push_back(gi);
+  // (the most work a matrix first: the launch ends with the short ones)
+  std::stable_sort(matrices.begin(), matrices.end(), [&](int x, int y) {
+    return work_of[x] / (double)L.groups[x].members.size() > work_of[y] / (double)L.groups[y].members.size();
+  });
+  for (size_t i = 0; i < matrices.size(); ++i) {
+    if (i % kMaxMerged == 0) add_unit(false).matrix = true;
+    L.units.back().groups.push_back(matrices[i]);
+  }
   const size_t first_beside = L.units.size();
   std::vector<long long> tiles_in(L.groups.size() + 1, 0);   // 128 x 128 tiles of each unit's smallest launches
   for (int gi : beside) {
@@ -305,10 +353,11 @@ void plan_lanes(Layout& L, const mona_options& opt) {
     L.units[u].groups.push_back(gi);
     tiles_in[u] += fewest_of[gi];
   }
-  const int parallel = (int)(L.units.size() - first_beside) + (row.empty() ? 0 : 1);
+  const int parallel = (int)(L.units.size() - first_beside) + (row.empty() && matrices.empty() ? 0 : 1);
   L.lanes = std::max(1, std::min(want, parallel));
   std::vector<double> load(L.lanes, 0.0);
   for (int gi : row) load[0] += work_of[gi];
+  for (int gi : matrices) load[0] += work_of[gi];
   std::vector<std::pair<double, size_t>> order;
   for (size_t u = first_beside; u < L.units.size(); ++u) {
     double work = 0.0;
@@ -468,6 +517,45 @@ struct LaunchRecord {
 
 }  // namespace
 
+// One product of the plan.
+struct Op {
+  GemmArgs a;         // what `code` stands for (expand_op)
+  uint32_t code = 0;  // op code (OpField)
+  int kind = 0;       // OpKind
+  int group = 0;
+  int iter = 0;       // Newton-Schulz iteration it belongs to
+  bool large = false; // 256 x 256 kernel; otherwise the tile is chosen when the launch is put together
+};
+
+// One launch of the step: a product of one group, the products of a merged unit at one position of their chains, or
+// (chain >= 0) whole chains.
+struct Launch {
+  int n = 0;
+  Op* op[kMaxMerged];
+  bool wide = false;   // small tiles: eight wavefronts a tile (see launch_ns_small)
+  bool split = false;  // fp32 products on the bf16 matrix instructions (see launch_ns_split)
+  int chain = -1;      // index in Plan::chains
+  int matrix = -1;     // index in Plan::matrices
+  int wgs = 0;         // workgroups of a chain launch
+};
+
+// The products of one step as they are launched, lane by lane: what enqueue_step issues and mona_plan_info counts.
+struct Plan {
+  StepDesc step;
+  std::vector<GroupDesc> desc;              // by group
+  std::vector<std::vector<Op>> ops;         // by group
+  std::vector<int> o_buf;                   // by group: the ping-pong buffer that holds O_k afterwards
+  std::vector<std::vector<Launch>> lanes;
+  std::vector<ChainArgs> chains;
+  std::vector<MatrixBatch> matrices;
+  std::vector<std::vector<int>> chain_groups, matrix_groups;   // the groups of each, in order
+  int32_t ns_steps = -1;                    // what it was built for
+  uint32_t flags = 0;
+  bool one_by_one = false;
+  size_t chain_bytes = 0;                   // of rolls and flags, to be cleared before the products
+  int chain_tasks = 0;
+};
+
 struct mona_state {
   Layout L;
   mona_options opt;
@@ -506,6 +594,11 @@ struct mona_state {
   std::vector<std::pair<hipEvent_t, hipEvent_t>> event_pool;
   size_t pool_used = 0;
 
+  struct Plan* plan = nullptr;     // of the last step (see plan_for)
+  mona_state() = default;
+  mona_state(const mona_state&) = delete;
+  ~mona_state() { delete plan; }
+
   template <typename T> T* at(size_t off) const { return reinterpret_cast<T*>(arena + off); }
 };
 
@@ -514,39 +607,6 @@ namespace {
 double gemm_flops(const GemmArgs& a) {
   return 2.0 * a.tile_m * a.tile_n * (double)a.K * a.tiles_per_mat * a.count;
 }
-
-// One product of the plan.
-struct Op {
-  GemmArgs a;         // what `code` stands for (expand_op)
-  uint32_t code = 0;  // op code (OpField)
-  int kind = 0;       // OpKind
-  int group = 0;
-  int iter = 0;       // Newton-Schulz iteration it belongs to
-  bool large = false; // 256 x 256 kernel; otherwise the tile is chosen when the launch is put together
-};
-
-// One launch of the step: a product of one group, the products of a merged unit at one position of their chains, or
-// (chain >= 0) whole chains.
-struct Launch {
-  int n = 0;
-  Op* op[kMaxMerged];
-  bool wide = false;   // small tiles: eight wavefronts a tile (see launch_ns_small)
-  bool split = false;  // fp32 products on the bf16 matrix instructions (see launch_ns_split)
-  int chain = -1;      // index in Plan::chains
-  int wgs = 0;         // workgroups of a chain launch
-};
-
-// The products of one step as they are launched, lane by lane: what enqueue_step issues and mona_plan_info counts.
-struct Plan {
-  StepDesc step;
-  std::vector<GroupDesc> desc;              // by group
-  std::vector<std::vector<Op>> ops;         // by group
-  std::vector<int> o_buf;                   // by group: the ping-pong buffer that holds O_k afterwards
-  std::vector<std::vector<Launch>> lanes;
-  std::vector<ChainArgs> chains;
-  size_t chain_bytes = 0;                   // of rolls and flags, to be cleared before the products
-  int chain_tasks = 0;
-};
 
 void set_tile(const Plan& plan, Op& op, int tile) {
   op.code = (op.code & ~(3u << OPF_TILE)) | (tile == 32 ? 0u : tile == 64 ? 1u : tile == 128 ? 2u : 3u) << OPF_TILE;
@@ -718,20 +778,19 @@ long long tiles_at(Plan& plan, const std::vector<int>& groups, size_t pos, int t
 
 // Whether the products of these groups may go out as one launch (ns_chain_kernel) instead of one launch per position.
 //
-// Where the line lies.  A chain saves 2 to 4 us of every product, but its workgroups are one to a CU and its tiles 64 x 64
+// Where the line (kChainTiles, kChainWork) lies.  A chain saves 2 to 4 us of every product, but its workgroups are one to a CU and its tiles 64 x 64
 // at most, dealt without regard to the die they are on.  Measured, us per step with launches / as a chain, with the work of the
 // widest position (64 x 64 tiles times K, in thousands): 256 x 256 (4) 94 / 66, 512 x 512 (33) 111 / 98, 512 x 2048 (131) 147 / 130,
 // 4 x 300 x 900 (115) 131 / 111, 200 x 64 x 128 (51, fp32) 147 / 134, 768 x 768 (110) 133 / 131, 4 x 512 x 512 (131) 120 / 118;
 // beyond it 1024 x 1024 (262) 152 / 158, 6 x 384 x 1000 (221) 150 / 156, 30 x 256 x 512 (245) 155 / 180, 250 x 70 x 100
 // (192, 1000 tiles) 166 / 223, 700 x 2000 (270) 168 / 165.
-constexpr long long kChainTiles = 448, kChainWork = 140000;
 // The tile a chain takes at one position: 32 x 32 as long as every one has a CU of its own.
 int chain_tile(Plan& plan, const std::vector<int>& groups, size_t pos) {
   return tiles_at(plan, groups, pos, 32) <= device_cu_count() ? 32 : 64;
 }
 // Tasks of the chain, 0 if there is none.
 int chainable(const Layout& L, Plan& plan, const std::vector<int>& groups) {
-  if (!device_runs_chains() || groups.size() > (size_t)kMaxMerged) return 0;
+  if (!device_is_gfx950() || groups.size() > (size_t)kMaxMerged) return 0;
   size_t ops = 0, positions = 0;
   for (int gi : groups) {
     const Group& g = L.groups[gi];
@@ -751,7 +810,14 @@ int chainable(const Layout& L, Plan& plan, const std::vector<int>& groups) {
         work += (long long)a.tiles_per_mat * a.count * a.K;
       }
     if (work > kChainWork) return 0;
-    tasks += tiles_at(plan, groups, pos, chain_tile(plan, groups, pos));
+    const int tile = chain_tile(plan, groups, pos);
+    // A 64 x 64 tile takes the fp32 instructions 14 us with K = 512, where launches take the bf16 ones.  Measured, us per step
+    // with fp32 products as a chain / with launches: 512 x 512 (32 x 32) 139 / 186, 512 x 1408 199 / 245, but 768 x 768 323 / 238,
+    // 2 x 512 x 512 239 / 191, 16 x 256 x 256 162 / 135.
+    for (int gi : groups)
+      if (tile == 64 && L.groups[gi].f32 && L.groups[gi].p_pad > 128 && pos < plan.ops[gi].size() && plan.ops[gi][pos].a.symmetric)
+        return 0;
+    tasks += tiles_at(plan, groups, pos, tile);
   }
   return tasks <= kMaxChainTasks ? (int)tasks : 0;
 }
@@ -797,21 +863,32 @@ Launch build_chain(const mona_state* st, Plan& plan, const std::vector<int>& gro
   chain.wgs = (int)std::min<long long>(most, cus);
   chain.chain = (int)plan.chains.size();
   plan.chains.push_back(c);
+  plan.chain_groups.push_back(groups);
   plan.chain_tasks += round_up((int)tasks, 4);
   plan.chain_bytes = kMaxChains * sizeof(ChainRoll) + plan.chain_tasks * sizeof(uint32_t);
   return chain;
 }
 
-// `one_by_one`: every product as a launch of its own, on the tiles and with the split of K it has in the ordinary step.
-void build_plan(const mona_state* st, const mona_hparams& hp, Plan& plan, bool one_by_one) {
+// The hyper-parameters of a step that change nothing of its launches but their arguments.
+void set_step(const mona_state* st, const mona_hparams& hp, Plan& plan) {
   const Layout& L = st->L;
-  const size_t ngroups = L.groups.size();
   memset(&plan.step, 0, sizeof plan.step);
   plan.step.scales = st->at<MatScale>(L.scales_off);
   plan.step.stat = st->at<MatStatic>(L.stat_off);
   plan.step.dyn = st->at<MatDynamic>(L.dyn_off);
   plan.step.ns_a = hp.ns_a; plan.step.ns_b = hp.ns_b; plan.step.ns_c = hp.ns_c;
   plan.step.w_keep = 1.0f - hp.lr * hp.weight_decay;
+}
+float update_scale(const Group& g, const mona_hparams& hp) {
+  return hp.lr * hp.gamma_coeff * sqrtf((float)std::max(g.m, g.n));
+}
+
+// `one_by_one`: every product as a launch of its own, on the tiles and with the split of K it has in the ordinary step.
+void build_plan(const mona_state* st, const mona_hparams& hp, Plan& plan, bool one_by_one) {
+  const Layout& L = st->L;
+  const size_t ngroups = L.groups.size();
+  plan.ns_steps = hp.ns_steps; plan.flags = hp.flags; plan.one_by_one = one_by_one;
+  set_step(st, hp, plan);
   plan.ops.resize(ngroups);
   plan.lanes.resize(L.lanes);
   for (const Group& g : L.groups) {
@@ -825,7 +902,7 @@ void build_plan(const mona_state* st, const mona_hparams& hp, Plan& plan, bool o
     d.count = (int32_t)g.members.size();
     d.m = g.m; d.n = g.n; d.rows_pad = g.rows_pad; d.cols_pad = g.cols_pad;
     d.tall = g.tall; d.f32 = g.f32;
-    d.o_scale = hp.lr * hp.gamma_coeff * sqrtf((float)std::max(g.m, g.n));
+    d.o_scale = update_scale(g, hp);
     plan.desc.push_back(d);
   }
   for (size_t gi = 0; gi < ngroups; ++gi) plan.o_buf.push_back(OpBuilder(L.groups[gi], (int)gi, hp, plan).build());
@@ -847,7 +924,7 @@ void build_plan(const mona_state* st, const mona_hparams& hp, Plan& plan, bool o
   // Chains, where all of the step fits into them: a chain's workgroups wait on their CUs, so beside launches that fill the
   // chip it takes more than it gives (128 x 768 x 256 and 4 x 128 x 512: 628 us a step with launches, 687 with a chain).
   std::vector<std::vector<int>> chains;
-  bool all = std::all_of(L.units.begin(), L.units.end(), [](const Unit& u) { return u.merged; });
+  bool all = L.small_enough && std::all_of(L.units.begin(), L.units.end(), [](const Unit& u) { return u.merged; });
   for (size_t u = 0; all && u < L.units.size(); ++u) {
     auto joined = [&](std::vector<int> chain) {
       chain.insert(chain.end(), L.units[u].groups.begin(), L.units[u].groups.end());
@@ -874,7 +951,24 @@ void build_plan(const mona_state* st, const mona_hparams& hp, Plan& plan, bool o
   }
   for (const Unit& u : L.units) {
     std::vector<Launch>& lane = plan.lanes[u.lane];
-    if (u.merged) {
+    if (u.matrix && hp.ns_steps > 0 && !one_by_one) {
+      MatrixBatch b;
+      memset(&b, 0, sizeof b);
+      b.step = plan.step;
+      b.steps = hp.ns_steps;
+      b.store_o = (hp.flags & MONA_FLAG_KEEP_O) ? 1 : 0;
+      int matrices = 0;
+      for (int gi : u.groups) {
+        matrices += plan.desc[gi].count;
+        b.group[b.n] = plan.desc[gi];
+        b.end[b.n++] = matrices;
+      }
+      Launch l;
+      l.matrix = (int)plan.matrices.size();
+      plan.matrices.push_back(b);
+      plan.matrix_groups.push_back(u.groups);
+      lane.push_back(l);
+    } else if (u.merged) {
       for (size_t pos = 0;; ++pos) {
         Launch l;
         for (int gi : u.groups)
@@ -891,6 +985,37 @@ void build_plan(const mona_state* st, const mona_hparams& hp, Plan& plan, bool o
         }
     }
   }
+}
+
+// The plan of a step: the last one again, with this step's hyper-parameters, unless the number of iterations, the flags or the
+// kind of launches differ (building it takes 10 to 40 us of host time with eight groups, this 1 to 4).
+Plan& plan_for(mona_state* st, const mona_hparams& hp) {
+  const bool one_by_one = st->profiling > 1;
+  Plan* plan = st->plan;
+  if (!plan || plan->ns_steps != hp.ns_steps || plan->flags != hp.flags || plan->one_by_one != one_by_one) {
+    delete plan;
+    st->plan = nullptr;
+    st->plan = plan = new Plan();
+    build_plan(st, hp, *plan, one_by_one);
+    return *plan;
+  }
+  const Layout& L = st->L;
+  set_step(st, hp, *plan);
+  for (size_t gi = 0; gi < L.groups.size(); ++gi) plan->desc[gi].o_scale = update_scale(L.groups[gi], hp);
+  for (size_t i = 0; i < plan->chains.size(); ++i) {
+    plan->chains[i].step = plan->step;
+    for (size_t j = 0; j < plan->chain_groups[i].size(); ++j)
+      plan->chains[i].group[j].o_scale = plan->desc[plan->chain_groups[i][j]].o_scale;
+  }
+  for (size_t i = 0; i < plan->matrices.size(); ++i) {
+    plan->matrices[i].step = plan->step;
+    for (size_t j = 0; j < plan->matrix_groups[i].size(); ++j)
+      plan->matrices[i].group[j].o_scale = plan->desc[plan->matrix_groups[i][j]].o_scale;
+  }
+  for (auto& lane : plan->lanes)
+    for (Launch& l : lane)
+      for (int i = 0; i < l.n; ++i) expand_op(plan->step, plan->desc[l.op[i]->group], l.op[i]->code, l.op[i]->a);
+  return *plan;
 }
 
 // Static description of matrix i: where its state arrays and its working copy live.
@@ -1158,8 +1283,7 @@ int enqueue_step(mona_state* st, const mona_hparams* hp, hipStream_t s) {
     if (e__ != hipSuccess) return bail(e__, #expr);      \
   } while (0)
 
-  Plan plan;
-  build_plan(st, *hp, plan, st->profiling > 1);
+  Plan& plan = plan_for(st, *hp);
   for (size_t gi = 0; gi < L.groups.size(); ++gi) L.groups[gi].o_buf = plan.o_buf[gi];
 
   const bool prof = st->profiling > 0;
@@ -1233,21 +1357,22 @@ int enqueue_step(mona_state* st, const mona_hparams* hp, hipStream_t s) {
     if (l.split) return launch_ns_split(batch, q);
     return launch_ns_small(batch, L.groups[op[0]->group].f32, l.wide, q);
   };
-  if (!fork)                     // one lane after the other on the caller's stream
-    for (int lane = 1; lane < L.lanes; ++lane) {
-      plan.lanes[0].insert(plan.lanes[0].end(), plan.lanes[lane].begin(), plan.lanes[lane].end());
-      plan.lanes[lane].clear();
-    }
   // the lanes are fed in turn, so that no lane waits for the host to have enqueued all of another
+  // (without side streams one lane after the other on the caller's)
   std::vector<size_t> at(L.lanes, 0);
   for (bool more = true; more;) {
     more = false;
     for (int lane = 0; lane < L.lanes; ++lane) {
       const std::vector<Launch>& queue = plan.lanes[lane];
       if (at[lane] == queue.size()) continue;
+      if (!fork && lane > 0 && at[lane - 1] < plan.lanes[lane - 1].size()) break;
       more = true;
       const Launch& l = queue[at[lane]++];
-      hipStream_t gs = lane == 0 ? s : st->side[lane - 1];
+      hipStream_t gs = lane == 0 || !fork ? s : st->side[lane - 1];
+      if (l.matrix >= 0) {
+        STEP_TRY(launch_ns_matrix(plan.matrices[l.matrix], gs));
+        continue;
+      }
       if (l.chain >= 0) {
         STEP_TRY(launch_ns_chain(plan.chains[l.chain], l.wgs, gs));
         continue;

@@ -204,6 +204,14 @@ static_assert(sizeof(ChainArgs) <= 4000, "an argument block holds 4 KB");
 constexpr int kMaxChains = 4;
 constexpr size_t kChainBytes = kMaxChains * sizeof(ChainRoll) + kMaxChainTasks * sizeof(uint32_t);
 
+// One launch of the kernel that takes a whole matrix through all its iterations in one workgroup.
+struct MatrixBatch {
+  StepDesc step;
+  int32_t n, steps, store_o;
+  int32_t end[kMaxMerged];          // matrices up to and including group i
+  GroupDesc group[kMaxMerged];
+};
+
 constexpr int kXcds = 8;   // MI355X: 8 accelerator dies, workgroups are dealt to them round-robin
 // workgroups per die of a launch of small tiles
 inline long long slots_per_die(const GemmArgs& a) { return ((long long)a.tiles_per_mat * a.count + kXcds - 1) / kXcds; }
@@ -242,10 +250,12 @@ hipError_t launch_ns_gemm(const GemmArgs& a, int cu_cap, hipStream_t s);   // 25
 hipError_t launch_ns_small(GemmBatch& b, bool f32, bool wide, hipStream_t s);
 // fp32 products as bf16 ones, 64 x 64 or 128 x 128 tiles
 hipError_t launch_ns_split(GemmBatch& b, hipStream_t s);
+// all iterations of groups of bf16 matrices with a padded short side of 128 or 256, one workgroup per matrix
+hipError_t launch_ns_matrix(const MatrixBatch& b, hipStream_t s);
 // a whole chain of products on small tiles; `wgs` workgroups
 hipError_t launch_ns_chain(const ChainArgs& c, int wgs, hipStream_t s);
 int device_cu_count();
-bool device_runs_chains();
+bool device_is_gfx950();
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 
 }  // namespace mona

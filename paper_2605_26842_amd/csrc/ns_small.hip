@@ -587,8 +587,9 @@ hipError_t launch_ns_small(GemmBatch& b, bool f32, bool wide, hipStream_t s) {
   return hipGetLastError();
 }
 
-// The chain kernel stands on device-scope accesses that are coherent between the dies by themselves, as gfx950 has them.
-bool device_runs_chains() {
+// The chain kernel stands on device-scope accesses that are coherent between the dies by themselves, ns_matrix_kernel on 160 KB of
+// LDS, as gfx950 has them.
+bool device_is_gfx950() {
   static const bool yes = []() {
     int dev = 0, major = 0, minor = 0;
     return hipGetDevice(&dev) == hipSuccess &&

@@ -1,0 +1,70 @@
+"""The kernel that takes a whole matrix through all its iterations in one workgroup (ns_matrix_kernel) against the float64
+oracle: both short sides, wide and tall, panels that stay in LDS and panels that do not, remainders, odd and even T."""
+import dataclasses
+
+import pytest
+import torch
+
+from paper_2605_26842_amd import binding as B
+from paper_2605_26842_amd import workloads as wl
+from tests import gpu_harness as H
+
+pytestmark = pytest.mark.gpu
+
+COUNT = 120
+# (shapes, iterations): every shape COUNT times (as many as make the kernel the better choice at both short sides)
+CASES = {
+    "p 128, one panel": ([(100, 128)], 5),
+    "p 128, tall, two panels and a remainder": ([(300, 97)], 5),
+    "p 128, four panels": ([(128, 512), (512, 128)], 5),
+    "p 128, five panels": ([(120, 600), (640, 66)], 5),
+    "p 256, two panels": ([(256, 256), (200, 256)], 5),
+    "p 256, odd sides": ([(131, 389), (643, 255)], 5),
+    "p 256, six panels": ([(256, 768), (768, 256)], 5),
+    "one iteration": ([(100, 200), (600, 120), (200, 300), (400, 250)], 1),
+    "two iterations": ([(100, 200), (600, 120), (200, 300), (400, 250)], 2),
+}
+
+
+@pytest.mark.parametrize("name", CASES)
+@pytest.mark.parametrize("param", [torch.float32, torch.bfloat16])
+def test_matrix_kernel_against_the_oracle(name, param):
+    kinds, steps = CASES[name]
+    print(f"[case] {name}", flush=True)
+    shapes = [s for s in kinds for _ in range(COUNT)]
+    watch = [i * COUNT + k for i in range(len(kinds)) for k in (0, COUNT - 1)]
+    weights = [wl.draw_weight(s, 300 + i, param) for i, s in enumerate(shapes)]
+    hp = wl.HParams(ns_steps=steps)
+    assert B.MonaOptimizer([w.cuda() for w in weights]).plan_info(steps)["ns_launches"] == 1
+    grads = [[wl.GradientStream(s, 400 + 500 * k + i).next() for i, s in enumerate(shapes)] for k in range(2)]
+    opt, dev_w, hist = H.run_gpu(weights, grads, hp, 0, watch=watch)
+    if param == torch.float32:
+        H.check_history(weights, grads, hp, hist, watch, H.TOL_NS_BF16, label=name)
+        return
+    ref = H.run_oracle_for(weights, grads, hp, watch)
+    for k in range(2):
+        for i in watch:
+            assert H.rel_fro(hist[k][i].O, ref[i][k]["O"]) <= H.TOL_NS_BF16, (name, k, i)
+
+
+def test_zero_and_infinite_matrices_among_others():
+    """A matrix without gradients has O = 0 and decays; one with an infinite gradient keeps its parameter; the others go on."""
+    print("[case] zero, infinite", flush=True)
+    shapes = [(130, 300)] * COUNT
+    weights = [wl.draw_weight(s, 300 + i, torch.float32, "cuda:0") for i, s in enumerate(shapes)]
+    grads = [wl.GradientStream(s, 400 + i, "cuda:0").next() for i, s in enumerate(shapes)]
+    grads[3].zero_()
+    grads[5][7, 11] = float("inf")
+    before = [w.clone() for w in weights]
+    plain = [w.clone() for w in weights]
+    hp = wl.HParams()
+    opt = B.MonaOptimizer(weights)
+    opt.step(grads, hp)
+    assert opt.status()[3] == 1 and opt.status()[5] & 2
+    assert torch.allclose(weights[3], before[3] * (1.0 - hp.lr * hp.weight_decay), rtol=1e-6, atol=0.0)
+    assert torch.equal(weights[5], before[5])
+    alone = B.MonaOptimizer(plain)
+    alone.step([g if i not in (3, 5) else torch.ones_like(g) for i, g in enumerate(grads)], dataclasses.replace(hp))
+    for i in range(COUNT):
+        if i not in (3, 5):
+            assert torch.equal(weights[i], plain[i]), i
