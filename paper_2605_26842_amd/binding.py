@@ -16,6 +16,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libmona.so")
+HELPER_PATH = os.path.join(_HERE, "libmona_descriptors.so")
 
 MONA_OK, MONA_EINVAL, MONA_ESHAPE, MONA_ENOMEM, MONA_EHIP, MONA_EUNSUPPORTED = 0, -1, -2, -3, -4, -5
 MONA_F32, MONA_BF16 = 0, 1
@@ -136,6 +137,23 @@ def load_library(path: Optional[str] = None) -> C.CDLL:
     return lib
 
 
+_helper: Optional[C.PyDLL] = None
+
+
+def _load_helper() -> C.PyDLL:
+    """The library that reads lists of tensors (built with libmona.so); it works on Python objects, so the interpreter's lock stays held."""
+    global _helper
+    if _helper is None:
+        if not os.path.exists(HELPER_PATH):
+            raise FileNotFoundError(f"{HELPER_PATH} not found: build it first (python paper_2605_26842_amd/build.py)")
+        lib = C.PyDLL(HELPER_PATH)
+        lib.mona_fill_vectors.argtypes = [C.py_object, C.py_object, C.c_int64, C.c_void_p]
+        lib.mona_fill_matrices.argtypes = [C.py_object, C.py_object, C.c_int64, C.c_void_p]
+        lib.mona_fill_slots.argtypes = [C.py_object, C.py_object, C.c_int64, C.c_int32, C.c_void_p]
+        _helper = lib
+    return _helper
+
+
 def _check(rc: int) -> None:
     if rc != MONA_OK:
         raise MonaError(rc, load_library().mona_last_error().decode())
@@ -160,6 +178,8 @@ def make_matrices(weights: Sequence[torch.Tensor], grads: Optional[Sequence[torc
     """Array of mona_matrix descriptors for 2-D contiguous tensors."""
     n = len(weights)
     arr = (mona_matrix * n)()
+    if grads is not None and _load_helper().mona_fill_matrices(weights, grads, n, C.addressof(arr)):
+        return arr
     for i, w in enumerate(weights):
         if w.dim() != 2 or not w.is_contiguous():
             raise ValueError(f"matrix {i}: parameters must be contiguous 2-D tensors")
@@ -241,8 +261,6 @@ class MonaOptimizer:
         with torch.cuda.device(self.device):
             stream = torch.cuda.current_stream(self.device).cuda_stream
             self.state = mona_init_state(shapes_only, self.count, self.opts, self.arena, stream)
-        self._mats = None
-        self._mats_key = None
 
     def close(self) -> None:
         if getattr(self, "state", None):
@@ -261,20 +279,20 @@ class MonaOptimizer:
     def step(self, grads: Sequence[torch.Tensor], hp, slots: Optional[Sequence[torch.Tensor]] = None) -> None:
         """One MONA step over all matrices (asynchronous on torch's current stream).  `slots`: the
         caller-kept previous-gradient arrays of a MONA_ACCEL_CALLER_SLOT state."""
-        key = tuple(g.data_ptr() for g in grads)
-        if key != self._mats_key:
-            self._mats = make_matrices(self.weights, grads)
-            self._mats_key = key
+        mats = make_matrices(self.weights, grads)
         hpc = hp if isinstance(hp, mona_hparams) else make_hparams(hp)
         if slots is None:
-            mona_step(self.state, self._mats, self.count, hpc, self._stream())
+            mona_step(self.state, mats, self.count, hpc, self._stream())
             return
         arr = (C.c_void_p * self.count)()
+        if _load_helper().mona_fill_slots(self.weights, slots, self.count, _dtype_code(self.state_dtype), C.addressof(arr)):
+            mona_step_streaming(self.state, mats, arr, self.count, hpc, self._stream())
+            return
         for i, t in enumerate(slots):
             if t.shape != self.weights[i].shape or not t.is_contiguous() or t.dtype != self.state_dtype:
                 raise ValueError(f"slot {i}: must be contiguous, shaped like the parameter, of the state dtype")
             arr[i] = t.data_ptr()
-        mona_step_streaming(self.state, self._mats, arr, self.count, hpc, self._stream())
+        mona_step_streaming(self.state, mats, arr, self.count, hpc, self._stream())
 
     # ---- views of the state as torch tensors (no copy) ----
     def view(self, i: int, kind: int) -> torch.Tensor:
@@ -348,6 +366,8 @@ def make_vectors(params: Sequence[torch.Tensor], grads: Optional[Sequence[torch.
                  g_dtype: torch.dtype = torch.float32):
     """Array of mona_vector descriptors for contiguous tensors of any shape."""
     arr = (mona_vector * len(params))()
+    if grads is not None and _load_helper().mona_fill_vectors(params, grads, len(params), C.addressof(arr)):
+        return arr
     for i, w in enumerate(params):
         if not w.is_contiguous():
             raise ValueError(f"tensor {i}: parameters must be contiguous")
@@ -394,8 +414,7 @@ class AdamWOptimizer:
         self.state = handle.value
 
     def _stream(self) -> int:
-        with torch.cuda.device(self.device):
-            return torch.cuda.current_stream(self.device).cuda_stream
+        return torch.cuda.current_stream(self.device).cuda_stream
 
     def __del__(self):
         st = getattr(self, "state", None)

@@ -10,6 +10,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libmona.so")
 SOURCES = ("mona_api.hip", "state_update.hip", "ns_gemm.hip", "ns_small.hip", "ns_split.hip", "ns_matrix.hip", "adamw.hip")
+# reads the callers' tensors for the ctypes binding: host code against PyTorch's own headers
+HELPER_PATH = os.path.join(HERE, "libmona_descriptors.so")
+HELPER_SOURCE = "descriptors.cpp"
 ARCH = "gfx950"
 
 
@@ -18,6 +21,18 @@ def hipcc_path() -> str:
         if cand and os.path.exists(cand):
             return cand
     raise RuntimeError("hipcc not found (looked at $HIPCC, /opt/rocm/bin/hipcc and PATH)")
+
+
+def helper_command(out: str) -> list:
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(os.path.abspath(torch.__file__))
+    inc = os.path.join(root, "include")
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
+            "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, HELPER_SOURCE), "-o", out,
+            "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"]
 
 
 def build_library(verbose: bool = True, extra_flags=()) -> str:
@@ -40,11 +55,15 @@ def build_library(verbose: bool = True, extra_flags=()) -> str:
             print("[build]", " ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
         objs.append(obj)
+    cmd = helper_command(HELPER_PATH + ".tmp")
+    if verbose:
+        print("[build]", " ".join(cmd), flush=True)
+    procs.append((HELPER_SOURCE, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     for src, p in procs:
         out, _ = p.communicate()
         out = "\n".join(l for l in out.splitlines() if "not a recognized feature" not in l)
         if p.returncode != 0:
-            raise RuntimeError(f"hipcc failed on {src}:\n{out}")
+            raise RuntimeError(f"the compiler failed on {src}:\n{out}")
         if verbose and out.strip():
             print(out)
     tmp = LIB_PATH + ".tmp"
@@ -53,6 +72,7 @@ def build_library(verbose: bool = True, extra_flags=()) -> str:
         print("[build]", " ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
     os.replace(tmp, LIB_PATH)
+    os.replace(HELPER_PATH + ".tmp", HELPER_PATH)
     return LIB_PATH
 
 
