@@ -11,6 +11,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -993,11 +994,11 @@ Plan& plan_for(mona_state* st, const mona_hparams& hp) {
   const bool one_by_one = st->profiling > 1;
   Plan* plan = st->plan;
   if (!plan || plan->ns_steps != hp.ns_steps || plan->flags != hp.flags || plan->one_by_one != one_by_one) {
+    // (kept once it is whole: a caller may go on after an allocation that failed on the way)
+    std::unique_ptr<Plan> fresh(new Plan());
+    build_plan(st, hp, *fresh, one_by_one);
     delete plan;
-    st->plan = nullptr;
-    st->plan = plan = new Plan();
-    build_plan(st, hp, *plan, one_by_one);
-    return *plan;
+    return *(st->plan = fresh.release());
   }
   const Layout& L = st->L;
   set_step(st, hp, *plan);
