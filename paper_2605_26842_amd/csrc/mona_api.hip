@@ -216,9 +216,9 @@ long long launch_tiles(const Group& g, int kind, int tile, int count) {
 // Whether the matrices of a group get a workgroup each (ns_matrix_kernel), by what their iterations take that way and as
 // products, us of a step.  Alone, products take as long as their launches at least; beside other groups, whose launches they share
 // or run beside, only what they add.  Measured, us per step as products (launches, or a chain) / by matrix: 128 x 128 57 / 32,
-// 100 x 400 70 / 64, 24 x 128 x 512 90 / 75, 60 x 128 x 256 105 / 53, 250 x 70 x 100 170 / 52, 200 x 120 x 600 317 / 189,
-// 250 x 128 x 4000 1983 / 1521, but 40 x 128 x 2000 232 / 327; 256 x 256 x 256 426 / 255, 115 x 256 x 512 383 / 309, 128 x 768 x 256 both
-// ways 820 / 633, but 60 x 256 x 512 235 / 260, 79 x 256 x 834 and others 482 / 569; 4 x 171 x 66 beside 697 x 612 and 365 x 161 144 / 169.
+// 100 x 400 70 / 64, 24 x 128 x 512 90 / 75, 60 x 128 x 256 105 / 53, 250 x 70 x 100 170 / 52, 200 x 120 x 600 317 / 177,
+// 250 x 128 x 4000 1983 / 1367, but 40 x 128 x 2000 232 / 327; 256 x 256 x 256 426 / 245, 115 x 256 x 512 383 / 291, 128 x 768 x 256 both
+// ways 818 / 606, but 60 x 256 x 512 235 / 260, 79 x 256 x 834 and others 482 / 569; 4 x 171 x 66 beside 697 x 612 and 365 x 161 144 / 169.
 bool by_matrix(const Group& g, bool alone) {
   if (g.f32 || g.fused || (g.p_pad != 128 && g.p_pad != 256) || !device_is_gfx950()) return false;
   const double count = (double)g.members.size(), panels = std::max(g.rows_pad, g.cols_pad) / 128;

@@ -11,12 +11,17 @@
 //
 // P = 128: B takes 32 registers, so the S of the next iteration is accumulated from every panel while it is in LDS, and up to four
 // panels (q <= 512) stay there from the first iteration to the last.  P = 256: B takes 128 registers, S 128 accumulators, so
-// they take turns, the squares lie over the panels, and every iteration reads X twice (from L2 or the last-level cache) and writes
-// it once.  Eight wavefronts, one workgroup per CU.
+// they take turns, the squares lie over the panels, and every iteration reads X twice and writes it once.  Eight wavefronts, one workgroup per CU.
 //
-// Measured, us per step, products in launches (or chains) -> here: 128 x 768 x 256 both ways 820 -> 633, 250 x 70 x 100 170 -> 52,
-// 256 x 256 x 256 426 -> 255, 300 x 128 x 128 202 -> 88, one 128 x 128 57 -> 32.  A panel costs 2.2 us an iteration (P = 128, in LDS;
-// 2.9 through memory) or 7.9 us (P = 256, twice) on a CU, of which the multiplications are 1 and 4: the wavefronts meet three
+// Panels that do not stay in LDS come from a die's 4 MB of L2, 128 KB for each of its 32 workgroups, or from behind it.  Passes that go
+// the same way all the time find nothing there; so they go to and fro, and X is renewed in place, which halves what the steps
+// touch.  Measured, us per step, one way and between two buffers -> to and fro in place: 250 x 128 x 4000 1505 -> 1367, 300 x 128 x 1000
+// 559 -> 498, 256 x 200 x 700 644 -> 622, 128 x 256 x 1024 572 -> 543, 256 x 256 x 256 258 -> 245.  Letting the second panel of a pass
+// arrive while the first is multiplied gains nothing on top.
+//
+// Measured, us per step, products in launches (or chains) -> here: 128 x 768 x 256 both ways 818 -> 606, 250 x 70 x 100 170 -> 52,
+// 256 x 256 x 256 426 -> 245, 300 x 128 x 128 202 -> 88, one 128 x 128 57 -> 32.  A panel costs 2.2 us an iteration (P = 128) or
+// 7.3 us (P = 256, twice) on a CU, of which the multiplications are 1 and 4: the wavefronts meet three
 // times a panel, and the vector instructions of the epilogue (2.5 an element) do not run beside matrix instructions.
 //
 // LDS: rows of 256 or 512 bytes, chunk c (16 bytes) of row r at c ^ swizzle(r): 16 consecutive rows hit 16 different
@@ -143,15 +148,20 @@ __device__ __forceinline__ void run_matrix(const StepDesc& st, const GroupDesc& 
   const int panels = (TALL ? g.rows_pad : g.cols_pad) / kPanel;
   const bool resident = panels <= G::RESIDENT;
   const int64_t x_stride = (int64_t)g.rows_pad * g.cols_pad;
-  bf16_t* const X[2] = {reinterpret_cast<bf16_t*>(g.x) + member * x_stride, reinterpret_cast<bf16_t*>(g.x + g.x_step) + member * x_stride};
+  bf16_t* const x0 = reinterpret_cast<bf16_t*>(g.x) + member * x_stride;
+  // (O goes where products one by one would leave it)
+  bf16_t* const out_at = (steps & 1) ? reinterpret_cast<bf16_t*>(g.x + g.x_step) + member * x_stride : x0;
   const int mi = g.members[member];
   const MatScale sc = st.scales[mi];
   const bool skip_w = (sc.status & 2u) != 0;
   void* const wptr = st.dyn[mi].w;
   const int w_is_bf16 = st.stat[mi].w_dtype;
 
-  auto buffer = [&](int j) { return (uint32_t)(G::PANELS_AT + (resident ? j : j & 1) * G::PANEL); };
-  // requests panel j of `src`: every wavefront a share of its chunks
+  // A pass goes over the panels forwards or (back) backwards, i counts them as they come.  Where they do not stay in LDS, passes
+  // alternate and X is renewed in place: the panels that the pass before had last are still in L2 then.
+  auto panel = [&](int i, bool back) { return back ? panels - 1 - i : i; };
+  auto buffer = [&](int i) { return (uint32_t)(G::PANELS_AT + (resident ? i : i & 1) * G::PANEL); };
+  // requests the i-th panel of a pass: every wavefront a share of its chunks
   // (unit u of a panel is chunk u % CPR of row u / CPR as it stands in LDS; a thread's units are 512 apart, a multiple of
   // sixteen rows, so they share their swizzle and are `rows` rows apart in memory)
   constexpr int UNITS = G::PANEL / 16 / kMatThreads, ROWS = kMatThreads / CPR;
@@ -160,10 +170,10 @@ __device__ __forceinline__ void run_matrix(const StepDesc& st, const GroupDesc& 
     const int u = wave * 64 + L.lane, row = u / CPR, c = (u % CPR) ^ swizzle(row);
     return TALL ? (size_t)(j * kPanel + row) * ld + c * 8 : (size_t)row * ld + j * kPanel + c * 8;
   };
-  auto request = [&](const bf16_t* src, int j) {
-    char* const to = lds + buffer(j) + wave * 1024;
+  auto request = [&](int i_th, bool back) {
+    char* const to = lds + buffer(i_th) + wave * 1024;
     const Lane L;
-    const bf16_t* const from = src + unit_at(L, j);
+    const bf16_t* const from = x0 + unit_at(L, panel(i_th, back));
     static_for<UNITS>([&](auto i) {
       __builtin_amdgcn_global_load_lds((const MONA_AS1 void*)(from + (size_t)(i * ROWS) * ld),
                                        (MONA_AS3 void*)(to + i * kMatThreads * 16), 16, 0, 0);
@@ -231,23 +241,23 @@ __device__ __forceinline__ void run_matrix(const StepDesc& st, const GroupDesc& 
   const int rg = wave >> 1, cg = wave & 1;
   const int pr = rg * (P / 4);
 
-  request(X[0], 0);
-  if (panels > 1) request(X[0], 1);
+  request(0, false);
+  if (panels > 1) request(1, false);
   if (resident)
-    for (int j = 2; j < panels; ++j) request(X[0], j);
-  int src = 0;
+    for (int i = 2; i < panels; ++i) request(i, false);
   for (int t = 0; t < steps; ++t) {
     const bool first = t == 0, last = t + 1 == steps;
-    const bf16_t* const from = X[src];
-    bf16_t* const to = X[src ^ 1];
+    // direction of the apply: against the pass before it (P = 256: the S of this iteration, always forwards)
+    const bool back = !resident && (!G::kFused || (t & 1) == 0);
+    bf16_t* const to = last ? out_at : x0;
     // the loads of the panel (in issue order before the `later` newest accesses) have landed for every wavefront
     auto arrive = [&](auto later) { MONA_WAIT_VM(later); meet(); };
     if (first || !G::kFused) {
       clear();
-      for (int j = 0; j < panels; ++j) {
+      for (int i = 0; i < panels; ++i) {
         arrive(IC<0>{});
-        if (j >= 1 && j + 1 < panels && !resident) request(from, j + 1);
-        gram(buffer(j));
+        if (i >= 1 && i + 1 < panels && !resident) request(i + 1, false);
+        gram(buffer(i));
       }
     }
     // ---- S and B ----
@@ -272,8 +282,8 @@ __device__ __forceinline__ void run_matrix(const StepDesc& st, const GroupDesc& 
     }
     meet();
     if (G::kFused && first && !resident) {       // the first pass has been over all panels
-      request(from, 0);
-      request(from, 1);
+      request(0, back);
+      request(1, back);
     }
     clear();
     {
@@ -322,16 +332,17 @@ __device__ __forceinline__ void run_matrix(const StepDesc& st, const GroupDesc& 
     }
     if constexpr (!G::kFused) {
       meet();                                    // every wavefront has its B
-      request(from, 0);
-      if (panels > 1) request(from, 1);
+      request(0, back);
+      if (panels > 1) request(1, back);
     }
     if (G::kFused) clear();
     // ---- Y_j <- a Y_j + B Y_j ----
-    for (int j = 0; j < panels; ++j) {
-      const uint32_t at = buffer(j);
+    for (int i_th = 0; i_th < panels; ++i_th) {
+      const uint32_t at = buffer(i_th);
+      const int j = panel(i_th, back);
       // (the stores of the panel before may still be on their way)
-      if (j > 0 && !last && !resident) arrive(IC<UNITS>{}); else arrive(IC<0>{});
-      if (j >= 1 && j + 1 < panels && !resident) request(from, j + 1);
+      if (i_th > 0 && !last && !resident) arrive(IC<UNITS>{}); else arrive(IC<0>{});
+      if (i_th >= 1 && i_th + 1 < panels && !resident) request(i_th + 1, back);
       f32x16 y[G::RB][G::CB];
 #pragma unroll
       for (int i = 0; i < G::RB; ++i)
@@ -449,12 +460,12 @@ __device__ __forceinline__ void run_matrix(const StepDesc& st, const GroupDesc& 
       }
       if (G::kFused && !last) gram(at);
     }
-    src ^= 1;
     if (!last && !resident) {
       MONA_WAIT_VM(0);                           // this wavefront's part of the new X is in memory
       meet();
-      request(X[src], 0);
-      if (panels > 1) request(X[src], 1);
+      const bool next = G::kFused && !back;
+      request(0, next);
+      if (panels > 1) request(1, next);
     }
   }
 }
