@@ -1572,7 +1572,10 @@ int mona_step_noalloc(const mona_matrix* mat, const mona_options* opts, void* g_
   st.k = k;
   hipStream_t s = static_cast<hipStream_t>(stream);
   // The array keeps what the last call left in it: the padding of the working matrices and the scales must
-  // start from zero (stores of a kernel, not a memset: the call may be under graph capture).
+  // start from zero (stores of a kernel, not a memset: the call may be under graph capture).  A matrix without padding
+  // needs none of that: every buffer is written whole before it is read (us a step with and without the clearing: 512 x 1408
+  // 118.5 and 115.6, 1024 x 1024 156 and 152).
+  const bool padded = L.groups[0].rows_pad != mat->m || L.groups[0].cols_pad != mat->n;
   MatStatic ms;
   void* o_ptr = nullptr;
   fill_static(L, *mat, 0, base, g_prev, acc, mom, ms, o_ptr);
@@ -1582,7 +1585,7 @@ int mona_step_noalloc(const mona_matrix* mat, const mona_options* opts, void* g_
                                 st.at<void*>(L.optr_off), st.at<BlockWork>(L.blocks_off), (int)L.blocks.size(),
                                 reinterpret_cast<int32_t*>(base + L.groups[0].members_off),
                                 st.at<int32_t>(L.order_off), st.at<MatScale>(L.scales_off), base + L.work_begin,
-                                L.work_bytes, s));
+                                padded ? L.work_bytes : 0, s));
   rc = enqueue_step(&st, hp, s);
   if (rc) return rc;
   note_unstable_alpha(hp);

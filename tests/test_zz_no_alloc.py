@@ -53,6 +53,20 @@ def test_noalloc_matches_mona_step_twice_in_a_row():
     run_pair((96, 200), 4300, 2, torch.float32, torch.float32, wl.HParams(ns_steps=0))
 
 
+@pytest.mark.parametrize("shape, steps", [((256, 128), 5), ((128, 640), 5), ((512, 1408), 2), ((768, 384), 1), ((256, 256), 0)])
+def test_noalloc_without_padding_after_another_matrix(shape, steps):
+    """The workspace is not cleared for a matrix without padding: what a larger one with an infinite gradient left is not read."""
+    dev = "cuda:0"
+    print(f"[case] noalloc {shape}, T = {steps}, after 500 x 1400", flush=True)
+    w, g, a, b, m = (torch.zeros((500, 1400), dtype=torch.float32, device=dev) for _ in range(5))
+    g.normal_()
+    g[3, 5] = float("inf")
+    for k in range(2):
+        B.mona_step_noalloc(B.make_matrices([w], [g]), None, a.data_ptr(), b.data_ptr(), m.data_ptr(),
+                            B.make_hparams(wl.HParams()), k, torch.cuda.current_stream().cuda_stream)
+    run_pair(shape, 4400, 2, torch.float32, torch.float32, wl.HParams(ns_steps=steps))
+
+
 def test_noalloc_rejects_what_does_not_fit():
     dev = "cuda:0"
     shape = (2048, 8192)
