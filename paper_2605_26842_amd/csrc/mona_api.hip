@@ -218,7 +218,9 @@ long long launch_tiles(const Group& g, int kind, int tile, int count) {
 // or run beside, only what they add.  Measured, us per step as products (launches, or a chain) / by matrix: 128 x 128 57 / 32,
 // 100 x 400 70 / 64, 24 x 128 x 512 90 / 75, 60 x 128 x 256 105 / 53, 250 x 70 x 100 170 / 52, 200 x 120 x 600 317 / 177,
 // 250 x 128 x 4000 1983 / 1367, but 40 x 128 x 2000 232 / 327; 256 x 256 x 256 426 / 245, 115 x 256 x 512 383 / 291, 128 x 768 x 256 both
-// ways 818 / 606, but 60 x 256 x 512 235 / 260, 79 x 256 x 834 and others 482 / 569; 4 x 171 x 66 beside 697 x 612 and 365 x 161 144 / 169.
+// ways 818 / 606, but 60 x 256 x 512 235 / 260, 79 x 256 x 834 and others 482 / 569; 4 x 171 x 66 beside 697 x 612 and 365 x 161 144 / 169;
+// 50 x 256 x 256 170 / 147, 84 x 256 x 256 213 / 162, 70 x 130 x 200 148 / 134, 86 x 256 x 768 474 / 376, but 36 x 256 x 256 140 / 140, 52 x 160 x 140
+// 126 / 148, 50 x 140 x 380 160 / 205.
 bool by_matrix(const Group& g, bool alone) {
   if (g.f32 || g.fused || (g.p_pad != 128 && g.p_pad != 256) || !device_is_gfx950()) return false;
   const double count = (double)g.members.size(), panels = std::max(g.rows_pad, g.cols_pad) / 128;
@@ -228,7 +230,10 @@ bool by_matrix(const Group& g, bool alone) {
     return rounds * 5.0 * (2.2 + (panels <= 4 ? 2.2 : 2.9) * panels) < std::max(0.2 * units, latency);
   }
   const double unit = panels <= 4 ? 0.75 : count >= kMinSingles256 ? 0.45 : 0.55;
-  return rounds * 5.0 * (9.5 + 7.9 * panels) < std::max(unit * units, alone ? 80.0 : 0.0);
+  // (products leave out 64 x 64 tiles of padding, this kernel does not)
+  const double real = (double)(round_up(g.m, 64) * (int64_t)round_up(g.n, 64)) / ((double)g.rows_pad * g.cols_pad);
+  const double latency = alone ? std::min(30.0 + units * real, 160.0) : 0.0;
+  return rounds * 5.0 * (9.5 + 7.8 * panels) < std::max(unit * units, latency);
 }
 
 // Whether the groups of the step, all together, are as little as a chain takes (of five literal iterations: the exact check
