@@ -299,15 +299,14 @@ __device__ __forceinline__ void run_matrix(const StepDesc& st, const GroupDesc& 
     {
       const Lane L;
       const uint32_t sq = square_at(L);
-      // (the scale of the unscaled copy goes into the first B and, below, into the first a)
-      const float cb = first ? sc.inv * st.ns_b : st.ns_b, cc = first ? sc.inv * st.ns_c : st.ns_c;
       u32x2 out[G::GM][G::GN][4];
       static_for<G::GM>([&](auto i) {
         static_for<G::GN>([&](auto j) {
           static_for<4>([&](auto v) {
             const bf16x4 e = __builtin_bit_cast(bf16x4, at8((sq ^ xor_at(j, v)) + i * 32 * SPITCH));
-            out[i][j][v] = pack(fmaf(cc, acc[i][j][4 * v], cb * (float)e.x), fmaf(cc, acc[i][j][4 * v + 1], cb * (float)e.y),
-                                fmaf(cc, acc[i][j][4 * v + 2], cb * (float)e.z), fmaf(cc, acc[i][j][4 * v + 3], cb * (float)e.w));
+            auto poly = [&](float x, bf16_t y) { return fmaf(st.ns_c, x, st.ns_b * (float)y); };
+            out[i][j][v] = pack(poly(acc[i][j][4 * v], e.x), poly(acc[i][j][4 * v + 1], e.y), poly(acc[i][j][4 * v + 2], e.z),
+                                poly(acc[i][j][4 * v + 3], e.w));
           });
           asm volatile("" ::: "memory");         // a block's values at a time: there is no room for those of all blocks
         });
@@ -392,14 +391,28 @@ __device__ __forceinline__ void run_matrix(const StepDesc& st, const GroupDesc& 
         return TALL ? at8((pan ^ xor_at(i, v)) + c * 32 * PITCH) : at8((pan ^ xor_at(c, v)) + i * 32 * PITCH);
       };
       u32x2 out[G::RB][G::CB][4];
-      const float ce = first ? sc.inv * st.ns_a : st.ns_a;
+      // The scale of the unscaled copy enters behind the sum, and every rounding is that of the products in launches: at
+      // P = 256 of the large-tile kernel (whose bits these are), at P = 128 of finish_tile().  In B or in a instead it rounds B in
+      // other places, which moves W by 2e-3 of its norm in a step.
+      const float post = first ? sc.inv : 1.0f, ce = P == 256 ? post * st.ns_a : st.ns_a;
       static_for<G::RB>([&](auto i) {
         static_for<G::CB>([&](auto c) {
-          static_for<4>([&](auto v) {
-            const bf16x4 e = __builtin_bit_cast(bf16x4, panel8(i, c, v));
-            out[i][c][v] = pack(fmaf(ce, (float)e.x, y[i][c][4 * v]), fmaf(ce, (float)e.y, y[i][c][4 * v + 1]),
-                                fmaf(ce, (float)e.z, y[i][c][4 * v + 2]), fmaf(ce, (float)e.w, y[i][c][4 * v + 3]));
-          });
+          auto renew = [&](auto unit) {
+            auto value = [&](bf16_t x, float sum) {
+              if constexpr (P == 128) {
+                const float r = sum + ce * (float)x;
+                return unit ? r : post * r;
+              } else {
+                return unit ? fmaf(ce, (float)x, sum) : fmaf(post, sum, ce * (float)x);
+              }
+            };
+            static_for<4>([&](auto v) {
+              const bf16x4 e = __builtin_bit_cast(bf16x4, panel8(i, c, v));
+              out[i][c][v] = pack(value(e.x, y[i][c][4 * v]), value(e.y, y[i][c][4 * v + 1]), value(e.z, y[i][c][4 * v + 2]),
+                                  value(e.w, y[i][c][4 * v + 3]));
+            });
+          };
+          if (post == 1.0f) renew(IC<1>{}); else renew(IC<0>{});
           asm volatile("" ::: "memory");
         });
       });

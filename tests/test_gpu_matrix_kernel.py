@@ -68,3 +68,31 @@ def test_zero_and_infinite_matrices_among_others():
     for i in range(COUNT):
         if i not in (3, 5):
             assert torch.equal(weights[i], plain[i]), i
+
+
+@pytest.mark.parametrize("shape", [(256, 768), (768, 256)])
+@pytest.mark.parametrize("param", [torch.float32, torch.bfloat16])
+def test_the_bits_of_the_large_tile_kernel(shape, param):
+    """A short side of 256: every sum runs over K in the order of the large-tile kernel and is rounded in the same places (the
+    scale of the first iteration behind the sum of the apply), so the parameters are the same, bit for bit.  The large
+    tiles: the same matrices, fewer of them, beside matrices that fill the chip with such tiles."""
+    print(f"[case] {shape}", flush=True)
+    few, dev = 36, "cuda:0"
+
+    def run(shapes, level):
+        weights = [wl.draw_weight(s, 300 + i, param, dev) for i, s in enumerate(shapes)]
+        opt = B.MonaOptimizer(weights)
+        opt.set_profiling(level)
+        for k in range(2):
+            opt.step([wl.GradientStream(s, 400 + 1000 * k + i, dev).next() for i, s in enumerate(shapes)], wl.HParams())
+        torch.cuda.synchronize()
+        return opt, weights
+
+    beside = [shape] * few + [(1024, 1024)] * 16
+    opt, _ = run(beside, 2)
+    assert {r["tile"] for r in opt.last_step_launches()} == {256256}
+    alone = B.MonaOptimizer([wl.draw_weight(shape, i, param, dev) for i in range(COUNT)])
+    assert alone.plan_info(5)["ns_launches"] == 1
+    want, got = run(beside, 0)[1], run([shape] * COUNT, 0)[1]
+    for i in range(few):
+        assert torch.equal(want[i], got[i]), i
