@@ -289,7 +289,8 @@ int mona_mean_step_times(mona_state* st, float* ms_out, int32_t* steps_out);
  *   kind: 0 = Gram (X X^T), 1 = poly (b S + c S S [+ a I]), 2 = apply (a X + B X, or R X),
  *         3 = product of two commuting symmetric p x p matrices (fused schedule)
  *   tile:  block tile of the kernel, rows * 1000 + columns (e.g. 256128)
- *   flops: MFMA flop the product issues (tiles x 2 x rows x columns x K), padding included */
+ *   flops: MFMA flop the product issues (tiles x 2 x rows x columns x K), padding included (an fp32
+ *          product counts once where it is carried out as six bf16 ones) */
 typedef struct mona_launch_time {
   int32_t kind, group, iter, tile;
   int32_t m, n, count;   /* shape of the group's matrices and how many there are */
@@ -302,8 +303,9 @@ int mona_last_step_launches(mona_state* st, mona_launch_time* out, int32_t max_r
 /* Number of kernel launches and executed MFMA flop of the Newton-Schulz part of one ordinary
  * step (products of several small shape groups that share a launch count as one launch, and so do all
  * products of a step whose groups are so small that they run as one chain, or of groups whose matrices
- * get a workgroup each; host-only bookkeeping, for roofline reporting).  Profiling level 2 launches and
- * times every product by itself all the same. */
+ * get a workgroup each; host-only bookkeeping, for roofline reporting).  The flop include padding, and both triangles of
+ * S and S S where a matrix has a workgroup to itself; an fp32 product counts once where it is carried out as six bf16
+ * ones.  Profiling level 2 launches and times every product by itself all the same. */
 int mona_plan_info(mona_state* st, int32_t ns_steps, int64_t* launches_out,
                    double* ns_flops_executed_out, double* elementwise_bytes_out);
 

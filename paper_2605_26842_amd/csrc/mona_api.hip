@@ -610,8 +610,27 @@ struct mona_state {
 
 namespace {
 
+// Flop that the matrix units execute, padding included (an fp32 product counts once, however it is carried out): of a
+// product, ...
 double gemm_flops(const GemmArgs& a) {
   return 2.0 * a.tile_m * a.tile_n * (double)a.K * a.tiles_per_mat * a.count;
+}
+// ... of `steps` iterations of a group whose matrices get a workgroup each (both triangles of S and S S), ...
+double matrix_flops(const GroupDesc& g, int steps) {
+  const double p = g.tall ? g.cols_pad : g.rows_pad, q = g.tall ? g.rows_pad : g.cols_pad;
+  return steps * (4.0 * p * p * q + 2.0 * p * p * p) * g.count;
+}
+// ... and of a launch.
+double launch_flops(const Plan& plan, const Launch& l) {
+  double flops = 0.0;
+  if (l.matrix >= 0)
+    for (int gi : plan.matrix_groups[l.matrix]) flops += matrix_flops(plan.desc[gi], plan.ns_steps);
+  else if (l.chain >= 0)
+    for (int gi : plan.chain_groups[l.chain])
+      for (const Op& op : plan.ops[gi]) flops += gemm_flops(op.a);
+  else
+    for (int i = 0; i < l.n; ++i) flops += gemm_flops(l.op[i]->a);
+  return flops;
 }
 
 void set_tile(const Plan& plan, Op& op, int tile) {
@@ -1776,9 +1795,10 @@ int mona_plan_info(mona_state* st, int32_t ns_steps, int64_t* launches_out, doub
   build_plan(st, hp, plan, false);
   double flops = 0.0;
   int64_t launches = 0;
-  for (const auto& lane : plan.lanes) launches += (int64_t)lane.size();
-  for (const auto& ops : plan.ops)
-    for (const Op& op : ops) flops += gemm_flops(op.a);
+  for (const auto& lane : plan.lanes) {
+    launches += (int64_t)lane.size();
+    for (const Launch& l : lane) flops += launch_flops(plan, l);
+  }
   double bytes = 0.0;
   for (int i = 0; i < L.count; ++i) {
     const double ne = (double)st->mats[i].m * st->mats[i].n;
