@@ -313,7 +313,7 @@ def main() -> int:
                 groups_seen.add(r["group"])
     w_bytes = 2 * n_elem_bytes_w(workload)
     if args.per_launch:
-        kinds = {0: "gram", 1: "poly", 2: "apply", 3: "sym"}
+        kinds = {0: "gram", 1: "poly", 2: "apply", 3: "sym", 4: "whole"}
         for r in launches:
             tf = r["flops"] / (r["ms"] * 1e-3) / 1e12 if r["ms"] > 0 else 0.0
             print(f"[launch] {kinds[r['kind']]:5s} {r['m']}x{r['n']} x{r['count']} iter {r['iter']} tile {r['tile']}: "

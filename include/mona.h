@@ -282,13 +282,16 @@ int mona_mean_step_times(mona_state* st, float* ms_out, int32_t* steps_out);
 
 /* With mona_set_profiling(st, 2) every Newton-Schulz product of a step is launched by itself, in a row on
  * the caller's stream, and bracketed by its own pair of events.  Products of several small shape groups that
- * an ordinary step puts into one launch keep the tiles and the split of K they have there, so the results are
- * those of an ordinary step bit for bit; their times add up to more than the common launch takes.
- * mona_last_step_launches waits for the step and fills up to max_records entries, one per product (out may
- * be NULL to query the count).
+ * an ordinary step puts into one launch keep the tiles and the split of K they have there, and groups whose matrices get a
+ * workgroup each (all iterations in one launch) are launched group by group, so the results are
+ * those of an ordinary step bit for bit; the times add up to more than a common launch takes.
+ * mona_last_step_launches waits for the step and fills up to max_records entries, one per product or such
+ * group (out may be NULL to query the count).
  *   kind: 0 = Gram (X X^T), 1 = poly (b S + c S S [+ a I]), 2 = apply (a X + B X, or R X),
- *         3 = product of two commuting symmetric p x p matrices (fused schedule)
- *   tile:  block tile of the kernel, rows * 1000 + columns (e.g. 256128)
+ *         3 = product of two commuting symmetric p x p matrices (fused schedule),
+ *         4 = all iterations of the group's matrices, a workgroup each (iter 0)
+ *   tile:  block tile of the kernel, rows * 1000 + columns (e.g. 256128); kind 4: the padded short side and 128, the
+ *          part of the long side it takes at a time
  *   flops: MFMA flop the product issues (tiles x 2 x rows x columns x K), padding included (an fp32
  *          product counts once where it is carried out as six bf16 ones) */
 typedef struct mona_launch_time {
@@ -305,7 +308,8 @@ int mona_last_step_launches(mona_state* st, mona_launch_time* out, int32_t max_r
  * products of a step whose groups are so small that they run as one chain, or of groups whose matrices
  * get a workgroup each; host-only bookkeeping, for roofline reporting).  The flop include padding, and both triangles of
  * S and S S where a matrix has a workgroup to itself; an fp32 product counts once where it is carried out as six bf16
- * ones.  Profiling level 2 launches and times every product by itself all the same. */
+ * ones.  Profiling level 2 launches and times every product, or group of matrices with a workgroup each, by itself
+ * all the same. */
 int mona_plan_info(mona_state* st, int32_t ns_steps, int64_t* launches_out,
                    double* ns_flops_executed_out, double* elementwise_bytes_out);
 

@@ -515,6 +515,7 @@ void build_layout(const mona_matrix* mats, int count, const mona_options& opt, b
   L.total = off;
 }
 
+constexpr int kWholeMatrices = 4;      // kind of a record that is no product (OpKind)
 struct LaunchRecord {
   int kind, group, iter, tile;
   double flops;
@@ -908,7 +909,9 @@ float update_scale(const Group& g, const mona_hparams& hp) {
   return hp.lr * hp.gamma_coeff * sqrtf((float)std::max(g.m, g.n));
 }
 
-// `one_by_one`: every product as a launch of its own, on the tiles and with the split of K it has in the ordinary step.
+// `one_by_one`: every product as a launch of its own, on the tiles and with the split of K it has in the ordinary step, and every
+// group whose matrices get a workgroup each as a launch of its own: that kernel has no products to take apart, and products in
+// its place would sum and round in other places.
 void build_plan(const mona_state* st, const mona_hparams& hp, Plan& plan, bool one_by_one) {
   const Layout& L = st->L;
   const size_t ngroups = L.groups.size();
@@ -976,23 +979,27 @@ void build_plan(const mona_state* st, const mona_hparams& hp, Plan& plan, bool o
   }
   for (const Unit& u : L.units) {
     std::vector<Launch>& lane = plan.lanes[u.lane];
-    if (u.matrix && hp.ns_steps > 0 && !one_by_one) {
-      MatrixBatch b;
-      memset(&b, 0, sizeof b);
-      b.step = plan.step;
-      b.steps = hp.ns_steps;
-      b.store_o = (hp.flags & MONA_FLAG_KEEP_O) ? 1 : 0;
-      int matrices = 0;
-      for (int gi : u.groups) {
-        matrices += plan.desc[gi].count;
-        b.group[b.n] = plan.desc[gi];
-        b.end[b.n++] = matrices;
+    if (u.matrix && hp.ns_steps > 0) {
+      const size_t most = one_by_one ? 1 : u.groups.size();
+      for (size_t first = 0; first < u.groups.size(); first += most) {
+        MatrixBatch b;
+        memset(&b, 0, sizeof b);
+        b.step = plan.step;
+        b.steps = hp.ns_steps;
+        b.store_o = (hp.flags & MONA_FLAG_KEEP_O) ? 1 : 0;
+        const std::vector<int> groups(u.groups.begin() + first, u.groups.begin() + first + most);
+        int matrices = 0;
+        for (int gi : groups) {
+          matrices += plan.desc[gi].count;
+          b.group[b.n] = plan.desc[gi];
+          b.end[b.n++] = matrices;
+        }
+        Launch l;
+        l.matrix = (int)plan.matrices.size();
+        plan.matrices.push_back(b);
+        plan.matrix_groups.push_back(groups);
+        lane.push_back(l);
       }
-      Launch l;
-      l.matrix = (int)plan.matrices.size();
-      plan.matrices.push_back(b);
-      plan.matrix_groups.push_back(u.groups);
-      lane.push_back(l);
     } else if (u.merged) {
       for (size_t pos = 0;; ++pos) {
         Launch l;
@@ -1395,7 +1402,19 @@ int enqueue_step(mona_state* st, const mona_hparams* hp, hipStream_t s) {
       const Launch& l = queue[at[lane]++];
       hipStream_t gs = lane == 0 || !fork ? s : st->side[lane - 1];
       if (l.matrix >= 0) {
+        if (!each) {
+          STEP_TRY(launch_ns_matrix(plan.matrices[l.matrix], gs));
+          continue;
+        }
+        LaunchRecord rec;                        // (one group)
+        if (!get_event_pair(st, &rec.e0, &rec.e1)) return bail(hipErrorOutOfMemory, "hipEventCreate");
+        STEP_TRY(hipEventRecord(rec.e0, gs));
         STEP_TRY(launch_ns_matrix(plan.matrices[l.matrix], gs));
+        STEP_TRY(hipEventRecord(rec.e1, gs));
+        rec.kind = kWholeMatrices; rec.group = plan.matrix_groups[l.matrix][0]; rec.iter = 0;
+        rec.tile = L.groups[rec.group].p_pad * 1000 + 128;
+        rec.flops = launch_flops(plan, l);
+        st->records.push_back(rec);
         continue;
       }
       if (l.chain >= 0) {

@@ -96,3 +96,27 @@ def test_the_bits_of_the_large_tile_kernel(shape, param):
     want, got = run(beside, 0)[1], run([shape] * COUNT, 0)[1]
     for i in range(few):
         assert torch.equal(want[i], got[i]), i
+
+
+@pytest.mark.parametrize("shapes", [[(768, 256)] * 128 + [(256, 768)] * 128 + [(100, 300)] * 80,
+                                    [(256, 512)] * COUNT + [(2048, 2048)] * 8 + [(100, 100)] * 200 + [(30, 500)] * 3])
+def test_groups_timed_one_by_one_give_the_same_bits(shapes):
+    """Profiling level 2 launches and times the groups of the kernel one by one, and the step's results stay what they are."""
+    print(f"[case] {len(shapes)} matrices", flush=True)
+    ends = []
+    for level in (0, 2):
+        weights = [wl.draw_weight(s, 300 + i, torch.bfloat16, "cuda:0") for i, s in enumerate(shapes)]
+        opt = B.MonaOptimizer(weights)
+        opt.set_profiling(level)
+        for k in range(2):
+            opt.step([wl.GradientStream(s, 400 + 1000 * k + i, "cuda:0").next() for i, s in enumerate(shapes)], wl.HParams())
+        torch.cuda.synchronize()
+        ends.append(weights)
+    records = opt.last_step_launches()
+    whole = [(r["m"], r["n"]) for r in records if r["kind"] == 4]
+    assert len(whole) == len(set(whole)) and set(whole) >= {s for s in shapes if max(s) < 800 and min(s) > 64}
+    assert all(r["ms"] > 0 and r["flops"] > 0 for r in records)
+    flops = opt.plan_info(5)["ns_flops_issued"]
+    assert abs(sum(r["flops"] for r in records) - flops) <= 1e-9 * flops
+    for i, (x, y) in enumerate(zip(*ends)):
+        assert torch.equal(x, y), i
