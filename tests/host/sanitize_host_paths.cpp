@@ -1,8 +1,10 @@
 // Host-only exercise of libmona's boundary for a sanitizer build (AddressSanitizer + UndefinedBehaviorSanitizer
-// on the host code; no GPU needed): every entry point that can run without a device -- the arena layout over
-// random lists of matrices, and the argument checks of the others -- is called many times.
+// on the host code; no GPU needed, see fake_hip.h): the arena layout over random lists of matrices, the argument checks
+// of the entry points, and steps of states whose plan is kept, renewed and rebuilt as hyper-parameters, flags, iterations and the
+// profiling level change from step to step.
 // Build and run: tests/host/run_sanitizers.sh
 #include "../../include/mona.h"
+#include "fake_hip.h"
 
 #include <cstdio>
 #include <cstdlib>
@@ -16,8 +18,71 @@ static int failures = 0;
     if (!(cond)) { std::printf("FAILED %s:%d: %s\n", __FILE__, __LINE__, #cond); ++failures; } \
   } while (0)
 
+// A state of random matrices through steps of every kind.
+static void steps(std::mt19937& rng) {
+  std::vector<mona_matrix> mats;
+  const int groups = 1 + (int)(rng() % 12);
+  for (int g = 0; g < groups; ++g) {
+    auto side = [&] { return rng() % 2 ? 1 + (int)(rng() % 300) : 64 * (1 + (int)(rng() % (rng() % 8 ? 8 : 40))); };
+    mona_matrix q;
+    std::memset(&q, 0, sizeof q);
+    q.m = side(); q.n = side(); q.w_dtype = rng() % 2; q.g_dtype = rng() % 2;
+    q.w = reinterpret_cast<void*>((uintptr_t)16); q.g = q.w;
+    mats.insert(mats.end(), 1 + rng() % (rng() % 2 ? 3 : 130), q);
+  }
+  const int n = (int)mats.size();
+  mona_options o;
+  std::memset(&o, 0, sizeof o);
+  o.ns_precision = rng() % 4 == 0; o.state_dtype = rng() % 2; o.ns_schedule = rng() % 4;
+  o.overlap = rng() % 2; o.max_streams = rng() % 5;
+  size_t bytes = 0;
+  EXPECT(mona_state_size(mats.data(), n, &o, &bytes) == MONA_OK);
+  char* arena = static_cast<char*>(std::aligned_alloc(256, (bytes + 255) / 256 * 256));
+  char stream;
+  mona_state* st = nullptr;
+  EXPECT(mona_init_state(mats.data(), n, &o, arena, bytes, &stream, &st) == MONA_OK);
+  mona_hparams hp;
+  std::memset(&hp, 0, sizeof hp);
+  hp.lr = 0.1f; hp.momentum = 0.9f; hp.beta_a = 0.9f; hp.ns_steps = 5; hp.ns_a = hp.ns_b = hp.ns_c = hp.gamma_coeff = 1.0f;
+  for (int k = 0; k < 10; ++k) {
+    if (rng() % 2) hp.lr *= 0.9f;
+    if (rng() % 3 == 0) hp.ns_steps = (int)(rng() % 70) / (rng() % 4 ? 10 : 1);
+    if (rng() % 3 == 0) hp.flags = rng() % 8;
+    if (rng() % 3 == 0) EXPECT(mona_set_profiling(st, rng() % 3) == MONA_OK);
+    int64_t launches = 0;
+    double flops = 0.0;
+    EXPECT(mona_plan_info(st, hp.ns_steps, &launches, &flops, nullptr) == MONA_OK);
+    EXPECT(mona_step(st, mats.data(), n, &hp, rng() % 4 ? &stream : nullptr) == MONA_OK);
+    int32_t records = 0;
+    if (mona_last_step_launches(st, nullptr, 0, &records) == MONA_OK) {
+      std::vector<mona_launch_time> rec(records);
+      EXPECT(mona_last_step_launches(st, rec.data(), records, &records) == MONA_OK);
+    }
+    if (rng() % 8 == 0) {            // a launch that fails half way, and the state after it
+      fake::fail = "norm_finalize_kernel";
+      EXPECT(mona_step(st, mats.data(), n, &hp, &stream) == MONA_EHIP);
+      EXPECT(mona_step(st, mats.data(), n, &hp, &stream) == MONA_EHIP);
+      size_t saved = 0;
+      EXPECT(mona_state_export_size(st, &saved) == MONA_OK);
+      std::vector<char> block(saved);
+      EXPECT(mona_state_import(st, block.data(), saved, k, &stream) == MONA_OK);
+    }
+  }
+  EXPECT(mona_free_state(st) == MONA_OK);
+  std::free(arena);
+  o.accel_form = 0;
+  for (int k = 0; k < 3; ++k) {
+    void* const any = reinterpret_cast<void*>((uintptr_t)256);
+    const int rc = mona_step_noalloc(&mats[rng() % n], &o, any, any, any, &hp, k, &stream);
+    EXPECT(rc == MONA_OK || rc == MONA_ENOMEM);
+  }
+}
+
 int main() {
+  fake::capability_major = 9;
+  fake::capability_minor = 5;
   std::mt19937 rng(12345);
+  for (int round = 0; round < 60; ++round) steps(rng);
   auto dim = [&](int hi) { return 1 + (int)(rng() % hi); };
   for (int round = 0; round < 300; ++round) {
     const int count = 1 + (int)(rng() % 40);

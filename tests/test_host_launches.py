@@ -23,3 +23,9 @@ def test_what_the_host_enqueues(program, tmp_path):
     out = subprocess.run([exe], capture_output=True, text=True, timeout=60)
     print(out.stdout)
     assert out.returncode == 0, out.stdout + out.stderr
+
+
+@pytest.mark.skipif(not os.path.exists("/opt/rocm/bin/hipcc"), reason="no hipcc")
+def test_host_code_under_sanitizers(tmp_path):
+    out = subprocess.run(["bash", os.path.join(HERE, "run_sanitizers.sh"), str(tmp_path)], capture_output=True, text=True, timeout=300)
+    assert out.returncode == 0, out.stdout[-3000:] + out.stderr[-3000:]
