@@ -90,6 +90,7 @@ struct Unit {
 
 struct Layout {
   int count = 0;
+  bool gfx950 = false;       // the device's architecture: chains and ns_matrix_kernel are planned for this one only
   int ssize = 4;             // bytes per element of the stored G_{k-1}, A (or C)
   bool one_buffer = false;   // no G_{k-1}; acc_off holds C
   bool caller_slot = false;  // G_{k-1} is kept by the caller (streaming variant)
@@ -222,7 +223,7 @@ long long launch_tiles(const Group& g, int kind, int tile, int count) {
 // 50 x 256 x 256 170 / 147, 84 x 256 x 256 213 / 162, 70 x 130 x 200 148 / 134, 86 x 256 x 768 474 / 376, but 36 x 256 x 256 140 / 140, 52 x 160 x 140
 // 126 / 148, 50 x 140 x 380 160 / 205.
 bool by_matrix(const Group& g, bool alone) {
-  if (g.f32 || g.fused || (g.p_pad != 128 && g.p_pad != 256) || !device_is_gfx950()) return false;
+  if (g.f32 || g.fused || (g.p_pad != 128 && g.p_pad != 256)) return false;
   const double count = (double)g.members.size(), panels = std::max(g.rows_pad, g.cols_pad) / 128;
   const double units = count * panels, rounds = std::ceil(count / (double)kChipTiles);
   if (g.p_pad == 128) {    // (four panels stay in LDS)
@@ -295,11 +296,11 @@ void plan_lanes(Layout& L, const mona_options& opt) {
     work_of[gi] = per * (double)g.members.size() * (g.f32 ? 16.0 : 1.0);
   }
   // A workgroup for each matrix: not where a chain that some groups need anyway takes all of them (the others cost it little).
-  const bool only = std::all_of(L.groups.begin(), L.groups.end(), [](const Group& g) { return by_matrix(g, true); });
+  const bool only = L.gfx950 && std::all_of(L.groups.begin(), L.groups.end(), [](const Group& g) { return by_matrix(g, true); });
   L.small_enough = all_in_a_chain(L);
   std::vector<int> matrices;
   for (int gi = 0; gi < ngroups; ++gi) {
-    if (only || (!L.small_enough && by_matrix(L.groups[gi], false))) { matrices.push_back(gi); continue; }
+    if (only || (L.gfx950 && !L.small_enough && by_matrix(L.groups[gi], false))) { matrices.push_back(gi); continue; }
     // Beside a group that keeps the caller's stream, only groups too small to fill the chip by
     // themselves go to the side streams (their launch latency hides behind the large group); a
     // mid-sized group there gained 0.3 % at most (4 squares of 4096 beside 384 experts), and in a row
@@ -392,7 +393,8 @@ void plan_lanes(Layout& L, const mona_options& opt) {
   }
 }
 
-void build_layout(const mona_matrix* mats, int count, const mona_options& opt, bool external_state, Layout& L) {
+// `launches`: also what the products are launched as, for which the device is asked (nothing of it changes the sizes).
+void build_layout(const mona_matrix* mats, int count, const mona_options& opt, bool external_state, bool launches, Layout& L) {
   L.count = count;
   L.external_state = external_state;
   L.ssize = opt.state_dtype == MONA_BF16 ? 2 : 4;
@@ -476,7 +478,10 @@ void build_layout(const mona_matrix* mats, int count, const mona_options& opt, b
   }
   L.work_bytes = off - L.work_begin;
 
-  plan_lanes(L, opt);
+  if (launches) {
+    L.gfx950 = device_is_gfx950();
+    plan_lanes(L, opt);
+  }
 
   // elementwise work table
   L.first_block.assign(count, 0);
@@ -816,7 +821,7 @@ int chain_tile(Plan& plan, const std::vector<int>& groups, size_t pos) {
 }
 // Tasks of the chain, 0 if there is none.
 int chainable(const Layout& L, Plan& plan, const std::vector<int>& groups) {
-  if (!device_is_gfx950() || groups.size() > (size_t)kMaxMerged) return 0;
+  if (!L.gfx950 || groups.size() > (size_t)kMaxMerged) return 0;
   size_t ops = 0, positions = 0;
   for (int gi : groups) {
     const Group& g = L.groups[gi];
@@ -1124,7 +1129,7 @@ int mona_state_size(const mona_matrix* mats, int32_t count, const mona_options* 
   rc = check_opts(opts, &o);
   if (rc) return rc;
   Layout L;
-  build_layout(mats, count, o, false, L);
+  build_layout(mats, count, o, false, false, L);
   *bytes_out = L.total;
   return MONA_OK;
 }
@@ -1142,7 +1147,7 @@ int mona_init_state(const mona_matrix* mats, int32_t count, const mona_options* 
   if ((uintptr_t)arena % kAlign) return fail(MONA_EINVAL, "arena must be 256-byte aligned");
   mona_state* st = new (std::nothrow) mona_state();
   if (!st) return fail(MONA_ENOMEM, "host allocation failed");
-  build_layout(mats, count, o, false, st->L);
+  build_layout(mats, count, o, false, true, st->L);
   const Layout& L = st->L;
   if (arena_bytes < L.total) {
     const size_t need = L.total;
@@ -1601,7 +1606,7 @@ int mona_step_noalloc(const mona_matrix* mat, const mona_options* opts, void* g_
     return fail(MONA_EINVAL, "g_prev, acc and mom must be 16-byte aligned");
   // the same plan a one-matrix mona_init_state would build, laid out over the scratch array
   mona_state st;
-  build_layout(mat, 1, o, true, st.L);
+  build_layout(mat, 1, o, true, true, st.L);
   const Layout& L = st.L;
   if (L.total > kScratchBytes)
     return fail(MONA_ENOMEM, "a %d x %d matrix needs %zu bytes of workspace; the static scratch of mona_step_noalloc "

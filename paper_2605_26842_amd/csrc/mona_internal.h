@@ -255,7 +255,7 @@ hipError_t launch_ns_matrix(const MatrixBatch& b, hipStream_t s);
 // a whole chain of products on small tiles; `wgs` workgroups
 hipError_t launch_ns_chain(const ChainArgs& c, int wgs, hipStream_t s);
 int device_cu_count();
-bool device_is_gfx950();
+bool device_is_gfx950();   // the current device
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 
 }  // namespace mona

@@ -26,6 +26,8 @@
 //     chunks XORed so that the rows one read touches lie on different banks.
 #include "ns_small_tile.h"
 
+#include <atomic>
+
 namespace mona {
 
 namespace {
@@ -590,13 +592,21 @@ hipError_t launch_ns_small(GemmBatch& b, bool f32, bool wide, hipStream_t s) {
 // The chain kernel stands on device-scope accesses that are coherent between the dies by themselves, ns_matrix_kernel on 160 KB of
 // LDS, as gfx950 has them.
 bool device_is_gfx950() {
-  static const bool yes = []() {
-    int dev = 0, major = 0, minor = 0;
-    return hipGetDevice(&dev) == hipSuccess &&
-           hipDeviceGetAttribute(&major, hipDeviceAttributeComputeCapabilityMajor, dev) == hipSuccess &&
-           hipDeviceGetAttribute(&minor, hipDeviceAttributeComputeCapabilityMinor, dev) == hipSuccess && major == 9 && minor == 5;
-  }();
-  return yes;
+  // by device: 0 not asked, 1 no, 2 yes (a query that failed says nothing of the next one)
+  static std::atomic<int> known[64];
+  int dev = -1, major = 0, minor = 0;
+  if (hipGetDevice(&dev) == hipSuccess && dev >= 0) {
+    const bool kept = dev < 64;
+    if (const int k = kept ? known[dev].load(std::memory_order_relaxed) : 0) return k == 2;
+    if (hipDeviceGetAttribute(&major, hipDeviceAttributeComputeCapabilityMajor, dev) == hipSuccess &&
+        hipDeviceGetAttribute(&minor, hipDeviceAttributeComputeCapabilityMinor, dev) == hipSuccess) {
+      const bool yes = major == 9 && minor == 5;
+      if (kept) known[dev].store(yes ? 2 : 1, std::memory_order_relaxed);
+      return yes;
+    }
+  }
+  (void)hipGetLastError();
+  return false;
 }
 
 hipError_t launch_ns_chain(const ChainArgs& c, int wgs, hipStream_t s) {

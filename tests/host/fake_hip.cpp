@@ -11,6 +11,7 @@ std::function<void(const Launch&)> on_launch;
 bool capturing = false;
 std::string fail;
 int capability_major = 256, capability_minor = 256;
+int device = 0, queries = 0;
 namespace {
 std::map<const void*, std::string> names;
 std::vector<std::function<void()>> recorded;
@@ -104,8 +105,10 @@ hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 hipError_t hipHostMalloc(void** p, size_t n, unsigned) { *p = std::malloc(n); return hipSuccess; }
 hipError_t hipHostFree(void* p) { std::free(p); return hipSuccess; }
-hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipGetDevice(int* d) { ++queries; *d = device; return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
+  ++queries;
+  if (failing("attribute")) return last = hipErrorNotInitialized;
   *v = a == hipDeviceAttributeComputeCapabilityMajor ? capability_major
        : a == hipDeviceAttributeComputeCapabilityMinor ? capability_minor : 256;
   return hipSuccess;

@@ -16,8 +16,10 @@ struct Launch {
 };
 extern std::function<void(const Launch&)> on_launch;   // called when a launch is carried out (not when it is recorded)
 extern bool capturing;                                 // all streams but the null stream
-extern std::string fail;                               // what to fail once: "copy" or a piece of a kernel's name
+extern std::string fail;                               // what to fail once: "copy", "attribute" or a piece of a kernel's name
 extern int capability_major, capability_minor;         // of the device (those of none that exists, unless a test says so)
+extern int device;                                     // the current device
+extern int queries;                                    // what was asked of the devices so far
 void replay();                                         // carries out what was recorded since capturing was set
 void clear_recorded();
 }  // namespace fake

@@ -14,7 +14,8 @@ CLANG = "/opt/rocm/lib/llvm/bin/clang++"
 pytestmark = pytest.mark.skipif(not all(map(os.path.exists, OBJECTS + [CLANG])), reason="library objects not built")
 
 
-@pytest.mark.parametrize("program", ["pointer_tables", "launch_plan", "chain_plan", "executed_flops", "matrix_plan"])
+@pytest.mark.parametrize("program", ["pointer_tables", "launch_plan", "chain_plan", "executed_flops", "matrix_plan",
+                                     "device_queries"])
 def test_what_the_host_enqueues(program, tmp_path):
     exe = str(tmp_path / program)
     subprocess.run([CLANG, "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
