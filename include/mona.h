@@ -265,6 +265,10 @@ int mona_state_step_count(mona_state* st, int64_t* k_out);
 /* bit 2 (informative): ||M||_F lay outside [2^-40, 2^40], so the working copy of M was rescaled by a power
  * of two before the products (the result is unaffected: Sec. 3.2's X_0 = M / ||M||_F is scale-free). */
 #define MONA_STATUS_RESCALED 0x4u
+/* bit 3: the launch that carries all products of this matrix waited for a part of them for about a second and ended without it;
+ * W may be updated in part or not at all.  Steps on one state that overlap in time, against the rule of mona_step, can
+ * bring this about. */
+#define MONA_STATUS_INCOMPLETE 0x8u
 int mona_state_status(mona_state* st, uint32_t* host_out, int32_t count, void* stream);
 
 /* Elapsed GPU time of the phases of the last mona_step, from HIP events recorded on the

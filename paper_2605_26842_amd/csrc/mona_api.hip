@@ -18,6 +18,7 @@
 #include <vector>
 
 using namespace mona;
+static_assert(kStatusIncomplete == MONA_STATUS_INCOMPLETE, "the same bit");
 
 namespace {
 thread_local std::string g_err;
@@ -607,6 +608,7 @@ struct mona_state {
   size_t pool_used = 0;
 
   struct Plan* plan = nullptr;     // of the last step (see plan_for)
+  int chain_patience = kPatience;  // polls of one wait of a chain
   mona_state() = default;
   mona_state(const mona_state&) = delete;
   ~mona_state() { delete plan; }
@@ -862,6 +864,7 @@ Launch build_chain(const mona_state* st, Plan& plan, const std::vector<int>& gro
   ChainArgs c;
   memset(&c, 0, sizeof c);
   c.step = plan.step;
+  c.patience = st->chain_patience;
   c.roll = reinterpret_cast<ChainRoll*>(area) + plan.chains.size();
   c.flags = reinterpret_cast<uint32_t*>(area + kMaxChains * sizeof(ChainRoll)) + plan.chain_tasks;
   struct Before { int32_t first = 0, per_mat = 0; };
@@ -1745,6 +1748,16 @@ int mona_state_status(mona_state* st, uint32_t* host_out, int32_t count, void* s
   HIP_TRY(hipMemcpyAsync(tmp.data(), st->arena + st->L.scales_off, sizeof(MatScale) * count, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   for (int i = 0; i < count; ++i) host_out[i] = tmp[i].status;
+  return MONA_OK;
+}
+
+// Not part of the ABI: how often the chains of a state's steps poll in one wait, for tests of what happens when a wait does
+// not end (with 0 none does).
+int mona_internal_chain_patience(mona_state* st, int32_t polls) {
+  if (!st || polls < 0) return fail(MONA_EINVAL, "state is NULL or polls is negative");
+  st->chain_patience = polls;
+  delete st->plan;                 // (it holds the figure)
+  st->plan = nullptr;
   return MONA_OK;
 }
 

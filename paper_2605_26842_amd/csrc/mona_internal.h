@@ -184,6 +184,8 @@ struct ChainOp {
   uint32_t code;           // op code; the group in the bits from OPF_GROUP on
 };
 constexpr uint32_t OPF_GROUP = 24;
+constexpr uint32_t kStatusIncomplete = 8u;           // MONA_STATUS_INCOMPLETE
+constexpr int kPatience = 1 << 20;                   // polls of one wait in a chain: about a second
 // Shared by the workgroups of a chain launch; zero when it starts.
 struct ChainRoll {
   uint32_t reported;       // workgroups that have reported, and whether the roll is closed
@@ -196,6 +198,7 @@ struct ChainArgs {
   ChainRoll* roll;
   uint32_t* flags;         // one for each task; zero when the launch starts
   int32_t ops, tasks;
+  int32_t patience;        // polls of one wait
   GroupDesc group[kMaxMerged];
   ChainOp op[kMaxChainOps];
 };

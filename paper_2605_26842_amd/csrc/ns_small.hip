@@ -490,9 +490,6 @@ __global__ __launch_bounds__(WIDE ? 512 : 256) void ns_small_kernel(const GemmBa
 // operation for every task, and a counter of finished tiles instead of flags: 96, 189 and 133.
 constexpr uint32_t kRollClosed = 0x80000000u;
 constexpr int kRollPolls = 64;      // about 50 us
-// A wait lasts microseconds.  Two steps on one workspace at the same time (which the entry points forbid) could clear each
-// other's flags: a workgroup that has polled for about a second goes on without, so that every launch ends.
-constexpr int kPatience = 1 << 20;
 
 __device__ __forceinline__ uint32_t device_load(const uint32_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -501,12 +498,18 @@ __device__ __forceinline__ void device_store(uint32_t* p, uint32_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// A wait lasts microseconds.  Two steps on one workspace at the same time (which the entry points forbid) could clear each
+// other's flags: a workgroup that has polled c.patience times in one wait marks the matrices of the chain and leaves, and so
+// do, one after the other, those that wait for its tiles, so that every launch ends and no parameter is formed from an incomplete
+// product.  (Looking whether wavefront 0 has given up costs every task an LDS read behind the barrier, 1 us of a step of 70 to
+// 114; hidden behind the first loads, or looked at in front of the stores, it costs 2: registers.)
 __global__ __launch_bounds__(512) void ns_chain_kernel(const ChainArgs c) {
   constexpr int LB = Geo<bf16_t, 64, true>::LDS, LF = Geo<float, 64, true>::LDS;
   __shared__ __attribute__((aligned(256))) char lds[LB > LF ? LB : LF];
-  __shared__ uint32_t shared;
+  __shared__ uint32_t shared, gave_up;
   ChainRoll* const roll = c.roll;
   if (threadIdx.x == 0) {
+    gave_up = 0u;
     const uint32_t n = __hip_atomic_fetch_add(&roll->reported, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (n == 0) {
       // the first to report closes the roll
@@ -522,7 +525,8 @@ __global__ __launch_bounds__(512) void ns_chain_kernel(const ChainArgs c) {
   const uint32_t number = __builtin_amdgcn_readfirstlane(shared);
   if (number & kRollClosed) return;
   __syncthreads();
-  int step = 0, patience = kPatience;
+  int step = 0, polls = c.patience;
+  asm volatile("" : "+s"(polls));    // (a register: the loads of a task's arguments would wait for it)
   for (int i = 0, first = 0, task = (int)number; task < c.tasks; task += step) {
     while (task >= c.op[i].end) first = c.op[i++].end;
     const uint32_t code = c.op[i].code;
@@ -537,10 +541,13 @@ __global__ __launch_bounds__(512) void ns_chain_kernel(const ChainArgs c) {
     if (threadIdx.x < 64) {
       for (int at = 0; at < per_mat; at += 64) {
         const int k = at + (int)threadIdx.x;
+        int patience = polls;
         while (patience > 0 && !__all(k >= per_mat || device_load(before + k) != 0u)) { --patience; __builtin_amdgcn_s_sleep(1); }
+        if (patience <= 0) { gave_up = 1u; break; }
       }
     }
     __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(gave_up) != 0u) break;
     // opaque: what the bodies below derive from the thread's number is not to be hoisted out of the loop, where twelve of
     // them would share the registers
     int tid = threadIdx.x;
@@ -559,13 +566,20 @@ __global__ __launch_bounds__(512) void ns_chain_kernel(const ChainArgs c) {
     if (step == 0) {
       if (threadIdx.x == 0) {
         uint32_t n = 0;
-        while (patience > 0 && (n = device_load(&roll->workgroups)) == 0u) { --patience; __builtin_amdgcn_s_sleep(1); }
-        shared = n != 0u ? n : gridDim.x;
+        for (int patience = polls; patience > 0 && (n = device_load(&roll->workgroups)) == 0u; --patience) __builtin_amdgcn_s_sleep(1);
+        shared = n;
+        if (n == 0u) gave_up = 1u;
       }
       __syncthreads();
       step = (int)__builtin_amdgcn_readfirstlane(shared);
+      if (step == 0) break;
     }
   }
+  if (gave_up != 0u)
+    for (int j = 0; j < kMaxMerged; ++j)
+      for (int i = threadIdx.x; i < c.group[j].count; i += 512)
+        __hip_atomic_fetch_or(const_cast<uint32_t*>(&c.step.scales[c.group[j].members[i]].status), kStatusIncomplete,
+                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 }  // namespace

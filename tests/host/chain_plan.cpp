@@ -108,6 +108,7 @@ static void run(const Shapes& shapes, int precision, int streams, int steps, int
     } else if (l.name.find("ns_chain_kernel") != std::string::npos) {
       const ChainArgs& c = *static_cast<const ChainArgs*>(l.args[0]);
       EXPECT(l.block == 512 && l.grid >= 1 && l.grid <= 256);
+      EXPECT(c.patience == kPatience);
       chains.push_back(c);
       for (int i = 0; i < c.ops; ++i) {
         GemmArgs a;

@@ -1,5 +1,7 @@
 """Chains of small products as one launch (ns_chain_kernel) at the sizes where they can go wrong: against the float64 oracle,
 against the same products launched one by one, and replayed from a HIP graph."""
+import ctypes
+
 import pytest
 import torch
 
@@ -75,3 +77,29 @@ def test_chains_replayed_from_a_graph():
         torch.cuda.synchronize()
         for i in range(len(shapes)):
             assert torch.equal(eager[i], graph_w[i]), (k, i)
+
+
+def test_a_wait_that_does_not_end():
+    """Chains whose waits may not poll at all: the launch ends, no parameter is touched, the status says so; the next step is whole."""
+    shapes, precision, _ = CASES["nine groups"]
+    print("[case] no polls", flush=True)
+    dev = "cuda:0"
+    weights = [wl.draw_weight(s, 300 + i, torch.float32, dev) for i, s in enumerate(shapes)]
+    plain = [w.clone() for w in weights]
+    opt, ref = B.MonaOptimizer(weights), B.MonaOptimizer(plain)
+    grads = [[wl.GradientStream(s, 500 + 20 * k + i, dev).next() for i, s in enumerate(shapes)] for k in range(2)]
+    before = [w.clone() for w in weights]
+    assert opt.lib.mona_internal_chain_patience(ctypes.c_void_p(opt.state), 0) == B.MONA_OK
+    opt.step(grads[0], wl.HParams())
+    assert all(s & B.MONA_STATUS_INCOMPLETE for s in opt.status())
+    for i in range(len(shapes)):
+        assert torch.equal(weights[i], before[i]), i
+    assert opt.lib.mona_internal_chain_patience(ctypes.c_void_p(opt.state), 1 << 20) == B.MONA_OK
+    ref.step(grads[0], wl.HParams())
+    for w, p in zip(weights, plain):
+        w.copy_(p)                   # (the state arrays are those of a whole step)
+    opt.step(grads[1], wl.HParams())
+    ref.step(grads[1], wl.HParams())
+    assert opt.status() == [0] * len(shapes)
+    for i in range(len(shapes)):
+        assert torch.equal(weights[i], plain[i]), i
