@@ -608,7 +608,7 @@ struct mona_state {
   size_t pool_used = 0;
 
   struct Plan* plan = nullptr;     // of the last step (see plan_for)
-  int chain_patience = kPatience;  // polls of one wait of a chain
+  int chain_roll_polls = kRollPolls, chain_patience = kPatience;   // (see ChainArgs)
   mona_state() = default;
   mona_state(const mona_state&) = delete;
   ~mona_state() { delete plan; }
@@ -864,6 +864,7 @@ Launch build_chain(const mona_state* st, Plan& plan, const std::vector<int>& gro
   ChainArgs c;
   memset(&c, 0, sizeof c);
   c.step = plan.step;
+  c.roll_polls = st->chain_roll_polls;
   c.patience = st->chain_patience;
   c.roll = reinterpret_cast<ChainRoll*>(area) + plan.chains.size();
   c.flags = reinterpret_cast<uint32_t*>(area + kMaxChains * sizeof(ChainRoll)) + plan.chain_tasks;
@@ -1751,12 +1752,13 @@ int mona_state_status(mona_state* st, uint32_t* host_out, int32_t count, void* s
   return MONA_OK;
 }
 
-// Not part of the ABI: how often the chains of a state's steps poll in one wait, for tests of what happens when a wait does
-// not end (with 0 none does).
-int mona_internal_chain_patience(mona_state* st, int32_t polls) {
-  if (!st || polls < 0) return fail(MONA_EINVAL, "state is NULL or polls is negative");
-  st->chain_patience = polls;
-  delete st->plan;                 // (it holds the figure)
+// Not part of the ABI: how often the chains of a state's steps poll the roll before they close it, and in one wait, for tests of
+// chains that begin without some of their workgroups (with 0 most do) and of waits that do not end (with 0 none does).
+int mona_internal_chain_polls(mona_state* st, int32_t roll, int32_t wait) {
+  if (!st || roll < 0 || wait < 0) return fail(MONA_EINVAL, "state is NULL or a figure is negative");
+  st->chain_roll_polls = roll;
+  st->chain_patience = wait;
+  delete st->plan;                 // (it holds the figures)
   st->plan = nullptr;
   return MONA_OK;
 }

@@ -185,19 +185,22 @@ struct ChainOp {
 };
 constexpr uint32_t OPF_GROUP = 24;
 constexpr uint32_t kStatusIncomplete = 8u;           // MONA_STATUS_INCOMPLETE
+constexpr int kRollPolls = 64;                       // about 50 us
 constexpr int kPatience = 1 << 20;                   // polls of one wait in a chain: about a second
 // Shared by the workgroups of a chain launch; zero when it starts.
 struct ChainRoll {
   uint32_t reported;       // workgroups that have reported, and whether the roll is closed
   uint32_t pad[31];
-  uint32_t workgroups;     // those that take part, once it is closed
-  uint32_t pad2[31];
+  uint32_t workgroups;     // those that had reported, once it is closed
+  uint32_t drawn;          // tasks drawn from then on, where it was closed without some
+  uint32_t pad2[30];
 };
 struct ChainArgs {
   StepDesc step;
   ChainRoll* roll;
   uint32_t* flags;         // one for each task; zero when the launch starts
   int32_t ops, tasks;
+  int32_t roll_polls;      // polls of the roll before it is closed without some
   int32_t patience;        // polls of one wait
   GroupDesc group[kMaxMerged];
   ChainOp op[kMaxChainOps];

@@ -474,10 +474,15 @@ __global__ __launch_bounds__(WIDE ? 512 : 256) void ns_small_kernel(const GemmBa
 // product before (ChainArgs::flags, one word a task), computes the tile and raises the task's flag.
 //   * No workgroup waits for one that does not run.  W is not the size of the grid but the number of workgroups that have
 //     reported when the first of them closes the roll (all of the grid, unless the chip is busy with something else for
-//     kRollPolls polls); whoever comes later leaves at once.  Tasks wait for lower numbers only, and a workgroup takes its
-//     own in order, so the lowest unfinished task always has all it needs.  (Numbers go by the order of reporting: a
+//     c.roll_polls polls).  Tasks wait for lower numbers only, and a workgroup takes its own in order, so the lowest unfinished
+//     task always has all it needs.  (Numbers go by the order of reporting: a
 //     workgroup begins its first task before the roll is closed.  Waiting for that, so as to give every die
 //     neighbouring tiles by the workgroup's index, costs 6 to 7 us a step and gains at most 4 where the tiles are many.)
+//   * Where the roll was closed without some, the tasks behind the first W are drawn from a counter instead, in order, so that
+//     whoever comes later takes its share from then on: a chain that began on the few CUs another stream's kernels had left
+//     would otherwise keep to them when the chip is free again.  Measured, us per step beside steps of 64 x 2048 x 1024 on
+//     another stream, launches / chain without latecomers / with: 256 x 512 650 / 430 / 265, 512 x 1408 870 / 1400 to 4800 / 310, nine
+//     ragged matrices 865 / 480 to 1100 / 270, 4 x 300 x 900 1060 / 1100 to 4400 / 355; alone the code costs nine ragged matrices 1 us.
 //   * The dies have an L2 each.  What one workgroup writes and another reads goes through device-scope (sc1) accesses, which
 //     are coherent by themselves; a flag follows when the stores have completed (vmcnt 0 in every wavefront, then the
 //     barrier).  Measured from the last store of a product to the first operands of the next: about 2 us, against 4 to 6 us
@@ -489,7 +494,6 @@ __global__ __launch_bounds__(WIDE ? 512 : 256) void ns_small_kernel(const GemmBa
 // matrices in both precisions 189 -> 83 (which had waited for the host).  Tickets instead of fixed numbers, drawn by an atomic
 // operation for every task, and a counter of finished tiles instead of flags: 96, 189 and 133.
 constexpr uint32_t kRollClosed = 0x80000000u;
-constexpr int kRollPolls = 64;      // about 50 us
 
 __device__ __forceinline__ uint32_t device_load(const uint32_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -502,11 +506,15 @@ __device__ __forceinline__ void device_store(uint32_t* p, uint32_t v) {
 // other's flags: a workgroup that has polled c.patience times in one wait marks the matrices of the chain and leaves, and so
 // do, one after the other, those that wait for its tiles, so that every launch ends and no parameter is formed from an incomplete
 // product.  (Looking whether wavefront 0 has given up costs every task an LDS read behind the barrier, 1 us of a step of 70 to
-// 114; hidden behind the first loads, or looked at in front of the stores, it costs 2: registers.)
+// 114; hidden behind the first loads, or looked at in front of the stores, it costs 2.)
+//
+// F32: some of the groups have fp32 products.  Both kinds of products together are 66 KB of code, bf16 alone 33 (256 x 512: 0.9 us a
+// step less; a CU shares 64 KB of instruction cache with another).
+template <bool F32>
 __global__ __launch_bounds__(512) void ns_chain_kernel(const ChainArgs c) {
   constexpr int LB = Geo<bf16_t, 64, true>::LDS, LF = Geo<float, 64, true>::LDS;
   __shared__ __attribute__((aligned(256))) char lds[LB > LF ? LB : LF];
-  __shared__ uint32_t shared, gave_up;
+  __shared__ uint32_t shared, drawn, gave_up;
   ChainRoll* const roll = c.roll;
   if (threadIdx.x == 0) {
     gave_up = 0u;
@@ -514,7 +522,7 @@ __global__ __launch_bounds__(512) void ns_chain_kernel(const ChainArgs c) {
     if (n == 0) {
       // the first to report closes the roll
       uint32_t seen = 1;
-      for (int i = 0; i < kRollPolls && (seen = device_load(&roll->reported)) < gridDim.x; ++i) __builtin_amdgcn_s_sleep(8);
+      for (int i = 0; i < c.roll_polls && (seen = device_load(&roll->reported)) < gridDim.x; ++i) __builtin_amdgcn_s_sleep(8);
       if (seen < gridDim.x)
         seen = __hip_atomic_fetch_or(&roll->reported, kRollClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       device_store(&roll->workgroups, seen);
@@ -523,11 +531,33 @@ __global__ __launch_bounds__(512) void ns_chain_kernel(const ChainArgs c) {
   }
   __syncthreads();
   const uint32_t number = __builtin_amdgcn_readfirstlane(shared);
-  if (number & kRollClosed) return;
   __syncthreads();
-  int step = 0, polls = c.patience;
-  asm volatile("" : "+s"(polls));    // (a register: the loads of a task's arguments would wait for it)
-  for (int i = 0, first = 0, task = (int)number; task < c.tasks; task += step) {
+  // step: 0 not known yet, < 0 where the tasks are drawn
+  int workgroups = 0, step = 0;
+  // the number of workgroups that had reported when the roll was closed (0: the wait did not end)
+  auto ask = [&]() {
+    if (threadIdx.x == 0) {
+      uint32_t n = 0;
+      for (int patience = c.patience; patience > 0 && (n = device_load(&roll->workgroups)) == 0u; --patience) __builtin_amdgcn_s_sleep(1);
+      shared = n;
+      if (n == 0u) gave_up = 1u;
+    }
+    __syncthreads();
+    workgroups = (int)__builtin_amdgcn_readfirstlane(shared);
+    step = workgroups == (int)gridDim.x ? workgroups : -1;
+  };
+  auto draw = [&]() -> int {
+    if (threadIdx.x == 0)
+      drawn = (uint32_t)workgroups + __hip_atomic_fetch_add(&roll->drawn, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    return (int)__builtin_amdgcn_readfirstlane(drawn);
+  };
+  int task = (int)number;
+  if (number & kRollClosed) {        // a latecomer
+    ask();
+    task = workgroups != 0 ? draw() : c.tasks;
+  }
+  for (int i = 0, first = 0; task < c.tasks;) {
     while (task >= c.op[i].end) first = c.op[i++].end;
     const uint32_t code = c.op[i].code;
     const GroupDesc& g = c.group[code >> OPF_GROUP];
@@ -541,8 +571,8 @@ __global__ __launch_bounds__(512) void ns_chain_kernel(const ChainArgs c) {
     if (threadIdx.x < 64) {
       for (int at = 0; at < per_mat; at += 64) {
         const int k = at + (int)threadIdx.x;
-        int patience = polls;
-        while (patience > 0 && !__all(k >= per_mat || device_load(before + k) != 0u)) { --patience; __builtin_amdgcn_s_sleep(1); }
+        int patience = c.patience;
+        while (patience > 0 && !__all(k >= per_mat || device_load(before + k) != 0u)) --patience;
         if (patience <= 0) { gave_up = 1u; break; }
       }
     }
@@ -558,22 +588,17 @@ __global__ __launch_bounds__(512) void ns_chain_kernel(const ChainArgs c) {
       else if (!a.trans_p) small_tile<E, tile, true, false, true, true>(a, t, v, tid, lds);
       else small_tile<E, tile, true, true, true, true>(a, t, v, tid, lds);
     };
-    if (g.f32) { if (a.tile_m == 32) run(0.0f, IC<32>{}); else run(0.0f, IC<64>{}); }
+    if (F32 && g.f32) { if constexpr (F32) { if (a.tile_m == 32) run(0.0f, IC<32>{}); else run(0.0f, IC<64>{}); } }
     else { if (a.tile_m == 32) run(bf16_t{}, IC<32>{}); else run(bf16_t{}, IC<64>{}); }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // this wavefront's stores are where every die sees them
     __syncthreads();
     if (threadIdx.x == 0) device_store(c.flags + task, 1u);
-    if (step == 0) {
-      if (threadIdx.x == 0) {
-        uint32_t n = 0;
-        for (int patience = polls; patience > 0 && (n = device_load(&roll->workgroups)) == 0u; --patience) __builtin_amdgcn_s_sleep(1);
-        shared = n;
-        if (n == 0u) gave_up = 1u;
-      }
-      __syncthreads();
-      step = (int)__builtin_amdgcn_readfirstlane(shared);
-      if (step == 0) break;
+    if (step <= 0) {
+      if (step == 0) ask();
+      if (workgroups == 0) break;
+      if (step < 0) { task = draw(); continue; }
     }
+    task += step;
   }
   if (gave_up != 0u)
     for (int j = 0; j < kMaxMerged; ++j)
@@ -625,7 +650,10 @@ bool device_is_gfx950() {
 
 hipError_t launch_ns_chain(const ChainArgs& c, int wgs, hipStream_t s) {
   if (c.ops < 1 || c.ops > kMaxChainOps || c.tasks < 1 || wgs < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(ns_chain_kernel, dim3(wgs), dim3(512), 0, s, c);
+  bool f32 = false;
+  for (int j = 0; j < kMaxMerged; ++j) f32 = f32 || c.group[j].f32;
+  if (f32) hipLaunchKernelGGL(ns_chain_kernel<true>, dim3(wgs), dim3(512), 0, s, c);
+  else hipLaunchKernelGGL(ns_chain_kernel<false>, dim3(wgs), dim3(512), 0, s, c);
   return hipGetLastError();
 }
 

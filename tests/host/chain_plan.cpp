@@ -1,5 +1,5 @@
 // The chain launches of a step (ns_chain_kernel) followed on the host: their tasks carried out in number by any number of
-// workgroups come to an end and respect the order of every chain, the rolls and flags they use are cleared before, and
+// workgroups, latecomers among them, come to an end and respect the order of every chain, the rolls and flags they use are cleared before, and
 // their products are those that are launched one by one at profiling level 2.  Needs no GPU (fake_hip.h); built and run by
 // tests/test_host_launches.py.
 #include "../../include/mona.h"
@@ -26,8 +26,9 @@ typedef std::vector<std::tuple<int, int, int>> Shapes;   // count, m, n
 
 struct Task { int op, mat; };
 
-// W workgroups, each with its tasks in order, one of those that can go on at a time
-static void carry_out(const ChainArgs& c, int workgroups, std::mt19937& rng) {
+// W workgroups, each with its tasks in order, one of those that can go on at a time.  late: so many more that come at any time,
+// and all tasks behind the first W are drawn in order by whoever has finished one or has come.
+static void carry_out(const ChainArgs& c, int workgroups, int late, std::mt19937& rng) {
   std::vector<Task> tasks;
   std::vector<int> first_of(c.ops), tiles_of(c.ops);
   for (int i = 0, first = 0; i < c.ops; first = c.op[i++].end) {
@@ -49,10 +50,12 @@ static void carry_out(const ChainArgs& c, int workgroups, std::mt19937& rng) {
   std::vector<char> done(tasks.size(), 0);
   std::vector<int> at(workgroups);
   for (int w = 0; w < workgroups; ++w) at[w] = w;
+  int drawn = workgroups;
   size_t left = tasks.size();
   while (left > 0) {
+    if (late > 0 && (int)at.size() < workgroups + late && rng() % 16 == 0) at.push_back(drawn++);
     std::vector<int> ready;
-    for (int w = 0; w < workgroups; ++w) {
+    for (int w = 0; w < (int)at.size(); ++w) {
       if (at[w] >= (int)tasks.size()) continue;
       const Task& t = tasks[at[w]];
       const ChainOp& op = c.op[t.op];
@@ -64,7 +67,7 @@ static void carry_out(const ChainArgs& c, int workgroups, std::mt19937& rng) {
     if (ready.empty()) return;
     const int w = ready[rng() % ready.size()];
     done[at[w]] = 1;
-    at[w] += workgroups;
+    at[w] = late > 0 ? drawn++ : at[w] + workgroups;
     --left;
   }
 }
@@ -108,7 +111,7 @@ static void run(const Shapes& shapes, int precision, int streams, int steps, int
     } else if (l.name.find("ns_chain_kernel") != std::string::npos) {
       const ChainArgs& c = *static_cast<const ChainArgs*>(l.args[0]);
       EXPECT(l.block == 512 && l.grid >= 1 && l.grid <= 256);
-      EXPECT(c.patience == kPatience);
+      EXPECT(c.patience == kPatience && c.roll_polls == kRollPolls);
       chains.push_back(c);
       for (int i = 0; i < c.ops; ++i) {
         GemmArgs a;
@@ -138,7 +141,8 @@ static void run(const Shapes& shapes, int precision, int streams, int steps, int
   }
   EXPECT(chains.empty() || (zero >= arena && zero + zero_bytes <= arena + bytes));
   for (const ChainArgs& c : chains)
-    for (int w : {1, 2, 7, 256}) carry_out(c, w, rng);
+    for (int w : {1, 2, 7, 256})
+      for (int late : {0, 1, 20}) carry_out(c, w, late, rng);
   chains_seen += (int)chains.size();
   const Products ordinary = products;
   products.clear();

@@ -79,6 +79,26 @@ def test_chains_replayed_from_a_graph():
             assert torch.equal(eager[i], graph_w[i]), (k, i)
 
 
+def polls(opt, roll, wait):
+    return opt.lib.mona_internal_chain_polls(ctypes.c_void_p(opt.state), roll, wait)
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_chains_begun_without_some(name):
+    """A roll that is closed at once: those that come later draw their tasks, and the results are the same bits."""
+    shapes, precision, _ = CASES[name]
+    print(f"[case] {name}", flush=True)
+    dev = "cuda:0"
+    weights = [wl.draw_weight(s, 300 + i, torch.float32, dev) for i, s in enumerate(shapes)]
+    opt = B.MonaOptimizer(weights, ns_precision=precision)
+    assert polls(opt, 0, 1 << 20) == B.MONA_OK
+    for k in range(2):
+        opt.step([wl.GradientStream(s, 400 + 50 * k + i, dev).next() for i, s in enumerate(shapes)], wl.HParams())
+    assert opt.status() == [0] * len(shapes)
+    for i, (x, y) in enumerate(zip(weights, steps(shapes, precision, 0))):
+        assert torch.equal(x, y), (name, i)
+
+
 def test_a_wait_that_does_not_end():
     """Chains whose waits may not poll at all: the launch ends, no parameter is touched, the status says so; the next step is whole."""
     shapes, precision, _ = CASES["nine groups"]
@@ -89,12 +109,12 @@ def test_a_wait_that_does_not_end():
     opt, ref = B.MonaOptimizer(weights), B.MonaOptimizer(plain)
     grads = [[wl.GradientStream(s, 500 + 20 * k + i, dev).next() for i, s in enumerate(shapes)] for k in range(2)]
     before = [w.clone() for w in weights]
-    assert opt.lib.mona_internal_chain_patience(ctypes.c_void_p(opt.state), 0) == B.MONA_OK
+    assert polls(opt, 64, 0) == B.MONA_OK
     opt.step(grads[0], wl.HParams())
     assert all(s & B.MONA_STATUS_INCOMPLETE for s in opt.status())
     for i in range(len(shapes)):
         assert torch.equal(weights[i], before[i]), i
-    assert opt.lib.mona_internal_chain_patience(ctypes.c_void_p(opt.state), 1 << 20) == B.MONA_OK
+    assert polls(opt, 64, 1 << 20) == B.MONA_OK
     ref.step(grads[0], wl.HParams())
     for w, p in zip(weights, plain):
         w.copy_(p)                   # (the state arrays are those of a whole step)
