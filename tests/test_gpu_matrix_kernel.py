@@ -120,3 +120,22 @@ def test_groups_timed_one_by_one_give_the_same_bits(shapes):
     assert abs(sum(r["flops"] for r in records) - flops) <= 1e-9 * flops
     for i, (x, y) in enumerate(zip(*ends)):
         assert torch.equal(x, y), i
+
+
+def test_matrix_kernel_beside_other_groups():
+    """Matrices with a workgroup each beside large tiles, merged small products of both precisions and a long chain of K."""
+    kinds = [(256, 512, COUNT), (1024, 1024, 16), (100, 100, 200), (30, 500, 3), (300, 700, 2), (120, 600, 150)]
+    print("[case] beside", flush=True)
+    shapes = [(m, n) for m, n, c in kinds for _ in range(c)]
+    firsts = [sum(c for _, _, c in kinds[:i]) for i in range(len(kinds))]
+    watch = [f + k for f, (_, _, c) in zip(firsts, kinds) for k in (0, c - 1)]
+    weights = [wl.draw_weight(s, 300 + i, torch.float32) for i, s in enumerate(shapes)]
+    opt = B.MonaOptimizer([w.cuda() for w in weights])
+    grads = [[wl.GradientStream(s, 400 + 500 * k + i).next() for i, s in enumerate(shapes)] for k in range(2)]
+    opt.set_profiling(2)
+    opt.step([g.cuda() for g in grads[0]], wl.HParams())
+    records = opt.last_step_launches()
+    assert {(r["m"], r["n"]) for r in records if r["kind"] == 4} == {(256, 512), (100, 100), (120, 600)}
+    assert 256256 in {r["tile"] for r in records if r["kind"] != 4}
+    opt, dev_w, hist = H.run_gpu(weights, grads, wl.HParams(), 0, watch=watch)
+    H.check_history(weights, grads, wl.HParams(), hist, watch, H.TOL_NS_BF16, label="beside")

@@ -15,15 +15,17 @@ pytestmark = pytest.mark.gpu
 
 # (shapes, ns_precision, matrices to check)
 CASES = {
+    # (so few tiles go out as chains, see test_gpu_chains.py; "more of them" below are launches of their own)
     # a tile and one more row or column, short and long K (one to eleven slabs a wavefront), wide and tall
     "edges of 64": ([(65, 65), (128, 129), (129, 128), (192, 1300), (1300, 192), (66, 2700)], 0, range(6)),
     # more groups than one launch takes, of unequal sizes
     "eleven groups": ([(70 + 13 * i, 90 + 40 * ((7 * i) % 11)) for i in range(11)], 0, range(11)),
     # enough 128 x 128 tiles, at most one a CU (13 x 10) and more (13 x 20), last tile partly padding
     "tiles of 128": ([(500, 610)] * 13 + [(610, 500)] * 2, 0, (0, 12, 13, 14)),
-    # the most products of one tile, and of three, that stay on small tiles, and one matrix more: 256 x 256 tiles
+    # matrices with a workgroup each, around the count from which a single tile each is large under a forced schedule
     "111 large tiles": ([(256, 512)] * 111, 0, (0, 110)),
     "112 large tiles": ([(256, 512)] * 112, 0, (0, 111)),
+    # the most tiles of 256 x 256 that a product has on small tiles, and the fewest that it has on large ones
     "126 large tiles": ([(500, 510)] * 42, 0, (0, 41)),
     "129 large tiles": ([(500, 510)] * 43, 0, (0, 42)),
     # groups that fill half the chip run apart, the smaller ones share their launches, in either precision
@@ -36,6 +38,46 @@ CASES = {
     "fp32 edges": ([(3, 5), (64, 64), (65, 200), (200, 65), (130, 1030)], 1, range(5)),
     "fp32 tiles of 128": ([(700, 1100)] * 10 + [(1100, 700)], 1, (0, 9, 10)),
 }
+
+
+# Too many tiles for a chain, too few matrices for a workgroup each: (shapes, ns_precision, matrices to check, launches, tiles)
+MORE = {
+    "edges of 64, more of them": ([s for s in CASES["edges of 64"][0] for _ in range(6)], 0, range(0, 36, 6), 15, {64064, 128128}),
+    "eleven groups, more of them": ([s for s in CASES["eleven groups"][0] for _ in range(8)], 0, range(0, 88, 8), 30, {64064, 128128}),
+    "edges of 128": ([(129, 1100)] * 16 + [(1100, 257)] * 10, 0, (0, 15, 16, 25), 15, {64064, 128128}),
+    "fp32 edges, more of them": ([s for s in CASES["fp32 edges"][0] for _ in range(40)], 1, range(0, 200, 40), 45, {64064}),
+}
+
+
+@pytest.mark.parametrize("name", MORE)
+def test_launches_of_small_products_against_the_oracle(name):
+    shapes, precision, watch, launches, tiles = MORE[name]
+    print(f"[case] {name}", flush=True)
+    weights = [wl.draw_weight(s, 300 + i, torch.float32) for i, s in enumerate(shapes)]
+    opt = B.MonaOptimizer([w.cuda() for w in weights], ns_precision=precision)
+    assert opt.plan_info(5)["ns_launches"] == launches
+    grads = [[wl.GradientStream(s, 400 + i).next() for i, s in enumerate(shapes)]]
+    opt.set_profiling(2)
+    opt.step([g.cuda() for g in grads[0]], wl.HParams())
+    assert {r["tile"] for r in opt.last_step_launches()} == tiles
+    opt, dev_w, hist = H.run_gpu(weights, grads, wl.HParams(), precision, watch=watch)
+    H.check_history(weights, grads, wl.HParams(), hist, watch, H.TOL_NS_F32 if precision else H.TOL_NS_BF16, label=name)
+
+
+@pytest.mark.parametrize("count, tiles", [(111, {128128}), (112, {256256})])
+def test_single_large_tiles_under_a_forced_schedule(count, tiles):
+    """p x p products of a single large tile: on small tiles up to 111 matrices, on large ones from 112 on (the pairwise schedule:
+    literal iterations of so many take the kernel with a workgroup for each matrix)."""
+    print(f"[case] {count}", flush=True)
+    shapes, watch = [(256, 512)] * count, (0, count - 1)
+    weights = [wl.draw_weight(s, 300 + i, torch.float32) for i, s in enumerate(shapes)]
+    opt = B.MonaOptimizer([w.cuda() for w in weights], ns_schedule=B.MONA_NS_SCHEDULE_PAIRS)
+    grads = [[wl.GradientStream(s, 400 + i).next() for i, s in enumerate(shapes)]]
+    opt.set_profiling(2)
+    opt.step([g.cuda() for g in grads[0]], wl.HParams())
+    assert {r["tile"] for r in opt.last_step_launches() if r["kind"] != 2} == tiles
+    opt, dev_w, hist = H.run_gpu(weights, grads, wl.HParams(), 0, watch=watch, ns_schedule=B.MONA_NS_SCHEDULE_PAIRS)
+    H.check_history(weights, grads, wl.HParams(), hist, watch, H.TOL_NS_BF16, label=str(count))
 
 
 @pytest.mark.parametrize("name", CASES)

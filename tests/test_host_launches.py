@@ -15,7 +15,7 @@ pytestmark = pytest.mark.skipif(not all(map(os.path.exists, OBJECTS + [CLANG])),
 
 
 @pytest.mark.parametrize("program", ["pointer_tables", "launch_plan", "chain_plan", "executed_flops", "matrix_plan",
-                                     "device_queries"])
+                                     "device_queries", "kept_plan"])
 def test_what_the_host_enqueues(program, tmp_path):
     exe = str(tmp_path / program)
     subprocess.run([CLANG, "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
