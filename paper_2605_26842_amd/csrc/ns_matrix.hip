@@ -391,25 +391,21 @@ __device__ __forceinline__ void run_matrix(const StepDesc& st, const GroupDesc& 
         return TALL ? at8((pan ^ xor_at(i, v)) + c * 32 * PITCH) : at8((pan ^ xor_at(c, v)) + i * 32 * PITCH);
       };
       u32x2 out[G::RB][G::CB][4];
-      // The scale of the unscaled copy enters behind the sum, and every rounding is that of the products in launches: at
-      // P = 256 of the large-tile kernel (whose bits these are), at P = 128 of finish_tile().  In B or in a instead it rounds B in
-      // other places, which moves W by 2e-3 of its norm in a step.
-      const float post = first ? sc.inv : 1.0f, ce = P == 256 ? post * st.ns_a : st.ns_a;
+      // The scale of the unscaled copy enters behind the sum, and every rounding is that of the large-tile kernel (at P = 256 these
+      // are its bits).  In B and in a instead it rounds B in other places, which moves W by 2e-3 of its norm in a step.  (A
+      // block's own values are read in front of the branch: read in both arms they cost 1 % of a step at P = 256.)
+      const float post = first ? sc.inv : 1.0f, ce = post * st.ns_a;
       static_for<G::RB>([&](auto i) {
         static_for<G::CB>([&](auto c) {
+          bf16x4 own[4];
+          static_for<4>([&](auto v) { own[v] = __builtin_bit_cast(bf16x4, panel8(i, c, v)); });
           auto renew = [&](auto unit) {
             auto value = [&](bf16_t x, float sum) {
-              if constexpr (P == 128) {
-                const float r = sum + ce * (float)x;
-                return unit ? r : post * r;
-              } else {
-                return unit ? fmaf(ce, (float)x, sum) : fmaf(post, sum, ce * (float)x);
-              }
+              return unit ? fmaf(ce, (float)x, sum) : fmaf(post, sum, ce * (float)x);
             };
             static_for<4>([&](auto v) {
-              const bf16x4 e = __builtin_bit_cast(bf16x4, panel8(i, c, v));
-              out[i][c][v] = pack(value(e.x, y[i][c][4 * v]), value(e.y, y[i][c][4 * v + 1]), value(e.z, y[i][c][4 * v + 2]),
-                                  value(e.w, y[i][c][4 * v + 3]));
+              out[i][c][v] = pack(value(own[v].x, y[i][c][4 * v]), value(own[v].y, y[i][c][4 * v + 1]),
+                                  value(own[v].z, y[i][c][4 * v + 2]), value(own[v].w, y[i][c][4 * v + 3]));
             });
           };
           if (post == 1.0f) renew(IC<1>{}); else renew(IC<0>{});
