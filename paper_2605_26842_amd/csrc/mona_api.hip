@@ -894,6 +894,7 @@ Launch build_chain(const mona_state* st, Plan& plan, const std::vector<int>& gro
     launches.push_back(l);
   }
   c.tasks = (int32_t)tasks;
+  for (int i = c.ops; i < kMaxChainOps + 3; ++i) c.op[i].end = INT32_MAX;
   Launch chain;
   chain.wgs = (int)std::min<long long>(most, cus);
   chain.chain = (int)plan.chains.size();

@@ -203,7 +203,7 @@ struct ChainArgs {
   int32_t roll_polls;      // polls of the roll before it is closed without some
   int32_t patience;        // polls of one wait
   GroupDesc group[kMaxMerged];
-  ChainOp op[kMaxChainOps];
+  ChainOp op[kMaxChainOps + 3];   // (looked through four at a time; those behind the last one end nowhere)
 };
 static_assert(sizeof(ChainArgs) <= 4000, "an argument block holds 4 KB");
 // What every step clears before its products: the rolls and the flags of its chain launches, one after the other.

@@ -482,7 +482,8 @@ __global__ __launch_bounds__(WIDE ? 512 : 256) void ns_small_kernel(const GemmBa
 //     whoever comes later takes its share from then on: a chain that began on the few CUs another stream's kernels had left
 //     would otherwise keep to them when the chip is free again.  Measured, us per step beside steps of 64 x 2048 x 1024 on
 //     another stream, launches / chain without latecomers / with: 256 x 512 650 / 430 / 265, 512 x 1408 870 / 1400 to 4800 / 310, nine
-//     ragged matrices 865 / 480 to 1100 / 270, 4 x 300 x 900 1060 / 1100 to 4400 / 355; alone the code costs nine ragged matrices 1 us.
+//     ragged matrices 865 / 480 to 1100 / 270, 4 x 300 x 900 1060 / 1100 to 4400 / 355; alone the code costs nine ragged
+//     matrices 1 us.
 //   * The dies have an L2 each.  What one workgroup writes and another reads goes through device-scope (sc1) accesses, which
 //     are coherent by themselves; a flag follows when the stores have completed (vmcnt 0 in every wavefront, then the
 //     barrier).  Measured from the last store of a product to the first operands of the next: about 2 us, against 4 to 6 us
@@ -515,8 +516,8 @@ __global__ __launch_bounds__(512) void ns_chain_kernel(const ChainArgs c) {
   constexpr int LB = Geo<bf16_t, 64, true>::LDS, LF = Geo<float, 64, true>::LDS;
   __shared__ __attribute__((aligned(256))) char lds[LB > LF ? LB : LF];
   __shared__ uint32_t shared, drawn, gave_up;
-  ChainRoll* const roll = c.roll;
   if (threadIdx.x == 0) {
+    ChainRoll* const roll = c.roll;
     gave_up = 0u;
     const uint32_t n = __hip_atomic_fetch_add(&roll->reported, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (n == 0) {
@@ -537,6 +538,8 @@ __global__ __launch_bounds__(512) void ns_chain_kernel(const ChainArgs c) {
   // the number of workgroups that had reported when the roll was closed (0: the wait did not end)
   auto ask = [&]() {
     if (threadIdx.x == 0) {
+      ChainRoll* roll = c.roll;
+      asm volatile("" : "+v"(roll));     // (looked up anew: kept from the beginning it would take registers of every task)
       uint32_t n = 0;
       for (int patience = c.patience; patience > 0 && (n = device_load(&roll->workgroups)) == 0u; --patience) __builtin_amdgcn_s_sleep(1);
       shared = n;
@@ -547,8 +550,11 @@ __global__ __launch_bounds__(512) void ns_chain_kernel(const ChainArgs c) {
     step = workgroups == (int)gridDim.x ? workgroups : -1;
   };
   auto draw = [&]() -> int {
-    if (threadIdx.x == 0)
+    if (threadIdx.x == 0) {
+      ChainRoll* roll = c.roll;
+      asm volatile("" : "+v"(roll));
       drawn = (uint32_t)workgroups + __hip_atomic_fetch_add(&roll->drawn, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     __syncthreads();
     return (int)__builtin_amdgcn_readfirstlane(drawn);
   };
@@ -557,8 +563,12 @@ __global__ __launch_bounds__(512) void ns_chain_kernel(const ChainArgs c) {
     ask();
     task = workgroups != 0 ? draw() : c.tasks;
   }
-  for (int i = 0, first = 0; task < c.tasks;) {
-    while (task >= c.op[i].end) first = c.op[i++].end;
+  for (int i = 0; task < c.tasks;) {
+    // (four products at a time: a position has one for each group, and each look is a round trip to the scalar cache; nine ragged
+    // matrices in seven groups 81.0 -> 79.5 us a step)
+    for (int passed = 4; passed == 4; i += passed)
+      passed = (task >= c.op[i].end) + (task >= c.op[i + 1].end) + (task >= c.op[i + 2].end) + (task >= c.op[i + 3].end);
+    const int first = i > 0 ? c.op[i - 1].end : 0;
     const uint32_t code = c.op[i].code;
     const GroupDesc& g = c.group[code >> OPF_GROUP];
     GemmArgs a;
