@@ -199,8 +199,10 @@ bool large_tiles(const Group& g, int kind, int count) {
   // (three runs, within 0.3 %) with the line at 192 / 128 / 112 tiles: from 128 tiles on large tiles are faster, 4 x 2048 x 2048
   // (144 tiles a p x p product) 1043 / 847 / 847, 4096 x 4096 (136) 1816 / 1454 / 1452; below, they lose, 12 x 1024 x 2048 (120)
   // 748 / 748 / 768, 4 x 1792 x 1792 (112) 694 / 694 / 714, 8 x 1280 x 1280 (120) 568 / 568 / 580, 20 x 768 x 768 (120 and 180)
-  // 461 / 431 / 429, except where every symmetric product is a single tile, 115 x 256 x 512 349 / 349 / 325, 120 x 256 x 256
-  // 267 / 267 / 248 (but not where the apply alone has them, 60 x 256 x 500 - / 246 / 265, 8 x 256 x 3840 - / 227 / 236).
+  // 461 / 431 / 429.  Where every symmetric product is a single tile the line lies at 112 (literal iterations of so many take
+  // the kernel with a workgroup for each matrix, so this is for forced schedules): chunks of three / of two, 115 x 256 x 512
+  // 424 / 421 on small tiles and 399 / 401 on large ones, 115 x 256 x 1024 619 / 645 and 597 / 630, 127 x 200 x 250 333 / 316 and 324 / 311, but
+  // 120 x 256 x 256 322 / 306 and 331 / 318.
   return tiles >= kMinTiles256 || (g.p_pad == 256 && count >= kMinSingles256);
 }
 bool small_tiles_only(const Group& g) {
@@ -218,9 +220,9 @@ long long launch_tiles(const Group& g, int kind, int tile, int count) {
 // Whether the matrices of a group get a workgroup each (ns_matrix_kernel), by what their iterations take that way and as
 // products, us of a step.  Alone, products take as long as their launches at least; beside other groups, whose launches they share
 // or run beside, only what they add.  Measured, us per step as products (launches, or a chain) / by matrix: 128 x 128 57 / 32,
-// 100 x 400 70 / 64, 24 x 128 x 512 90 / 75, 60 x 128 x 256 105 / 53, 250 x 70 x 100 170 / 52, 200 x 120 x 600 317 / 177,
-// 250 x 128 x 4000 1983 / 1367, but 40 x 128 x 2000 232 / 327; 256 x 256 x 256 426 / 245, 115 x 256 x 512 383 / 291, 128 x 768 x 256 both
-// ways 818 / 606, but 60 x 256 x 512 235 / 260, 79 x 256 x 834 and others 482 / 569; 4 x 171 x 66 beside 697 x 612 and 365 x 161 144 / 169;
+// 100 x 400 70 / 64, 24 x 128 x 512 90 / 75, 60 x 128 x 256 105 / 53, 250 x 70 x 100 170 / 45, 200 x 120 x 600 317 / 177,
+// 250 x 128 x 4000 1983 / 1372, but 40 x 128 x 2000 232 / 327; 256 x 256 x 256 426 / 243, 115 x 256 x 512 383 / 290, 128 x 768 x 256 both
+// ways 831 / 626, but 60 x 256 x 512 235 / 260, 79 x 256 x 834 and others 482 / 569; 4 x 171 x 66 beside 697 x 612 and 365 x 161 144 / 169;
 // 50 x 256 x 256 170 / 147, 84 x 256 x 256 213 / 162, 70 x 130 x 200 148 / 134, 86 x 256 x 768 474 / 376, but 36 x 256 x 256 140 / 140, 52 x 160 x 140
 // 126 / 148, 50 x 140 x 380 160 / 205.
 bool by_matrix(const Group& g, bool alone) {

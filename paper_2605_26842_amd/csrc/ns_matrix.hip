@@ -13,14 +13,15 @@
 // panels (q <= 512) stay there from the first iteration to the last.  P = 256: B takes 128 registers, S 128 accumulators, so
 // they take turns, the squares lie over the panels, and every iteration reads X twice and writes it once.  Eight wavefronts, one workgroup per CU.
 //
-// Panels that do not stay in LDS come from a die's 4 MB of L2, 128 KB for each of its 32 workgroups, or from behind it.  Passes that go
-// the same way all the time find nothing there; so they go to and fro, and X is renewed in place, which halves what the steps
-// touch.  Measured, us per step, one way and between two buffers -> to and fro in place: 250 x 128 x 4000 1505 -> 1367, 300 x 128 x 1000
-// 559 -> 498, 256 x 200 x 700 644 -> 622, 128 x 256 x 1024 572 -> 543, 256 x 256 x 256 258 -> 245.  Letting the second panel of a pass
-// arrive while the first is multiplied gains nothing on top.
+// Panels that do not stay in LDS come from a die's 4 MB of L2, 128 KB for each of its 32 workgroups, or from behind it.  X is renewed
+// in place, which halves what the steps touch, and passes go to and fro.  Measured, us per step, between two buffers and one way ->
+// in place, to and fro: 250 x 128 x 4000 1505 -> 1367, 300 x 128 x 1000 559 -> 503, 256 x 200 x 700 644 -> 620, 128 x 256 x 1024 572 -> 541,
+// 256 x 256 x 256 258 -> 243.  It is the place that counts: in place but one way, 0.3 % slower to 0.5 % faster, although to
+// and fro 53 instead of 46 % of the requests find their line in L2 (128 x 768 x 256 both ways; 60 instead of 58 % at 250 x 128 x 4000) and
+// 8 % less comes from behind it.  Letting the second panel of a pass arrive while the first is multiplied gains nothing on top.
 //
-// Measured, us per step, products in launches (or chains) -> here: 128 x 768 x 256 both ways 818 -> 606, 250 x 70 x 100 170 -> 52,
-// 256 x 256 x 256 426 -> 245, 300 x 128 x 128 202 -> 88, one 128 x 128 57 -> 32.  A panel costs 2.2 us an iteration (P = 128) or
+// Measured, us per step, products in launches (or chains) -> here: 128 x 768 x 256 both ways 831 -> 626, 250 x 70 x 100 170 -> 45,
+// 256 x 256 x 256 426 -> 243, 300 x 128 x 128 202 -> 82, one 128 x 128 57 -> 31.  A panel costs 2.2 us an iteration (P = 128) or
 // 7.3 us (P = 256, twice) on a CU, of which the multiplications are 1 and 4: the wavefronts meet three
 // times a panel, and the vector instructions of the epilogue (2.5 an element) do not run beside matrix instructions.
 //

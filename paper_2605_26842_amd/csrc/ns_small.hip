@@ -10,8 +10,8 @@
 //     is in flight at once and a long one never waits for a single round trip per stage;
 //   * a launch of few tiles uses 64 x 64 tiles whose wavefronts split K between them (each its own slabs of LDS, no
 //     workgroup barrier before the sum), a launch of more tiles 128 x 128 (the host decides, product by product).
-// Measured, us per step, one chain of launches per group on a register-staged 128 x 128 kernel -> here: one 256 x 512
-// matrix 170 -> 99, 512 x 1408 269 -> 137, nine ragged matrices 980 -> 189 (chains: below), a block of hidden size 1000 664 -> 509.
+// Measured, us per step, one chain of launches per group on a register-staged 128 x 128 kernel -> here: a block of hidden size 1000
+// 664 -> 505.  (Steps as small as one 256 x 512 matrix, 170 -> 99, or nine ragged ones, 980 -> 189, are one launch now: chains, below.)
 // A launch costs 5 us (64 x 64) to 9 - 11 us (128 x 128) beside its K loop, and 1024 of K 4.7 and 9.4 us for a tile on a CU of
 // its own, 8.6 and 19.4 us for two.
 //
@@ -491,8 +491,8 @@ __global__ __launch_bounds__(WIDE ? 512 : 256) void ns_small_kernel(const GemmBa
 //     another 2 us a step.
 //   * 32 x 32 tiles, K split between the eight wavefronts, where every one has a CU of its own: a tile of 64 x 64 takes 2.8 us
 //     with K = 256 and 4.4 with 512, one of 32 x 32 2.1 and 2.5 (the CU's own 64 bytes a cycle from L2, and latency).
-// Measured, us per step, launches -> chain: one 256 x 512 matrix 99 -> 72, 512 x 1408 without allocation 137 -> 118, nine ragged
-// matrices in both precisions 189 -> 83 (which had waited for the host).  Tickets instead of fixed numbers, drawn by an atomic
+// Measured, us per step, launches -> chain: one 256 x 512 matrix 99 -> 73, 512 x 1408 without allocation 137 -> 114, nine ragged
+// matrices in both precisions 189 -> 84 (which had waited for the host).  Tickets instead of fixed numbers, drawn by an atomic
 // operation for every task, and a counter of finished tiles instead of flags: 96, 189 and 133.
 constexpr uint32_t kRollClosed = 0x80000000u;
 

@@ -16,7 +16,7 @@
 // products a stage and wavefront against 88 instructions of splitting.
 //
 // Measured against the fp32 instructions, us per step: a block of hidden size 1024 (4 x 1024 x 1024, 1024 x 4096 both ways)
-// 2287 -> 1665, 2048 x 2048 1910 -> 1239, 64 x 1024 x 2048 21270 -> 15180 (there 1080 TFLOP/s of bf16 products, the rate
+// 2288 -> 1672, 2048 x 2048 1910 -> 1239, 64 x 1024 x 2048 21270 -> 15180 (there 1080 TFLOP/s of bf16 products, the rate
 // the power limit leaves the large-tile kernel too), 42 x 256 x 207 303 -> 285; the relative error of the update against 64 bits
 // on these shapes 0.9e-6 to 1.7e-6 -> 0.6e-6 to 1.0e-6.  Letting one wavefront of a SIMD split while the other multiplies, or
 // weaving both into one stream by scheduling groups, is 16 and 5 % slower; a single set of accumulators is as fast.
