@@ -99,6 +99,34 @@ def test_chains_begun_without_some(name):
         assert torch.equal(x, y), (name, i)
 
 
+def test_chains_beside_another_stream():
+    """Kernels of another stream hold the CUs for some hundred us at a time, so chains begin with those that are free."""
+    print("[case] beside", flush=True)
+    shapes, precision, _ = CASES["seven tiles by eight, four times"]
+    dev = "cuda:0"
+    big = [wl.draw_weight((2048, 1024), 700 + i, torch.float32, dev) for i in range(32)]
+    big_g = [wl.GradientStream((2048, 1024), 800 + i, dev).next() for i in range(32)]
+    grads = [[wl.GradientStream(s, 400 + 50 * k + i, dev).next() for i, s in enumerate(shapes)] for k in range(2)]
+    ends = []
+    for busy in (False, True):
+        weights = [wl.draw_weight(s, 300 + i, torch.float32, dev) for i, s in enumerate(shapes)]
+        opt, other = B.MonaOptimizer(weights, ns_precision=precision), B.MonaOptimizer(big)
+        torch.cuda.synchronize()
+        here, there = torch.cuda.Stream(), torch.cuda.Stream()
+        if busy:
+            with torch.cuda.stream(there):
+                for _ in range(6):
+                    other.step(big_g, wl.HParams())
+        with torch.cuda.stream(here):
+            for k in range(20):
+                opt.step(grads[k % 2], wl.HParams())
+            assert opt.status() == [0] * len(shapes)
+        torch.cuda.synchronize()
+        ends.append(weights)
+    for i, (x, y) in enumerate(zip(*ends)):
+        assert torch.equal(x, y), i
+
+
 def test_a_wait_that_does_not_end():
     """Chains whose waits may not poll at all: the launch ends, no parameter is touched, the status says so; the next step is whole."""
     shapes, precision, _ = CASES["nine groups"]
