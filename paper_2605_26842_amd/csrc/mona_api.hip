@@ -76,6 +76,7 @@ struct Group {
   int o_buf = 1;             // which ping-pong buffer holds O_k of the last step
   size_t x_off[2] = {0, 0};  // byte offsets in the arena: ping-pong X buffers
   size_t pp_off[6] = {0, 0, 0, 0, 0, 0};
+  size_t fresh_off = 0;      // byte offset of the group's part of a fresh chain's buffers
   size_t members_off = 0;
   int64_t x_stride = 0, s_stride = 0;  // elements per matrix
 };
@@ -111,6 +112,7 @@ struct Layout {
   std::vector<Unit> units;             // what the products of the groups are launched as, in launch order per lane
   int lanes = 1;
   bool small_enough = false;           // all groups together are as little as a chain takes
+  size_t fresh_bytes = 0;              // ... what a buffer for every product of kFreshSteps literal iterations takes (0: not that)
   int late_group = -1;                 // group whose elementwise pass runs beside the products of the others
   std::vector<int32_t> order;          // matrix indices: early matrices, then those of the late group
   int num_early = 0;
@@ -300,7 +302,6 @@ void plan_lanes(Layout& L, const mona_options& opt) {
   }
   // A workgroup for each matrix: not where a chain that some groups need anyway takes all of them (the others cost it little).
   const bool only = L.gfx950 && std::all_of(L.groups.begin(), L.groups.end(), [](const Group& g) { return by_matrix(g, true); });
-  L.small_enough = all_in_a_chain(L);
   std::vector<int> matrices;
   for (int gi = 0; gi < ngroups; ++gi) {
     if (only || (L.gfx950 && !L.small_enough && by_matrix(L.groups[gi], false))) { matrices.push_back(gi); continue; }
@@ -480,6 +481,13 @@ void build_layout(const mona_matrix* mats, int count, const mona_options& opt, b
     for (int b = 0; b < g.npp; ++b) { g.pp_off[b] = off; off = align_up(off + cnt * g.s_stride * g.esize); }
   }
   L.work_bytes = off - L.work_begin;
+  L.small_enough = all_in_a_chain(L);
+  if (L.small_enough && L.groups.size() <= (size_t)(kMaxMerged * kMaxChains) &&
+      std::all_of(L.groups.begin(), L.groups.end(), [](const Group& g) { return !g.fused; }))
+    for (Group& g : L.groups) {
+      g.fresh_off = L.fresh_bytes;
+      L.fresh_bytes += 2 * kFreshSteps * (g.pp_off[1] - g.pp_off[0]) + (kFreshSteps - 1) * (g.x_off[1] - g.x_off[0]);
+    }
 
   if (launches) {
     L.gfx950 = device_is_gfx950();
@@ -569,6 +577,8 @@ struct Plan {
   bool one_by_one = false;
   size_t chain_bytes = 0;                   // of rolls and flags, to be cleared before the products
   int chain_tasks = 0;
+  bool fresh = false;                       // every product has a buffer of its own
+  FillArgs fill;                            // what these are filled with before the products
 };
 
 struct mona_state {
@@ -611,6 +621,8 @@ struct mona_state {
 
   struct Plan* plan = nullptr;     // of the last step (see plan_for)
   int chain_roll_polls = kRollPolls, chain_patience = kPatience;   // (see ChainArgs)
+  char* fresh = nullptr;           // a buffer for every product of a chain: a part of the pool, or of the scratch of mona_step_noalloc
+  bool from_pool = false;
   mona_state() = default;
   mona_state(const mona_state&) = delete;
   ~mona_state() { delete plan; }
@@ -868,6 +880,7 @@ Launch build_chain(const mona_state* st, Plan& plan, const std::vector<int>& gro
   c.step = plan.step;
   c.roll_polls = st->chain_roll_polls;
   c.patience = st->chain_patience;
+  c.fresh = plan.fresh;
   c.roll = reinterpret_cast<ChainRoll*>(area) + plan.chains.size();
   c.flags = reinterpret_cast<uint32_t*>(area + kMaxChains * sizeof(ChainRoll)) + plan.chain_tasks;
   struct Before { int32_t first = 0, per_mat = 0; };
@@ -921,6 +934,31 @@ float update_scale(const Group& g, const mona_hparams& hp) {
   return hp.lr * hp.gamma_coeff * sqrtf((float)std::max(g.m, g.n));
 }
 
+// What the products of `steps` iterations of a group write before the last one: X_1 .., and all S and B.
+void add_fill(Plan& plan, const Group& g, size_t gi, int steps) {
+  const GroupDesc& d = plan.desc[gi];
+  int tile = 32;
+  for (const Op& op : plan.ops[gi]) tile = std::max(tile, (int)op.a.tile_m);
+  auto add = [&](char* at, int buffers, int64_t stride, int cols_pad, int rows, int cols) {
+    if (buffers <= 0) return;
+    FillItem& t = plan.fill.item[plan.fill.n++];
+    t.at = at;
+    t.stride = (uint32_t)(stride * g.esize);
+    t.pitch = (uint32_t)(cols_pad * g.esize);
+    t.rows = (uint32_t)round_up(rows, tile);
+    t.width = (uint32_t)(round_up(cols, tile) * g.esize / 16);
+    t.cover_rows = (uint32_t)round_up(rows, 32);
+    t.cover = (uint32_t)(round_up(cols, 32) * g.esize / 16);
+    t.pieces = (uint32_t)(buffers * d.count) * t.rows * t.width;
+    plan.fill.groups += (int)((t.pieces + kFillPieces - 1) / kFillPieces);
+    t.end = (uint32_t)plan.fill.groups;
+  };
+  const int p = std::min(g.m, g.n);
+  // (the matrices of a buffer and the buffers follow each other without a gap)
+  add(d.fresh, 2 * steps, g.s_stride, g.p_pad, p, p);
+  add(d.fresh + 2 * kFreshSteps * d.pp_step, steps - 1, g.x_stride, g.cols_pad, g.m, g.n);
+}
+
 // `one_by_one`: every product as a launch of its own, on the tiles and with the split of K it has in the ordinary step, and every
 // group whose matrices get a workgroup each as a launch of its own: that kernel has no products to take apart, and products in
 // its place would sum and round in other places.
@@ -928,6 +966,7 @@ void build_plan(const mona_state* st, const mona_hparams& hp, Plan& plan, bool o
   const Layout& L = st->L;
   const size_t ngroups = L.groups.size();
   plan.ns_steps = hp.ns_steps; plan.flags = hp.flags; plan.one_by_one = one_by_one;
+  memset(&plan.fill, 0, sizeof plan.fill);
   set_step(st, hp, plan);
   plan.ops.resize(ngroups);
   plan.lanes.resize(L.lanes);
@@ -938,6 +977,7 @@ void build_plan(const mona_state* st, const mona_hparams& hp, Plan& plan, bool o
     d.x_step = (int64_t)(g.x_off[1] - g.x_off[0]);
     d.pp = st->arena + g.pp_off[0];
     d.pp_step = (int64_t)(g.pp_off[1] - g.pp_off[0]);
+    if (st->fresh) d.fresh = st->fresh + g.fresh_off;
     d.members = reinterpret_cast<const int32_t*>(st->arena + g.members_off);
     d.count = (int32_t)g.members.size();
     d.m = g.m; d.n = g.n; d.rows_pad = g.rows_pad; d.cols_pad = g.cols_pad;
@@ -980,6 +1020,11 @@ void build_plan(const mona_state* st, const mona_hparams& hp, Plan& plan, bool o
   for (const auto& groups : chains) tasks += all ? round_up(chainable(L, plan, groups), 4) : 0;
   all = all && tasks <= kMaxChainTasks;
   if (all) {
+    plan.fresh = st->fresh != nullptr && hp.ns_steps <= kFreshSteps;
+    for (size_t gi = 0; plan.fresh && gi < ngroups; ++gi) {
+      for (Op& op : plan.ops[gi]) op.code |= (uint32_t)(op.iter + 1) << OPF_FRESH;
+      plan.o_buf[gi] = 1;
+    }
     for (size_t i = 0; i < chains.size(); ++i) {
       std::vector<Launch> singles;
       const Launch chain = build_chain(st, plan, chains[i], singles);
@@ -987,6 +1032,7 @@ void build_plan(const mona_state* st, const mona_hparams& hp, Plan& plan, bool o
       if (one_by_one) lane.insert(lane.end(), singles.begin(), singles.end());
       else lane.push_back(chain);
     }
+    for (size_t gi = 0; plan.fresh && gi < ngroups; ++gi) add_fill(plan, L.groups[gi], gi, hp.ns_steps);
     return;
   }
   for (const Unit& u : L.units) {
@@ -1123,6 +1169,65 @@ bool get_event_pair(mona_state* st, hipEvent_t* a, hipEvent_t* b) {
 
 }  // namespace
 
+// ---- buffers of fresh chains ------------------------------------------------------------------------------
+namespace {
+
+// The caller's arena holds two X and two p x p matrices to a matrix, which the products of a chain take in turn.  Where every product
+// is to have a buffer of its own (ns_chain_kernel), the others come from a static array, of which every GPU the library runs on
+// holds its own copy, like the one of mona_step_noalloc.  A state takes its part when it is built and gives it back when it is
+// freed; one that finds no room runs its chains with flags.  256 x 512 takes 2.3 MB, nine ragged matrices 14.
+constexpr size_t kPoolBytes = (size_t)128 << 20, kPoolUnit = (size_t)1 << 18;
+constexpr int kPoolUnits = (int)(kPoolBytes / kPoolUnit), kMaxDevices = 64;
+static __device__ __align__(256) unsigned char chain_pool[kPoolBytes];
+// A part that was given back may still be in use by steps on their way, on streams that this side does not know.
+enum : uint8_t { UNIT_FREE = 0, UNIT_TAKEN = 1, UNIT_GIVEN_BACK = 2 };
+struct Pool {
+  char* base = nullptr;              // device address, looked up once
+  uint8_t unit[kPoolUnits] = {};
+};
+std::mutex g_pool_mu;
+Pool g_pool[kMaxDevices];
+
+char* find_room(Pool& pool, int units) {
+  for (int run = 0, i = 0; i < kPoolUnits; ++i) {
+    run = pool.unit[i] == UNIT_FREE ? run + 1 : 0;
+    if (run < units) continue;
+    const int first = i + 1 - units;
+    std::fill_n(pool.unit + first, units, (uint8_t)UNIT_TAKEN);
+    return pool.base + (size_t)first * kPoolUnit;
+  }
+  return nullptr;
+}
+// (a device without the array, or no room: nullptr, and no error)
+char* take_from_pool(int device, size_t bytes) {
+  const int units = (int)((bytes + kPoolUnit - 1) / kPoolUnit);
+  if (device < 0 || device >= kMaxDevices || units < 1 || units > kPoolUnits) return nullptr;
+  std::lock_guard<std::mutex> lock(g_pool_mu);
+  Pool& pool = g_pool[device];
+  if (!pool.base) {
+    void* p = nullptr;
+    if (hipGetSymbolAddress(&p, HIP_SYMBOL(chain_pool)) != hipSuccess || !p) { (void)hipGetLastError(); return nullptr; }
+    pool.base = static_cast<char*>(p);
+  }
+  if (char* at = find_room(pool, units)) return at;
+  if (std::find(pool.unit, pool.unit + kPoolUnits, (uint8_t)UNIT_GIVEN_BACK) == pool.unit + kPoolUnits) return nullptr;
+  // freeing pinned memory waits for the device, and so for every step of a state that was freed
+  void* mark = nullptr;
+  if (hipHostMalloc(&mark, 64, hipHostMallocDefault) != hipSuccess || hipHostFree(mark) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  std::replace(pool.unit, pool.unit + kPoolUnits, (uint8_t)UNIT_GIVEN_BACK, (uint8_t)UNIT_FREE);
+  return find_room(pool, units);
+}
+void give_back(int device, const char* at, size_t bytes) {
+  std::lock_guard<std::mutex> lock(g_pool_mu);
+  Pool& pool = g_pool[device];
+  std::fill_n(pool.unit + (at - pool.base) / kPoolUnit, (bytes + kPoolUnit - 1) / kPoolUnit, (uint8_t)UNIT_GIVEN_BACK);
+}
+
+}  // namespace
+
 extern "C" {
 
 const char* mona_last_error(void) { return g_err.c_str(); }
@@ -1180,6 +1285,7 @@ int mona_init_state(const mona_matrix* mats, int32_t count, const mona_options* 
     if (st->late_stream) (void)hipStreamDestroy(st->late_stream);
     if (st->late_fork) (void)hipEventDestroy(st->late_fork);
     if (st->late_done) (void)hipEventDestroy(st->late_done);
+    if (st->from_pool) give_back(st->device, st->fresh, L.fresh_bytes);
     delete st;
     (void)hipGetLastError();
     return code;
@@ -1191,6 +1297,10 @@ int mona_init_state(const mona_matrix* mats, int32_t count, const mona_options* 
   } while (0)
 
   INIT_TRY(hipGetDevice(&st->device));
+  if (L.gfx950 && L.fresh_bytes > 0) {
+    st->fresh = take_from_pool(st->device, L.fresh_bytes);
+    st->from_pool = st->fresh != nullptr;
+  }
   for (int i = 0; i < kRing && count > kInlineMats; ++i) {   // shorter lists need no staging
     void* p = nullptr;
     INIT_TRY(hipHostMalloc(&p, sizeof(MatDynamic) * (size_t)count, hipHostMallocDefault));
@@ -1366,7 +1476,7 @@ int enqueue_step(mona_state* st, const mona_hparams* hp, hipStream_t s) {
     STEP_TRY(pass(L.range_end[1], L.range_end[2], 0, st->late_stream));
     STEP_TRY(pass(L.range_end[2], L.range_end[3], 1, st->late_stream));
     STEP_TRY(launch_norm_finalize(stat, partials, scales, order + L.num_early, count - L.num_early,
-                                  L.max_blocks, hp->ns_eps, nullptr, 0, st->late_stream));
+                                  L.max_blocks, hp->ns_eps, nullptr, 0, nullptr, st->late_stream));
     STEP_TRY(hipEventRecord(st->late_done, st->late_stream));
   }
   STEP_TRY(pass(0, L.range_end[0], 0, s));
@@ -1377,7 +1487,7 @@ int enqueue_step(mona_state* st, const mona_hparams* hp, hipStream_t s) {
   }
   if (L.one_buffer && !muon_only) st->last_beta_a = hp->beta_a;
   STEP_TRY(launch_norm_finalize(stat, partials, scales, order, overlap ? L.num_early : count, L.max_blocks, hp->ns_eps,
-                                st->arena + L.chain_off, plan.chain_bytes, s));
+                                st->arena + L.chain_off, plan.chain_bytes, &plan.fill, s));
   if (prof) STEP_TRY(hipEventRecord(ev[1], s));
 
   // Newton-Schulz (Eq. newton_schulz), T iterations per shape group
@@ -1570,7 +1680,6 @@ namespace {
 constexpr size_t kScratchBytes = MONA_NOALLOC_SCRATCH_BYTES;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes + kChainBytes];
 
-constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices];   // device address of `scratch` on each device, looked up once
 
@@ -1624,13 +1733,16 @@ int mona_step_noalloc(const mona_matrix* mat, const mona_options* opts, void* g_
   st.opt = o;
   st.mats.assign(mat, mat + 1);
   st.arena = base;
+  if (L.gfx950 && L.fresh_bytes > 0 && align_up(L.total) + L.fresh_bytes <= kScratchBytes) st.fresh = base + align_up(L.total);
   st.k = k;
   hipStream_t s = static_cast<hipStream_t>(stream);
   // The array keeps what the last call left in it: the padding of the working matrices and the scales must
   // start from zero (stores of a kernel, not a memset: the call may be under graph capture).  A matrix without padding
   // needs none of that: every buffer is written whole before it is read (us a step with and without the clearing: 512 x 1408
   // 118.5 and 115.6, 1024 x 1024 156 and 152).
+  // (a fresh chain reads the first buffer of X and those that the step itself fills)
   const bool padded = L.groups[0].rows_pad != mat->m || L.groups[0].cols_pad != mat->n;
+  const size_t clear = plan_for(&st, *hp).fresh ? L.groups[0].x_off[1] - L.groups[0].x_off[0] : L.work_bytes;
   MatStatic ms;
   void* o_ptr = nullptr;
   fill_static(L, *mat, 0, base, g_prev, acc, mom, ms, o_ptr);
@@ -1640,7 +1752,7 @@ int mona_step_noalloc(const mona_matrix* mat, const mona_options* opts, void* g_
                                 st.at<void*>(L.optr_off), st.at<BlockWork>(L.blocks_off), (int)L.blocks.size(),
                                 reinterpret_cast<int32_t*>(base + L.groups[0].members_off),
                                 st.at<int32_t>(L.order_off), st.at<MatScale>(L.scales_off), base + L.work_begin,
-                                padded ? L.work_bytes : 0, s));
+                                padded ? clear : 0, s));
   rc = enqueue_step(&st, hp, s);
   if (rc) return rc;
   note_unstable_alpha(hp);
@@ -1668,6 +1780,7 @@ int mona_free_state(mona_state* st) {
   if (st->late_stream) { (void)hipStreamSynchronize(st->late_stream); (void)hipStreamDestroy(st->late_stream); }
   if (st->late_fork) (void)hipEventDestroy(st->late_fork);
   if (st->late_done) (void)hipEventDestroy(st->late_done);
+  if (st->from_pool) give_back(st->device, st->fresh, st->L.fresh_bytes);
   delete st;
   return MONA_OK;
 }
@@ -1696,8 +1809,8 @@ int mona_state_view(mona_state* st, int32_t i, int32_t kind, mona_view* out) {
       out->rows = out->cols = out->ld = 1; out->dtype = MONA_F32;
       break;
     case MONA_VIEW_O: {
-      // every chunk of iterations reads one ping-pong buffer and writes the other; with T = 0 the update
-      // kernel writes buffer 1
+      // every chunk of iterations reads one ping-pong buffer and writes the other (a fresh chain writes buffer 1); with T = 0 the
+      // update kernel writes buffer 1
       out->ptr = st->arena + g.x_off[g.o_buf] + (size_t)L.rank_in_group[i] * g.x_stride * g.esize;
       out->ld = g.cols_pad;
       out->dtype = g.f32 ? MONA_F32 : MONA_BF16;

@@ -64,6 +64,7 @@ struct GemmArgs {
   int64_t strideP, strideQ, strideE, strideC;  // elements between consecutive matrices of the group
   int32_t ldp, ldq, lde, ldc;
   int32_t K;                // padded, a multiple of 128
+  int32_t k_real;           // without padding
   int32_t tile_m, tile_n;   // BM, BN of the kernel that will run
   int32_t trans_p, trans_q; // 1: the operand is stored K-major
   int32_t tiles_m, tiles_n; // tiles that hold rows or columns of the result; tiles of padding alone are left out
@@ -91,6 +92,8 @@ struct GroupDesc {
   char* x;                  // ping-pong buffer 0 of X; buffer 1 is x_step bytes on
   char* pp;                 // p x p matrix 0; the others every pp_step bytes
   int64_t x_step, pp_step;
+  char* fresh;              // products with a buffer each: S_0, B_0, S_1, .. of kFreshSteps iterations every pp_step bytes, then X_1, ..
+                            // every x_step bytes
   const int32_t* members;   // group member -> matrix index
   int32_t count, m, n;      // matrices, their shape
   int32_t rows_pad, cols_pad;
@@ -116,15 +119,20 @@ enum OpField : uint32_t {
   OPF_STORE = 16,   // (with LAST) also stores O
   OPF_TP = 17, OPF_TQ = 18,   // the operand is read K-major
   OPF_TILE = 19,    // 0: 32 x 32, 1: 64 x 64, 2: 128 x 128, 3: 256 x 256
+  OPF_FRESH = 21,   // t + 1 in iteration t of a literal schedule whose products have a buffer each (0: none such)
 };
+constexpr int kFreshSteps = 5;   // iterations that the workspace of small steps has such buffers for
 __host__ __device__ inline uint32_t op_field(uint32_t code, uint32_t at, uint32_t mask = 1u) { return (code >> at) & mask; }
 
 __host__ __device__ inline void expand_op(const StepDesc& st, const GroupDesc& g, uint32_t code, GemmArgs& a) {
   const uint32_t kind = op_field(code, OPF_KIND, 3u), src = op_field(code, OPF_SRC);
   const int32_t p_pad = g.tall ? g.cols_pad : g.rows_pad, p_real = g.m < g.n ? g.m : g.n;
   const int64_t x_stride = (int64_t)g.rows_pad * g.cols_pad, s_stride = (int64_t)p_pad * p_pad;
-  char* const xs = g.x + (src ? g.x_step : 0);
-  auto pp = [&](uint32_t at) { return g.pp + (int64_t)op_field(code, at, 7u) * g.pp_step; };
+  const int32_t fresh = (int32_t)op_field(code, OPF_FRESH, 7u);
+  char* const pps = fresh ? g.fresh + 2 * (fresh - 1) * g.pp_step : g.pp;
+  auto fresh_x = [&](int32_t t) { return g.fresh + 2 * kFreshSteps * g.pp_step + (t - 1) * g.x_step; };   // X_t, t > 0
+  char* const xs = fresh > 1 ? fresh_x(fresh - 1) : g.x + (src && !fresh ? g.x_step : 0);
+  auto pp = [&](uint32_t at) { return pps + (int64_t)op_field(code, at, 7u) * g.pp_step; };
   const bool apply = kind == OP_APPLY, last = op_field(code, OPF_LAST), first = op_field(code, OPF_FIRST);
   a.count = g.count;
   a.members = g.members; a.scales = st.scales; a.stat = st.stat; a.dyn = st.dyn;
@@ -137,10 +145,11 @@ __host__ __device__ inline void expand_op(const StepDesc& st, const GroupDesc& g
   a.P = pp(OPF_P); a.Q = pp(OPF_Q); a.C = pp(OPF_C); a.E = nullptr;
   a.strideP = a.strideQ = a.strideE = a.strideC = s_stride;
   a.ldp = a.ldq = a.lde = a.ldc = p_pad;
-  a.K = p_pad;
+  a.K = p_pad; a.k_real = p_real;
   if (kind == OP_GRAM) {                        // S = X X^T (tall: X^T X)
     a.P = a.Q = xs; a.strideP = a.strideQ = x_stride; a.ldp = a.ldq = g.cols_pad;
     a.K = g.tall ? g.rows_pad : g.cols_pad;
+    a.k_real = g.tall ? g.m : g.n;
     if (first) a.post = POST_INV2;
   } else if (kind == OP_POLY) {                 // b S + c S S (+ a I)
     a.E = a.P;
@@ -149,7 +158,7 @@ __host__ __device__ inline void expand_op(const StepDesc& st, const GroupDesc& g
   } else if (apply) {                           // a X + B X (tall: a X + X B), or B X alone
     if (g.tall) { a.P = xs; a.strideP = x_stride; a.ldp = g.cols_pad; }
     else        { a.Q = xs; a.strideQ = x_stride; a.ldq = g.cols_pad; }
-    a.C = g.x + (src ? 0 : g.x_step);
+    a.C = fresh && !last ? fresh_x(fresh) : g.x + (src && !fresh ? 0 : g.x_step);
     a.strideE = a.strideC = x_stride;
     a.lde = a.ldc = g.cols_pad;
     if (op_field(code, OPF_E)) { a.E = xs; a.beta = st.ns_a; }
@@ -202,6 +211,7 @@ struct ChainArgs {
   int32_t ops, tasks;
   int32_t roll_polls;      // polls of the roll before it is closed without some
   int32_t patience;        // polls of one wait
+  int32_t fresh;           // every product has a buffer of its own, filled beforehand (FillArgs): no flags are needed
   GroupDesc group[kMaxMerged];
   ChainOp op[kMaxChainOps + 3];   // (looked through four at a time; those behind the last one end nowhere)
 };
@@ -209,6 +219,26 @@ static_assert(sizeof(ChainArgs) <= 4000, "an argument block holds 4 KB");
 // What every step clears before its products: the rolls and the flags of its chain launches, one after the other.
 constexpr int kMaxChains = 4;
 constexpr size_t kChainBytes = kMaxChains * sizeof(ChainRoll) + kMaxChainTasks * sizeof(uint32_t);
+
+// What the buffers of fresh chains are filled with before the products: no result holds it (a store turns it into another NaN), so
+// a reader sees of each value whether it has been written.  The tiles of a chain read and write whole multiples of 32 or 64; of these
+// the ones behind the next multiple of 32 are filled with the zeros of padding.
+constexpr uint32_t kUnwritten = 0xffffffffu;
+constexpr int kFillPieces = 1024;
+struct FillItem {
+  char* at;                // buffers of equal shape
+  uint32_t end;            // workgroups (of kFillPieces pieces of 16 bytes each) up to and including this item
+  uint32_t pieces;         // of this item
+  uint32_t rows, pitch;    // of a buffer: rows to fill, bytes from one to the next
+  uint32_t cover_rows, cover;   // rows, pieces of a row that results will stand in
+  uint32_t width;          // pieces of a row to fill
+  uint32_t stride;         // bytes from one buffer to the next
+};
+struct FillArgs {
+  int32_t n, groups;       // items, workgroups
+  FillItem item[2 * kMaxMerged * kMaxChains];
+};
+static_assert(2 * kMaxMerged * kMaxChains <= 64, "a lane for each item");
 
 // One launch of the kernel that takes a whole matrix through all its iterations in one workgroup.
 struct MatrixBatch {
@@ -239,10 +269,11 @@ hipError_t launch_state_update(const MatStatic* stat, const MatDynamic* dyn, con
                                float mu, float beta_a, float alpha, int use_prev, hipStream_t s);
 // norms, scales and the repair of flagged working copies
 // `list` (DEVICE, may be NULL = matrices 0 .. count - 1): the matrix indices to finalise; max_blocks: the most
-// elementwise blocks any of them has; zero: memory to clear on the way (a multiple of 16 bytes)
+// elementwise blocks any of them has; zero: memory to clear on the way (a multiple of 16 bytes); fill: buffers of fresh
+// chains to fill, or NULL
 hipError_t launch_norm_finalize(const MatStatic* stat, const double* partials, MatScale* scales,
                                 const int32_t* list, int count, int max_blocks, float eps, void* zero, size_t zero_bytes,
-                                hipStream_t s);
+                                const FillArgs* fill, hipStream_t s);
 // a one-matrix state prepared by one kernel from its arguments (no host copy): tables, scale, cleared workspace
 hipError_t launch_single_prepare(const MatStatic& ms, const MatDynamic& md, void* o_ptr, MatStatic* stat,
                                  MatDynamic* dyn, void** o_ptrs, BlockWork* work, int num_blocks, int32_t* members,

@@ -216,18 +216,21 @@ struct Geo {
   static constexpr bool kPrivate = WC == 1;         // every wavefront loads what it alone reads
   static constexpr int SLAB = T * 64;               // bytes of one operand's slab
   static constexpr int STAGE = KS * 2 * SLAB;
-  // wide: one workgroup per CU with 128 KB of ring; else two with 64 KB each
-  static constexpr int STAGES = (WIDE ? 131072 : 65536) / STAGE;
+  // wide: one workgroup per CU with 128 KB of ring (T = 32: 96, the shares of the sum behind it); else two with 64 KB each
+  static constexpr int STAGES = (T == 32 ? 98304 : WIDE ? 131072 : 65536) / STAGE;
   static constexpr int LDW = staged_ld(T);
   static constexpr int RING = STAGES * STAGE, STAGING = KS * T * LDW * 4;
-  static constexpr int LDS = RING > STAGING ? RING : STAGING;
+  static constexpr int SUM_AT = T == 32 ? RING : 0;
+  static constexpr int LDS = T == 32 ? RING + STAGING : RING > STAGING ? RING : STAGING;
   static_assert(T == 32 || T == 64 || T == 128, "32, 64 or 128");
 };
 
 // C tile (ti, tj) of matrix t.mat.  lds: Geo<E, T, WIDE>::LDS bytes, 256-byte aligned.  SHARED: other workgroups of this
-// launch write the operands and read the result.
-template <typename E, int T, bool WIDE, bool TP, bool TQ, bool SHARED>
-__device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, const TileMatrix& v, int tid, char* lds) {
+// launch write the operands and read the result (Sharing).  FRESH: every wavefront fetches its operands again until all of them
+// have been written, at most `patience` times; if one gives up, nothing is stored and the result is false.
+template <typename E, int T, bool WIDE, bool TP, bool TQ, int SHARED>
+__device__ __forceinline__ bool small_tile(const GemmArgs& a, const TileId& t, const TileMatrix& v, int tid, char* lds,
+                                           int patience = 0, uint32_t* gave_up = nullptr) {
   typedef Geo<E, T, WIDE> G;
   constexpr int ES = G::ES, CH = Chunk<E>::N;
   typedef typename Chunk<E>::vec vec_t;
@@ -238,8 +241,10 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, c
   const int m0 = t.ti * T, n0 = t.tj * T;
 
   // E operand of the epilogue: requested first, so that it has arrived long before it is used
-  vec_t ev[TileChunks<E, T, G::THREADS>::PER_LANE];
-  load_e<E, T, G::THREADS, SHARED>(a, t, tid, ev);
+  auto epilogue = [&]() {
+    if constexpr (T == 32) return Finish32<E, G::KS, SHARED>(a, t, v, tid);
+    else return FinishTile<E, T, G::KS, G::THREADS, SHARED>(a, t, tid);
+  }();
 
   // ---- direct loads: lane l of load q fetches unit S (16 bytes) of the slab ----
   constexpr int NL = G::kPrivate ? T / 16 : 2;      // loads per operand, wavefront and stage
@@ -264,17 +269,21 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, c
   });
   const size_t incp = TP ? (size_t)G::BK * a.ldp : (size_t)G::BK;
   const size_t incq = TQ ? (size_t)G::BK * a.ldq : (size_t)G::BK;
-  auto issue = [&](int stage, int kt) {
+  auto issue_p = [&](int stage, int kt) {
     char* const sp = lds + stage * G::STAGE + kg * 2 * G::SLAB + (G::kPrivate ? 0 : w4 * NL * 1024);
     static_for<NL>([&](auto q) {
       __builtin_amdgcn_global_load_lds((const MONA_AS1 void*)(gp[q] + kt * incp), (MONA_AS3 void*)(sp + q * 1024), 16, 0,
                                        SHARED ? kDeviceScope : 0);
     });
+  };
+  auto issue_q = [&](int stage, int kt) {
+    char* const sp = lds + stage * G::STAGE + kg * 2 * G::SLAB + (G::kPrivate ? 0 : w4 * NL * 1024);
     static_for<NL>([&](auto q) {
       __builtin_amdgcn_global_load_lds((const MONA_AS1 void*)(gq[q] + kt * incq),
                                        (MONA_AS3 void*)(sp + G::SLAB + q * 1024), 16, 0, SHARED ? kDeviceScope : 0);
     });
   };
+  auto issue = [&](int stage, int kt) { issue_p(stage, kt); issue_q(stage, kt); };
 
   // ---- fragment addresses, per lane, of stage 0 ----
   const uint32_t base = (uint32_t)(uintptr_t)(MONA_AS3 const char*)lds + kg * 2 * G::SLAB;
@@ -310,14 +319,39 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, c
 
   // one stage: fragment reads and products (the operand roles are swapped, so a block is accumulated transposed:
   // a lane holds one output row and, per group of four registers, four consecutive columns)
-  auto read_then = [&](int stage, auto&& after_reads) {
+  // FRESH: what of a stage has been read again and again until it was whole
+  auto whole = [&](int kt, int stage, auto&& read, auto&& look) {
+    read();
+    if constexpr (SHARED == FRESH) {
+      for (;;) {
+        Unwritten<E> p, q;
+        look([&](const auto& x) { p.see(x); }, [&](const auto& x) { q.see(x); });
+        const bool more_p = __any(p.any()), more_q = __any(q.any());
+        if (!more_p && !more_q) break;
+        if (patience <= 0) { *gave_up = 1u; break; }
+        --patience;
+        if (more_p) issue_p(stage, kt);
+        if (more_q) issue_q(stage, kt);
+        MONA_WAIT_VM(0);
+        read();
+      }
+    }
+  };
+  auto read_then = [&](int kt, int stage, auto&& after_reads) {
     const uint32_t so = stage * G::STAGE;
     if constexpr (T == 32 && ES == 2) {
       u32x4 ar[2], br[2];
       u32x2 al[2], ah[2], bl[2], bh[2];
-      if constexpr (!TP && !TQ) read1_rr(ar, br, fa[0] + so, fa[1] + so, fb[0] + so, fb[1] + so);
-      else if constexpr (!TP) read1_rt(ar, bl, bh, fa[0] + so, fa[1] + so, fb[0] + so);
-      else read1_tt(al, ah, bl, bh, fa[0] + so, fb[0] + so);
+      whole(kt, stage, [&]() {
+        if constexpr (!TP && !TQ) read1_rr(ar, br, fa[0] + so, fa[1] + so, fb[0] + so, fb[1] + so);
+        else if constexpr (!TP) read1_rt(ar, bl, bh, fa[0] + so, fa[1] + so, fb[0] + so);
+        else read1_tt(al, ah, bl, bh, fa[0] + so, fb[0] + so);
+      }, [&](auto&& p, auto&& q) {
+        static_for<2>([&](auto kk) {
+          if constexpr (TP) { p(al[kk]); p(ah[kk]); } else p(ar[kk]);
+          if constexpr (TQ) { q(bl[kk]); q(bh[kk]); } else q(br[kk]);
+        });
+      });
       after_reads();
       static_for<2>([&](auto kk) {
         bf16x8 pa, qb;
@@ -329,9 +363,14 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, c
       static_for<2>([&](auto kk) {
         f32x4 ar, br;
         float at[4], bt[4];
-        if constexpr (!TP && !TQ) read32_1_rr(ar, br, fa[kk] + so, fb[kk] + so);
-        else if constexpr (!TP) read32_1_rt<kk>(ar, bt, fa[kk] + so, fb[0] + so);
-        else read32_1_tt<kk>(at, bt, fa[0] + so, fb[0] + so);
+        whole(kt, stage, [&]() {
+          if constexpr (!TP && !TQ) read32_1_rr(ar, br, fa[kk] + so, fb[kk] + so);
+          else if constexpr (!TP) read32_1_rt<kk>(ar, bt, fa[kk] + so, fb[0] + so);
+          else read32_1_tt<kk>(at, bt, fa[0] + so, fb[0] + so);
+        }, [&](auto&& p, auto&& q) {
+          if constexpr (TP) static_for<4>([&](auto e) { p(at[e]); }); else p(ar);
+          if constexpr (TQ) static_for<4>([&](auto e) { q(bt[e]); }); else q(br);
+        });
         if constexpr (kk == 1) after_reads();
         static_for<4>([&](auto e) {
           float pa, qb;
@@ -343,14 +382,27 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, c
     } else if constexpr (ES == 2) {
       u32x4 ar[2][2], br[2][2];
       u32x2 al[2][2], ah[2][2], bl[2][2], bh[2][2];
-      if constexpr (!TP && !TQ) read_rr(ar, br, fa[0] + so, fa[1] + so, fb[0] + so, fb[1] + so);
-      else if constexpr (!TP) read_rt<T>(ar, bl, bh, fa[0] + so, fa[1] + so, fb[0] + so, fb[1] + so);
-      else read_tt<T>(al, ah, bl, bh, fa[0] + so, fa[1] + so, fb[0] + so, fb[1] + so);
+      auto rest = [&]() {
+        if constexpr (!TP && !TQ) rest_rr(ar, br);
+        else if constexpr (!TP) rest_rt(ar, bl, bh);
+        else rest_tt(al, ah, bl, bh);
+      };
+      whole(kt, stage, [&]() {
+        if constexpr (!TP && !TQ) read_rr(ar, br, fa[0] + so, fa[1] + so, fb[0] + so, fb[1] + so);
+        else if constexpr (!TP) read_rt<T>(ar, bl, bh, fa[0] + so, fa[1] + so, fb[0] + so, fb[1] + so);
+        else read_tt<T>(al, ah, bl, bh, fa[0] + so, fa[1] + so, fb[0] + so, fb[1] + so);
+        if constexpr (SHARED == FRESH) rest();
+      }, [&](auto&& p, auto&& q) {
+        static_for<2>([&](auto kk) {
+          static_for<2>([&](auto i) {
+            if constexpr (TP) { p(al[kk][i]); p(ah[kk][i]); } else p(ar[kk][i]);
+            if constexpr (TQ) { q(bl[kk][i]); q(bh[kk][i]); } else q(br[kk][i]);
+          });
+        });
+      });
       static_for<2>([&](auto kk) {
         if constexpr (kk == 1) {
-          if constexpr (!TP && !TQ) rest_rr(ar, br);
-          else if constexpr (!TP) rest_rt(ar, bl, bh);
-          else rest_tt(al, ah, bl, bh);
+          if constexpr (SHARED != FRESH) rest();
           after_reads();
         }
         static_for<2>([&](auto i) {
@@ -366,9 +418,16 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, c
       static_for<2>([&](auto kk) {
         f32x4 ar[2], br[2];
         float at[2][4], bt[2][4];
-        if constexpr (!TP && !TQ) read32_rr(ar, br, fa[kk] + so, fb[kk] + so);
-        else if constexpr (!TP) read32_rt<T, kk>(ar, bt, fa[kk] + so, fb[0] + so, fb[1] + so);
-        else read32_tt<T, kk>(at, bt, fa[0] + so, fa[1] + so, fb[0] + so, fb[1] + so);
+        whole(kt, stage, [&]() {
+          if constexpr (!TP && !TQ) read32_rr(ar, br, fa[kk] + so, fb[kk] + so);
+          else if constexpr (!TP) read32_rt<T, kk>(ar, bt, fa[kk] + so, fb[0] + so, fb[1] + so);
+          else read32_tt<T, kk>(at, bt, fa[0] + so, fa[1] + so, fb[0] + so, fb[1] + so);
+        }, [&](auto&& p, auto&& q) {
+          static_for<2>([&](auto i) {
+            if constexpr (TP) static_for<4>([&](auto e) { p(at[i][e]); }); else p(ar[i]);
+            if constexpr (TQ) static_for<4>([&](auto e) { q(bt[i][e]); }); else q(br[i]);
+          });
+        });
         if constexpr (kk == 1) after_reads();
         static_for<4>([&](auto e) {
           static_for<2>([&](auto i) {
@@ -384,8 +443,9 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, c
     }
   };
 
-  // stages this wavefront goes through: K is a multiple of 128, a whole number of slabs
-  const int KT = G::kPrivate ? (a.K / G::KB - kg + G::KS - 1) / G::KS : a.K / G::BK;
+  // stages this wavefront goes through: K is a multiple of 128, a whole number of slabs; slabs of padding alone are left out where
+  // every wavefront has its own
+  const int KT = G::kPrivate ? ((a.k_real + 31) / 32 * 32 / G::KB - kg + G::KS - 1) / G::KS : a.K / G::BK;
   constexpr int S = G::STAGES, LPS = 2 * NL;
   // wait until at most min(later, MAX) stages' loads are outstanding
   auto wait_stages = [&](int later) {
@@ -404,7 +464,7 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, c
     for (int kt = 0; kt < KT; ++kt) {
       const int later = KT - 1 - kt;
       wait_stages(later);
-      read_then(stage, [&]() { if (kt + S < KT) issue(stage, kt + S); });
+      read_then(kt, stage, [&]() { if (kt + S < KT) issue(stage, kt + S); });
       stage = stage + 1 == S ? 0 : stage + 1;
     }
   } else {
@@ -417,14 +477,14 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, c
       wait_stages(later);
       __builtin_amdgcn_s_barrier();     // bare: a fence would drain the loads in flight
       if (kt + S - 1 < KT) issue(stage == 0 ? S - 1 : stage - 1, kt + S - 1);
-      read_then(stage, []() {});
+      read_then(kt, stage, []() {});
       stage = stage + 1 == S ? 0 : stage + 1;
     }
   }
 
-  // ---- epilogue: the K shares of the tile meet in LDS, every global access is a 16-byte piece of a row ----
-  __syncthreads();                                  // every wavefront has finished reading operands
-  float* const sum = reinterpret_cast<float*>(lds);
+  // ---- epilogue: the K shares of the tile meet in LDS, every global access is a piece of a row ----
+  if constexpr (T != 32) __syncthreads();           // every wavefront has finished reading operands
+  float* const sum = reinterpret_cast<float*>(lds + G::SUM_AT);
   {
     float* const mine = sum + kg * T * G::LDW + (wm * 64 + frow) * G::LDW + wn * 64 + 4 * half;
     static_for<NB>([&](auto i) {
@@ -436,8 +496,22 @@ __device__ __forceinline__ void small_tile(const GemmArgs& a, const TileId& t, c
       });
     });
   }
+  if constexpr (SHARED == FRESH) {
+    // the E operand likewise, a wavefront's pieces at a time
+    while (a.E) {
+      Unwritten<E> u;
+      epilogue.see(u);
+      if (!__any(u.any())) break;
+      if (patience <= 0) { *gave_up = 1u; break; }
+      --patience;
+      epilogue.load_e(a, t);
+    }
+  }
   __syncthreads();
-  finish_tile<E, T, G::KS, G::THREADS, SHARED>(a, t, v, tid, ev, sum);
+  if constexpr (SHARED == FRESH)
+    if (__builtin_amdgcn_readfirstlane(*gave_up) != 0u) return false;
+  epilogue.run(a, t, v, sum);
+  return true;
 }
 
 // One workgroup per tile.  Group g of the batch owns the slots [slot_end[g - 1], slot_end[g]) of every die: workgroup
@@ -457,9 +531,9 @@ __global__ __launch_bounds__(WIDE ? 512 : 256) void ns_small_kernel(const GemmBa
   if (!t.valid) return;
   const TileMatrix v = look_up(a, t);
   auto run = [&](auto tile) {
-    if (!a.trans_p && !a.trans_q) small_tile<E, tile, WIDE, false, false, false>(a, t, v, threadIdx.x, lds);
-    else if (!a.trans_p) small_tile<E, tile, WIDE, false, true, false>(a, t, v, threadIdx.x, lds);
-    else small_tile<E, tile, WIDE, true, true, false>(a, t, v, threadIdx.x, lds);
+    if (!a.trans_p && !a.trans_q) small_tile<E, tile, WIDE, false, false, OWN_LAUNCH>(a, t, v, threadIdx.x, lds);
+    else if (!a.trans_p) small_tile<E, tile, WIDE, false, true, OWN_LAUNCH>(a, t, v, threadIdx.x, lds);
+    else small_tile<E, tile, WIDE, true, true, OWN_LAUNCH>(a, t, v, threadIdx.x, lds);
   };
   if constexpr (WIDE)
     if (a.tile_m == 32) { run(IC<32>{}); return; }
@@ -471,7 +545,15 @@ __global__ __launch_bounds__(WIDE ? 512 : 256) void ns_small_kernel(const GemmBa
 // A chain of small products is bound by what every launch of its own costs: 5 to 7 us with 16 to 100 tiles, of which the
 // products themselves are two to four.  Here the tiles of all products are tasks, numbered product by product in the
 // order of the chains; workgroup w of W takes the tasks w, w + W, w + 2 W, ..., waits for the tiles of its matrix in the
-// product before (ChainArgs::flags, one word a task), computes the tile and raises the task's flag.
+// product before, computes the tile and says so.  How it waits:
+//   * With a buffer for every product (NEW; the pool in mona_api.hip) the data are their own flag: the buffers are filled beforehand with a
+//     pattern that no result holds, and a wavefront fetches its share of the operands again until none of it is left (Unwritten, in
+//     whole() below).  That takes the wait for the stores, the flag's way and the fetch behind it out of every product, and no barrier
+//     stands before one.  A product takes 2.9 us then (1.2 to 1.5 from the last store to the last wavefront's operands, 2.8 where
+//     128 workgroups ask for the same B), 4 with flags.
+//   * Otherwise it polls a flag a task (ChainArgs::flags) of the tiles in the product before, and raises its own.
+// Measured, us per step, with flags -> without: 256 x 512 73 -> 59, 512 x 1408 114 -> 96, nine ragged matrices 83.5 -> 78 (filling 9 MB
+// takes 4 of it).
 //   * No workgroup waits for one that does not run.  W is not the size of the grid but the number of workgroups that have
 //     reported when the first of them closes the roll (all of the grid, unless the chip is busy with something else for
 //     c.roll_polls polls).  Tasks wait for lower numbers only, and a workgroup takes its own in order, so the lowest unfinished
@@ -491,7 +573,7 @@ __global__ __launch_bounds__(WIDE ? 512 : 256) void ns_small_kernel(const GemmBa
 //     another 2 us a step.
 //   * 32 x 32 tiles, K split between the eight wavefronts, where every one has a CU of its own: a tile of 64 x 64 takes 2.8 us
 //     with K = 256 and 4.4 with 512, one of 32 x 32 2.1 and 2.5 (the CU's own 64 bytes a cycle from L2, and latency).
-// Measured, us per step, launches -> chain: one 256 x 512 matrix 99 -> 73, 512 x 1408 without allocation 137 -> 114, nine ragged
+// Measured, us per step, launches -> chain with flags: one 256 x 512 matrix 99 -> 73, 512 x 1408 without allocation 137 -> 114, nine ragged
 // matrices in both precisions 189 -> 84 (which had waited for the host).  Tickets instead of fixed numbers, drawn by an atomic
 // operation for every task, and a counter of finished tiles instead of flags: 96, 189 and 133.
 constexpr uint32_t kRollClosed = 0x80000000u;
@@ -511,7 +593,7 @@ __device__ __forceinline__ void device_store(uint32_t* p, uint32_t v) {
 //
 // F32: some of the groups have fp32 products.  Both kinds of products together are 66 KB of code, bf16 alone 33 (256 x 512: 0.9 us a
 // step less; a CU shares 64 KB of instruction cache with another).
-template <bool F32>
+template <bool F32, bool NEW>
 __global__ __launch_bounds__(512) void ns_chain_kernel(const ChainArgs c) {
   constexpr int LB = Geo<bf16_t, 64, true>::LDS, LF = Geo<float, 64, true>::LDS;
   __shared__ __attribute__((aligned(256))) char lds[LB > LF ? LB : LF];
@@ -578,7 +660,9 @@ __global__ __launch_bounds__(512) void ns_chain_kernel(const ChainArgs c) {
     // the tiles of this matrix in the product before, 64 flags at a time
     const int per_mat = c.op[i].before_per_mat;
     const uint32_t* const before = c.flags + c.op[i].before + t.mat * per_mat;
-    if (threadIdx.x < 64) {
+    if constexpr (NEW) {
+      if (per_mat > 0 && c.patience <= 0 && threadIdx.x == 0) gave_up = 1u;
+    } else if (threadIdx.x < 64) {
       for (int at = 0; at < per_mat; at += 64) {
         const int k = at + (int)threadIdx.x;
         int patience = c.patience;
@@ -586,23 +670,33 @@ __global__ __launch_bounds__(512) void ns_chain_kernel(const ChainArgs c) {
         if (patience <= 0) { gave_up = 1u; break; }
       }
     }
-    __syncthreads();
-    if (__builtin_amdgcn_readfirstlane(gave_up) != 0u) break;
+    if constexpr (!NEW) {
+      __syncthreads();
+      if (__builtin_amdgcn_readfirstlane(gave_up) != 0u) break;
+    }
     // opaque: what the bodies below derive from the thread's number is not to be hoisted out of the loop, where twelve of
     // them would share the registers
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     auto run = [&](auto element, auto tile) {
       typedef decltype(element) E;
-      if (!a.trans_p && !a.trans_q) small_tile<E, tile, true, false, false, true>(a, t, v, tid, lds);
-      else if (!a.trans_p) small_tile<E, tile, true, false, true, true>(a, t, v, tid, lds);
-      else small_tile<E, tile, true, true, true, true>(a, t, v, tid, lds);
+      constexpr int SHARED = NEW ? FRESH : FLAGGED;
+      if (!a.trans_p && !a.trans_q) return small_tile<E, tile, true, false, false, SHARED>(a, t, v, tid, lds, c.patience, &gave_up);
+      if (!a.trans_p) return small_tile<E, tile, true, false, true, SHARED>(a, t, v, tid, lds, c.patience, &gave_up);
+      return small_tile<E, tile, true, true, true, SHARED>(a, t, v, tid, lds, c.patience, &gave_up);
     };
-    if (F32 && g.f32) { if constexpr (F32) { if (a.tile_m == 32) run(0.0f, IC<32>{}); else run(0.0f, IC<64>{}); } }
-    else { if (a.tile_m == 32) run(bf16_t{}, IC<32>{}); else run(bf16_t{}, IC<64>{}); }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // this wavefront's stores are where every die sees them
-    __syncthreads();
-    if (threadIdx.x == 0) device_store(c.flags + task, 1u);
+    bool whole;
+    if (F32 && g.f32) { if constexpr (F32) whole = a.tile_m == 32 ? run(0.0f, IC<32>{}) : run(0.0f, IC<64>{}); }
+    else whole = a.tile_m == 32 ? run(bf16_t{}, IC<32>{}) : run(bf16_t{}, IC<64>{});
+    if constexpr (NEW) {
+      // (the stores need not be waited for: the next tile may begin as soon as LDS has been read)
+      if (!whole) break;
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    } else {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // this wavefront's stores are where every die sees them
+      __syncthreads();
+      if (threadIdx.x == 0) device_store(c.flags + task, 1u);
+    }
     if (step <= 0) {
       if (step == 0) ask();
       if (workgroups == 0) break;
@@ -662,8 +756,9 @@ hipError_t launch_ns_chain(const ChainArgs& c, int wgs, hipStream_t s) {
   if (c.ops < 1 || c.ops > kMaxChainOps || c.tasks < 1 || wgs < 1) return hipErrorInvalidValue;
   bool f32 = false;
   for (int j = 0; j < kMaxMerged; ++j) f32 = f32 || c.group[j].f32;
-  if (f32) hipLaunchKernelGGL(ns_chain_kernel<true>, dim3(wgs), dim3(512), 0, s, c);
-  else hipLaunchKernelGGL(ns_chain_kernel<false>, dim3(wgs), dim3(512), 0, s, c);
+  auto* const kernel = c.fresh ? (f32 ? ns_chain_kernel<true, true> : ns_chain_kernel<false, true>)
+                               : (f32 ? ns_chain_kernel<true, false> : ns_chain_kernel<false, false>);
+  hipLaunchKernelGGL(kernel, dim3(wgs), dim3(512), 0, s, c);
   return hipGetLastError();
 }
 

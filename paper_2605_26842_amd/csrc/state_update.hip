@@ -9,6 +9,8 @@
 // A and G_{k-1}, and A_k = C_k + (1 - beta_a) G_k) it reads G, C, M and writes C, M and the copy: 22 B.
 #include "mona_internal.h"
 
+#include <type_traits>
+
 namespace mona {
 
 namespace {
@@ -195,7 +197,8 @@ __global__ __launch_bounds__(kEwThreads) void state_update_kernel(
 // sums, one wavefront per matrix before: 34 us for the 7 696 partial sums of a 3328 x 9472 matrix, 6 us for 1 536, and
 // 4 - 5 us more for a launch of its own that looked for flagged matrices; now 4 - 7 us in all where no matrix is flagged.
 //
-// The flags of the products that follow are cleared on the way (ns_chain_kernel).
+// The flags of the products that follow are cleared on the way, and (FILL) the buffers of fresh chains filled by workgroups behind
+// those of the matrices (ns_chain_kernel).
 //
 // The repair has to stay wide whatever the length of the list: one expert without gradients in a long list would
 // otherwise hold up every product behind it.  Where the list is too long for one workgroup to every kRepairBlocks
@@ -247,12 +250,38 @@ __device__ __forceinline__ void repair_copy(const MatStatic& ms, const MatScale&
   }
 }
 
+// What a chain's buffers hold before its products, by one workgroup (of `block`): kFillPieces pieces, all of one item.  (The item is
+// looked up by all lanes at once: one by one, each look is a round trip.)
+__device__ __forceinline__ void fill_pieces(const FillArgs& f, uint32_t block) {
+  const int lane = threadIdx.x & 63;
+  const uint64_t before = __ballot(lane < f.n && f.item[lane].end <= block);
+  const int i = __builtin_amdgcn_readfirstlane(__popcll(before));
+  const FillItem t = f.item[i];
+  const uint32_t first = i > 0 ? f.item[i - 1].end : 0u;
+#pragma unroll
+  for (int k = 0; k < kFillPieces / kEwThreads; ++k) {
+    const uint32_t at = (block - first) * kFillPieces + k * kEwThreads + threadIdx.x;
+    if (at >= t.pieces) break;
+    const uint32_t line = at / t.width, c = at - line * t.width, buffer = line / t.rows, r = line - buffer * t.rows;
+    const uint32_t v = r < t.cover_rows && c < t.cover ? kUnwritten : 0u;
+    *reinterpret_cast<uint4*>(t.at + (size_t)buffer * t.stride + (size_t)r * t.pitch + c * 16) = uint4{v, v, v, v};
+  }
+}
+
+struct NoFill {};
+template <typename Fill>
 __global__ __launch_bounds__(kEwThreads) void norm_finalize_kernel(const MatStatic* __restrict__ stat,
                                                                    const double* __restrict__ partials,
                                                                    MatScale* __restrict__ scales,
                                                                    const int32_t* __restrict__ list, float eps,
                                                                    int per_mat, int repair, uint4* __restrict__ zero,
-                                                                   int n16) {
+                                                                   int n16, const Fill fill, int norm_groups) {
+  if constexpr (!std::is_same_v<Fill, NoFill>) {
+    if ((int)blockIdx.x >= norm_groups) {
+      fill_pieces(fill, blockIdx.x - norm_groups);
+      return;
+    }
+  }
   __shared__ double red[kEwThreads / 64];
   __shared__ double total_sum;
   const int li = blockIdx.x / per_mat, part = blockIdx.x % per_mat;
@@ -289,7 +318,7 @@ __global__ __launch_bounds__(kEwThreads) void norm_finalize_kernel(const MatStat
   }
   r.inv2 = r.inv * r.inv;
   if (part == 0 && threadIdx.x == 0) scales[mat] = r;
-  for (int i = blockIdx.x * kEwThreads + threadIdx.x; i < n16; i += gridDim.x * kEwThreads) zero[i] = uint4{0u, 0u, 0u, 0u};
+  for (int i = blockIdx.x * kEwThreads + threadIdx.x; i < n16; i += norm_groups * kEwThreads) zero[i] = uint4{0u, 0u, 0u, 0u};
   if (repair && (r.status & 6u)) repair_copy(ms, r, part, per_mat);
 }
 
@@ -424,7 +453,7 @@ hipError_t launch_write_dyn(const DynTable& t, int n, MatDynamic* dyn, hipStream
 
 hipError_t launch_norm_finalize(const MatStatic* stat, const double* partials, MatScale* scales,
                                 const int32_t* list, int count, int max_blocks, float eps, void* zero, size_t zero_bytes,
-                                hipStream_t s) {
+                                const FillArgs* fill, hipStream_t s) {
   if (count <= 0) return hipSuccess;
   // Workgroups of kRepairBlocks blocks' worth of elements each, as long as all of them are resident at once (eight to a
   // CU); otherwise one a matrix, and the repair in a launch of its own.  Measured, us per step without and with one
@@ -434,8 +463,14 @@ hipError_t launch_norm_finalize(const MatStatic* stat, const double* partials, M
   int per_mat = (max_blocks + kRepairBlocks - 1) / kRepairBlocks;
   const bool apart = per_mat > 1 && (long long)count * per_mat > kRepairGroups;
   if (apart) per_mat = 1;
-  hipLaunchKernelGGL(norm_finalize_kernel, dim3(count * per_mat), dim3(kEwThreads), 0, s, stat, partials, scales, list,
-                     eps, per_mat, apart ? 0 : 1, static_cast<uint4*>(zero), (int)(zero_bytes / 16));
+  const int groups = count * per_mat;
+  if (fill && fill->groups > 0) {
+    hipLaunchKernelGGL(norm_finalize_kernel<FillArgs>, dim3(groups + fill->groups), dim3(kEwThreads), 0, s, stat, partials, scales, list,
+                       eps, per_mat, apart ? 0 : 1, static_cast<uint4*>(zero), (int)(zero_bytes / 16), *fill, groups);
+  } else {
+    hipLaunchKernelGGL(norm_finalize_kernel<NoFill>, dim3(groups), dim3(kEwThreads), 0, s, stat, partials, scales, list,
+                       eps, per_mat, apart ? 0 : 1, static_cast<uint4*>(zero), (int)(zero_bytes / 16), NoFill{}, groups);
+  }
   if (apart) {
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
