@@ -144,14 +144,15 @@ int main() {
       release(s);
     }
   {
-    // behind eight that fill the pool one runs with flags, and after the first has been freed the next has its part
+    // of nine the last finds no room and runs with flags (eight fit where nothing lies between them); after the first has been
+    // freed the next has its part
     std::vector<State> all;
     std::vector<char> used(pool.size(), 0);
     for (int i = 0; i < 9; ++i) {
       all.push_back(make({{1, 768, 768}}, 0));
-      step(all.back(), 5, i < 8, pool);
+      step(all.back(), 5, i < 6 ? 1 : i == 8 ? 0 : -1, pool);
       size_t shared = 0;
-      for (size_t k = 0; i < 8 && k < pool.size(); ++k)
+      for (size_t k = 0; k < pool.size(); ++k)
         if (pool[k] != kOutside) shared += used[k]++;
       EXPECT(shared == 0);
     }
