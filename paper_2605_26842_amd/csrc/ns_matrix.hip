@@ -20,10 +20,17 @@
 // and fro 53 instead of 46 % of the requests find their line in L2 (128 x 768 x 256 both ways; 60 instead of 58 % at 250 x 128 x 4000) and
 // 8 % less comes from behind it.  Letting the second panel of a pass arrive while the first is multiplied gains nothing on top.
 //
-// Measured, us per step, products in launches (or chains) -> here: 128 x 768 x 256 both ways 831 -> 626, 250 x 70 x 100 170 -> 45,
-// 256 x 256 x 256 426 -> 243, 300 x 128 x 128 202 -> 82, one 128 x 128 57 -> 31.  A panel costs 2.2 us an iteration (P = 128) or
+// P = 256: nobody reads the renewed panel in LDS, so it is not renewed there: each wavefront turns its own values into rows in 4 KB of its
+// own and stores them while the other one of its SIMD multiplies, and the workgroup meets once a panel instead of three times.  Cycles a
+// panel of 768 x 256, the wait for it / multiplying / renewing / storing: 1.1k / 3.0k / 4.8k / 0.95k before, 2.6k / 3.0k / 1.8k / 1.4k now; what
+// is left of the wait is the way from behind L2.  us per step: 128 x 768 x 256 both ways 622 -> 611, 128 x 256 x 1024 532 -> 513, 115 x 256 x 512
+// 289 -> 278, 256 x 256 x 256 246 -> 236.  W in pieces of 4 values where its rows are no multiple of 8: 256 x 200 x 700 558 -> 503,
+// 250 x 70 x 100 49 -> 46.
+//
+// Measured, us per step, products in launches (or chains) -> here: 128 x 768 x 256 both ways 831 -> 611, 250 x 70 x 100 170 -> 45,
+// 256 x 256 x 256 426 -> 236, 300 x 128 x 128 202 -> 82, one 128 x 128 57 -> 31.  A panel costs 2.2 us an iteration (P = 128) or
 // 7.3 us (P = 256, twice) on a CU, of which the multiplications are 1 and 4: the wavefronts meet three
-// times a panel, and the vector instructions of the epilogue (2.5 an element) do not run beside matrix instructions.
+// times a panel (P = 128), and the vector instructions of the epilogue (2.5 an element) do not run beside matrix instructions.
 //
 // LDS: rows of 256 or 512 bytes, chunk c (16 bytes) of row r at c ^ swizzle(r): 16 consecutive rows hit 16 different
 // chunks (row-major fragments, one ds_read_b128), four consecutive rows four different groups of 64 bytes (K-major ones, two
@@ -43,7 +50,8 @@ struct MatGeo {
   static constexpr int PANEL = P * kPanel * 2, SQUARE = P * P * 2;
   static constexpr int RESIDENT = P == 128 ? 4 : 0;            // panels that may stay in LDS
   static constexpr int PANELS_AT = P == 128 ? SQUARE : 0;      // where the panels begin
-  static constexpr int LDS = P == 128 ? SQUARE + RESIDENT * PANEL : 2 * PANEL;
+  static constexpr int STAGING_AT = 2 * PANEL, STAGING = 4096; // P = 256: 32 rows of 128 bytes for each wavefront
+  static constexpr int LDS = P == 128 ? SQUARE + RESIDENT * PANEL : STAGING_AT + kMatWaves * STAGING;
   static constexpr int GM = P / 64, GN = P / 128;              // 32 x 32 blocks of a wavefront in a P x P product (2 x 4 wavefronts)
   static constexpr int RB = P / 128, CB = 2;                   // in the apply (4 wavefronts along p, 2 along the panel)
   static constexpr int KS = P / 16;                            // products along p
@@ -238,6 +246,31 @@ __device__ __forceinline__ void run_matrix(const StepDesc& st, const GroupDesc& 
     return __builtin_bit_cast(u32x2, r);
   };
 
+  // W <- (1 - eta lambda) W - eta gamma O, O as stored in the working precision, of 8 values of a row
+  auto update = [&](const bf16x8& o, int wr, int wc) {
+    if (wr >= g.m || wc >= g.n) return;
+    const size_t wi = (size_t)wr * g.n + wc;
+    auto some = [&](auto* const p, auto count) {      // `count` neighbours at a time
+      typedef std::remove_pointer_t<decltype(p + 0)> W;
+      constexpr int N = decltype(count)::value;
+      typedef W vec __attribute__((ext_vector_type(N)));
+      static_for<8 / N>([&](auto q) {
+        if (wc + q * N >= g.n) return;
+        vec* const at = reinterpret_cast<vec*>(p + q * N);
+        vec w = *at;
+#pragma unroll
+        for (int e = 0; e < N; ++e) w[e] = (W)fmaf(st.w_keep, (float)w[e], -(g.o_scale * (float)o[q * N + e]));
+        *at = w;
+      });
+    };
+    auto row = [&](auto* const p) {
+      if (sizeof(*p) == 2 && g.n % 8 == 0) { if constexpr (sizeof(*p) == 2) some(p, IC<8>{}); }
+      else if (g.n % 4 == 0) some(p, IC<4>{});
+      else some(p, IC<1>{});
+    };
+    if (w_is_bf16) row(static_cast<bf16_t*>(wptr) + wi); else row(static_cast<float*>(wptr) + wi);
+  };
+
   // ---- apply: wavefront (rg, cg) has rows rg P / 4 .., columns 64 cg .. of the panel ----
   const int rg = wave >> 1, cg = wave & 1;
   const int pr = rg * (P / 4);
@@ -413,59 +446,49 @@ __device__ __forceinline__ void run_matrix(const StepDesc& st, const GroupDesc& 
           asm volatile("" ::: "memory");
         });
       });
-      meet();
-      static_for<G::RB>([&](auto i) {
-        static_for<G::CB>([&](auto c) {
-          static_for<4>([&](auto v) { panel8(i, c, v) = out[i][c][v]; });
+      if constexpr (G::kFused) {
+        meet();
+        static_for<G::RB>([&](auto i) {
+          static_for<G::CB>([&](auto c) {
+            static_for<4>([&](auto v) { panel8(i, c, v) = out[i][c][v]; });
+          });
         });
-      });
-      meet();
-      // to memory, 16 bytes a lane along the rows (between iterations resident panels stay where they are)
-      const char* const unit = lds + at + (wave * 64 + L2.lane) * 16;
-      if (last ? store_o != 0 : !resident) {
-        bf16_t* const p = to + unit_at(L2, j);
-        static_for<UNITS>([&](auto i) {
-          *reinterpret_cast<u32x4*>(p + (size_t)(i * ROWS) * ld) = *reinterpret_cast<const u32x4*>(unit + i * kMatThreads * 16);
-        });
-      }
-      if (last && !skip_w) {
-        // W <- (1 - eta lambda) W - eta gamma O, O as stored in the working precision
-        const bool vec = g.n % 8 == 0;
-        static_for<UNITS>([&](auto i) {
-          const int u = i * kMatThreads + wave * 64 + L2.lane, row = u / CPR, c = (u % CPR) ^ swizzle(row);
-          const int wr = TALL ? j * kPanel + row : row, wc = TALL ? c * 8 : j * kPanel + c * 8;
-          if (wr < g.m && wc < g.n) {
-            const bf16x8 o = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(unit + i * kMatThreads * 16));
-            const size_t wi = (size_t)wr * g.n + wc;
-            if (vec && w_is_bf16) {
-              bf16x8* const p = reinterpret_cast<bf16x8*>(static_cast<bf16_t*>(wptr) + wi);
-              bf16x8 w = *p;
-#pragma unroll
-              for (int e = 0; e < 8; ++e) w[e] = (bf16_t)fmaf(st.w_keep, (float)w[e], -(g.o_scale * (float)o[e]));
-              *p = w;
-            } else if (vec) {
-              f32x4* const p = reinterpret_cast<f32x4*>(static_cast<float*>(wptr) + wi);
-              static_for<2>([&](auto q) {
-                f32x4 w = p[q];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) w[e] = fmaf(st.w_keep, w[e], -(g.o_scale * (float)o[q * 4 + e]));
-                p[q] = w;
-              });
-            } else {
-#pragma unroll
-              for (int e = 0; e < 8; ++e) {
-                if (wc + e < g.n) {
-                  if (w_is_bf16) {
-                    bf16_t* const p = static_cast<bf16_t*>(wptr) + wi + e;
-                    *p = (bf16_t)fmaf(st.w_keep, (float)*p, -(g.o_scale * (float)o[e]));
-                  } else {
-                    float* const p = static_cast<float*>(wptr) + wi + e;
-                    *p = fmaf(st.w_keep, *p, -(g.o_scale * (float)o[e]));
-                  }
-                }
-              }
-            }
-          }
+        meet();
+        // to memory, 16 bytes a lane along the rows (between iterations resident panels stay where they are)
+        const char* const unit = lds + at + (wave * 64 + L2.lane) * 16;
+        if (last ? store_o != 0 : !resident) {
+          bf16_t* const p = to + unit_at(L2, j);
+          static_for<UNITS>([&](auto i) {
+            *reinterpret_cast<u32x4*>(p + (size_t)(i * ROWS) * ld) = *reinterpret_cast<const u32x4*>(unit + i * kMatThreads * 16);
+          });
+        }
+        if (last && !skip_w) {
+          static_for<UNITS>([&](auto i) {
+            const int u = i * kMatThreads + wave * 64 + L2.lane, row = u / CPR, c = (u % CPR) ^ swizzle(row);
+            update(__builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(unit + i * kMatThreads * 16)),
+                   TALL ? j * kPanel + row : row, TALL ? c * 8 : j * kPanel + c * 8);
+          });
+        }
+      } else {
+        // Nobody reads the new values here, so the panel is left as it is and the wavefronts need not meet: each turns its own into rows
+        // in a place of its own, 32 rows of 64 values at a time (chunk c of row r at c ^ (r mod 8)), and stores them, 8 rows of 128
+        // bytes to an instruction, while the other one of its SIMD multiplies.
+        char* const mine = lds + G::STAGING_AT + wave * G::STAGING;
+        const int first_row = TALL ? j * kPanel + cg * 64 : pr, first_col = TALL ? pr : j * kPanel + cg * 64;
+        static_for<2>([&](auto rb) {
+          static_for<2>([&](auto cb) {
+            static_for<4>([&](auto v) {
+              const int chunk = (4 * cb + v) ^ (L2.frow & 7);
+              *reinterpret_cast<u32x2*>(mine + L2.frow * 128 + chunk * 16 + L2.half * 8) = TALL ? out[cb][rb][v] : out[rb][cb][v];
+            });
+          });
+          const int r8 = L2.lane >> 3, c8 = L2.lane & 7;
+          u32x4 x[4];
+          static_for<4>([&](auto k) { x[k] = *reinterpret_cast<const u32x4*>(mine + (8 * k + r8) * 128 + ((c8 ^ r8) << 4)); });
+          const int row = first_row + rb * 32 + r8, col = first_col + c8 * 8;
+          bf16_t* const p = to + (size_t)row * ld + col;
+          if (!last || store_o) static_for<4>([&](auto k) { *reinterpret_cast<u32x4*>(p + (size_t)(8 * k) * ld) = x[k]; });
+          if (last && !skip_w) static_for<4>([&](auto k) { update(__builtin_bit_cast(bf16x8, x[k]), row + 8 * k, col); });
         });
       }
       if (G::kFused && !last) gram(at);
