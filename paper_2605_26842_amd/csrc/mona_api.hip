@@ -107,6 +107,7 @@ struct Layout {
   std::vector<BlockWork> blocks;       // ordered: fp32-gradient matrices first, then bf16
   std::vector<int> first_block, num_blocks;
   int max_blocks = 0;                  // most blocks of any matrix
+  int keep = 0;                        // what the caches are to keep of the elementwise pass
   // The block table is ordered: early groups (fp32-gradient matrices, then bf16), then the late group (same).
   int range_end[4] = {0, 0, 0, 0};     // ends of those four ranges of blocks
   std::vector<Unit> units;             // what the products of the groups are launched as, in launch order per lane
@@ -253,6 +254,17 @@ bool all_in_a_chain(const Layout& L) {
     for (int i = 0; i < 2; ++i) { tiles[i] += of[i]; work[i] += of[i] * k[i]; }
   }
   return std::max(tiles[0], tiles[1]) <= kChainTiles && std::max(work[0], work[1]) <= kChainWork;
+}
+
+// What the elementwise pass moves: reads G, G_prev, A, M; writes G_prev, A, M and the working copy of M (one-buffer form: C in place of
+// G_prev and A).
+double pass_bytes(const Layout& L, const mona_matrix* mats) {
+  double bytes = 0.0;
+  for (int i = 0; i < L.count; ++i) {
+    const double gsz = mats[i].g_dtype == MONA_BF16 ? 2 : 4, aux = (L.one_buffer ? 1 : 2) * L.ssize;
+    bytes += (double)mats[i].m * mats[i].n * (gsz + aux + 4 + aux + 4 + L.groups[L.group_of[i]].esize);
+  }
+  return bytes;
 }
 
 // Streams and order of the step.
@@ -493,6 +505,10 @@ void build_layout(const mona_matrix* mats, int count, const mona_options& opt, b
     L.gfx950 = device_is_gfx950();
     plan_lanes(L, opt);
   }
+
+  double copies = 0.0;
+  for (const Group& g : L.groups) copies += (double)g.m * g.n * (double)g.members.size() * g.esize;
+  L.keep = choose_keep(pass_bytes(L, mats), copies);
 
   // elementwise work table
   L.first_block.assign(count, 0);
@@ -1401,9 +1417,14 @@ int mona_step_streaming(mona_state* st, const mona_matrix* mats, void* const* sl
 
 namespace {
 
+// Whether one launch does all that stands before the products (launch_begin): the step of a few small matrices.
+bool begins_at_once(const mona_state* st, const Plan& plan) {
+  return !plan.chains.empty() && st->profiling < 2 && st->L.count <= kBeginMats && st->L.late_group < 0;
+}
+
 // Enqueues the kernels of one step (Alg. 1 for every matrix) on `s` and the side streams.  The per-matrix
-// tables in the arena must already name this step's w / g pointers.
-int enqueue_step(mona_state* st, const mona_hparams* hp, hipStream_t s) {
+// tables in the arena must already name this step's w / g pointers, or (steps that begin at once) `table` does.
+int enqueue_step(mona_state* st, const mona_hparams* hp, hipStream_t s, const BeginTable* table) {
   Layout& L = st->L;
   const int count = L.count;
   const MatStatic* stat = st->at<MatStatic>(L.stat_off);
@@ -1467,7 +1488,7 @@ int enqueue_step(mona_state* st, const mona_hparams* hp, hipStream_t s) {
   const int32_t* order = st->at<int32_t>(L.order_off);
   auto pass = [&](int r0, int r1, int g_bf16, hipStream_t q) {
     return launch_state_update(stat, dyn, blocks + r0, partials + r0, r1 - r0, g_bf16, sbf, one, hp->momentum,
-                               hp->beta_a, hp->alpha, use_prev, q);
+                               hp->beta_a, hp->alpha, use_prev, L.keep, q);
   };
   if (overlap) {
     STEP_TRY(hipEventRecord(st->late_fork, s));
@@ -1479,14 +1500,21 @@ int enqueue_step(mona_state* st, const mona_hparams* hp, hipStream_t s) {
                                   L.max_blocks, hp->ns_eps, nullptr, 0, nullptr, st->late_stream));
     STEP_TRY(hipEventRecord(st->late_done, st->late_stream));
   }
-  STEP_TRY(pass(0, L.range_end[0], 0, s));
-  STEP_TRY(pass(L.range_end[0], L.range_end[1], 1, s));
-  if (!overlap) {
-    STEP_TRY(pass(L.range_end[1], L.range_end[2], 0, s));
-    STEP_TRY(pass(L.range_end[2], L.range_end[3], 1, s));
+  const bool at_once = begins_at_once(st, plan);
+  if (at_once) {
+    const BeginTable none = {};
+    STEP_TRY(launch_begin(stat, blocks, scales, partials, st->at<MatDynamic>(L.dyn_off), nblocks, sbf, one, hp->momentum, hp->beta_a,
+                          hp->alpha, use_prev, hp->ns_eps, st->arena + L.chain_off, plan.chain_bytes, plan.fill, table ? *table : none, s));
+  } else {
+    STEP_TRY(pass(0, L.range_end[0], 0, s));
+    STEP_TRY(pass(L.range_end[0], L.range_end[1], 1, s));
+    if (!overlap) {
+      STEP_TRY(pass(L.range_end[1], L.range_end[2], 0, s));
+      STEP_TRY(pass(L.range_end[2], L.range_end[3], 1, s));
+    }
   }
   if (L.one_buffer && !muon_only) st->last_beta_a = hp->beta_a;
-  STEP_TRY(launch_norm_finalize(stat, partials, scales, order, overlap ? L.num_early : count, L.max_blocks, hp->ns_eps,
+  if (!at_once) STEP_TRY(launch_norm_finalize(stat, partials, scales, order, overlap ? L.num_early : count, L.max_blocks, hp->ns_eps,
                                 st->arena + L.chain_off, plan.chain_bytes, &plan.fill, s));
   if (prof) STEP_TRY(hipEventRecord(ev[1], s));
 
@@ -1629,6 +1657,8 @@ int step_impl(mona_state* st, const mona_matrix* mats, void* const* slots, int32
     HIP_TRY(hipStreamIsCapturing(s, &cap));
     if (cap != hipStreamCaptureStatusNone) st->captured = true;
   }
+  BeginTable table;
+  table.n = 0;
   bool changed = !st->dyn_valid || st->captured;
   if (!changed)
     for (int i = 0; i < count; ++i)
@@ -1642,7 +1672,10 @@ int step_impl(mona_state* st, const mona_matrix* mats, void* const* slots, int32
       st->last_dyn[i].g = mats[i].g;
       st->last_dyn[i].slot = slots ? slots[i] : nullptr;
     }
-    if (count <= kInlineMats || st->captured) {
+    if (begins_at_once(st, plan_for(st, *hp))) {
+      table.n = count;
+      std::copy(st->last_dyn.begin(), st->last_dyn.end(), table.v);
+    } else if (count <= kInlineMats || st->captured) {
       for (int first = 0; first < count; first += kInlineMats) {
         const int n = std::min(kInlineMats, count - first);
         DynTable t;
@@ -1660,10 +1693,11 @@ int step_impl(mona_state* st, const mona_matrix* mats, void* const* slots, int32
       st->ring_used[slot] = true;
       st->ring_next = (slot + 1) % kRing;
     }
-    st->dyn_valid = true;
+    st->dyn_valid = table.n == 0;
   }
-  rc = enqueue_step(st, hp, s);
+  rc = enqueue_step(st, hp, s, &table);
   if (rc) return rc;
+  st->dyn_valid = true;
   note_unstable_alpha(hp);
   return MONA_OK;
 }
@@ -1753,7 +1787,7 @@ int mona_step_noalloc(const mona_matrix* mat, const mona_options* opts, void* g_
                                 reinterpret_cast<int32_t*>(base + L.groups[0].members_off),
                                 st.at<int32_t>(L.order_off), st.at<MatScale>(L.scales_off), base + L.work_begin,
                                 padded ? clear : 0, s));
-  rc = enqueue_step(&st, hp, s);
+  rc = enqueue_step(&st, hp, s, nullptr);
   if (rc) return rc;
   note_unstable_alpha(hp);
   return MONA_OK;
@@ -1954,15 +1988,7 @@ int mona_plan_info(mona_state* st, int32_t ns_steps, int64_t* launches_out, doub
     launches += (int64_t)lane.size();
     for (const Launch& l : lane) flops += launch_flops(plan, l);
   }
-  double bytes = 0.0;
-  for (int i = 0; i < L.count; ++i) {
-    const double ne = (double)st->mats[i].m * st->mats[i].n;
-    const double gsz = st->mats[i].g_dtype == MONA_BF16 ? 2 : 4;
-    // state pass: read G, G_prev, A, M; write G_prev, A, M and the working copy of M
-    // (one-buffer form: C in place of G_prev and A)
-    const double aux = (L.one_buffer ? 1 : 2) * L.ssize;
-    bytes += ne * (gsz + aux + 4 + aux + 4 + L.groups[L.group_of[i]].esize);
-  }
+  const double bytes = pass_bytes(L, st->mats.data());
   if (launches_out) *launches_out = launches;
   if (ns_flops_executed_out) *ns_flops_executed_out = flops;
   if (elementwise_bytes_out) *elementwise_bytes_out = bytes;

@@ -38,6 +38,7 @@ struct MatScale {
   float norm;       // ||M||_F
   uint32_t status;  // MONA_STATUS_* bits
   int32_t xexp;     // the working copy holds M 2^xexp (0 unless the norm left the safe window)
+  uint32_t arrived; // workgroups that have finished their part of the matrix in the launch that begins a small step; 0 outside of it
 };
 
 // One entry per block of the elementwise grid.
@@ -261,12 +262,22 @@ struct DynTable {
   MatDynamic v[kInlineMats];
 };
 
+// the same for the launch that begins a small step; n = 0: the table in memory holds them
+constexpr int kBeginMats = 32;
+struct BeginTable {
+  int32_t n;
+  MatDynamic v[kBeginMats];
+};
+static_assert(sizeof(FillArgs) + sizeof(BeginTable) + 128 <= 4000, "an argument block holds 4 KB");
+
 // kernels (defined in the .hip files)
 // dyn[0 .. n) = t.v[0 .. n), n <= kInlineMats
 hipError_t launch_write_dyn(const DynTable& t, int n, MatDynamic* dyn, hipStream_t s);
 hipError_t launch_state_update(const MatStatic* stat, const MatDynamic* dyn, const BlockWork* work,
                                double* partials, int num_blocks, int g_bf16, int state_bf16, int one_buffer,
-                               float mu, float beta_a, float alpha, int use_prev, hipStream_t s);
+                               float mu, float beta_a, float alpha, int use_prev, int keep, hipStream_t s);
+// what the caches are to keep of a pass over all matrices that moves so many bytes, so many of them working copies
+int choose_keep(double pass_bytes, double copy_bytes);
 // norms, scales and the repair of flagged working copies
 // `list` (DEVICE, may be NULL = matrices 0 .. count - 1): the matrix indices to finalise; max_blocks: the most
 // elementwise blocks any of them has; zero: memory to clear on the way (a multiple of 16 bytes); fill: buffers of fresh
@@ -274,6 +285,11 @@ hipError_t launch_state_update(const MatStatic* stat, const MatDynamic* dyn, con
 hipError_t launch_norm_finalize(const MatStatic* stat, const double* partials, MatScale* scales,
                                 const int32_t* list, int count, int max_blocks, float eps, void* zero, size_t zero_bytes,
                                 const FillArgs* fill, hipStream_t s);
+// the elementwise pass of matrices of any gradient dtype with what launch_write_dyn and launch_norm_finalize do, as one launch; the
+// matrices are few and small (`partials` in the order of `work`, all of a matrix's blocks in it)
+hipError_t launch_begin(const MatStatic* stat, const BlockWork* work, MatScale* scales, double* partials, MatDynamic* dyn, int num_blocks,
+                        int state_bf16, int one_buffer, float mu, float beta_a, float alpha, int use_prev, float eps, void* zero,
+                        size_t zero_bytes, const FillArgs& fill, const BeginTable& table, hipStream_t s);
 // a one-matrix state prepared by one kernel from its arguments (no host copy): tables, scale, cleared workspace
 hipError_t launch_single_prepare(const MatStatic& ms, const MatDynamic& md, void* o_ptr, MatStatic* stat,
                                  MatDynamic* dyn, void** o_ptrs, BlockWork* work, int num_blocks, int32_t* members,

@@ -18,20 +18,29 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef bf16_t bf16x4 __attribute__((ext_vector_type(4)));
 
-// The state is streamed: every array is read once and written once per step and is not touched
-// again before the next step, so the accesses are marked non-temporal.
-template <typename V> __device__ __forceinline__ V stream_load(const V* p) { return __builtin_nontemporal_load(p); }
-template <typename V> __device__ __forceinline__ void stream_store(V* p, V v) { __builtin_nontemporal_store(v, p); }
-__device__ __forceinline__ f32x4 load4(const float* p) { return stream_load(reinterpret_cast<const f32x4*>(p)); }
-__device__ __forceinline__ f32x4 load4(const bf16_t* p) {
-  bf16x4 v = stream_load(reinterpret_cast<const bf16x4*>(p));
+// What of a pass the caches are to keep (choose_keep).  Non-temporal accesses leave nothing of an array that is read once and written
+// once in the 256 MB cache behind the L2s.  Measured, us per pass, with nothing / the working copy / everything kept: 64 x 1000 x 2000
+// 725 / 676 / -, 64 x 768 x 768 200 / 188 / -, 128 x 768 x 256 both ways 261 / 247 / -, 128 x 1000 x 2000 1452 / 1401 / -, 256 x 1000 x 2000 2927 /
+// 2897 / -, 32 x 4096 x 4096 2896 / 2934 / -, 200 x 257 x 130 (200 MB in all) 47 / 45 / 38.
+enum Keep : int { KEEP_NOTHING = 0, KEEP_COPY = 1, KEEP_ALL = 2 };
+template <bool STREAM, typename V> __device__ __forceinline__ V load(const V* p) {
+  if constexpr (STREAM) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+template <bool STREAM, typename V> __device__ __forceinline__ void store(V* p, V v) {
+  if constexpr (STREAM) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+template <bool STREAM> __device__ __forceinline__ f32x4 load4(const float* p) { return load<STREAM>(reinterpret_cast<const f32x4*>(p)); }
+template <bool STREAM> __device__ __forceinline__ f32x4 load4(const bf16_t* p) {
+  bf16x4 v = load<STREAM>(reinterpret_cast<const bf16x4*>(p));
   f32x4 r = {(float)v.x, (float)v.y, (float)v.z, (float)v.w};
   return r;
 }
-__device__ __forceinline__ void store4(float* p, f32x4 v) { stream_store(reinterpret_cast<f32x4*>(p), v); }
-__device__ __forceinline__ void store4(bf16_t* p, f32x4 v) {
+template <bool STREAM> __device__ __forceinline__ void store4(float* p, f32x4 v) { store<STREAM>(reinterpret_cast<f32x4*>(p), v); }
+template <bool STREAM> __device__ __forceinline__ void store4(bf16_t* p, f32x4 v) {
   bf16x4 r = {(bf16_t)v.x, (bf16_t)v.y, (bf16_t)v.z, (bf16_t)v.w};  // round to nearest even
-  stream_store(reinterpret_cast<bf16x4*>(p), r);
+  store<STREAM>(reinterpret_cast<bf16x4*>(p), r);
 }
 __device__ __forceinline__ float load1(const float* p) { return *p; }
 __device__ __forceinline__ float load1(const bf16_t* p) { return (float)*p; }
@@ -83,48 +92,95 @@ __device__ __forceinline__ float mona_element_one_buffer(float g, float& cbuf, f
 
 enum StateMode : int { MODE_MUON = 0, MODE_TWO_BUFFER = 1, MODE_ONE_BUFFER = 2 };
 
+// An array whose values a later reader in the same launch may need (M and its working copy) goes through to memory (THROUGH: device
+// scope, the array is below 4 GB).
+constexpr int kDeviceScope = 16;   // sc1
+template <bool THROUGH, bool STREAM>
+struct Out {
+  char* p;
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ explicit Out(void* base) : p(static_cast<char*>(base)) {
+    if constexpr (THROUGH) r = __builtin_amdgcn_make_buffer_rsrc(base, 0, -1, 0x00020000);
+  }
+  __device__ __forceinline__ void put4(int64_t i, f32x4 v, bool f32) const {
+    if constexpr (!THROUGH) {
+      if (f32) store4<STREAM>(reinterpret_cast<float*>(p) + i, v); else store4<STREAM>(reinterpret_cast<bf16_t*>(p) + i, v);
+    } else if (f32) {
+      typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, (int)(uint32_t)(i * 4), 0, kDeviceScope);
+    } else {
+      typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+      const bf16x4 h = {(bf16_t)v.x, (bf16_t)v.y, (bf16_t)v.z, (bf16_t)v.w};
+      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, h), r, (int)(uint32_t)(i * 2), 0, kDeviceScope);
+    }
+  }
+  __device__ __forceinline__ void put2(int64_t i, float a, float b, bool f32) const {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef bf16_t bf16x2 __attribute__((ext_vector_type(2)));
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    const f32x2 v = {a, b};
+    const bf16x2 h = {(bf16_t)a, (bf16_t)b};
+    if constexpr (!THROUGH) {
+      if (f32) *reinterpret_cast<f32x2*>(reinterpret_cast<float*>(p) + i) = v; else *reinterpret_cast<bf16x2*>(reinterpret_cast<bf16_t*>(p) + i) = h;
+    } else if (f32) {
+      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)(uint32_t)(i * 4), 0, kDeviceScope);
+    } else {
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, h), r, (int)(uint32_t)(i * 2), 0, kDeviceScope);
+    }
+  }
+  __device__ __forceinline__ void put(int64_t i, float v, bool f32) const {
+    if constexpr (!THROUGH) {
+      if (f32) reinterpret_cast<float*>(p)[i] = v; else reinterpret_cast<bf16_t*>(p)[i] = (bf16_t)v;
+    } else if (f32) {
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, (int)(uint32_t)(i * 4), 0, kDeviceScope);
+    } else {
+      __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, (bf16_t)v), r, (int)(uint32_t)(i * 2), 0, kDeviceScope);
+    }
+  }
+};
+
 // MODE_MUON is plain Muon (Eq. muon_momentum fed with G_k itself): the acceleration buffers
 // are neither read nor written.
-template <typename GT, typename ST, int MODE>
-__global__ __launch_bounds__(kEwThreads) void state_update_kernel(
-    const MatStatic* __restrict__ stat, const MatDynamic* __restrict__ dyn,
-    const BlockWork* __restrict__ work, double* __restrict__ partials, Coef c) {
-  __shared__ double red[kEwThreads / 64];
-  const BlockWork bw = work[blockIdx.x];
-  const MatStatic ms = stat[bw.mat];
-  const GT* __restrict__ g = static_cast<const GT*>(dyn[bw.mat].g);
+// One chunk of a matrix by one workgroup; returns this thread's share of the sum of squares.
+template <typename GT, typename ST, int MODE, int KEEP, bool THROUGH>
+__device__ __forceinline__ double update_chunk(const MatStatic& ms, const MatDynamic& md, int chunk, const Coef& c) {
+  const GT* __restrict__ g = static_cast<const GT*>(md.g);
   // G_{k-1} lives in the arena, or (streaming variant) in the slot the caller keeps
-  ST* __restrict__ gp = static_cast<ST*>(ms.g_prev ? ms.g_prev : dyn[bw.mat].slot);
+  ST* __restrict__ gp = static_cast<ST*>(ms.g_prev ? ms.g_prev : md.slot);
   ST* __restrict__ ac = static_cast<ST*>(ms.acc);
   float* __restrict__ mo = ms.mom;
   // working copy of M_k for the matrix products: bf16, or fp32 for matrices orthogonalised in fp32
+  constexpr bool STREAM = KEEP != KEEP_ALL;
+  const Out<THROUGH, STREAM> mom(ms.mom);
+  const Out<THROUGH, KEEP == KEEP_NOTHING> x(ms.x);
   bf16_t* __restrict__ xh = static_cast<bf16_t*>(ms.x);
   float* __restrict__ xf = static_cast<float*>(ms.x);
   const bool xf32 = ms.x_f32 != 0;
 
   const int total = ms.m * ms.n;
-  const int base = bw.chunk * kEwChunk;
+  const int base = chunk * kEwChunk;
   const int count = min(kEwChunk, total - base);
   const int n = ms.n, ldx = ms.ldx;
   double ss = 0.0;
 
-  if ((n & 3) == 0) {
-    // rows are a multiple of 4 elements: 4-element groups never straddle a row
-    constexpr int kIter = kEwChunk / (kEwThreads * 4);
-    constexpr int kBatch = 4;
-    static_assert(kIter % kBatch == 0, "chunk must be a multiple of the batch");
+  // Groups of 4 elements as they lie in the arrays; where rows are no multiple of 4, a group may straddle two rows of the padded copy,
+  // which it is stored to in pairs or one by one (element by element throughout, a chunk took sixteen round trips: nine ragged matrices 7.7 us)
+  constexpr int kIter = kEwChunk / (kEwThreads * 4);
+  constexpr int kBatch = 4;
+  static_assert(kIter % kBatch == 0, "chunk must be a multiple of the batch");
+  auto groups = [&](auto whole) {
     for (int it0 = 0; it0 < kIter; it0 += kBatch) {
       f32x4 vg[kBatch], vp[kBatch], va[kBatch], vm[kBatch];
       int idx[kBatch];
 #pragma unroll
       for (int b = 0; b < kBatch; ++b) {
         const int i = ((it0 + b) * kEwThreads + threadIdx.x) * 4;
-        idx[b] = (i < count) ? base + i : -1;
+        idx[b] = (i + 4 <= count) ? base + i : -1;
         if (idx[b] >= 0) {
-          vg[b] = load4(g + idx[b]);
-          if constexpr (MODE == MODE_TWO_BUFFER) vp[b] = load4(gp + idx[b]);
-          if constexpr (MODE != MODE_MUON) va[b] = load4(ac + idx[b]);
-          vm[b] = load4(mo + idx[b]);
+          vg[b] = load4<STREAM>(g + idx[b]);
+          if constexpr (MODE == MODE_TWO_BUFFER) vp[b] = load4<STREAM>(gp + idx[b]);
+          if constexpr (MODE != MODE_MUON) va[b] = load4<STREAM>(ac + idx[b]);
+          vm[b] = load4<STREAM>(mo + idx[b]);
         }
       }
 #pragma unroll
@@ -145,39 +201,72 @@ __global__ __launch_bounds__(kEwThreads) void state_update_kernel(
           const f32x4 a = {a4[0], a4[1], a4[2], a4[3]};
           const f32x4 mnew = {n4[0], n4[1], n4[2], n4[3]};
           ss += (double)mnew.x * mnew.x + (double)mnew.y * mnew.y + (double)mnew.z * mnew.z + (double)mnew.w * mnew.w;
-          if constexpr (MODE == MODE_TWO_BUFFER) store4(gp + idx[b], vg[b]);   // G_{k-1} <- G_k
-          if constexpr (MODE != MODE_MUON) store4(ac + idx[b], a);              // A_k, or C_{k+1}
-          store4(mo + idx[b], mnew);
+          if constexpr (MODE == MODE_TWO_BUFFER) store4<STREAM>(gp + idx[b], vg[b]);   // G_{k-1} <- G_k
+          if constexpr (MODE != MODE_MUON) store4<STREAM>(ac + idx[b], a);              // A_k, or C_{k+1}
+          if constexpr (THROUGH) mom.put4(idx[b], mnew, true); else store4<STREAM>(mo + idx[b], mnew);
           // the padded copy can exceed 2^31 elements although m * n does not: 64-bit offset
-          const int64_t xo = (ldx == n) ? (int64_t)idx[b] : (int64_t)(idx[b] / n) * ldx + (idx[b] % n);
-          if (xf32) store4(xf + xo, mnew); else store4(xh + xo, mnew);
+          if constexpr (whole) {
+            const int64_t xo = (ldx == n) ? (int64_t)idx[b] : (int64_t)(idx[b] / n) * ldx + (idx[b] % n);
+            if constexpr (THROUGH) x.put4(xo, mnew, xf32);
+            else if (xf32) store4<KEEP == KEEP_NOTHING>(xf + xo, mnew);
+            else store4<KEEP == KEEP_NOTHING>(xh + xo, mnew);
+          } else {
+            const int row = idx[b] / n;
+            int col = idx[b] - row * n;
+            int64_t row_at = (int64_t)row * ldx;
+            if ((n & 1) == 0) {
+              x.put2(row_at + col, n4[0], n4[1], xf32);
+              col += 2;
+              if (col == n) { col = 0; row_at += ldx; }
+              x.put2(row_at + col, n4[2], n4[3], xf32);
+            } else {
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                if (col == n) { col = 0; row_at += ldx; }
+                x.put(row_at + col, n4[e], xf32);
+                ++col;
+              }
+            }
+          }
         }
       }
     }
-  } else {
-    for (int i = threadIdx.x; i < count; i += kEwThreads) {
-      const int id = base + i;
-      const float gv = load1(g + id);
-      float mnew;
-      if constexpr (MODE == MODE_TWO_BUFFER) {
-        float a = load1(ac + id);
-        mnew = mona_element(gv, load1(gp + id), a, mo[id], c);
-        store1(gp + id, gv);
-        store1(ac + id, a);
-      } else if constexpr (MODE == MODE_ONE_BUFFER) {
-        float cb = load1(ac + id);
-        mnew = mona_element_one_buffer(gv, cb, mo[id], c);
-        store1(ac + id, cb);
-      } else {
-        mnew = c.mu * mo[id] + gv;
-      }
-      ss += (double)mnew * mnew;
-      mo[id] = mnew;
-      const int64_t xo = (int64_t)(id / n) * ldx + (id % n);
-      if (xf32) xf[xo] = mnew; else xh[xo] = (bf16_t)mnew;
+  };
+  if ((n & 3) == 0) groups(std::true_type{}); else groups(std::false_type{});
+  // the last elements of a matrix
+  if (const int i = (count & ~3) + (int)threadIdx.x; i < count) {
+    const int id = base + i;
+    const float gv = load1(g + id);
+    float mnew;
+    if constexpr (MODE == MODE_TWO_BUFFER) {
+      float a = load1(ac + id);
+      mnew = mona_element(gv, load1(gp + id), a, mo[id], c);
+      store1(gp + id, gv);
+      store1(ac + id, a);
+    } else if constexpr (MODE == MODE_ONE_BUFFER) {
+      float cb = load1(ac + id);
+      mnew = mona_element_one_buffer(gv, cb, mo[id], c);
+      store1(ac + id, cb);
+    } else {
+      mnew = c.mu * mo[id] + gv;
     }
+    ss += (double)mnew * mnew;
+    mom.put(id, mnew, true);
+    const int64_t xo = (int64_t)(id / n) * ldx + (id % n);
+    x.put(xo, mnew, xf32);
   }
-  const double t = block_sum(ss, red);
+  return ss;
+}
+
+template <typename GT, typename ST, int MODE, int KEEP>
+__global__ __launch_bounds__(kEwThreads) void state_update_kernel(
+    const MatStatic* __restrict__ stat, const MatDynamic* __restrict__ dyn,
+    const BlockWork* __restrict__ work, double* __restrict__ partials, Coef c) {
+  __shared__ double red[kEwThreads / 64];
+  const BlockWork bw = work[blockIdx.x];
+  const MatStatic ms = stat[bw.mat];
+  const MatDynamic md = dyn[bw.mat];
+  const double t = block_sum(update_chunk<GT, ST, MODE, KEEP, false>(ms, md, bw.chunk, c), red);
   if (threadIdx.x == 0) partials[blockIdx.x] = t;
 }
 
@@ -208,19 +297,20 @@ constexpr double kNormHi = 1099511627776.0;         // 2^40
 constexpr int kRepairBlocks = 16, kRepairGroups = 2048;
 
 // The share of workgroup `part` of `parts` in the rewriting of one flagged working copy.  Bound by HBM once wide enough:
-// 16-byte loads of M, four in flight per lane, one 32-bit division for four elements.
+// 16-byte loads of M, four (or U) in flight per lane, one 32-bit division for four elements.
+template <int U = 4>
 __device__ __forceinline__ void repair_copy(const MatStatic& ms, const MatScale& r, int part, int parts) {
   const bool clear = (r.status & 2u) != 0;
-  // m * n is below 2^31, and the walk passes its end by at most 4 x 2048 x 256 units: 32 bits hold every index
+  // m * n is below 2^31, and the walk passes its end by at most U x 2048 x 256 units: 32 bits hold every index
   const uint32_t n = (uint32_t)ms.n, total = (uint32_t)ms.m * n;
   const uint32_t units = (total + 3) / 4, step = (uint32_t)parts * kEwThreads;
   bf16_t* __restrict__ xh = static_cast<bf16_t*>(ms.x);
   float* __restrict__ xf = static_cast<float*>(ms.x);
   const float* __restrict__ mom = ms.mom;
-  for (uint32_t u0 = (uint32_t)part * kEwThreads + threadIdx.x; u0 < units; u0 += 4 * step) {
-    f32x4 v[4];
+  for (uint32_t u0 = (uint32_t)part * kEwThreads + threadIdx.x; u0 < units; u0 += U * step) {
+    f32x4 v[U];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < U; ++j) {
       const uint32_t id = 4 * (u0 + j * step);
       v[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
       if (clear || id >= total) continue;
@@ -229,7 +319,7 @@ __device__ __forceinline__ void repair_copy(const MatStatic& ms, const MatScale&
         for (uint32_t e = 0; e < total - id; ++e) v[j][e] = mom[id + e];
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < U; ++j) {
       const uint32_t id = 4 * (u0 + j * step);
       if (id >= total) continue;
 #pragma unroll
@@ -268,6 +358,34 @@ __device__ __forceinline__ void fill_pieces(const FillArgs& f, uint32_t block) {
   }
 }
 
+// The scale of a matrix whose squares add up to s.
+__device__ __forceinline__ MatScale scale_of(double s, float eps) {
+  const double norm = sqrt(s);
+  const double den = norm + (double)eps;
+  MatScale r;
+  r.norm = (float)fmin(norm, 3.402823466e38);
+  r.status = 0u;
+  r.xexp = 0;
+  const bool finite = (s == s) && (s <= 1.7e308);
+  if (!finite) {
+    r.norm = (float)norm;
+    r.inv = 0.0f;
+    r.status = 2u;
+  } else if (den <= 0.0) {
+    r.inv = 0.0f;
+    r.status = 1u;
+  } else if (norm == 0.0 || (norm >= kNormLo && norm <= kNormHi)) {
+    r.inv = 1.0f / ((float)norm + eps);
+  } else {
+    r.xexp = -ilogb(norm);
+    r.inv = (float)ldexp(1.0 / den, -r.xexp);
+    r.status = 4u;
+  }
+  r.inv2 = r.inv * r.inv;
+  r.arrived = 0u;
+  return r;
+}
+
 struct NoFill {};
 template <typename Fill>
 __global__ __launch_bounds__(kEwThreads) void norm_finalize_kernel(const MatStatic* __restrict__ stat,
@@ -295,31 +413,53 @@ __global__ __launch_bounds__(kEwThreads) void norm_finalize_kernel(const MatStat
   if (threadIdx.x == 0) total_sum = s;
   __syncthreads();
   s = total_sum;
-  const double norm = sqrt(s);
-  const double den = norm + (double)eps;
-  MatScale r;
-  r.norm = (float)fmin(norm, 3.402823466e38);
-  r.status = 0u;
-  r.xexp = 0;
-  const bool finite = (s == s) && (s <= 1.7e308);
-  if (!finite) {
-    r.norm = (float)norm;
-    r.inv = 0.0f;
-    r.status = 2u;
-  } else if (den <= 0.0) {
-    r.inv = 0.0f;
-    r.status = 1u;
-  } else if (norm == 0.0 || (norm >= kNormLo && norm <= kNormHi)) {
-    r.inv = 1.0f / ((float)norm + eps);
-  } else {
-    r.xexp = -ilogb(norm);
-    r.inv = (float)ldexp(1.0 / den, -r.xexp);
-    r.status = 4u;
-  }
-  r.inv2 = r.inv * r.inv;
+  const MatScale r = scale_of(s, eps);
   if (part == 0 && threadIdx.x == 0) scales[mat] = r;
   for (int i = blockIdx.x * kEwThreads + threadIdx.x; i < n16; i += norm_groups * kEwThreads) zero[i] = uint4{0u, 0u, 0u, 0u};
   if (repair && (r.status & 6u)) repair_copy(ms, r, part, per_mat);
+}
+
+// All that stands before the products of a small step in one launch (BeginArgs::tables: the pointers too): the elementwise pass, norms,
+// scales, repair, what chains need cleared and filled.  Three launches of a few workgroups take 12 us, of which the work is a third.  The
+// workgroup that finishes a matrix last (MatScale::arrived) adds up the partial sums, in the order of norm_finalize_kernel, and repairs the
+// working copy alone if it must: what it reads of the others has gone through to memory before they counted themselves.
+// Measured, us per step, three launches -> one: 256 x 512 58.8 -> 54.6, nine ragged matrices 75.0 -> 70.3, 512 x 1408 without allocation (two
+// -> one) 96.0 -> 91.3.
+template <typename ST, int MODE>
+__global__ __launch_bounds__(kEwThreads) void begin_norm_finalize_kernel(
+    const MatStatic* __restrict__ stat, const BlockWork* __restrict__ work, MatScale* scales, double* partials, MatDynamic* dyn,
+    Coef c, float eps, uint4* __restrict__ zero, int n16, const FillArgs fill, int update_groups, const BeginTable table) {
+  __shared__ double red[kEwThreads / 64];
+  __shared__ double total_sum;
+  __shared__ uint32_t count;
+  for (int i = blockIdx.x * kEwThreads + threadIdx.x; i < n16; i += gridDim.x * kEwThreads) zero[i] = uint4{0u, 0u, 0u, 0u};
+  if ((int)blockIdx.x >= update_groups) {
+    fill_pieces(fill, blockIdx.x - update_groups);
+    return;
+  }
+  const BlockWork bw = work[blockIdx.x];
+  const MatStatic ms = stat[bw.mat];
+  const MatDynamic md = table.n > 0 ? table.v[bw.mat] : dyn[bw.mat];
+  if (table.n > 0 && bw.chunk == 0 && threadIdx.x == 0) dyn[bw.mat] = md;
+  const double ss = ms.g_dtype ? update_chunk<bf16_t, ST, MODE, KEEP_ALL, true>(ms, md, bw.chunk, c)
+                               : update_chunk<float, ST, MODE, KEEP_ALL, true>(ms, md, bw.chunk, c);
+  double s = block_sum(ss, red);
+  if (threadIdx.x == 0)
+    __hip_atomic_store(partials + blockIdx.x, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wavefront's stores are where every die sees them
+  __syncthreads();
+  if (threadIdx.x == 0) count = __hip_atomic_fetch_add(&scales[bw.mat].arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  if ((int)count != ms.num_blocks - 1) return;
+  s = 0.0;
+  for (int i = threadIdx.x; i < ms.num_blocks; i += kEwThreads)
+    s += __hip_atomic_load(partials + ms.first_block + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  s = block_sum(s, red);
+  if (threadIdx.x == 0) total_sum = s;
+  __syncthreads();
+  const MatScale r = scale_of(total_sum, eps);
+  if (threadIdx.x == 0) scales[bw.mat] = r;
+  if (r.status & 6u) repair_copy<16>(ms, r, 0, 1);
 }
 
 // The repair of a long list: every workgroup scans the flags, leaves at once when none is set, and takes its share of
@@ -404,29 +544,40 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(uint4* __restrict__ p, s
 
 template <typename GT, typename ST, int MODE>
 hipError_t launch_su(const MatStatic* stat, const MatDynamic* dyn, const BlockWork* work, double* partials,
-                     int num_blocks, Coef c, hipStream_t s) {
-  hipLaunchKernelGGL((state_update_kernel<GT, ST, MODE>), dim3(num_blocks), dim3(kEwThreads), 0, s, stat, dyn,
-                     work, partials, c);
+                     int num_blocks, Coef c, int keep, hipStream_t s) {
+  auto* const kernel = keep == KEEP_ALL ? state_update_kernel<GT, ST, MODE, KEEP_ALL>
+                       : keep == KEEP_COPY ? state_update_kernel<GT, ST, MODE, KEEP_COPY> : state_update_kernel<GT, ST, MODE, KEEP_NOTHING>;
+  // (long passes over four fp32 arrays with three workgroups to a CU instead of five, by LDS that nothing uses: 192 x 2048 x 1024 2203 ->
+  // 2190 us, 48 x 4096 x 4096 4447 -> 4393; shorter ones gain and lose 1 %, a step with one bf16 array loses 0.8 %)
+  const size_t lds = keep == KEEP_NOTHING && MODE == MODE_TWO_BUFFER && sizeof(ST) == 4 ? 160 * 1024 / 3 / 256 * 256 - 256 : 0;
+  hipLaunchKernelGGL(kernel, dim3(num_blocks), dim3(kEwThreads), lds, s, stat, dyn, work, partials, c);
   return hipGetLastError();
 }
 template <int MODE>
 hipError_t launch_su_mode(const MatStatic* stat, const MatDynamic* dyn, const BlockWork* work, double* partials,
-                          int num_blocks, int g_bf16, int state_bf16, Coef c, hipStream_t s) {
+                          int num_blocks, int g_bf16, int state_bf16, Coef c, int keep, hipStream_t s) {
   switch ((g_bf16 ? 2 : 0) | (state_bf16 ? 1 : 0)) {
-    case 0: return launch_su<float, float, MODE>(stat, dyn, work, partials, num_blocks, c, s);
-    case 1: return launch_su<float, bf16_t, MODE>(stat, dyn, work, partials, num_blocks, c, s);
-    case 2: return launch_su<bf16_t, float, MODE>(stat, dyn, work, partials, num_blocks, c, s);
-    default: return launch_su<bf16_t, bf16_t, MODE>(stat, dyn, work, partials, num_blocks, c, s);
+    case 0: return launch_su<float, float, MODE>(stat, dyn, work, partials, num_blocks, c, keep, s);
+    case 1: return launch_su<float, bf16_t, MODE>(stat, dyn, work, partials, num_blocks, c, keep, s);
+    case 2: return launch_su<bf16_t, float, MODE>(stat, dyn, work, partials, num_blocks, c, keep, s);
+    default: return launch_su<bf16_t, bf16_t, MODE>(stat, dyn, work, partials, num_blocks, c, keep, s);
   }
 }
 
 }  // namespace
 
+// Everything where all that a pass moves fits into the cache, the working copies where these take at most twice as much: what the products
+// read first is still there, and the copies' lines are not turned out one by one between the loads.
+int choose_keep(double pass_bytes, double copy_bytes) {
+  constexpr double kCache = 256.0 * 1024 * 1024;
+  return pass_bytes <= kCache ? KEEP_ALL : copy_bytes <= 2.0 * kCache ? KEEP_COPY : KEEP_NOTHING;
+}
+
 // The gradient dtype may differ between matrices: the host orders the work table by gradient
 // dtype and launches each dtype's range of blocks separately.
 hipError_t launch_state_update(const MatStatic* stat, const MatDynamic* dyn, const BlockWork* work,
                                double* partials, int num_blocks, int g_bf16, int state_bf16, int one_buffer,
-                               float mu, float beta_a, float alpha, int use_prev, hipStream_t s) {
+                               float mu, float beta_a, float alpha, int use_prev, int keep, hipStream_t s) {
   if (num_blocks <= 0) return hipSuccess;
   Coef c;
   c.mu = mu;
@@ -438,11 +589,23 @@ hipError_t launch_state_update(const MatStatic* stat, const MatDynamic* dyn, con
   c.use_prev = use_prev == 1;
   if (use_prev == 2) {
     // the state dtype does not matter: the acceleration buffers are not touched
-    if (g_bf16) return launch_su<bf16_t, float, MODE_MUON>(stat, dyn, work, partials, num_blocks, c, s);
-    return launch_su<float, float, MODE_MUON>(stat, dyn, work, partials, num_blocks, c, s);
+    if (g_bf16) return launch_su<bf16_t, float, MODE_MUON>(stat, dyn, work, partials, num_blocks, c, keep, s);
+    return launch_su<float, float, MODE_MUON>(stat, dyn, work, partials, num_blocks, c, keep, s);
   }
-  if (one_buffer) return launch_su_mode<MODE_ONE_BUFFER>(stat, dyn, work, partials, num_blocks, g_bf16, state_bf16, c, s);
-  return launch_su_mode<MODE_TWO_BUFFER>(stat, dyn, work, partials, num_blocks, g_bf16, state_bf16, c, s);
+  if (one_buffer) return launch_su_mode<MODE_ONE_BUFFER>(stat, dyn, work, partials, num_blocks, g_bf16, state_bf16, c, keep, s);
+  return launch_su_mode<MODE_TWO_BUFFER>(stat, dyn, work, partials, num_blocks, g_bf16, state_bf16, c, keep, s);
+}
+
+hipError_t launch_begin(const MatStatic* stat, const BlockWork* work, MatScale* scales, double* partials, MatDynamic* dyn, int num_blocks,
+                        int state_bf16, int one_buffer, float mu, float beta_a, float alpha, int use_prev, float eps, void* zero,
+                        size_t zero_bytes, const FillArgs& fill, const BeginTable& table, hipStream_t s) {
+  const Coef c = {mu, beta_a, 1.0f - beta_a, alpha, use_prev == 1};
+  auto* const kernel = use_prev == 2 ? begin_norm_finalize_kernel<float, MODE_MUON>
+                       : one_buffer ? (state_bf16 ? begin_norm_finalize_kernel<bf16_t, MODE_ONE_BUFFER> : begin_norm_finalize_kernel<float, MODE_ONE_BUFFER>)
+                       : state_bf16 ? begin_norm_finalize_kernel<bf16_t, MODE_TWO_BUFFER> : begin_norm_finalize_kernel<float, MODE_TWO_BUFFER>;
+  hipLaunchKernelGGL(kernel, dim3(num_blocks + fill.groups), dim3(kEwThreads), 0, s, stat, work, scales, partials, dyn, c, eps,
+                     static_cast<uint4*>(zero), (int)(zero_bytes / 16), fill, num_blocks, table);
+  return hipGetLastError();
 }
 
 hipError_t launch_write_dyn(const DynTable& t, int n, MatDynamic* dyn, hipStream_t s) {

@@ -70,7 +70,7 @@ static void step(const State& s, int steps, int want_fresh, std::vector<char>& p
   std::fill(pool.begin(), pool.end(), kOutside);
   bool any = false, fresh = false;
   fake::on_launch = [&](const fake::Launch& l) {
-    if (l.name.find("norm_finalize_kernel") != std::string::npos && l.name.find("FillArgs") != std::string::npos) {
+    if (l.name.find("begin_norm_finalize_kernel") != std::string::npos) {
       const FillArgs& f = *static_cast<const FillArgs*>(l.args[9]);
       uint32_t groups = 0;
       for (int i = 0; i < f.n; ++i) {
