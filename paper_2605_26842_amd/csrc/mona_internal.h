@@ -78,6 +78,7 @@ struct GemmArgs {
   int32_t post;             // PostScale, indexed through `members`
   int32_t epilogue;         // GemmEpilogue
   int32_t store_out;        // EPI_UPDATE: also store O
+  int32_t w_f32;            // EPI_UPDATE: some parameters of the group are fp32
   const int32_t* members;   // group member -> matrix index
   const MatScale* scales;   // per matrix
   const MatStatic* stat;    // per matrix (EPI_UPDATE: real m, n, w dtype)
@@ -99,6 +100,7 @@ struct GroupDesc {
   int32_t count, m, n;      // matrices, their shape
   int32_t rows_pad, cols_pad;
   int32_t tall, f32;
+  int32_t w_f32;            // some of the parameters are fp32
   float o_scale;            // eta * gamma
 };
 struct StepDesc {
@@ -140,7 +142,7 @@ __host__ __device__ inline void expand_op(const StepDesc& st, const GroupDesc& g
   a.symmetric = apply ? 0 : 1;
   a.trans_p = (int32_t)op_field(code, OPF_TP); a.trans_q = (int32_t)op_field(code, OPF_TQ);
   a.alpha = 1.0f; a.beta = 0.0f; a.diag = 0.0f; a.diag_n = p_real;
-  a.post = POST_NONE; a.epilogue = EPI_STORE; a.store_out = 0;
+  a.post = POST_NONE; a.epilogue = EPI_STORE; a.store_out = 0; a.w_f32 = g.w_f32;
   a.w_keep = st.w_keep; a.o_scale = g.o_scale;
   // operands: the p x p matrices numbered by the code, an X operand in place of one or both
   a.P = pp(OPF_P); a.Q = pp(OPF_Q); a.C = pp(OPF_C); a.E = nullptr;

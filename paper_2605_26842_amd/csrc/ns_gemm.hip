@@ -68,15 +68,20 @@ __device__ __forceinline__ void tr_read_8_rows(u32x2 (&lo)[4], u32x2 (&hi)[4], u
 // values from then on), and the stores of the passes then stream without any wait.  HAS_E is a template
 // parameter for the same reason: a run-time test around the loads would make every later use look as if
 // it might still be pending.
-template <int MI, int NPF, int NPRE, bool UPD, bool HAS_E, bool DIAG>
+template <int MI, int NPF, int NPRE, bool UPD, bool W32, bool HAS_E, bool DIAG>
 struct BlockEpilogue {
   static constexpr int NI = 2, WN = 64, CH = 8, PASSES = MI * 4;
   static constexpr int kStageBytesPerWave = 32 * WN * 4;
   static_assert(NPF == 8 || NPF == 16, "settle() is written for batches of 8 or 16 passes");
+  // 16 bytes of a row of W: rows of any length, so they are aligned like its elements (the compiler emits one access all the same)
+  typedef u32x4 bf16_piece __attribute__((aligned(2)));
+  typedef u32x4 f32_piece __attribute__((aligned(4)));
 
   const GemmArgs& a;
   int lane, row_w0, col_w0;
-  bool mirror, skip_w, w_pref;
+  bool mirror;
+  enum : int { W_NONE = 0, W_BF16 = 1, W_F32 = 2 };
+  int w_kind;                    // parameters this tile updates
   bool has_diag;                 // this wavefront's part of the tile holds elements of the main diagonal that get a.diag
   float c_acc, c_e;              // out = c_acc * accumulator + c_e * E  (post-scale folded in)
   // tile-relative addressing: wavefront-uniform 64-bit bases plus 32-bit lane offsets
@@ -84,8 +89,8 @@ struct BlockEpilogue {
   char* __restrict__ Ct;
   char* __restrict__ Cm;         // base of the mirrored tile
   uint32_t e_off, c_off;         // lane offsets (bytes) of pass 0; a wavefront tile spans < 2^32 bytes
-  int wm_real, wn_real, w_is_bf16;
-  void* wptr;
+  int wm_real, wn_real;
+  MONA_AS1 char* wptr;           // (named global: a flat access counts as an LDS one too, and the waits for staging would wait for it)
   u32x4 ev[HAS_E ? NPF : 1];
   u32x4 wv[UPD ? NPF : 1];     // parameter chunks, only in the launch that carries the update
 
@@ -107,6 +112,10 @@ struct BlockEpilogue {
     }
   }
 
+  // (behind a wait) all parameter chunks are ordinary values
+  __device__ __forceinline__ void settle_w() {
+    asm volatile("" : "+v"(wv[0]), "+v"(wv[1]), "+v"(wv[2]), "+v"(wv[3]), "+v"(wv[4]), "+v"(wv[5]), "+v"(wv[6]), "+v"(wv[7]));
+  }
   // the same for one block row of the launch that carries the update: its block rows alternate between
   // the two halves of the batch registers, and the next row is requested only after this wait, so
   // nothing but this row's chunks (and the previous row's stores) is outstanding here
@@ -146,16 +155,15 @@ struct BlockEpilogue {
     Cm = reinterpret_cast<char*>(C + (size_t)col0 * a.ldc + row0);
     e_off = 2u * (uint32_t)(prow * a.lde + q * CH);
     c_off = 2u * (uint32_t)(prow * a.ldc + q * CH);
-    wm_real = wn_real = w_is_bf16 = 0;
-    skip_w = true;
+    wm_real = wn_real = 0;
+    w_kind = W_NONE;
     wptr = nullptr;
     if constexpr (UPD) {
       const MatStatic& ms = a.stat[mi];
-      wm_real = ms.m; wn_real = ms.n; w_is_bf16 = ms.w_dtype;
-      wptr = a.dyn[mi].w;
-      skip_w = (a.scales[mi].status & 2u) != 0;
+      wm_real = ms.m; wn_real = ms.n;
+      wptr = (MONA_AS1 char*)a.dyn[mi].w;
+      w_kind = (a.scales[mi].status & 2u) != 0 ? W_NONE : ms.w_dtype ? W_BF16 : W_F32;
     }
-    w_pref = UPD && !skip_w && w_is_bf16 && (wn_real % CH) == 0;
   }
 
   // first row of pass p inside the wavefront tile: block row p / 4, rows 8 (p % 4) .. + 7
@@ -167,9 +175,21 @@ struct BlockEpilogue {
     if constexpr (HAS_E) ev[slot] = *reinterpret_cast<const u32x4*>(Et + (e_off + 2u * (uint32_t)(pass_row(P) * a.lde)));
     if constexpr (UPD) {
       const int grow = row_w0 + pass_row(P) + (lane >> 3), gcol = col_w0 + (lane & 7) * CH;
-      if (w_pref && grow < wm_real && gcol + CH <= wn_real)
-        wv[slot] = *reinterpret_cast<const u32x4*>(static_cast<const bf16_t*>(wptr) + (size_t)grow * wn_real + gcol);
+      if (w_kind == W_BF16 && grow < wm_real && gcol + CH <= wn_real)
+        wv[slot] = *(const MONA_AS1 bf16_piece*)(wptr + ((size_t)grow * wn_real + gcol) * 2);
     }
+  }
+  // W32 (launches with fp32 parameters; the code for them costs others 0.3 %): those of a block row take the whole batch, two registers' worth a pass, so they are requested when its staging begins
+  template <int I>
+  __device__ __forceinline__ void prefetch_w32() {
+    static_for<4>([&](auto k) {
+      const int grow = row_w0 + pass_row(I * 4 + k) + (lane >> 3), gcol = col_w0 + (lane & 7) * CH;
+      if (grow < wm_real && gcol + CH <= wn_real) {
+        const MONA_AS1 f32_piece* const w = (const MONA_AS1 f32_piece*)(wptr + ((size_t)grow * wn_real + gcol) * 4);
+        wv[2 * k] = w[0];
+        wv[2 * k + 1] = w[1];
+      }
+    });
   }
   __device__ __forceinline__ void prefetch_first() {
     static_for<NPRE>([&](auto p) { prefetch<p>(); });
@@ -203,6 +223,8 @@ struct BlockEpilogue {
     const int prow = lane >> 3, q = lane & 7;            // passes: row inside the pass and 8-column chunk
     const uint32_t stage_addr = (uint32_t)(uintptr_t)(MONA_AS3 const char*)stage;
     static_for<MI>([&](auto i) {
+      if constexpr (UPD && W32)
+        if (w_kind == W_F32) prefetch_w32<i>();
       wave_sync();         // previous block row fully consumed
       static_for<NI>([&](auto j) {
         static_for<4>([&](auto vg) {
@@ -216,6 +238,7 @@ struct BlockEpilogue {
       // after the staging writes so that they overlap the latency
       if constexpr (UPD) {
         settle_half<i & 1>();
+        if constexpr (W32) settle_w();
         if constexpr (i + 1 < MI) static_for<4>([&](auto k) { prefetch<(i + 1) * 4 + k>(); });
       } else if constexpr ((i * 4) % NPF == 0) {
         if constexpr (i > 0) static_for<NPF>([&](auto k) { prefetch<i * 4 + k>(); });
@@ -260,23 +283,31 @@ struct BlockEpilogue {
         if (!UPD || a.store_out) *reinterpret_cast<bf16x8*>(Ct + (c_off + 2u * (uint32_t)(pass_row(p) * a.ldc))) = ov;
         // the rounded row, for the transposed store below: inside the fp32 row just read
         if (mirror) *reinterpret_cast<bf16x8*>(stage + r * 256 + (r & 3) * 32 + q * 16) = ov;
-        if (UPD && !skip_w && grow < wm_real) {
+        if (UPD && w_kind != W_NONE && grow < wm_real) {
           // W <- (1 - eta lambda) W - eta gamma O, O as stored in the working precision
           const size_t wi = (size_t)grow * wn_real + gcol;
-          if (w_pref && gcol + CH <= wn_real) {
+          if (w_kind == W_BF16 && gcol + CH <= wn_real) {
             bf16x8 w_in = __builtin_bit_cast(bf16x8, wv[UPD ? slot : 0]);
 #pragma unroll
             for (int e = 0; e < CH; ++e) w_in[e] = (bf16_t)(a.w_keep * (float)w_in[e] - a.o_scale * (float)ov[e]);
-            *reinterpret_cast<bf16x8*>(static_cast<bf16_t*>(wptr) + wi) = w_in;
+            *(MONA_AS1 bf16_piece*)(wptr + wi * 2) = __builtin_bit_cast(u32x4, w_in);
+          } else if (W32 && gcol + CH <= wn_real) {
+            MONA_AS1 f32_piece* const to = (MONA_AS1 f32_piece*)(wptr + wi * 4);
+            static_for<2>([&](auto h) {
+              f32x4 w_in = __builtin_bit_cast(f32x4, wv[UPD ? 2 * pp + h : 0]);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) w_in[e] = a.w_keep * w_in[e] - a.o_scale * (float)ov[4 * h + e];
+              to[h] = __builtin_bit_cast(u32x4, w_in);
+            });
           } else {
 #pragma unroll
             for (int e = 0; e < CH; ++e) {
               if (gcol + e < wn_real) {
-                if (w_is_bf16) {
-                  bf16_t* w = static_cast<bf16_t*>(wptr) + wi + e;
+                if (w_kind == W_BF16) {
+                  MONA_AS1 bf16_t* w = (MONA_AS1 bf16_t*)wptr + wi + e;
                   *w = (bf16_t)(a.w_keep * (float)*w - a.o_scale * (float)ov[e]);
                 } else {
-                  float* w = static_cast<float*>(wptr) + wi + e;
+                  MONA_AS1 float* w = (MONA_AS1 float*)wptr + wi + e;
                   *w = a.w_keep * *w - a.o_scale * (float)ov[e];
                 }
               }
@@ -375,7 +406,7 @@ __device__ __forceinline__ void lds_read_t(FragT& f, uint32_t addr) {
   asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.hi) : "v"(addr), "n"(OFF + PITCH4));
 }
 
-template <int BM, int BN, int WGM, int WGN, int STAGES, int MIN_BLOCKS, bool TP, bool TQ, bool UPD, bool HAS_E, bool DIAG>
+template <int BM, int BN, int WGM, int WGN, int STAGES, int MIN_BLOCKS, bool TP, bool TQ, bool UPD, bool HAS_E, bool DIAG, bool W32 = false>
 __global__ __launch_bounds__(64 * WGM * WGN, MIN_BLOCKS) void ns_gemm_bf16_dma_kernel(const GemmArgs a) {
   constexpr int BK = 32;
   constexpr int NW = WGM * WGN;
@@ -557,7 +588,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, MIN_BLOCKS) void ns_gemm_bf16_dma_k
 
   static_assert(STAGES == 4, "the pipeline below is written for a ring of 4 stages");
   // (the launch that carries the update has no registers for an early request during the last K steps)
-  typedef BlockEpilogue<MI, /*batch*/ (UPD ? 8 : 16), /*early*/ (UPD ? 0 : 2), UPD, HAS_E, DIAG> Epi;
+  typedef BlockEpilogue<MI, /*batch*/ (UPD ? 8 : 16), /*early*/ (UPD ? 0 : 2), UPD, W32, HAS_E, DIAG> Epi;
   Epi epi(a);
   static_assert(NI == Epi::NI && (3 * STAGE_U * 16 + NW * Epi::kStageBytesPerWave) <= LDS_U * 16,
                 "epilogue staging: stage 3 and the LDS behind the ring");
@@ -675,6 +706,10 @@ hipError_t launch_ns_gemm(const GemmArgs& a, int cu_cap, hipStream_t s) {
   else if (transP && transQ && !upd && has_e) MONA_LAUNCH_DMA(true, true, false, true);
   else if (!transP && transQ && !upd && has_e) MONA_LAUNCH_DMA(false, true, false, true);
   else if (!transP && transQ && !upd && !has_e) MONA_LAUNCH_DMA(false, true, false, false);
+  else if (!transP && transQ && upd && a.w_f32 && has_e)
+    hipLaunchKernelGGL((ns_gemm_bf16_dma_kernel<256, 256, 2, 4, 4, 1, false, true, true, true, false, true>), dim3(pgrid), dim3(512), 0, s, a);
+  else if (!transP && transQ && upd && a.w_f32)
+    hipLaunchKernelGGL((ns_gemm_bf16_dma_kernel<256, 256, 2, 4, 4, 1, false, true, true, false, false, true>), dim3(pgrid), dim3(512), 0, s, a);
   else if (!transP && transQ && upd && has_e) MONA_LAUNCH_DMA(false, true, true, true);
   else if (!transP && transQ && upd && !has_e) MONA_LAUNCH_DMA(false, true, true, false);
   else return hipErrorInvalidValue;

@@ -158,7 +158,6 @@ __device__ __forceinline__ void finish_tile(const GemmArgs& a, const TileId& t, 
   const int wm_real = v.m, wn_real = v.n, w_is_bf16 = v.w_dtype;
   void* const wptr = v.w;
   const float post = v.post;
-  const bool w_vec = wn_real % CH == 0;             // rows of W are whole chunks, 16-byte (fp32: 32-byte) aligned
   const Array<E, SHARED> C(static_cast<E*>(a.C) + (size_t)t.mat * a.strideC, a.strideC * ES);
 #pragma unroll
   for (int u = 0; u < U; ++u) {
@@ -202,16 +201,19 @@ __device__ __forceinline__ void finish_tile(const GemmArgs& a, const TileId& t, 
     if (update && !skip_w && grow < wm_real) {
       // W <- (1 - eta lambda) W - eta gamma O, O as stored in the working precision
       const size_t wi = (size_t)grow * wn_real + gcol;
-      if (w_vec && gcol + CH <= wn_real) {
+      if (gcol + CH <= wn_real) {
+        // (rows of any length: pieces are aligned like their elements, which the compiler makes one access of all the same)
         if (w_is_bf16) {
           typedef bf16_t wv_t __attribute__((ext_vector_type(CH)));
-          wv_t* wp = reinterpret_cast<wv_t*>(static_cast<bf16_t*>(wptr) + wi);
+          typedef wv_t piece __attribute__((aligned(2)));
+          piece* wp = reinterpret_cast<piece*>(static_cast<bf16_t*>(wptr) + wi);
           wv_t w = *wp;
 #pragma unroll
           for (int e = 0; e < CH; ++e) w[e] = (bf16_t)fmaf(a.w_keep, (float)w[e], -(a.o_scale * (float)ov[e]));
           *wp = w;
         } else {
-          f32x4* wp = reinterpret_cast<f32x4*>(static_cast<float*>(wptr) + wi);
+          typedef f32x4 piece __attribute__((aligned(4)));
+          piece* wp = reinterpret_cast<piece*>(static_cast<float*>(wptr) + wi);
           static_for<CH / 4>([&](auto q) {
             f32x4 w = wp[q];
 #pragma unroll

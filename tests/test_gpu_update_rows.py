@@ -1,0 +1,40 @@
+"""The parameter update in the last product of large and of small tiles, for rows of W of any length (pieces of 8 values that are aligned
+like one, the last one of a row partly outside) and for bf16 and fp32 parameters in one group, against the update formed from the stored
+O in float64."""
+import pytest
+import torch
+
+from paper_2605_26842_amd import binding as B
+from paper_2605_26842_amd import workloads as wl
+from tests import gpu_harness as H
+
+pytestmark = pytest.mark.gpu
+
+# (shape, how many, schedule): large tiles in the literal and in a fused schedule, tall and wide; 128 x 128 and 64 x 64 tiles
+CASES = {
+    "large tiles, literal": ((505, 509), 44, B.MONA_NS_SCHEDULE_LITERAL),
+    "large tiles, tall": ((1022, 510), 20, B.MONA_NS_SCHEDULE_FUSED),
+    "large tiles, wide": ((510, 1023), 20, B.MONA_NS_SCHEDULE_FUSED),
+    "tiles of 128": ((500, 613), 13, B.MONA_NS_SCHEDULE_AUTO),
+    "tiles of 64": ((385, 1007), 6, B.MONA_NS_SCHEDULE_AUTO),
+    "a chain": ((97, 131), 2, B.MONA_NS_SCHEDULE_AUTO),
+}
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_update_of_rows_of_any_length(name):
+    shape, count, schedule = CASES[name]
+    print(f"[case] {name}", flush=True)
+    kinds = [torch.bfloat16 if i % 2 else torch.float32 for i in range(count)]
+    weights = [wl.draw_weight(shape, 300 + i, kinds[i]) for i in range(count)]
+    grads = [[wl.GradientStream(shape, 500 + i).next() for i in range(count)]]
+    watch = (0, 1, count - 2, count - 1)
+    hp = wl.HParams()
+    opt, _, hist = H.run_gpu(weights, grads, hp, 0, watch=watch, ns_schedule=schedule)
+    for i in watch:
+        s = hist[0][i]
+        want = H.expected_update(s.W_before, s.O, hp, False)
+        terms = abs(s.W_before) + abs(want - s.W_before)
+        # half an ulp for the store and three fp32 roundings of the terms
+        ulp = 2.0 ** -8 if kinds[i] == torch.bfloat16 else 2.0 ** -23
+        assert (abs(s.W - want) <= abs(want) * ulp + terms * 2.0 ** -22).all(), i
