@@ -24,7 +24,7 @@
 // own and stores them while the other one of its SIMD multiplies, and the workgroup meets once a panel instead of three times.  Cycles a
 // panel of 768 x 256, the wait for it / multiplying / renewing / storing: 1.1k / 3.0k / 4.8k / 0.95k before, 2.6k / 3.0k / 1.8k / 1.4k now; what
 // is left of the wait is the way from behind L2.  us per step: 128 x 768 x 256 both ways 622 -> 611, 128 x 256 x 1024 532 -> 513, 115 x 256 x 512
-// 289 -> 278, 256 x 256 x 256 246 -> 236.  W in pieces of 4 values where its rows are no multiple of 8: 256 x 200 x 700 558 -> 503,
+// 289 -> 278, 256 x 256 x 256 246 -> 236.  W in pieces of 8 values whatever the length of its rows: 256 x 200 x 700 558 -> 503,
 // 250 x 70 x 100 49 -> 46.
 //
 // Measured, us per step, products in launches (or chains) -> here: 128 x 768 x 256 both ways 831 -> 611, 250 x 70 x 100 170 -> 45,
@@ -250,23 +250,30 @@ __device__ __forceinline__ void run_matrix(const StepDesc& st, const GroupDesc& 
   auto update = [&](const bf16x8& o, int wr, int wc) {
     if (wr >= g.m || wc >= g.n) return;
     const size_t wi = (size_t)wr * g.n + wc;
-    auto some = [&](auto* const p, auto count) {      // `count` neighbours at a time
+    // (rows of any length: pieces are aligned like their elements, which the compiler makes one access of all the same)
+    auto row = [&](auto* const p) {
       typedef std::remove_pointer_t<decltype(p + 0)> W;
-      constexpr int N = decltype(count)::value;
-      typedef W vec __attribute__((ext_vector_type(N)));
-      static_for<8 / N>([&](auto q) {
-        if (wc + q * N >= g.n) return;
-        vec* const at = reinterpret_cast<vec*>(p + q * N);
+      auto renewed = [&](W w, int e) { return (W)fmaf(st.w_keep, (float)w, -(g.o_scale * (float)o[e])); };
+      auto some = [&](auto first, auto count) {
+        constexpr int F = decltype(first)::value, N = decltype(count)::value;
+        typedef W vec __attribute__((ext_vector_type(N)));
+        typedef vec piece __attribute__((aligned(sizeof(W))));
+        piece* const at = reinterpret_cast<piece*>(p + F);
         vec w = *at;
 #pragma unroll
-        for (int e = 0; e < N; ++e) w[e] = (W)fmaf(st.w_keep, (float)w[e], -(g.o_scale * (float)o[q * N + e]));
+        for (int e = 0; e < N; ++e) w[e] = renewed(w[e], F + e);
         *at = w;
+      };
+      if (sizeof(W) == 2 && wc + 8 <= g.n) {
+        if constexpr (sizeof(W) == 2) some(IC<0>{}, IC<8>{});
+        return;
+      }
+      static_for<2>([&](auto h) {
+        if (wc + 4 * h + 4 <= g.n) { some(IC<4 * h>{}, IC<4>{}); return; }
+#pragma unroll
+        for (int e = 4 * h; e < 4 * h + 4; ++e)
+          if (wc + e < g.n) p[e] = renewed(p[e], e);
       });
-    };
-    auto row = [&](auto* const p) {
-      if (sizeof(*p) == 2 && g.n % 8 == 0) { if constexpr (sizeof(*p) == 2) some(p, IC<8>{}); }
-      else if (g.n % 4 == 0) some(p, IC<4>{});
-      else some(p, IC<1>{});
     };
     if (w_is_bf16) row(static_cast<bf16_t*>(wptr) + wi); else row(static_cast<float*>(wptr) + wi);
   };
