@@ -296,9 +296,29 @@ constexpr double kNormLo = 9.094947017729282e-13;   // 2^-40
 constexpr double kNormHi = 1099511627776.0;         // 2^40
 constexpr int kRepairBlocks = 16, kRepairGroups = 2048;
 
+// M as a repair reads it.  SHARED: other workgroups of the same launch have stored it (at device scope, Out), so it is read at device scope
+// too: a line at the edge of two chunks may stand in this die's L2 as it was before the other chunk's workgroup stored its part (M is
+// 16-byte aligned at least, chunks are 16 KB).
+template <bool SHARED>
+struct In {
+  const float* p;
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ explicit In(float* base) : p(base) {
+    if constexpr (SHARED) r = __builtin_amdgcn_make_buffer_rsrc(base, 0, -1, 0x00020000);
+  }
+  __device__ __forceinline__ f32x4 get4(uint32_t i) const {
+    if constexpr (SHARED) return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)(i * 4u), 0, kDeviceScope));
+    else return *reinterpret_cast<const f32x4*>(p + i);
+  }
+  __device__ __forceinline__ float get(uint32_t i) const {
+    if constexpr (SHARED) return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)(i * 4u), 0, kDeviceScope));
+    else return p[i];
+  }
+};
+
 // The share of workgroup `part` of `parts` in the rewriting of one flagged working copy.  Bound by HBM once wide enough:
 // 16-byte loads of M, four (or U) in flight per lane, one 32-bit division for four elements.
-template <int U = 4>
+template <int U = 4, bool SHARED = false>
 __device__ __forceinline__ void repair_copy(const MatStatic& ms, const MatScale& r, int part, int parts) {
   const bool clear = (r.status & 2u) != 0;
   // m * n is below 2^31, and the walk passes its end by at most U x 2048 x 256 units: 32 bits hold every index
@@ -306,7 +326,7 @@ __device__ __forceinline__ void repair_copy(const MatStatic& ms, const MatScale&
   const uint32_t units = (total + 3) / 4, step = (uint32_t)parts * kEwThreads;
   bf16_t* __restrict__ xh = static_cast<bf16_t*>(ms.x);
   float* __restrict__ xf = static_cast<float*>(ms.x);
-  const float* __restrict__ mom = ms.mom;
+  const In<SHARED> mom(ms.mom);
   for (uint32_t u0 = (uint32_t)part * kEwThreads + threadIdx.x; u0 < units; u0 += U * step) {
     f32x4 v[U];
 #pragma unroll
@@ -314,9 +334,9 @@ __device__ __forceinline__ void repair_copy(const MatStatic& ms, const MatScale&
       const uint32_t id = 4 * (u0 + j * step);
       v[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
       if (clear || id >= total) continue;
-      if (total - id >= 4) v[j] = *reinterpret_cast<const f32x4*>(mom + id);
+      if (total - id >= 4) v[j] = mom.get4(id);
       else
-        for (uint32_t e = 0; e < total - id; ++e) v[j][e] = mom[id + e];
+        for (uint32_t e = 0; e < total - id; ++e) v[j][e] = mom.get(id + e);
     }
 #pragma unroll
     for (int j = 0; j < U; ++j) {
@@ -422,7 +442,7 @@ __global__ __launch_bounds__(kEwThreads) void norm_finalize_kernel(const MatStat
 // All that stands before the products of a small step in one launch (BeginArgs::tables: the pointers too): the elementwise pass, norms,
 // scales, repair, what chains need cleared and filled.  Three launches of a few workgroups take 12 us, of which the work is a third.  The
 // workgroup that finishes a matrix last (MatScale::arrived) adds up the partial sums, in the order of norm_finalize_kernel, and repairs the
-// working copy alone if it must: what it reads of the others has gone through to memory before they counted themselves.
+// working copy alone if it must: what it reads of the others, at device scope, has gone through to memory before they counted themselves.
 // Measured, us per step, three launches -> one: 256 x 512 58.8 -> 54.6, nine ragged matrices 75.0 -> 70.3, 512 x 1408 without allocation (two
 // -> one) 96.0 -> 91.3.
 template <typename ST, int MODE>
@@ -459,7 +479,7 @@ __global__ __launch_bounds__(kEwThreads) void begin_norm_finalize_kernel(
   __syncthreads();
   const MatScale r = scale_of(total_sum, eps);
   if (threadIdx.x == 0) scales[bw.mat] = r;
-  if (r.status & 6u) repair_copy<16>(ms, r, 0, 1);
+  if (r.status & 6u) repair_copy<16, true>(ms, r, 0, 1);
 }
 
 // The repair of a long list: every workgroup scans the flags, leaves at once when none is set, and takes its share of
