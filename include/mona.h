@@ -30,7 +30,8 @@
  *     owns only host-side bookkeeping and a few small pinned host tables.  (Two static
  *     arrays belong to its code on every GPU: the workspace of mona_step_noalloc, 32 MiB,
  *     and 128 MiB of buffers that small steps use where they find room there; a state takes
- *     its part at init, which waits for the device if only parts of freed states are left.)
+ *     its part at init, which waits for the device if only parts of freed states are left, and
+ *     keeps it until the process ends if a step of it has been captured into a graph.)
  */
 #ifndef MONA_H
 #define MONA_H
@@ -223,7 +224,7 @@ int mona_step_noalloc(const mona_matrix* mat, const mona_options* opts, void* g_
                       const mona_hparams* hp, int64_t k, void* stream);
 
 /* Release host bookkeeping (waits for the state's pinned tables to be idle).  The arena
- * is not touched. */
+ * is not touched: a captured step may be replayed as long as the arena and the arrays it names live. */
 int mona_free_state(mona_state* st);
 
 typedef enum mona_view_kind {

@@ -1192,7 +1192,8 @@ namespace {
 // The caller's arena holds two X and two p x p matrices to a matrix, which the products of a chain take in turn.  Where every product
 // is to have a buffer of its own (ns_chain_kernel), the others come from a static array, of which every GPU the library runs on
 // holds its own copy, like the one of mona_step_noalloc.  A state takes its part when it is built and gives it back when it is
-// freed; one that finds no room runs its chains with flags.  256 x 512 takes 2.3 MB, nine ragged matrices 14.
+// freed, unless a step of it has been captured: a graph may be replayed later on, on the arena that is the caller's, and its launches
+// name the part.  A state that finds no room runs its chains with flags.  256 x 512 takes 2.3 MB, nine ragged matrices 14.
 constexpr size_t kPoolBytes = (size_t)128 << 20, kPoolUnit = (size_t)1 << 18;
 constexpr int kPoolUnits = (int)(kPoolBytes / kPoolUnit), kMaxDevices = 64;
 static __device__ __align__(256) unsigned char chain_pool[kPoolBytes];
@@ -1815,7 +1816,7 @@ int mona_free_state(mona_state* st) {
   if (st->late_stream) { (void)hipStreamSynchronize(st->late_stream); (void)hipStreamDestroy(st->late_stream); }
   if (st->late_fork) (void)hipEventDestroy(st->late_fork);
   if (st->late_done) (void)hipEventDestroy(st->late_done);
-  if (st->from_pool) give_back(st->device, st->fresh, st->L.fresh_bytes);
+  if (st->from_pool && !st->captured) give_back(st->device, st->fresh, st->L.fresh_bytes);
   delete st;
   return MONA_OK;
 }

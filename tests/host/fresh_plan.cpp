@@ -4,6 +4,7 @@
 #include "../../include/mona.h"
 #include "fake_hip.h"
 
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -160,6 +161,29 @@ int main() {
     all.front() = make({{1, 768, 768}}, 0);
     step(all.front(), 5, 1, pool);
     for (State& s : all) release(s);
+  }
+  {
+    // a recorded step may be replayed after its state has been freed: nobody else ever gets the part that its launches name
+    State s = make({{1, 256, 512}}, 0);
+    step(s, 5, 1, pool);
+    const std::vector<char> recorded = pool;
+    fake::capturing = true;
+    step(s, 5, -1, pool);
+    fake::capturing = false;
+    fake::clear_recorded();
+    release(s);
+    std::vector<State> all;
+    size_t fresh = 0;
+    for (int i = 0; i < 70; ++i) {
+      all.push_back(make({{1, 256, 512}}, 0));
+      step(all.back(), 5, -1, pool);
+      size_t shared = 0;
+      for (size_t k = 0; k < pool.size(); ++k) shared += pool[k] != kOutside && recorded[k] != kOutside;
+      EXPECT(shared == 0);
+      fresh += std::count_if(pool.begin(), pool.end(), [](char c) { return c != kOutside; }) > 0;
+    }
+    EXPECT(fresh > 40 && fresh < 70);                  // (the pool was full in the end, and asked for parts given back)
+    for (State& other : all) release(other);
   }
   for (int round = 0; round < 60; ++round) {
     Shapes shapes;
