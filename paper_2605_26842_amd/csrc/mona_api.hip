@@ -1421,7 +1421,7 @@ namespace {
 
 // Whether one launch does all that stands before the products (launch_begin): the step of a few small matrices.
 bool begins_at_once(const mona_state* st, const Plan& plan) {
-  return !plan.chains.empty() && st->profiling < 2 && st->L.count <= kBeginMats && st->L.late_group < 0;
+  return !plan.chains.empty() && st->profiling < 2 && st->L.count <= kBeginMats && st->L.max_blocks <= kBeginBlocks && st->L.late_group < 0;
 }
 
 // Enqueues the kernels of one step (Alg. 1 for every matrix) on `s` and the side streams.  The per-matrix

@@ -38,7 +38,9 @@ struct MatScale {
   float norm;       // ||M||_F
   uint32_t status;  // MONA_STATUS_* bits
   int32_t xexp;     // the working copy holds M 2^xexp (0 unless the norm left the safe window)
-  uint32_t arrived; // workgroups that have finished their part of the matrix in the launch that begins a small step; 0 outside of it
+  // of the launch that begins a small step, 0 outside of it (begin_norm_finalize_kernel): workgroups that have finished their part of the
+  // matrix and those of them that stay; what the last of them found; pieces of a repair that were drawn and those who have left
+  uint32_t arrived, verdict, shares;
 };
 
 // One entry per block of the elementwise grid.
@@ -205,7 +207,8 @@ struct ChainRoll {
   uint32_t pad[31];
   uint32_t workgroups;     // those that had reported, once it is closed
   uint32_t drawn;          // tasks drawn from then on, where it was closed without some
-  uint32_t pad2[30];
+  uint32_t spoiled;        // (first roll, before the chain) a workgroup of the pass has found a chunk that is out of range by itself
+  uint32_t pad2[29];
 };
 struct ChainArgs {
   StepDesc step;
@@ -266,6 +269,7 @@ struct DynTable {
 
 // the same for the launch that begins a small step; n = 0: the table in memory holds them
 constexpr int kBeginMats = 32;
+constexpr int kBeginBlocks = 8192;   // blocks of one matrix that MatScale counts in 16 bits (a chain has no room for so many)
 struct BeginTable {
   int32_t n;
   MatDynamic v[kBeginMats];

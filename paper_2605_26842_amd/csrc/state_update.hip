@@ -291,7 +291,8 @@ __global__ __launch_bounds__(kEwThreads) void state_update_kernel(
 //
 // The repair has to stay wide whatever the length of the list: one expert without gradients in a long list would
 // otherwise hold up every product behind it.  Where the list is too long for one workgroup to every kRepairBlocks
-// blocks' worth of elements of every matrix, repair is 0 here and rescue_kernel does it (4 us of a step of 2 ms and more).
+// blocks' worth of elements of every matrix, repair is 0 here and rescue_kernel does it (4 us of a step of 2 ms and more); small steps
+// have it in their first launch (begin_norm_finalize_kernel).
 constexpr double kNormLo = 9.094947017729282e-13;   // 2^-40
 constexpr double kNormHi = 1099511627776.0;         // 2^40
 constexpr int kRepairBlocks = 16, kRepairGroups = 2048;
@@ -316,48 +317,61 @@ struct In {
   }
 };
 
-// The share of workgroup `part` of `parts` in the rewriting of one flagged working copy.  Bound by HBM once wide enough:
-// 16-byte loads of M, four (or U) in flight per lane, one 32-bit division for four elements.
-template <int U = 4, bool SHARED = false>
-__device__ __forceinline__ void repair_copy(const MatStatic& ms, const MatScale& r, int part, int parts) {
+// Rewrites a flagged working copy: the units (of 4 elements) first + thread, every step'th from there, below end.  Bound by HBM once wide
+// enough: 16-byte loads of M, U in flight per lane; a unit's row and column follow from the one's before it.
+template <int U, bool SHARED>
+__device__ __forceinline__ void repair_units(const MatStatic& ms, const MatScale& r, uint32_t first, uint32_t end, uint32_t step) {
   const bool clear = (r.status & 2u) != 0;
   // m * n is below 2^31, and the walk passes its end by at most U x 2048 x 256 units: 32 bits hold every index
-  const uint32_t n = (uint32_t)ms.n, total = (uint32_t)ms.m * n;
-  const uint32_t units = (total + 3) / 4, step = (uint32_t)parts * kEwThreads;
+  const uint32_t n = (uint32_t)ms.n, total = (uint32_t)ms.m * n, whole = total / 4;
   bf16_t* __restrict__ xh = static_cast<bf16_t*>(ms.x);
   float* __restrict__ xf = static_cast<float*>(ms.x);
   const In<SHARED> mom(ms.mom);
-  for (uint32_t u0 = (uint32_t)part * kEwThreads + threadIdx.x; u0 < units; u0 += U * step) {
+  uint32_t u = first + threadIdx.x;
+  uint32_t row = 4 * u / n, col = 4 * u - row * n;
+  const uint32_t rows = 4 * step / n, cols = 4 * step - rows * n;
+  for (; u < end; u += U * step) {
     f32x4 v[U];
 #pragma unroll
     for (int j = 0; j < U; ++j) {
-      const uint32_t id = 4 * (u0 + j * step);
+      const uint32_t at = u + j * step;
       v[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-      if (clear || id >= total) continue;
-      if (total - id >= 4) v[j] = mom.get4(id);
+      if (clear || at >= end) continue;
+      if (at < whole) v[j] = mom.get4(4 * at);
       else
-        for (uint32_t e = 0; e < total - id; ++e) v[j][e] = mom.get(id + e);
+        for (uint32_t e = 0; e < total - 4 * at; ++e) v[j][e] = mom.get(4 * at + e);
     }
 #pragma unroll
     for (int j = 0; j < U; ++j) {
-      const uint32_t id = 4 * (u0 + j * step);
-      if (id >= total) continue;
+      const uint32_t at = u + j * step;
+      if (at < end) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[j][e] = ldexpf(v[j][e], r.xexp);
-      uint32_t row = id / n, col = id - row * n;
-      if (n % 4 == 0) {                              // the four elements are in one row, 16-byte aligned there
-        const int64_t xo = (int64_t)row * ms.ldx + col;
-        if (ms.x_f32) *reinterpret_cast<f32x4*>(xf + xo) = v[j];
-        else *reinterpret_cast<bf16x4*>(xh + xo) = bf16x4{(bf16_t)v[j].x, (bf16_t)v[j].y, (bf16_t)v[j].z, (bf16_t)v[j].w};
-        continue;
+        for (int e = 0; e < 4; ++e) v[j][e] = ldexpf(v[j][e], r.xexp);
+        if (n % 4 == 0) {                            // the four elements are in one row, 16-byte aligned there
+          const int64_t xo = (int64_t)row * ms.ldx + col;
+          if (ms.x_f32) *reinterpret_cast<f32x4*>(xf + xo) = v[j];
+          else *reinterpret_cast<bf16x4*>(xh + xo) = bf16x4{(bf16_t)v[j].x, (bf16_t)v[j].y, (bf16_t)v[j].z, (bf16_t)v[j].w};
+        } else {
+          int64_t row_at = (int64_t)row * ms.ldx;
+          uint32_t c = col;
+#pragma unroll
+          for (uint32_t e = 0; e < 4; ++e) {
+            if (at < whole || e < total - 4 * at) {
+              if (ms.x_f32) xf[row_at + c] = v[j][e]; else xh[row_at + c] = (bf16_t)v[j][e];
+            }
+            if (++c == n) { c = 0; row_at += ms.ldx; }
+          }
+        }
       }
-      for (uint32_t e = 0; e < 4 && e < total - id; ++e) {
-        const int64_t xo = (int64_t)row * ms.ldx + col;
-        if (ms.x_f32) xf[xo] = v[j][e]; else xh[xo] = (bf16_t)v[j][e];
-        if (++col == n) { col = 0; ++row; }
-      }
+      row += rows;
+      col += cols;
+      if (col >= n) { col -= n; ++row; }
     }
   }
+}
+// ... the share of workgroup `part` of `parts`.
+__device__ __forceinline__ void repair_copy(const MatStatic& ms, const MatScale& r, int part, int parts) {
+  repair_units<4, false>(ms, r, (uint32_t)part * kEwThreads, ((uint32_t)ms.m * (uint32_t)ms.n + 3) / 4, (uint32_t)parts * kEwThreads);
 }
 
 // What a chain's buffers hold before its products, by one workgroup (of `block`): kFillPieces pieces, all of one item.  (The item is
@@ -402,7 +416,7 @@ __device__ __forceinline__ MatScale scale_of(double s, float eps) {
     r.status = 4u;
   }
   r.inv2 = r.inv * r.inv;
-  r.arrived = 0u;
+  r.arrived = r.verdict = r.shares = 0u;
   return r;
 }
 
@@ -439,19 +453,75 @@ __global__ __launch_bounds__(kEwThreads) void norm_finalize_kernel(const MatStat
   if (repair && (r.status & 6u)) repair_copy(ms, r, part, per_mat);
 }
 
-// All that stands before the products of a small step in one launch (BeginArgs::tables: the pointers too): the elementwise pass, norms,
+// All that stands before the products of a small step in one launch (BeginTable: the pointers too): the elementwise pass, norms,
 // scales, repair, what chains need cleared and filled.  Three launches of a few workgroups take 12 us, of which the work is a third.  The
-// workgroup that finishes a matrix last (MatScale::arrived) adds up the partial sums, in the order of norm_finalize_kernel, and repairs the
-// working copy alone if it must: what it reads of the others, at device scope, has gone through to memory before they counted themselves.
+// workgroup that finishes a matrix last (MatScale::arrived) adds up the partial sums, in the order of norm_finalize_kernel.
 // Measured, us per step, three launches -> one: 256 x 512 58.8 -> 54.6, nine ragged matrices 75.0 -> 70.3, 512 x 1408 without allocation (two
 // -> one) 96.0 -> 91.3.
+//
+// Repair: a workgroup that knows of a chunk whose squares alone put the norm out of range (its own, or ChainRoll::spoiled says so), or whose own
+// chunk is too small to keep it within, stays until the last one has given its verdict, and those that have stayed share the repair with it,
+// drawing pieces of the copy from a counter.  What they read of each other, at device scope, has gone through to memory before a workgroup
+// counted itself.  Nobody has to stay (the chip may have no room for those that are still to come): after kStayPolls looks a workgroup
+// leaves, and whoever is left does its share.  Whoever leaves last puts the counters back to zero.
+// Bound by what a CU can have on its way beyond L2, so by the workgroups that share it.  Measured, us per step, ordinary / all tiny / all large /
+// one value large / one not a number: 512 x 1408 90 / 104 / 108 / 101 / 96, 512 x 2048 104 / 120 / 128 / 116 / 112, 513 x 801 85 / 95 / 98 / 94 /
+// 91, 256 x 512 54.5 / 60 / 62 / 60 / 57.  The last workgroup alone: 512 x 1408 90 / 320 / 319 / 319 / 281; three launches, a workgroup to every 16
+// blocks: 115 / 142 / 142 / 142 / 123.  (`spoiled` beside the counters instead of on a line of its own cost ordinary steps 1 to 4 us.)
+constexpr int kStayPolls = 64;                                       // about 50 us
+constexpr double kSumLo = kNormLo * kNormLo, kSumHi = kNormHi * kNormHi;
+constexpr uint32_t kStayed = 1u << 16;                               // MatScale::arrived, shares: a workgroup that stays, that leaves
+// MatScale::verdict (not 0 once it is given): how many share the repair, whether there is any, what of MatScale it takes
+constexpr uint32_t kVerdict = 1u << 31, kRepair = 1u << 30, kClear = 1u << 29;
+constexpr int kExpAt = 16, kExpBias = 1024;
+
+__device__ __forceinline__ uint32_t device_load(uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void device_store(uint32_t* p, uint32_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// What a workgroup does from the verdict on (0: it has not waited for it).  `word`: of LDS.
+__device__ __forceinline__ void share_repair(const MatStatic& ms, MatScale* scale, uint32_t verdict, uint32_t* word) {
+  if (verdict & kRepair) {
+    MatScale r;
+    r.status = verdict & kClear ? 2u : 4u;
+    r.xexp = (int)(verdict >> kExpAt & 0x7ffu) - kExpBias;
+    // (a copy to be cleared by its rows, 16 bytes a unit; their padding is zero as it is)
+    const bool clear = (verdict & kClear) != 0;
+    const uint32_t units = clear ? (uint32_t)((int64_t)ms.m * ms.ldx / (ms.x_f32 ? 4 : 8)) : ((uint32_t)ms.m * (uint32_t)ms.n + 3) / 4;
+    const uint32_t pieces = min(2 * (verdict & 0xffffu), (uint32_t)ms.num_blocks), piece = (units + pieces - 1) / pieces;
+    for (;;) {
+      if (threadIdx.x == 0)
+        *word = __hip_atomic_fetch_add(&scale->shares, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xffffu;
+      __syncthreads();
+      const uint32_t mine = *word;
+      __syncthreads();
+      if (mine >= pieces) break;
+      const uint32_t first = mine * piece, end = min(first + piece, units);
+      if (!clear) repair_units<8, true>(ms, r, first, end, kEwThreads);
+      else
+        for (uint32_t u = first + threadIdx.x; u < end; u += kEwThreads) static_cast<uint4*>(ms.x)[u] = uint4{0u, 0u, 0u, 0u};
+    }
+  }
+  if (threadIdx.x != 0) return;
+  // (the verdict is in memory before the one who gave it has left, and looked up again by those who have not waited for it once they have)
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  const uint32_t left = __hip_atomic_fetch_add(&scale->shares, kStayed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 16;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  verdict = device_load(&scale->verdict);
+  if (verdict == 0u || left + 1 != (verdict & 0xffffu)) return;
+  device_store(&scale->arrived, 0u);
+  device_store(&scale->verdict, 0u);
+  device_store(&scale->shares, 0u);
+}
+
 template <typename ST, int MODE>
 __global__ __launch_bounds__(kEwThreads) void begin_norm_finalize_kernel(
     const MatStatic* __restrict__ stat, const BlockWork* __restrict__ work, MatScale* scales, double* partials, MatDynamic* dyn,
     Coef c, float eps, uint4* __restrict__ zero, int n16, const FillArgs fill, int update_groups, const BeginTable table) {
   __shared__ double red[kEwThreads / 64];
   __shared__ double total_sum;
-  __shared__ uint32_t count;
+  __shared__ uint32_t count, word;
   for (int i = blockIdx.x * kEwThreads + threadIdx.x; i < n16; i += gridDim.x * kEwThreads) zero[i] = uint4{0u, 0u, 0u, 0u};
   if ((int)blockIdx.x >= update_groups) {
     fill_pieces(fill, blockIdx.x - update_groups);
@@ -463,23 +533,61 @@ __global__ __launch_bounds__(kEwThreads) void begin_norm_finalize_kernel(
   if (table.n > 0 && bw.chunk == 0 && threadIdx.x == 0) dyn[bw.mat] = md;
   const double ss = ms.g_dtype ? update_chunk<bf16_t, ST, MODE, KEEP_ALL, true>(ms, md, bw.chunk, c)
                                : update_chunk<float, ST, MODE, KEEP_ALL, true>(ms, md, bw.chunk, c);
+  MatScale* const scale = scales + bw.mat;
   double s = block_sum(ss, red);
-  if (threadIdx.x == 0)
+  uint32_t spoiled = 0;
+  if (threadIdx.x == 0) {
+    // (only a hint: cleared above by workgroups that may still be to come, or that have not been heard of here)
+    uint32_t* const hint = &reinterpret_cast<ChainRoll*>(zero)->spoiled;
     __hip_atomic_store(partials + blockIdx.x, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!(s <= kSumHi)) device_store(hint, 1u);
+    spoiled = device_load(hint);
+  }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wavefront's stores are where every die sees them
   __syncthreads();
-  if (threadIdx.x == 0) count = __hip_atomic_fetch_add(&scales[bw.mat].arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (threadIdx.x == 0) {
+    const uint32_t stays = spoiled != 0u || !(s <= kSumHi) || (s > 0.0 && s < kSumLo) ? kStayed : 0u;
+    count = __hip_atomic_fetch_add(&scale->arrived, 1u + stays, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    word = stays;
+  }
   __syncthreads();
-  if ((int)count != ms.num_blocks - 1) return;
-  s = 0.0;
-  for (int i = threadIdx.x; i < ms.num_blocks; i += kEwThreads)
-    s += __hip_atomic_load(partials + ms.first_block + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  s = block_sum(s, red);
-  if (threadIdx.x == 0) total_sum = s;
+  const uint32_t arrived = count;
+  if ((int)(arrived & 0xffffu) != ms.num_blocks - 1) {
+    if (word == 0u) return;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      uint32_t v = 0;
+      for (int i = 0; i < kStayPolls && (v = device_load(&scale->verdict)) == 0u; ++i) __builtin_amdgcn_s_sleep(8);
+      word = v;
+    }
+  } else {
+    s = 0.0;
+    for (int i = threadIdx.x; i < ms.num_blocks; i += kEwThreads)
+      s += __hip_atomic_load(partials + ms.first_block + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s = block_sum(s, red);
+    if (threadIdx.x == 0) total_sum = s;
+    __syncthreads();
+    const MatScale r = scale_of(total_sum, eps);
+    const bool repair = (r.status & 6u) != 0, alone = arrived < kStayed;
+    if (threadIdx.x == 0) {
+      scale->inv = r.inv;
+      scale->inv2 = r.inv2;
+      scale->norm = r.norm;
+      scale->status = r.status;
+      scale->xexp = r.xexp;
+      if (alone && !repair) scale->arrived = 0u;
+    }
+    if (alone && !repair) return;
+    if (threadIdx.x == 0) {
+      word = kVerdict | (repair ? kRepair : 0u) | (r.status & 2u ? kClear : 0u) | (uint32_t)(r.xexp + kExpBias) << kExpAt |
+             ((arrived >> 16) + 1u);
+      device_store(&scale->verdict, word);
+    }
+  }
   __syncthreads();
-  const MatScale r = scale_of(total_sum, eps);
-  if (threadIdx.x == 0) scales[bw.mat] = r;
-  if (r.status & 6u) repair_copy<16, true>(ms, r, 0, 1);
+  const uint32_t verdict = word;
+  __syncthreads();
+  share_repair(ms, scale, verdict, &word);
 }
 
 // The repair of a long list: every workgroup scans the flags, leaves at once when none is set, and takes its share of
