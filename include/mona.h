@@ -300,8 +300,8 @@ int mona_mean_step_times(mona_state* st, float* ms_out, int32_t* steps_out);
  *         4 = all iterations of the group's matrices, a workgroup each (iter 0)
  *   tile:  block tile of the kernel, rows * 1000 + columns (e.g. 256128); kind 4: the padded short side and 128, the
  *          part of the long side it takes at a time
- *   flops: MFMA flop the product issues (tiles x 2 x rows x columns x K), padding included (an fp32
- *          product counts once where it is carried out as six bf16 ones) */
+ *   flops: MFMA flop the product issues (tiles x 2 x rows x columns x K), padding included, of K only what tiles of
+ *          32 and 64 do not leave out (an fp32 product counts once where it is carried out as six bf16 ones) */
 typedef struct mona_launch_time {
   int32_t kind, group, iter, tile;
   int32_t m, n, count;   /* shape of the group's matrices and how many there are */

@@ -649,9 +649,10 @@ struct mona_state {
 namespace {
 
 // Flop that the matrix units execute, padding included (an fp32 product counts once, however it is carried out): of a
-// product, ...
-double gemm_flops(const GemmArgs& a) {
-  return 2.0 * a.tile_m * a.tile_n * (double)a.K * a.tiles_per_mat * a.count;
+// product (tiles of 32 and 64 leave out the slabs of 32 along K that are padding alone, but for split ones), ...
+double gemm_flops(const GemmArgs& a, bool split) {
+  const int k = a.tile_m <= 64 && !split ? std::min(round_up(a.k_real, 32), a.K) : a.K;
+  return 2.0 * a.tile_m * a.tile_n * (double)k * a.tiles_per_mat * a.count;
 }
 // ... of `steps` iterations of a group whose matrices get a workgroup each (both triangles of S and S S), ...
 double matrix_flops(const GroupDesc& g, int steps) {
@@ -665,9 +666,9 @@ double launch_flops(const Plan& plan, const Launch& l) {
     for (int gi : plan.matrix_groups[l.matrix]) flops += matrix_flops(plan.desc[gi], plan.ns_steps);
   else if (l.chain >= 0)
     for (int gi : plan.chain_groups[l.chain])
-      for (const Op& op : plan.ops[gi]) flops += gemm_flops(op.a);
+      for (const Op& op : plan.ops[gi]) flops += gemm_flops(op.a, false);
   else
-    for (int i = 0; i < l.n; ++i) flops += gemm_flops(l.op[i]->a);
+    for (int i = 0; i < l.n; ++i) flops += gemm_flops(l.op[i]->a, l.split);
   return flops;
 }
 
@@ -1593,7 +1594,7 @@ int enqueue_step(mona_state* st, const mona_hparams* hp, hipStream_t s, const Be
         STEP_TRY(launch(l, l.op + i, 1, cu_cap, gs));
         STEP_TRY(hipEventRecord(rec.e1, gs));
         rec.kind = op.kind; rec.group = op.group; rec.iter = op.iter; rec.tile = op.a.tile_m * 1000 + op.a.tile_n;
-        rec.flops = gemm_flops(op.a);
+        rec.flops = gemm_flops(op.a, l.split);
         st->records.push_back(rec);
       }
     }

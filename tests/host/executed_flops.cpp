@@ -3,6 +3,7 @@
 #include "../../include/mona.h"
 #include "fake_hip.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -21,7 +22,14 @@ static std::string what;
 
 typedef std::vector<std::tuple<int, int, int>> Shapes;   // count, m, n
 
-static double product(const GemmArgs& a) { return 2.0 * a.tile_m * a.tile_n * (double)a.K * a.tiles_per_mat * a.count; }
+// A product's tiles times the K they go through: the long side of a Gram product's matrices, the short one of any other's, in whole slabs of 32
+// on tiles of 32 and 64 (not those of split fp32 products), otherwise with all of its padding, to a multiple of 128.
+static double product(const GemmArgs& a, const std::vector<mona_matrix>& mats, bool split) {
+  const mona_matrix& q = mats[a.members[0]];
+  const bool gram = a.symmetric && a.P == a.Q && !a.E;
+  const int k = gram ? std::max(q.m, q.n) : std::min(q.m, q.n), unit = a.tile_m <= 64 && !split ? 32 : 128;
+  return 2.0 * a.tile_m * a.tile_n * (double)((k + unit - 1) / unit * unit) * a.tiles_per_mat * a.count;
+}
 
 static void run(const Shapes& shapes, int precision, int steps) {
   std::vector<mona_matrix> m;
@@ -67,16 +75,16 @@ static void run(const Shapes& shapes, int precision, int steps) {
       for (int i = 0; i < c.ops; ++i) {
         GemmArgs a;
         expand_op(c.step, c.group[c.op[i].code >> OPF_GROUP], c.op[i].code, a);
-        flops += product(a);
+        flops += product(a, m, false);
       }
       ++chain_launches;
     } else if (l.name.find("ns_small_kernel") != std::string::npos) {
       const bool split = l.name.find("ns_small_kernel_split") != std::string::npos;   // (an fp32 product counts once)
       const GemmBatch& b = *static_cast<const GemmBatch*>(l.args[0]);
-      for (int i = 0; i < b.n; ++i) flops += product(b.a[i]);
+      for (int i = 0; i < b.n; ++i) flops += product(b.a[i], m, split);
       ++(split ? split_launches : other_launches);
     } else {
-      flops += product(*static_cast<const GemmArgs*>(l.args[0]));
+      flops += product(*static_cast<const GemmArgs*>(l.args[0]), m, false);
       ++other_launches;
     }
   };
@@ -86,6 +94,17 @@ static void run(const Shapes& shapes, int precision, int steps) {
   EXPECT(mona_step(st, m.data(), n, &hp, &one) == MONA_OK);
   EXPECT(launches == plan_launches);
   EXPECT(std::fabs(flops - plan_flops) <= 1e-9 * flops);
+  // and what the records of launches timed one by one say
+  EXPECT(mona_set_profiling(st, 2) == MONA_OK);
+  flops = 0.0;
+  EXPECT(mona_step(st, m.data(), n, &hp, &one) == MONA_OK);
+  int32_t records = 0;
+  EXPECT(mona_last_step_launches(st, nullptr, 0, &records) == MONA_OK);
+  std::vector<mona_launch_time> record(records);
+  EXPECT(mona_last_step_launches(st, record.data(), records, &records) == MONA_OK);
+  double recorded = 0.0;
+  for (const mona_launch_time& r : record) recorded += r.flops;
+  EXPECT(std::fabs(flops - recorded) <= 1e-9 * flops);
   fake::on_launch = nullptr;
   EXPECT(mona_free_state(st) == MONA_OK);
   std::free(arena);

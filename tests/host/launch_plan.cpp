@@ -60,7 +60,9 @@ static void run(const Shapes& shapes, int precision, int streams, int schedule, 
     const int k = small ? static_cast<const GemmBatch*>(l.args[0])->n : 1;
     const GemmArgs* a = small ? static_cast<const GemmBatch*>(l.args[0])->a : static_cast<const GemmArgs*>(l.args[0]);
     for (int i = 0; i < k; ++i) {
-      flops += 2.0 * a[i].tile_m * a[i].tile_n * (double)a[i].K * a[i].tiles_per_mat * a[i].count;
+      // (tiles of 32 and 64 stop behind the last value of K that is no padding, in steps of 32, but for those of split products)
+      const bool stops = a[i].tile_m <= 64 && l.name.find("ns_small_kernel_split") == std::string::npos;
+      flops += 2.0 * a[i].tile_m * a[i].tile_n * (double)(stops ? (a[i].k_real + 31) / 32 * 32 : a[i].K) * a[i].tiles_per_mat * a[i].count;
       int again = 0;
       while (products.count({a[i].C, again})) ++again;
       products[{a[i].C, again}] = {a[i].tile_m, a[i].K, l.name};
