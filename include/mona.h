@@ -28,10 +28,11 @@
  *   - the library allocates no device memory for state or workspace: the caller hands
  *     it one arena (e.g. a torch uint8 tensor) sized by mona_state_size(); the library
  *     owns only host-side bookkeeping and a few small pinned host tables.  (Two static
- *     arrays belong to its code on every GPU: the workspace of mona_step_noalloc, 32 MiB,
- *     and 128 MiB of buffers that small steps use where they find room there; a state takes
- *     its part at init, which waits for the device if only parts of freed states are left, and
- *     keeps it until the process ends if a step of it has been captured into a graph.)
+ *     arrays belong to its code, each on a GPU from the first call there that needs it until
+ *     the process ends: the workspace of mona_step_noalloc, 32 MiB, and 128 MiB of buffers that
+ *     small steps use where they find room there; a state takes its part at init, which waits
+ *     for the device if only parts of freed states are left, and keeps it until the process
+ *     ends if a step of it has been captured into a graph.)
  */
 #ifndef MONA_H
 #define MONA_H

@@ -9,7 +9,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libmona.so")
-SOURCES = ("mona_api.hip", "state_update.hip", "ns_gemm.hip", "ns_small.hip", "ns_split.hip", "ns_matrix.hip", "adamw.hip")
+SOURCES = ("mona_api.hip", "chain_pool.hip", "state_update.hip", "ns_gemm.hip", "ns_small.hip", "ns_split.hip", "ns_matrix.hip", "adamw.hip")
 # reads the callers' tensors for the ctypes binding: host code against PyTorch's own headers
 HELPER_PATH = os.path.join(HERE, "libmona_descriptors.so")
 HELPER_SOURCE = "descriptors.cpp"

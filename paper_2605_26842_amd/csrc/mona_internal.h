@@ -276,6 +276,11 @@ struct BeginTable {
 };
 static_assert(sizeof(FillArgs) + sizeof(BeginTable) + 128 <= 4000, "an argument block holds 4 KB");
 
+constexpr int kMaxDevices = 64;      // device ordinals that static arrays are looked up for
+// a part of the pool of chain buffers on `device`, the current one (chain_pool.hip; nullptr: no room), and back again
+char* take_from_pool(int device, size_t bytes);
+void give_back(int device, const char* at, size_t bytes);
+
 // kernels (defined in the .hip files)
 // dyn[0 .. n) = t.v[0 .. n), n <= kInlineMats
 hipError_t launch_write_dyn(const DynTable& t, int n, MatDynamic* dyn, hipStream_t s);

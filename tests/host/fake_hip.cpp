@@ -42,6 +42,7 @@ void carry_out(const Launch& l) {
 }
 }  // namespace
 
+std::vector<Array>& arrays() { static std::vector<Array> all; return all; }
 void replay() { for (auto& f : recorded) f(); }
 void clear_recorded() { recorded.clear(); }
 }  // namespace fake
@@ -49,9 +50,12 @@ void clear_recorded() { recorded.clear(); }
 using namespace fake;
 
 extern "C" {
-void** __hipRegisterFatBinary(const void*) { static void* handle = nullptr; return &handle; }
+// (a source of the library has a module of its own: its arrays take device memory when something of it is used first)
+void** __hipRegisterFatBinary(const void*) { static void* handles[64] = {}; static int n = 0; return &handles[n++]; }
 void __hipUnregisterFatBinary(void**) {}
-void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
+void __hipRegisterVar(void** module, void*, char*, char*, int, size_t bytes, int, int) {
+  arrays().push_back({module, bytes});
+}
 void __hipRegisterFunction(void**, const void* host, char*, const char* name, unsigned, void*, void*, void*, void*, int*) {
   names[host] = name;
 }

@@ -20,6 +20,8 @@ extern std::string fail;                               // what to fail once: "co
 extern int capability_major, capability_minor;         // of the device (those of none that exists, unless a test says so)
 extern int device;                                     // the current device
 extern int queries;                                    // what was asked of the devices so far
+struct Array { const void* source; size_t bytes; };              // a static device array and the source it belongs to
+std::vector<Array>& arrays();
 void replay();                                         // carries out what was recorded since capturing was set
 void clear_recorded();
 }  // namespace fake

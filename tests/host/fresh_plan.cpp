@@ -138,6 +138,14 @@ int main() {
   fake::capability_minor = 5;
   std::vector<char> pool(kPool / 16);
   std::mt19937 rng(3);
+  // the pool is in a source of its own: who needs another static array does not carry it too
+  int pools = 0;
+  for (const fake::Array& a : fake::arrays()) {
+    if (a.bytes != kPool) continue;
+    ++pools;
+    EXPECT(std::count_if(fake::arrays().begin(), fake::arrays().end(), [&](const fake::Array& b) { return b.source == a.source; }) == 1);
+  }
+  EXPECT(pools == 1);
   for (int precision = 0; precision < 2; ++precision)
     for (int steps : {1, 2, 5, 6}) {
       State s = make({{1, 256, 512}}, precision);
