@@ -1855,6 +1855,8 @@ int mona_internal_chain_polls(mona_state* st, int32_t roll, int32_t wait) {
   st->plan = nullptr;
   return MONA_OK;
 }
+// Not part of the ABI: whether the chains of a state's last step had a buffer for every product (1), ran with flags (0), or it had none (-1).
+int mona_internal_chain_kind(mona_state* st) { return !st || !st->plan || st->plan->chains.empty() ? -1 : st->plan->fresh ? 1 : 0; }
 
 int mona_set_profiling(mona_state* st, int32_t on) {
   if (!st) return fail(MONA_EINVAL, "state is NULL");
