@@ -999,7 +999,8 @@ void build_plan(const mona_state* st, const mona_hparams& hp, Plan& plan, bool o
     d.count = (int32_t)g.members.size();
     d.m = g.m; d.n = g.n; d.rows_pad = g.rows_pad; d.cols_pad = g.cols_pad;
     d.tall = g.tall; d.f32 = g.f32;
-    d.w_f32 = std::any_of(g.members.begin(), g.members.end(), [&](int i) { return st->mats[i].w_dtype == MONA_F32; });
+    const bool w_f32 = std::any_of(g.members.begin(), g.members.end(), [&](int i) { return st->mats[i].w_dtype == MONA_F32; });
+    d.w_rows = w_f32 ? ROWS_ANY : g.n % 8 ? ROWS_BF16 : ROWS_WHOLE;
     d.o_scale = update_scale(g, hp);
     plan.desc.push_back(d);
   }

@@ -53,6 +53,10 @@ constexpr int kEwThreads = 256;
 constexpr int kEwChunk = 4096;  // elements per block of the elementwise kernel
 
 // ---- Newton-Schulz product kernels -------------------------------------------------
+// How the update of large tiles may take the parameters of a group, 8 values of a row at a time: all of them bf16 and rows a multiple of 8, all
+// bf16, or any.
+enum UpdateRows : int32_t { ROWS_WHOLE = 0, ROWS_BF16 = 1, ROWS_ANY = 2 };
+
 // out = post * (beta * E + alpha * (P Q^T)) + diag * I,   P: M x K,  Q: N x K  (logical shapes)
 // An operand flagged "transposed" is stored K-major (K x M or K x N, rows of length ld).
 enum GemmEpilogue : int32_t {
@@ -80,7 +84,7 @@ struct GemmArgs {
   int32_t post;             // PostScale, indexed through `members`
   int32_t epilogue;         // GemmEpilogue
   int32_t store_out;        // EPI_UPDATE: also store O
-  int32_t w_f32;            // EPI_UPDATE: some parameters of the group are fp32
+  int32_t w_rows;           // EPI_UPDATE: UpdateRows
   const int32_t* members;   // group member -> matrix index
   const MatScale* scales;   // per matrix
   const MatStatic* stat;    // per matrix (EPI_UPDATE: real m, n, w dtype)
@@ -102,7 +106,7 @@ struct GroupDesc {
   int32_t count, m, n;      // matrices, their shape
   int32_t rows_pad, cols_pad;
   int32_t tall, f32;
-  int32_t w_f32;            // some of the parameters are fp32
+  int32_t w_rows;           // UpdateRows
   float o_scale;            // eta * gamma
 };
 struct StepDesc {
@@ -144,7 +148,7 @@ __host__ __device__ inline void expand_op(const StepDesc& st, const GroupDesc& g
   a.symmetric = apply ? 0 : 1;
   a.trans_p = (int32_t)op_field(code, OPF_TP); a.trans_q = (int32_t)op_field(code, OPF_TQ);
   a.alpha = 1.0f; a.beta = 0.0f; a.diag = 0.0f; a.diag_n = p_real;
-  a.post = POST_NONE; a.epilogue = EPI_STORE; a.store_out = 0; a.w_f32 = g.w_f32;
+  a.post = POST_NONE; a.epilogue = EPI_STORE; a.store_out = 0; a.w_rows = g.w_rows;
   a.w_keep = st.w_keep; a.o_scale = g.o_scale;
   // operands: the p x p matrices numbered by the code, an X operand in place of one or both
   a.P = pp(OPF_P); a.Q = pp(OPF_Q); a.C = pp(OPF_C); a.E = nullptr;

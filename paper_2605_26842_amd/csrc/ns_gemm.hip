@@ -68,12 +68,17 @@ __device__ __forceinline__ void tr_read_8_rows(u32x2 (&lo)[4], u32x2 (&hi)[4], u
 // values from then on), and the stores of the passes then stream without any wait.  HAS_E is a template
 // parameter for the same reason: a run-time test around the loads would make every later use look as if
 // it might still be pending.
-template <int MI, int NPF, int NPRE, bool UPD, bool W32, bool HAS_E, bool DIAG>
+template <int MI, int NPF, int NPRE, bool UPD, int ROWS, bool HAS_E, bool DIAG>
 struct BlockEpilogue {
   static constexpr int NI = 2, WN = 64, CH = 8, PASSES = MI * 4;
   static constexpr int kStageBytesPerWave = 32 * WN * 4;
   static_assert(NPF == 8 || NPF == 16, "settle() is written for batches of 8 or 16 passes");
-  // 16 bytes of a row of W: rows of any length, so they are aligned like its elements (the compiler emits one access all the same)
+  // 16 bytes of a row of W: rows of any length, so they are aligned like its elements (the compiler emits one access all the same).
+  // The forms of the update (UpdateRows) are kernels of their own: what a piece at the end of a row takes, element by element, is half of
+  // the code (fp32 again as much), and standing between the passes it costs those that have no such ends.  The launches with the update in
+  // a step of 128 x 2048 x 1024 and 64 x 1024 x 2048, side by side, us: 1006 and 749 as whole pieces, 1060 and 783 with ends in bf16, 1.3 %
+  // more again with the ones in fp32 (1040 and 777 with all of them, pieces of rows that are no multiple of 8 value by value).
+  static constexpr bool WHOLE = ROWS == ROWS_WHOLE, W32 = ROWS == ROWS_ANY;
   typedef u32x4 bf16_piece __attribute__((aligned(2)));
   typedef u32x4 f32_piece __attribute__((aligned(4)));
 
@@ -175,7 +180,7 @@ struct BlockEpilogue {
     if constexpr (HAS_E) ev[slot] = *reinterpret_cast<const u32x4*>(Et + (e_off + 2u * (uint32_t)(pass_row(P) * a.lde)));
     if constexpr (UPD) {
       const int grow = row_w0 + pass_row(P) + (lane >> 3), gcol = col_w0 + (lane & 7) * CH;
-      if (w_kind == W_BF16 && grow < wm_real && gcol + CH <= wn_real)
+      if ((W32 ? w_kind == W_BF16 : w_kind != W_NONE) && grow < wm_real && (WHOLE ? gcol < wn_real : gcol + CH <= wn_real))
         wv[slot] = *(const MONA_AS1 bf16_piece*)(wptr + ((size_t)grow * wn_real + gcol) * 2);
     }
   }
@@ -286,7 +291,7 @@ struct BlockEpilogue {
         if (UPD && w_kind != W_NONE && grow < wm_real) {
           // W <- (1 - eta lambda) W - eta gamma O, O as stored in the working precision
           const size_t wi = (size_t)grow * wn_real + gcol;
-          if (w_kind == W_BF16 && gcol + CH <= wn_real) {
+          if (WHOLE ? gcol < wn_real : (!W32 || w_kind == W_BF16) && gcol + CH <= wn_real) {
             bf16x8 w_in = __builtin_bit_cast(bf16x8, wv[UPD ? slot : 0]);
 #pragma unroll
             for (int e = 0; e < CH; ++e) w_in[e] = (bf16_t)(a.w_keep * (float)w_in[e] - a.o_scale * (float)ov[e]);
@@ -299,11 +304,11 @@ struct BlockEpilogue {
               for (int e = 0; e < 4; ++e) w_in[e] = a.w_keep * w_in[e] - a.o_scale * (float)ov[4 * h + e];
               to[h] = __builtin_bit_cast(u32x4, w_in);
             });
-          } else {
+          } else if (!WHOLE) {
 #pragma unroll
             for (int e = 0; e < CH; ++e) {
               if (gcol + e < wn_real) {
-                if (w_kind == W_BF16) {
+                if (!W32 || w_kind == W_BF16) {
                   MONA_AS1 bf16_t* w = (MONA_AS1 bf16_t*)wptr + wi + e;
                   *w = (bf16_t)(a.w_keep * (float)*w - a.o_scale * (float)ov[e]);
                 } else {
@@ -406,7 +411,7 @@ __device__ __forceinline__ void lds_read_t(FragT& f, uint32_t addr) {
   asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.hi) : "v"(addr), "n"(OFF + PITCH4));
 }
 
-template <int BM, int BN, int WGM, int WGN, int STAGES, int MIN_BLOCKS, bool TP, bool TQ, bool UPD, bool HAS_E, bool DIAG, bool W32 = false>
+template <int BM, int BN, int WGM, int WGN, int STAGES, int MIN_BLOCKS, bool TP, bool TQ, bool UPD, bool HAS_E, bool DIAG, int ROWS = ROWS_WHOLE>
 __global__ __launch_bounds__(64 * WGM * WGN, MIN_BLOCKS) void ns_gemm_bf16_dma_kernel(const GemmArgs a) {
   constexpr int BK = 32;
   constexpr int NW = WGM * WGN;
@@ -588,7 +593,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, MIN_BLOCKS) void ns_gemm_bf16_dma_k
 
   static_assert(STAGES == 4, "the pipeline below is written for a ring of 4 stages");
   // (the launch that carries the update has no registers for an early request during the last K steps)
-  typedef BlockEpilogue<MI, /*batch*/ (UPD ? 8 : 16), /*early*/ (UPD ? 0 : 2), UPD, W32, HAS_E, DIAG> Epi;
+  typedef BlockEpilogue<MI, /*batch*/ (UPD ? 8 : 16), /*early*/ (UPD ? 0 : 2), UPD, ROWS, HAS_E, DIAG> Epi;
   Epi epi(a);
   static_assert(NI == Epi::NI && (3 * STAGE_U * 16 + NW * Epi::kStageBytesPerWave) <= LDS_U * 16,
                 "epilogue staging: stage 3 and the LDS behind the ring");
@@ -688,8 +693,8 @@ hipError_t launch_ns_gemm(const GemmArgs& a, int cu_cap, hipStream_t s) {
   // persistent launch must be resident at once or the tile walk falls into two rounds)
   const int cap = (cu_cap >= kXcds && cu_cap < num_cus) ? cu_cap / kXcds * kXcds : num_cus;
   const int pgrid = grid < cap ? grid : cap;
-#define MONA_LAUNCH_DMA(TP_, TQ_, UPD_, E_)                                                                        \
-  hipLaunchKernelGGL((ns_gemm_bf16_dma_kernel<256, 256, 2, 4, 4, 1, TP_, TQ_, UPD_, E_, false>), dim3(pgrid), dim3(512), 0, s, a)
+#define MONA_LAUNCH_DMA(TP_, TQ_, UPD_, E_, ...)                                                                   \
+  hipLaunchKernelGGL((ns_gemm_bf16_dma_kernel<256, 256, 2, 4, 4, 1, TP_, TQ_, UPD_, E_, false, ##__VA_ARGS__>), dim3(pgrid), dim3(512), 0, s, a)
   const bool upd = a.epilogue == EPI_UPDATE, has_e = a.E != nullptr;
   // the plan uses: Gram and the products of two commuting symmetric matrices (no E; both operands row-major,
   // or both K-major); poly and the apply of a wide matrix (E, both operands K-major); the apply of a tall
@@ -706,12 +711,15 @@ hipError_t launch_ns_gemm(const GemmArgs& a, int cu_cap, hipStream_t s) {
   else if (transP && transQ && !upd && has_e) MONA_LAUNCH_DMA(true, true, false, true);
   else if (!transP && transQ && !upd && has_e) MONA_LAUNCH_DMA(false, true, false, true);
   else if (!transP && transQ && !upd && !has_e) MONA_LAUNCH_DMA(false, true, false, false);
-  else if (!transP && transQ && upd && a.w_f32 && has_e)
-    hipLaunchKernelGGL((ns_gemm_bf16_dma_kernel<256, 256, 2, 4, 4, 1, false, true, true, true, false, true>), dim3(pgrid), dim3(512), 0, s, a);
-  else if (!transP && transQ && upd && a.w_f32)
-    hipLaunchKernelGGL((ns_gemm_bf16_dma_kernel<256, 256, 2, 4, 4, 1, false, true, true, false, false, true>), dim3(pgrid), dim3(512), 0, s, a);
-  else if (!transP && transQ && upd && has_e) MONA_LAUNCH_DMA(false, true, true, true);
-  else if (!transP && transQ && upd && !has_e) MONA_LAUNCH_DMA(false, true, true, false);
+  else if (!transP && transQ && upd) {
+    auto with = [&](auto rows) {
+      if (has_e) MONA_LAUNCH_DMA(false, true, true, true, decltype(rows)::value);
+      else MONA_LAUNCH_DMA(false, true, true, false, decltype(rows)::value);
+    };
+    if (a.w_rows == ROWS_WHOLE) with(IC<ROWS_WHOLE>{});
+    else if (a.w_rows == ROWS_BF16) with(IC<ROWS_BF16>{});
+    else with(IC<ROWS_ANY>{});
+  }
   else return hipErrorInvalidValue;
 #undef MONA_LAUNCH_DMA
   return hipGetLastError();

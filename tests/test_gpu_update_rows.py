@@ -1,6 +1,6 @@
 """The parameter update in the last product of large and of small tiles, for rows of W of any length (pieces of 8 values that are aligned
-like one, the last one of a row partly outside) and for groups of bf16 parameters, of fp32 ones and of both, against the update formed from the
-stored O in float64."""
+like one, the last one of a row partly outside, or rows of whole pieces) and for groups of bf16 parameters, of fp32 ones and of both,
+against the update formed from the stored O in float64."""
 import ctypes
 
 import pytest
@@ -18,6 +18,9 @@ CASES = {
     "large tiles, literal": ((505, 509), 44, B.MONA_NS_SCHEDULE_LITERAL, 256256),
     "large tiles, tall": ((1022, 510), 20, B.MONA_NS_SCHEDULE_FUSED, 256256),
     "large tiles, wide": ((510, 1023), 20, B.MONA_NS_SCHEDULE_FUSED, 256256),
+    "large tiles, literal, rows of whole pieces": ((505, 504), 44, B.MONA_NS_SCHEDULE_LITERAL, 256256),
+    "large tiles, tall, rows of whole pieces": ((1022, 504), 20, B.MONA_NS_SCHEDULE_FUSED, 256256),
+    "large tiles, wide, rows of whole pieces": ((510, 1016), 20, B.MONA_NS_SCHEDULE_FUSED, 256256),
     "tiles of 128": ((500, 613), 13, B.MONA_NS_SCHEDULE_AUTO, 128128),
     "tiles of 128, a side just past three": ((385, 1007), 6, B.MONA_NS_SCHEDULE_AUTO, 128128),
     "tiles of 64": ((385, 1007), 3, B.MONA_NS_SCHEDULE_AUTO, 64064),
