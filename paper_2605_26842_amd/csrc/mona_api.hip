@@ -508,7 +508,7 @@ void build_layout(const mona_matrix* mats, int count, const mona_options& opt, b
 
   double copies = 0.0;
   for (const Group& g : L.groups) copies += (double)g.m * g.n * (double)g.members.size() * g.esize;
-  L.keep = choose_keep(pass_bytes(L, mats), copies);
+  L.keep = choose_keep(copies);
 
   // elementwise work table
   L.first_block.assign(count, 0);

@@ -291,8 +291,8 @@ hipError_t launch_write_dyn(const DynTable& t, int n, MatDynamic* dyn, hipStream
 hipError_t launch_state_update(const MatStatic* stat, const MatDynamic* dyn, const BlockWork* work,
                                double* partials, int num_blocks, int g_bf16, int state_bf16, int one_buffer,
                                float mu, float beta_a, float alpha, int use_prev, int keep, hipStream_t s);
-// what the caches are to keep of a pass over all matrices that moves so many bytes, so many of them working copies
-int choose_keep(double pass_bytes, double copy_bytes);
+// what the caches are to keep of a pass over all matrices that writes so many bytes of working copies
+int choose_keep(double copy_bytes);
 // norms, scales and the repair of flagged working copies
 // `list` (DEVICE, may be NULL = matrices 0 .. count - 1): the matrix indices to finalise; max_blocks: the most
 // elementwise blocks any of them has; zero: memory to clear on the way (a multiple of 16 bytes); fill: buffers of fresh

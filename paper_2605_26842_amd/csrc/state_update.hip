@@ -19,9 +19,14 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef bf16_t bf16x4 __attribute__((ext_vector_type(4)));
 
 // What of a pass the caches are to keep (choose_keep).  Non-temporal accesses leave nothing of an array that is read once and written
-// once in the 256 MB cache behind the L2s.  Measured, us per pass, with nothing / the working copy / everything kept: 64 x 1000 x 2000
-// 725 / 676 / -, 64 x 768 x 768 200 / 188 / -, 128 x 768 x 256 both ways 261 / 247 / -, 128 x 1000 x 2000 1452 / 1401 / -, 256 x 1000 x 2000 2927 /
-// 2897 / -, 32 x 4096 x 4096 2896 / 2934 / -, 200 x 257 x 130 (200 MB in all) 47 / 45 / 38.
+// once in the 256 MB cache behind the L2s.  Measured, us per pass, with nothing / the working copy kept: 64 x 1000 x 2000
+// 725 / 676, 64 x 768 x 768 200 / 188, 128 x 768 x 256 both ways 261 / 247, 128 x 1000 x 2000 1452 / 1401, 256 x 1000 x 2000 2927 /
+// 2897, 32 x 4096 x 4096 2896 / 2934.  Everything is kept by the launch that begins a small step only.  Elsewhere it pays where the next step
+// of the same state finds its arrays still there, but a program's forward and backward passes stand in between.  us per step with the
+// copy / everything kept, by states in turn that take 1.2 GB together: 128 x 128 x 128 42.4 / 48.5, 40 x 128 x 256 52.7 / 57.2, 24 x 128 x 512
+// 81.6 / 85.9, 100 x 128 x 512 111 / 119, 200 x 128 x 256 84.8 / 92, 6 x 384 x 1000 149.9 / 153.4, 60 x 256 x 512 240 / 245, 30 x 300 x 700 237.6 /
+// 241.3; by the same one or two, up to 100 MB of them, 1 to 2.5 % the other way (128 x 128 x 128 45.5 / 44.3, 6 x 384 x 1000 145 / 142).  It is the
+// loads that cost: plain ones with non-temporal stores 48.2 and 152.8, the other way round 45.2 and 151.
 enum Keep : int { KEEP_NOTHING = 0, KEEP_COPY = 1, KEEP_ALL = 2 };
 template <bool STREAM, typename V> __device__ __forceinline__ V load(const V* p) {
   if constexpr (STREAM) return __builtin_nontemporal_load(p);
@@ -673,8 +678,7 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(uint4* __restrict__ p, s
 template <typename GT, typename ST, int MODE>
 hipError_t launch_su(const MatStatic* stat, const MatDynamic* dyn, const BlockWork* work, double* partials,
                      int num_blocks, Coef c, int keep, hipStream_t s) {
-  auto* const kernel = keep == KEEP_ALL ? state_update_kernel<GT, ST, MODE, KEEP_ALL>
-                       : keep == KEEP_COPY ? state_update_kernel<GT, ST, MODE, KEEP_COPY> : state_update_kernel<GT, ST, MODE, KEEP_NOTHING>;
+  auto* const kernel = keep == KEEP_COPY ? state_update_kernel<GT, ST, MODE, KEEP_COPY> : state_update_kernel<GT, ST, MODE, KEEP_NOTHING>;
   // (long passes over four fp32 arrays with three workgroups to a CU instead of five, by LDS that nothing uses: 192 x 2048 x 1024 2203 ->
   // 2190 us, 48 x 4096 x 4096 4447 -> 4393; shorter ones gain and lose 1 %, a step with one bf16 array loses 0.8 %)
   const size_t lds = keep == KEEP_NOTHING && MODE == MODE_TWO_BUFFER && sizeof(ST) == 4 ? 160 * 1024 / 3 / 256 * 256 - 256 : 0;
@@ -694,11 +698,11 @@ hipError_t launch_su_mode(const MatStatic* stat, const MatDynamic* dyn, const Bl
 
 }  // namespace
 
-// Everything where all that a pass moves fits into the cache, the working copies where these take at most twice as much: what the products
-// read first is still there, and the copies' lines are not turned out one by one between the loads.
-int choose_keep(double pass_bytes, double copy_bytes) {
+// The working copies where these take at most twice what the cache holds: what the products read first is still there, and the copies' lines
+// are not turned out one by one between the loads.
+int choose_keep(double copy_bytes) {
   constexpr double kCache = 256.0 * 1024 * 1024;
-  return pass_bytes <= kCache ? KEEP_ALL : copy_bytes <= 2.0 * kCache ? KEEP_COPY : KEEP_NOTHING;
+  return copy_bytes <= 2.0 * kCache ? KEEP_COPY : KEEP_NOTHING;
 }
 
 // The gradient dtype may differ between matrices: the host orders the work table by gradient
