@@ -183,7 +183,8 @@ int mona_init_state(const mona_matrix* mats, int32_t count, const mona_options* 
  * pairs that fork and join its side streams -- no memset, no copy -- and may be recorded into a HIP graph
  * on a capturing stream.  The recorded step holds this call's w / g (and slot) pointers: a replay uses them
  * whatever eager steps, with whatever pointers, came before it.  A state that has been captured once writes its
- * pointers in front of every later step as well (one small launch for every 96 matrices).
+ * pointers in every later step as well (in the launch that begins the step where there is one for all that stands
+ * before the products; otherwise one small launch for every 96 matrices).
  * The hyper-parameters are baked into the recorded launches, and the host-side step
  * counter counts calls, not replays (it only matters for MONA_FLAG_FIRST_DIFF_ZERO at
  * the first step).

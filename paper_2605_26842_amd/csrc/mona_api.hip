@@ -222,12 +222,13 @@ long long launch_tiles(const Group& g, int kind, int tile, int count) {
 
 // Whether the matrices of a group get a workgroup each (ns_matrix_kernel), by what their iterations take that way and as
 // products, us of a step.  Alone, products take as long as their launches at least; beside other groups, whose launches they share
-// or run beside, only what they add.  Measured, us per step as products (launches, or a chain) / by matrix: 128 x 128 57 / 32,
-// 100 x 400 70 / 64, 24 x 128 x 512 90 / 75, 60 x 128 x 256 105 / 53, 250 x 70 x 100 170 / 45, 200 x 120 x 600 317 / 177,
-// 250 x 128 x 4000 1983 / 1372, but 40 x 128 x 2000 232 / 327; 256 x 256 x 256 426 / 243, 115 x 256 x 512 383 / 290, 128 x 768 x 256 both
-// ways 831 / 626, but 60 x 256 x 512 235 / 260, 79 x 256 x 834 and others 482 / 569; 4 x 171 x 66 beside 697 x 612 and 365 x 161 144 / 169;
-// 50 x 256 x 256 170 / 147, 84 x 256 x 256 213 / 162, 70 x 130 x 200 148 / 134, 86 x 256 x 768 474 / 376, but 36 x 256 x 256 140 / 140, 52 x 160 x 140
-// 126 / 148, 50 x 140 x 380 160 / 205.
+// or run beside, only what they add.  Measured, us per step as products (launches, or a chain) / by matrix: 128 x 128 47 / 32,
+// 8 x 128 x 128 46 / 33, 16 x 100 x 200 62 / 46, 24 x 128 x 512 80 / 76, 60 x 128 x 256 104 / 53, 250 x 70 x 100 161 / 45, 200 x 120 x 600 299 / 176,
+// 250 x 128 x 4000 1983 / 1372, but 100 x 400 49 / 68, 4 x 128 x 1024 64 / 136, 40 x 128 x 2000 222 / 309; 256 x 256 x 256 440 / 232,
+// 115 x 256 x 512 370 / 281, 128 x 768 x 256 both ways 831 / 611, but 60 x 256 x 512 231 / 239, 79 x 256 x 834 385 / 395; 4 x 171 x 66 beside
+// 697 x 612 and 365 x 161 144 / 169; 50 x 256 x 256 170 / 143, 84 x 256 x 256 213 / 157, 70 x 130 x 200 141 / 130, 86 x 256 x 768 438 / 358, but
+// 36 x 256 x 256 139 / 137, 28 x 256 x 256 114 / 132, 52 x 160 x 140 116 / 132, 50 x 140 x 380 150 / 171.  (The kernel with a padded short side
+// of 256, 120 matrices with 4, 8, 16 panels: 208, 374, 679 us, 204, 360, 672 by the rule; of 128 with 4 and 16: 67 and 267, 55 and 243.)
 bool by_matrix(const Group& g, bool alone) {
   if (g.f32 || g.fused || (g.p_pad != 128 && g.p_pad != 256)) return false;
   const double count = (double)g.members.size(), panels = std::max(g.rows_pad, g.cols_pad) / 128;
@@ -844,10 +845,12 @@ long long tiles_at(Plan& plan, const std::vector<int>& groups, size_t pos, int t
 //
 // Where the line (kChainTiles, kChainWork) lies.  A chain saves 2 to 4 us of every product, but its workgroups are one to a CU and its tiles 64 x 64
 // at most, dealt without regard to the die they are on.  Measured, us per step with launches / as a chain, with the work of the
-// widest position (64 x 64 tiles times K, in thousands): 256 x 256 (4) 94 / 66, 512 x 512 (33) 111 / 98, 512 x 2048 (131) 147 / 130,
-// 4 x 300 x 900 (115) 131 / 111, 200 x 64 x 128 (51, fp32) 147 / 134, 768 x 768 (110) 133 / 131, 4 x 512 x 512 (131) 120 / 118;
-// beyond it 1024 x 1024 (262) 152 / 158, 6 x 384 x 1000 (221) 150 / 156, 30 x 256 x 512 (245) 155 / 180, 250 x 70 x 100
-// (192, 1000 tiles) 166 / 223, 700 x 2000 (270) 168 / 165.
+// widest position (64 x 64 tiles times K, in thousands): 256 x 256 (4) 92 / 54, 512 x 512 (33) 109 / 74, 512 x 2048 (131) 145 / 104,
+// 4 x 300 x 900 (115) 122 / 87, 200 x 64 x 128 (51, fp32) 127 / 124, 768 x 768 (110) 130 / 106, 4 x 512 x 512 (131) 117 / 97,
+// 28 x 256 x 256 (115) 126 / 114.  Beyond it chains lose where the short side is 256 or less, 30 x 256 x 512 (245) 156 / 183, 20 x 256 x 512 (164)
+// 128 / 128, 36 x 256 x 256 (147) 140 / 152, 250 x 70 x 100 (192, 1000 tiles) 166 / 223, and win where it is longer: 1024 x 1024 (262) 150 / 125,
+// 6 x 384 x 1000 (221) 147 / 137, 700 x 2000 (270) 166 / 139, 2 x 640 x 1280 (256) 154 / 132.  The line is that of chains with flags and three
+// launches in front, which lost 4 % at 1024 x 1024 and 6 x 384 x 1000; tiles and work alone do not part the two kinds.
 // The tile a chain takes at one position: 32 x 32 as long as every one has a CU of its own.
 int chain_tile(Plan& plan, const std::vector<int>& groups, size_t pos) {
   return tiles_at(plan, groups, pos, 32) <= device_cu_count() ? 32 : 64;

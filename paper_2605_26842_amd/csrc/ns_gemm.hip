@@ -184,7 +184,8 @@ struct BlockEpilogue {
         wv[slot] = *(const MONA_AS1 bf16_piece*)(wptr + ((size_t)grow * wn_real + gcol) * 2);
     }
   }
-  // W32 (launches with fp32 parameters; the code for them costs others 0.3 %): those of a block row take the whole batch, two registers' worth a pass, so they are requested when its staging begins
+  // W32: the fp32 parameters of a block row take the whole batch, two registers' worth a pass, so they are requested when its staging
+  // begins
   template <int I>
   __device__ __forceinline__ void prefetch_w32() {
     static_for<4>([&](auto k) {

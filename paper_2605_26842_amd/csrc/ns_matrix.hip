@@ -28,9 +28,10 @@
 // 250 x 70 x 100 49 -> 46.
 //
 // Measured, us per step, products in launches (or chains) -> here: 128 x 768 x 256 both ways 831 -> 611, 250 x 70 x 100 170 -> 45,
-// 256 x 256 x 256 426 -> 236, 300 x 128 x 128 202 -> 82, one 128 x 128 57 -> 31.  A panel costs 2.2 us an iteration (P = 128) or
-// 7.3 us (P = 256, twice) on a CU, of which the multiplications are 1 and 4: the wavefronts meet three
-// times a panel (P = 128), and the vector instructions of the epilogue (2.5 an element) do not run beside matrix instructions.
+// 256 x 256 x 256 440 -> 232, 300 x 128 x 128 202 -> 82, one 128 x 128 47 (a chain) -> 32.  A panel costs an iteration 2.2 to 3.3 us (P = 128; the
+// kernel takes 67 us of 120 x 128 x 512 and 267 of 120 x 128 x 2048) or, in both passes together, 7.6 to 8.3 (P = 256; 208, 374 and 679 us of 120 x
+// 256 x 512, 1024 and 2048; 215, 388 and 718 while all panels were renewed in LDS), of which the multiplications are 1 and 4: the wavefronts
+// meet three times a panel (P = 128), and the vector instructions of the epilogue (2.5 an element) do not run beside matrix instructions.
 //
 // LDS: rows of 256 or 512 bytes, chunk c (16 bytes) of row r at c ^ swizzle(r): 16 consecutive rows hit 16 different
 // chunks (row-major fragments, one ds_read_b128), four consecutive rows four different groups of 64 bytes (K-major ones, two

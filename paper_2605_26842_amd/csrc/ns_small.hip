@@ -546,14 +546,16 @@ __global__ __launch_bounds__(WIDE ? 512 : 256) void ns_small_kernel(const GemmBa
 // products themselves are two to four.  Here the tiles of all products are tasks, numbered product by product in the
 // order of the chains; workgroup w of W takes the tasks w, w + W, w + 2 W, ..., waits for the tiles of its matrix in the
 // product before, computes the tile and says so.  How it waits:
-//   * With a buffer for every product (NEW; the pool in mona_api.hip) the data are their own flag: the buffers are filled beforehand with a
+//   * With a buffer for every product (NEW; the pool in chain_pool.hip) the data are their own flag: the buffers are filled beforehand with a
 //     pattern that no result holds, and a wavefront fetches its share of the operands again until none of it is left (Unwritten, in
 //     whole() below).  That takes the wait for the stores, the flag's way and the fetch behind it out of every product, and no barrier
-//     stands before one.  A product takes 2.9 us then (1.2 to 1.5 from the last store to the last wavefront's operands, 2.8 where
-//     128 workgroups ask for the same B), 4 with flags.
+//     stands before one.  A product of 256 x 512 takes 3.1 us then (1.2 to 1.5 from the last store to the last wavefront's operands, 2.8
+//     where 128 workgroups ask for the same B), 4.2 with flags.
 //   * Otherwise it polls a flag a task (ChainArgs::flags) of the tiles in the product before, and raises its own.
-// Measured, us per step, with flags -> without: 256 x 512 73 -> 59, 512 x 1408 114 -> 96, nine ragged matrices 83.5 -> 78 (filling 9 MB
-// takes 4 of it).
+// Measured, us per step, with flags -> without (one launch in front of both): 256 x 512 71.3 -> 54.5, 512 x 1408 111.1 -> 89.9, 700 x 700 116.3 -> 90.9,
+// 4 x 300 x 900 101.3 -> 87.6, 12 x 256 x 512 105.9 -> 95.3, 512 x 512 with fp32 products 131 -> 102.5, nine ragged matrices in both precisions
+// 74.5 -> 71.5.  Filling is what many matrices and much padding pay for it: 28 x 256 x 256 (51 MB) 113.5 -> 113.5; the two lists found that
+// lose are long ones (three launches in front), 40 x 160 x 140 (41 MB) 99.2 -> 101.1 and 100 x 60 x 60 with fp32 products (23 MB) 94.6 -> 98.3.
 //   * No workgroup waits for one that does not run.  W is not the size of the grid but the number of workgroups that have
 //     reported when the first of them closes the roll (all of the grid, unless the chip is busy with something else for
 //     c.roll_polls polls).  Tasks wait for lower numbers only, and a workgroup takes its own in order, so the lowest unfinished
@@ -573,8 +575,8 @@ __global__ __launch_bounds__(WIDE ? 512 : 256) void ns_small_kernel(const GemmBa
 //     another 2 us a step.
 //   * 32 x 32 tiles, K split between the eight wavefronts, where every one has a CU of its own: a tile of 64 x 64 takes 2.8 us
 //     with K = 256 and 4.4 with 512, one of 32 x 32 2.1 and 2.5 (the CU's own 64 bytes a cycle from L2, and latency).
-// Measured, us per step, launches -> chain with flags: one 256 x 512 matrix 99 -> 73, 512 x 1408 without allocation 137 -> 114, nine ragged
-// matrices in both precisions 189 -> 84 (which had waited for the host).  Tickets instead of fixed numbers, drawn by an atomic
+// Measured when all of them had flags, us per step, launches -> chain: one 256 x 512 matrix 99 -> 73, 512 x 1408 without allocation 137 -> 114, nine
+// ragged matrices in both precisions 189 -> 84 (which had waited for the host).  Tickets instead of fixed numbers, drawn by an atomic
 // operation for every task, and a counter of finished tiles instead of flags: 96, 189 and 133.
 constexpr uint32_t kRollClosed = 0x80000000u;
 

@@ -679,8 +679,9 @@ template <typename GT, typename ST, int MODE>
 hipError_t launch_su(const MatStatic* stat, const MatDynamic* dyn, const BlockWork* work, double* partials,
                      int num_blocks, Coef c, int keep, hipStream_t s) {
   auto* const kernel = keep == KEEP_COPY ? state_update_kernel<GT, ST, MODE, KEEP_COPY> : state_update_kernel<GT, ST, MODE, KEEP_NOTHING>;
-  // (long passes over four fp32 arrays with three workgroups to a CU instead of five, by LDS that nothing uses: 192 x 2048 x 1024 2203 ->
-  // 2190 us, 48 x 4096 x 4096 4447 -> 4393; shorter ones gain and lose 1 %, a step with one bf16 array loses 0.8 %)
+  // (long passes over four fp32 arrays with three workgroups to a CU instead of five, by LDS that nothing uses: the kernel, two runs of each,
+  // 192 x 2048 x 1024 2154, 2160 -> 2135, 2148 us, 48 x 4096 x 4096 4384, 4405 -> 4357, 4326: 0.6 to 1.8 % of it, a quarter of that of a step.
+  // Shorter ones gain and lose 1 %, a step with one bf16 array loses 0.8 %)
   const size_t lds = keep == KEEP_NOTHING && MODE == MODE_TWO_BUFFER && sizeof(ST) == 4 ? 160 * 1024 / 3 / 256 * 256 - 256 : 0;
   hipLaunchKernelGGL(kernel, dim3(num_blocks), dim3(kEwThreads), lds, s, stat, dyn, work, partials, c);
   return hipGetLastError();
