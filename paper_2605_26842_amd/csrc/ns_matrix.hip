@@ -490,9 +490,12 @@ __device__ __forceinline__ void run_matrix(const StepDesc& st, const GroupDesc& 
               *reinterpret_cast<u32x2*>(mine + L2.frow * 128 + chunk * 16 + L2.half * 8) = TALL ? out[cb][rb][v] : out[rb][cb][v];
             });
           });
+          // (other lanes of the wavefront wrote what is read here; its LDS accesses keep the order they stand in)
+          asm volatile("" ::: "memory");
           const int r8 = L2.lane >> 3, c8 = L2.lane & 7;
           u32x4 x[4];
           static_for<4>([&](auto k) { x[k] = *reinterpret_cast<const u32x4*>(mine + (8 * k + r8) * 128 + ((c8 ^ r8) << 4)); });
+          asm volatile("" ::: "memory");
           const int row = first_row + rb * 32 + r8, col = first_col + c8 * 8;
           bf16_t* const p = to + (size_t)row * ld + col;
           if (!last || store_o) static_for<4>([&](auto k) { *reinterpret_cast<u32x4*>(p + (size_t)(8 * k) * ld) = x[k]; });
